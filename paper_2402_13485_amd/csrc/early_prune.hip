@@ -17,7 +17,7 @@
 //                         written exactly once, so the sums do not depend on any order), or, for the
 //                         probability criterion, leaves (max, sum of exponentials) per row
 //                         and column tile
-//   early_head_f32_kernel plain fp32 variant with the same epilogue
+//   early_head_f32_kernel the same on the fp32 matrix instructions (early_head_f32.h)
 //   row_lse_kernel        probability criterion: log-sum-exp of every row from the tile
 //                         partials, log-probability of every child's token
 //   prune_compact_kernel  per sequence: the criterion's decision per node (rank against k, or
@@ -70,7 +70,7 @@ static PruneScratch carve_scratch(void *base, int B, int T_max, int vocab) {
   s.logq = reinterpret_cast<float *>(take(nt * 4));
   s.row_cap = (size_t)B * (T_max > 1 ? T_max - 1 : 1);  // a node with children is not a leaf
   // column parts of a row: one per wave column of a tile, at most four per 256 columns (two
-  // per 128-wide tile, four per 256-wide tile; the fp32 kernel has one per 256-wide slice)
+  // per 128-wide tile, four per 256-wide tile; the fp32 kernel has one per tile)
   s.parts = 4 * (((size_t)vocab + 255) / 256);
   s.lse_part = reinterpret_cast<float *>(take(s.row_cap * s.parts * 8));
   s.cnt_part = reinterpret_cast<int32_t *>(take((((size_t)vocab + 127) / 128) * nt * 4));
@@ -262,22 +262,31 @@ __device__ void prepare_tables(const PrepareArgs &a, int g) {
   }
 }
 
-// The children's own scores, bf16: workgroup (b, group) takes nodes 8*group .. +7 of
+// The children's own scores: workgroup (b, group) takes nodes 8*group .. +7 of
 // sequence b (few nodes per workgroup: the rows are fetched once, from all over the weight
 // matrix, and it is the number of workgroups that brings the bytes in flight).  Tile rows:
 // A row j = hidden state of the parent of node j, B row j = weight row of node j's token; the
 // diagonal of A . B^T holds the scores wanted (rows 8..15 of the 16-row tile repeat rows
-// 0..7).  All four waves fetch (coalesced, eight 256-deep steps ahead, through registers into
-// a padded double buffer in LDS); wave 0 runs the chain of 16x16x32 matrix instructions over
-// K in rising order, starting from zero: the chain the 352-row tiles of the scoring kernel run
-// for every element (the 32x32x16 chain of the 256-row tiles, two instructions per 32 of K,
-// gives the same bits: measured, and held to it by the test of equal scores on both shapes).
+// 0..7).  All four waves fetch (coalesced, eight 512-byte steps ahead, through registers into
+// a padded double buffer in LDS); wave 0 runs the chain of matrix instructions over
+// K in rising order, starting from zero.
+//   bf16: the chain of 16x16x32 instructions that the 352-row tiles of the scoring kernel run
+//     for every element (the 32x32x16 chain of the 256-row tiles, two instructions per 32 of K,
+//     gives the same bits: measured, and held to it by the test of equal scores on both shapes).
+//   fp32: the chain of 16x16x4 instructions of the fp32 scoring kernel: the four floats of a
+//     lane's 16-byte piece one after the other.  (One lane per node walking its two rows took
+//     78 us for 62 nodes of 1024 floats, a chain of 1024 dependent loads.)
 constexpr int kOwnNodes = 8;                      // children per workgroup
-constexpr int kOwnStep = 256;                     // K per fetch step
-constexpr int kOwnRowBytes = kOwnStep * 2 + 16;   // padded: the 8 rows start 4 banks apart
+constexpr int kOwnStepBytes = 512;                // bytes of a row per fetch step
+constexpr int kOwnRowBytes = kOwnStepBytes + 16;  // padded: the 8 rows start 4 banks apart
 constexpr int kOwnAhead = 8;
 
-__device__ void own_scores_bf16(const PrepareArgs &a, int b, int group) {
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));  // 16 bytes at a 4-byte aligned address
+
+template <bool kBf16>
+__device__ void own_scores(const PrepareArgs &a, int b, int group) {
+  constexpr int kElem = kBf16 ? 2 : 4, kPiece = 16 / kElem;  // bytes per element, elements per 16-byte piece
+  constexpr int kOwnStep = kOwnStepBytes / kElem;
   __shared__ __attribute__((aligned(16))) unsigned char s_tile[2][2][kOwnNodes * kOwnRowBytes];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -292,24 +301,49 @@ __device__ void own_scores_bf16(const PrepareArgs &a, int b, int group) {
   p = (p >= 0 && p < T) ? p : 0;
   int tk = a.token[base + nd];
   tk = (tk >= 0 && tk < a.vocab) ? tk : 0;
-  const uint16_t *a_src = reinterpret_cast<const uint16_t *>(a.hidden_states) + (base + p) * (size_t)a.hidden + ld_piece * 8;
-  const uint16_t *b_src = reinterpret_cast<const uint16_t *>(a.head_weight) + (size_t)tk * a.hidden + ld_piece * 8;
+  const char *a_src = reinterpret_cast<const char *>(a.hidden_states) + (base + p) * (size_t)a.hidden * kElem;
+  const char *b_src = reinterpret_cast<const char *>(a.head_weight) + (size_t)tk * a.hidden * kElem;
   const int n_steps = (a.hidden + kOwnStep - 1) / kOwnStep;
-  const int n_k32 = a.hidden / 32;
+  // 64-byte groups of a row (bf16: whole, the row length is a multiple of 32; fp32: the last
+  // one is filled with zeros, as in the scoring kernel)
+  const int n_groups = (a.hidden * kElem + 63) / 64;
   u32x4 ra[kOwnAhead], rb[kOwnAhead];
   auto fetch = [&](int slot, int step) {
-    const bool in = step < n_steps && step * kOwnStep + ld_piece * 8 < a.hidden;
-    const int off = in ? step * kOwnStep : 0;
-    ra[slot] = *reinterpret_cast<const u32x4 *>(a_src + off);
-    rb[slot] = *reinterpret_cast<const u32x4 *>(b_src + off);
+    const int x = step * kOwnStep + ld_piece * kPiece;  // the piece's first element
+    if (kBf16) {
+      const int off = (step < n_steps && x < a.hidden ? x : ld_piece * kPiece < a.hidden ? ld_piece * kPiece : 0) * kElem;
+      ra[slot] = *reinterpret_cast<const u32x4 *>(a_src + off);
+      rb[slot] = *reinterpret_cast<const u32x4 *>(b_src + off);
+    } else if (x + kPiece <= a.hidden) {
+      ra[slot] = *reinterpret_cast<const u32x4_a4 *>(a_src + (size_t)x * kElem);
+      rb[slot] = *reinterpret_cast<const u32x4_a4 *>(b_src + (size_t)x * kElem);
+    } else {
+      ra[slot] = rb[slot] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int j = 0; j < kPiece; ++j)
+        if (x + j < a.hidden) {
+          ra[slot][j] = reinterpret_cast<const uint32_t *>(a_src)[x + j];
+          rb[slot][j] = reinterpret_cast<const uint32_t *>(b_src)[x + j];
+        }
+    }
   };
 #pragma unroll
   for (int i = 0; i < kOwnAhead; ++i) fetch(i, i);
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  // fragment of the 16x16x32 instruction: lane -> row lane % 16 (rows 8..15 repeat rows 0..7),
-  // 8 consecutive k from 8 * (lane / 16)
+  // fragment of one 64-byte group: lane -> row lane % 16 (rows 8..15 repeat rows 0..7), 16-byte
+  // piece lane / 16
   const int c16 = lane & 15, kq = lane >> 4;
   const int frag_off = (c16 & (kOwnNodes - 1)) * kOwnRowBytes + kq * 16;
+  auto product = [&](const unsigned char *pa, const unsigned char *pb) {
+    if constexpr (kBf16) {
+      const bf16x8 fa = *reinterpret_cast<const bf16x8 *>(pa), fb = *reinterpret_cast<const bf16x8 *>(pb);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fb, acc, 0, 0, 0);
+    } else {
+      const f32x4 fa = *reinterpret_cast<const f32x4 *>(pa), fb = *reinterpret_cast<const f32x4 *>(pb);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[j], fb[j], acc, 0, 0, 0);
+    }
+  };
   for (int s0 = 0; s0 < n_steps; s0 += kOwnAhead) {
 #pragma unroll
     for (int i = 0; i < kOwnAhead; ++i) {
@@ -321,25 +355,17 @@ __device__ void own_scores_bf16(const PrepareArgs &a, int b, int group) {
       fetch(i, step + kOwnAhead);
       __syncthreads();  // the step is in LDS; wave 0 is done with the other buffer
       if (wave == 0) {
-        const int k32_left = n_k32 - step * (kOwnStep / 32);
-        if (k32_left >= kOwnStep / 32) {
+        constexpr int kGroups = kOwnStepBytes / 64;
+        const int left = n_groups - step * kGroups;
+        if (left >= kGroups) {
           // a whole step: no condition between the reads, so that all of them are in flight
           // before the first product needs its pair
 #pragma unroll
-          for (int ks = 0; ks < kOwnStep / 32; ++ks) {
-            const bf16x8 fa = *reinterpret_cast<const bf16x8 *>(buf_a + frag_off + ks * 64);
-            const bf16x8 fb = *reinterpret_cast<const bf16x8 *>(buf_b + frag_off + ks * 64);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fb, acc, 0, 0, 0);
-          }
+          for (int ks = 0; ks < kGroups; ++ks) product(buf_a + frag_off + ks * 64, buf_b + frag_off + ks * 64);
         } else {
 #pragma unroll
-          for (int ks = 0; ks < kOwnStep / 32; ++ks) {
-            if (ks < k32_left) {
-              const bf16x8 fa = *reinterpret_cast<const bf16x8 *>(buf_a + frag_off + ks * 64);
-              const bf16x8 fb = *reinterpret_cast<const bf16x8 *>(buf_b + frag_off + ks * 64);
-              acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fb, acc, 0, 0, 0);
-            }
-          }
+          for (int ks = 0; ks < kGroups; ++ks)
+            if (ks < left) product(buf_a + frag_off + ks * 64, buf_b + frag_off + ks * 64);
         }
       }
     }
@@ -356,23 +382,6 @@ __device__ void own_scores_bf16(const PrepareArgs &a, int b, int group) {
   if (c16 < kOwnNodes && kq == (c16 >> 2) && my_node > 0 && my_node < T) a.own[base + my_node] = diag;
 }
 
-// fp32: one lane per node, the same sequential fused multiply-add chain as the scoring kernel
-__device__ void own_scores_f32(const PrepareArgs &a, int b, int group) {
-  const int T = clamp_tree(a.n_nodes[b], a.T_max);
-  const int nd = kOwnNodes * group + (int)threadIdx.x;
-  if (threadIdx.x >= kOwnNodes || nd < 1 || nd >= T) return;
-  const size_t base = (size_t)b * a.T_max;
-  int p = a.parent[base + nd];
-  p = (p >= 0 && p < T) ? p : 0;
-  int tk = a.token[base + nd];
-  tk = (tk >= 0 && tk < a.vocab) ? tk : 0;
-  const float *h = reinterpret_cast<const float *>(a.hidden_states) + (base + p) * (size_t)a.hidden;
-  const float *w = reinterpret_cast<const float *>(a.head_weight) + (size_t)tk * a.hidden;
-  float acc = 0.f;
-  for (int x = 0; x < a.hidden; ++x) acc = fmaf(h[x], w[x], acc);
-  a.own[base + nd] = acc;
-}
-
 template <bool kBf16>
 __global__ __launch_bounds__(kScanThreads) void prune_prepare_kernel(PrepareArgs a) {
   const int table_groups = (a.B + kTableWaves - 1) / kTableWaves;
@@ -383,8 +392,7 @@ __global__ __launch_bounds__(kScanThreads) void prune_prepare_kernel(PrepareArgs
   const int groups = (a.T_max + kOwnNodes - 1) / kOwnNodes;
   const int ob = blockIdx.x - table_groups;
   const int b = ob / groups, group = ob - b * groups;
-  if (kBf16) own_scores_bf16(a, b, group);
-  else own_scores_f32(a, b, group);
+  own_scores<kBf16>(a, b, group);
 }
 
 // What the scoring kernels need besides the operands.
@@ -1153,55 +1161,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void early_head_bf16_kernel(
   }
 }
 
-// fp32 variant: one score per thread, a plain sequential dot product, then the same two
-// epilogues on a 256-wide slice of the row (column part = slice index).
-template <int KIND>
-__global__ __launch_bounds__(256) void early_head_f32_kernel(
-    int hidden, int vocab, int B, const float *__restrict__ hidden_states,
-    const float *__restrict__ head_weight, HeadTables tb) {
-  const int m = blockIdx.x;
-  if (m >= tb.row_base[B]) return;
-  const int v = blockIdx.y * 256 + threadIdx.x;
-  const bool in = v < vocab;
-  const float *h = hidden_states + (size_t)tb.row_src[m] * hidden;
-  const float *w = head_weight + (size_t)(in ? v : vocab - 1) * hidden;
-  float z = 0.f;
-  for (int x = 0; x < hidden; ++x) z = fmaf(h[x], w[x], z);
-  const int lane = threadIdx.x & 63;
-  if (KIND == 0) {
-    __shared__ int s_cnt[4];
-    const int pos = tb.row_info[2 * m], cc = tb.row_info[2 * m + 1];
-    for (int e = 0; e < cc; ++e) {
-      const int c = tb.child_list[pos + e];
-      const int t = tb.token[c];
-      const bool ok = t >= 0 && t < vocab;  // an id outside the vocabulary: the decision kernel fails it
-      const float own = tb.own[c];
-      const int cnt = __popcll(__ballot(ok && in && (z > own || (z == own && v < t))));
-      if (lane == 0) s_cnt[threadIdx.x >> 6] = cnt;
-      __syncthreads();
-      if (threadIdx.x == 0)
-        tb.cnt_part[(size_t)blockIdx.y * tb.cnt_stride + c] = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
-      __syncthreads();
-    }
-  } else {
-    float mx = in ? z : -INFINITY;
-    mx = wave_reduce_max(mx);
-    float sum = in ? expf(z - mx) : 0.f;
-    sum = wave_reduce_sum(sum);
-    __shared__ float s_m[4], s_s[4];
-    if (lane == 0) {
-      s_m[threadIdx.x >> 6] = mx;
-      s_s[threadIdx.x >> 6] = sum;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      for (int wv = 1; wv < 4; ++wv) lse_merge(mx, sum, s_m[wv], s_s[wv]);
-      float *dst = tb.lse_part + ((size_t)m * tb.parts + blockIdx.y) * 2;
-      dst[0] = mx;
-      dst[1] = sum;
-    }
-  }
-}
+#include "early_head_f32.h"
 
 // ------------------------------------------------------------------------------------
 // probability-based selection (Section 4.1, "Pruning Criterion", second criterion)
@@ -1218,7 +1178,7 @@ __global__ __launch_bounds__(kWave) void row_lse_kernel(int B, int vocab, int cu
   if (bf16) {
     n_parts = head_plan(m_total, vocab, cus, force).n_parts;
   } else {
-    n_parts = (vocab + 255) / 256;
+    n_parts = f32_plan(m_total, vocab).n_tiles;
   }
   const int lane = threadIdx.x;
   float mx = -INFINITY, sum = 0.f;
@@ -1296,7 +1256,7 @@ __global__ __launch_bounds__(PROPD_MAX_TREE * kCompactSplit) void prune_compact_
       if (bf16) {
         if (m_total > 0) n_tiles = head_plan(m_total, vocab, cus, force).n_tiles;
       } else if (m_total > 0) {
-        n_tiles = (vocab + 255) / 256;
+        n_tiles = f32_plan(m_total, vocab).n_tiles;
       }
     }
     int sum = 0;
@@ -1665,13 +1625,18 @@ static propd_status prune_impl(
                            hidden, vocab, B, cus, force, reinterpret_cast<const uint16_t *>(hidden_states),
                            reinterpret_cast<const uint16_t *>(head_weight), tb);
     } else {
-      dim3 grid((unsigned)ws.row_cap, (unsigned)((vocab + 255) / 256));
+      // two workgroups per compute unit (their LDS), fewer when even the largest row count has
+      // fewer tiles
+      const long long n_groups = ((vocab + 127) / 128 + kXcds - 1) / kXcds;
+      const long long most = kXcds * n_groups * (((long long)ws.row_cap + kF32MaxRows - 1) / kF32MaxRows);
+      const long long persistent = (2ll * cus + kXcds - 1) / kXcds * kXcds;
+      const unsigned grid = (unsigned)(most < persistent ? most : persistent);
       if (crit.kind == 0)
-        hipLaunchKernelGGL(early_head_f32_kernel<0>, grid, dim3(256), 0, st, hidden, vocab, B,
+        hipLaunchKernelGGL(early_head_f32_kernel<0>, dim3(grid), dim3(kF32Threads), 0, st, hidden, vocab, B,
                            reinterpret_cast<const float *>(hidden_states),
                            reinterpret_cast<const float *>(head_weight), tb);
       else
-        hipLaunchKernelGGL(early_head_f32_kernel<1>, grid, dim3(256), 0, st, hidden, vocab, B,
+        hipLaunchKernelGGL(early_head_f32_kernel<1>, dim3(grid), dim3(kF32Threads), 0, st, hidden, vocab, B,
                            reinterpret_cast<const float *>(hidden_states),
                            reinterpret_cast<const float *>(head_weight), tb);
     }
