@@ -131,9 +131,9 @@ PROPD_API propd_status propd_validate_tree(const propd_tree *tree, int32_t *flag
  *
  *   dt        PROPD_BF16: tensors are bf16, d in {64, 128}; scores, softmax and
  *             the output accumulation are fp32, the result is rounded to bf16.
- *             (d = 128, the head size of every model of Section 5.1, runs the tiled
- *             matrix-core kernel and needs 16-byte aligned tensors and workspace;
- *             d = 64 runs a plain one-wave-per-query kernel, without workspace.)
+ *             (Both run the tiled matrix-core kernel.  d = 128, the head size of every
+ *             model of Section 5.1, needs 16-byte aligned tensors and the workspace; d = 64
+ *             is served without either, by a plain and far slower kernel.)
  *             PROPD_F32: tensors are fp32, d in {64, 128}, fp32 throughout.
  *   q, k_tree, v_tree, out   [B,H,T_max,d]
  *   k_cache, v_cache         [B,H,L_max,d]; rows >= L_b are never used

@@ -1,7 +1,7 @@
 // Tree-masked attention over the cached prefix plus each node's own root path
 // (Section 2, "Verification"; Figure 2(b,c)).
 //
-// bf16 path (d = 128).  The work is a stream of K/V rows from HBM that all T
+// bf16 path (d = 64 and 128).  The work is a stream of K/V rows from HBM that all T
 // tree queries of a (sequence, head) pair share, so the kernel is organised
 // around reading every K and V row exactly once, as fast as HBM delivers them:
 //   - the work of a call is the list of 32-row K/V stages of all (sequence, head)
@@ -26,21 +26,44 @@
 //   - a unit cut by a range boundary leaves fp32 partials (O, max, sum), at most
 //     two per workgroup, and the workgroup holding its first piece leaves a record of the
 //     cut; a second kernel merges the pieces of every recorded cut, in their order.
-// fp32 path: a plain one-wave-per-query kernel, fp32 throughout.
+// Both head sizes run the same kernel.  d = 64 came from one wave per query (each lane walking K rows
+// of its own): 8 x 16 units of 64 queries x 2048 keys, 4150 -> 28 us + 5.5 us merge (67 MB of K/V).
+// fp32 path, and d = 64 without a workspace or 16-byte alignment: a plain one-wave-per-query
+// kernel, fp32 throughout.
 #include <type_traits>
 
 #include "common.h"
 
 namespace propd {
 
-constexpr int kD = 128;
 constexpr int kAttnThreads = 256;
-constexpr int kMaxGrid = 1024;                 // workgroups of the persistent kernel, at most
-constexpr int kStageRows = 32;                 // K/V rows per ring stage
-constexpr int kRowBytes = kD * 2;              // one bf16 row
-constexpr int kHalfStage = kStageRows * kRowBytes;  // K part of a stage; the V part follows
-constexpr int kStageBytes = 2 * kHalfStage;
-constexpr int kRingStages = 5;  // 16 KB each; two workgroups per CU share 160 KB
+constexpr int kMaxGrid = 1024;   // workgroups of the persistent kernel, at most
+constexpr int kStageRows = 32;   // K/V rows per ring stage
+constexpr int kRingStages = 5;
+
+// What depends on the head size D.
+template <int D>
+struct Geo {
+  static constexpr int kRowBytes = D * 2;                     // one bf16 row
+  static constexpr int kHalfStage = kStageRows * kRowBytes;   // K part of a stage; the V part follows
+  static constexpr int kStageBytes = 2 * kHalfStage;          // 16 KB (D = 128) or 8 KB
+  static constexpr int kChunks = kRowBytes / 16;              // 16-byte chunks of a row
+  static constexpr int kLdRows = 1024 / kRowBytes;            // rows that one direct load of a wave fills
+  static constexpr int kLoads = kHalfStage / 4096;            // direct loads of a wave per half stage
+  static constexpr int kKs = D / 16, kMb = D / 32;            // MFMA steps over d of QK^T; 32-wide blocks of d of PV
+  // Workgroups resident on a compute unit: what LDS (two rings of 80 KB at D = 128) and registers
+  // (254; 195 at D = 64) allow.  A bound of more workgroups spills, which this kernel must not:
+  // loads that it waits for by hand would land in registers given away meanwhile.
+  static constexpr int kPerCu = 2;
+  // Chunk c of row r of a stage lies at chunk position c ^ key(r).
+  //   K: the 16 rows x 16 bytes that one pass of a fragment read takes (one chunk column) fall
+  //      into 16 different bank groups (rows of 128 bytes: two rows share a 256-byte bank line)
+  //   V: so do the 4 rows x 64 bytes of one transposing read
+  static __device__ __forceinline__ int k_key(int r) { return D == 128 ? r & 15 : (r >> 1) & 7; }
+  static __device__ __forceinline__ int v_key(int r) {
+    return D == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : ((r >> 1) & 1) << 2;
+  }
+};
 
 struct AttnParams {
   const uint16_t *q, *k_cache, *v_cache, *k_tree, *v_tree;
@@ -48,7 +71,7 @@ struct AttnParams {
   const int32_t *seq_lens, *n_nodes;
   const uint64_t *anc;
   int B, H, T_max, L_max;
-  float scale_log2e;
+  float scale, scale_log2e;
   float *part_o;   // [2 * grid][4 waves][16 blocks][64 lanes][4]
   float *part_ml;  // [2 * grid][4 waves][m | l][64 lanes]
   int32_t *cuts;   // [grid][4] per workgroup: the unit whose first piece it holds (CutRecord)
@@ -80,6 +103,10 @@ __device__ __forceinline__ u32x2 lds_read_tr16(uint32_t addr) {
 
 // wait until at most N LDS operations of this wave are outstanding; the registers named
 // are the results being waited for, so that their uses cannot be scheduled above the wait
+template <int N>
+__device__ __forceinline__ void wait_lds(u32x2 (&a)[4]) {
+  asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]) : "n"(N));
+}
 template <int N>
 __device__ __forceinline__ void wait_lds(u32x2 (&a)[8]) {
   asm volatile("s_waitcnt lgkmcnt(%8)"
@@ -143,10 +170,10 @@ __device__ __forceinline__ void store_out_block(uint16_t *orow, const f32x16 &o,
   }
 }
 
-template <bool kUntracked>
-__device__ __forceinline__ void store_out_row(uint16_t *orow, const f32x16 (&o)[4], float inv, int g) {
+template <bool kUntracked, int MB>
+__device__ __forceinline__ void store_out_row(uint16_t *orow, const f32x16 (&o)[MB], float inv, int g) {
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb) store_out_block<kUntracked>(orow, o[mb], inv, g, mb);
+  for (int mb = 0; mb < MB; ++mb) store_out_block<kUntracked>(orow, o[mb], inv, g, mb);
 }
 
 // Partial results keep the register layout, so that a wave writes and reads them as
@@ -397,8 +424,102 @@ struct Walk {
   }
 };
 
-template <int NS>
-__global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnParams p) {
+__device__ __forceinline__ float plain_load(const float *p) { return *p; }
+__device__ __forceinline__ float plain_load(const uint16_t *p) { return bf16_bits_to_f32(*p); }
+__device__ __forceinline__ void plain_store(float *p, float x) { *p = x; }
+__device__ __forceinline__ void plain_store(uint16_t *p, float x) { *p = (uint16_t)f32_to_bf16_bits(x); }
+
+// One query by one wave, products, softmax and output sums in fp32; columns [c_lo, c_hi) of its
+// row are stored.  Rows of V with weight zero are not looked at, so a value that is not finite
+// reaches the queries that see it and no others.
+template <typename P>
+__device__ __forceinline__ void plain_query(const P &p, int unit, int i, int d, int c_lo, int c_hi) {
+  const int b = unit / p.H;
+  int L = p.seq_lens[b];
+  L = L < 0 ? 0 : (L > p.L_max ? p.L_max : L);
+  int T = p.n_nodes[b];
+  T = T < 1 ? 1 : (T > p.T_max ? p.T_max : T);
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint64_t a_lo = p.anc[((size_t)b * p.T_max + i) * 2];
+  const uint64_t a_hi = p.anc[((size_t)b * p.T_max + i) * 2 + 1];
+  const auto *q = p.q + ((size_t)unit * p.T_max + i) * d;
+  const auto *kc = p.k_cache + (size_t)unit * p.L_max * d;
+  const auto *vc = p.v_cache + (size_t)unit * p.L_max * d;
+  const auto *kt = p.k_tree + (size_t)unit * p.T_max * d;
+  const auto *vt = p.v_tree + (size_t)unit * p.T_max * d;
+
+  float m_run = -INFINITY, l_run = 0.f, o0 = 0.f, o1 = 0.f;  // lane owns columns lane, lane+64
+  const int total = L + T;
+  for (int j0 = 0; j0 < total; j0 += kWave) {
+    const int j = j0 + lane;
+    const bool in_cache = j < L;
+    const int jt = j - L;
+    const bool ok = in_cache || (j < total && test_bit128(a_lo, a_hi, jt));
+    float s = -INFINITY;
+    if (ok) {
+      const auto *kr = in_cache ? kc + (size_t)j * d : kt + (size_t)jt * d;
+      float acc = 0.f;
+      for (int x = 0; x < d; ++x) acc = fmaf(plain_load(q + x), plain_load(kr + x), acc);
+      s = acc * p.scale;
+    }
+    const float m_new = fmaxf(m_run, wave_reduce_max(s));
+    if (m_new == -INFINITY) continue;  // nothing visible in this chunk (uniform across the wave)
+    const float alpha = expf(m_run - m_new);
+    const float w = ok ? expf(s - m_new) : 0.f;
+    l_run = l_run * alpha + wave_reduce_sum(w);
+    o0 *= alpha;
+    o1 *= alpha;
+    m_run = m_new;
+    const uint64_t live = __ballot(w != 0.f);
+    for (uint64_t rest = live; rest; rest &= rest - 1) {
+      const int src = __ffsll((long long)rest) - 1;
+      const float wj = __shfl(w, src, kWave);
+      const int jj = j0 + src;
+      const auto *vr = jj < L ? vc + (size_t)jj * d : vt + (size_t)(jj - L) * d;
+      if (lane < d) o0 = fmaf(wj, plain_load(vr + lane), o0);
+      if (lane + 64 < d) o1 = fmaf(wj, plain_load(vr + lane + 64), o1);
+    }
+  }
+  auto *o = p.out + ((size_t)unit * p.T_max + i) * d;
+  if (lane >= c_lo && lane < c_hi) plain_store(o + lane, o0 / l_run);
+  if (lane + 64 >= c_lo && lane + 64 < c_hi) plain_store(o + lane + 64, o1 / l_run);
+}
+
+// The tiled kernels multiply masked rows by a weight of zero, which a value that is not finite
+// turns into NaN for every query of the tile.  D = 64 and fp32 operands keep such values to the
+// queries that see them: a result with a NaN in it is computed once more, query by query, by
+// plain_query.  `bad`: the lane's part of its query's row (query l32, both lane halves) holds
+// a NaN.  Returns whether the lane's query was taken over.
+template <typename P>
+__device__ __forceinline__ bool redo_not_finite(const P &p, bool bad, int unit, int t0, int d, int c_lo, int c_hi) {
+  const uint64_t both = __ballot(bad);
+  if (both == 0) return false;
+  const uint32_t queries = (uint32_t)both | (uint32_t)(both >> 32);
+  for (uint32_t rest = queries; rest; rest &= rest - 1)
+    plain_query(p, unit, t0 + __ffs((int)rest) - 1, d, c_lo, c_hi);
+  return ((queries >> (threadIdx.x & 31)) & 1u) != 0;
+}
+
+template <int MB>
+__device__ __forceinline__ bool has_nan(const f32x16 (&o)[MB]) {
+  float sum = 0.f;  // NaN as soon as a term is (and for +inf - inf, which then is done twice for nothing)
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sum += o[mb][r];
+  return sum != sum;
+}
+
+// D = 128 multiplies bf16 weights with V.  D = 64 keeps them in fp32 precision: a weight is the
+// sum of two bf16 values, both of which are multiplied, and the row sums are taken over the fp32
+// weights.  (The extra products are free, a stage is bound by its K/V bytes.)
+template <int NS, int D>
+__global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_kernel(AttnParams p) {
+  using G_ = Geo<D>;
+  constexpr int kRowBytes = G_::kRowBytes, kHalfStage = G_::kHalfStage, kStageBytes = G_::kStageBytes;
+  constexpr int kKs = G_::kKs, kMb = G_::kMb, kLoads = G_::kLoads;
+  constexpr bool kTwoPart = D == 64;  // weights as two bf16 values
+  constexpr int kParts = kTwoPart ? 2 : 1;
   static_assert(NS >= 4, "three stages are in use by the math, the rest is in flight");
   constexpr int kAhead = NS - 3;  // stages in flight beyond the newest one the math uses
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -427,16 +548,14 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnPar
   //      rows or the tree rows of a unit) at a time.  One direct load moves 64 lanes x 16
   //      bytes = 4 rows into 1 KB of LDS that is contiguous in lane order, so the swizzle is
   //      applied on the global side: the lane that fills chunk c of LDS row r fetches chunk
-  //      c ^ key(r) of the global row.  Keys: K rows r & 15 (a 16-byte read of one chunk
-  //      column over 16 rows touches 16 distinct chunks); V rows ((r & 3) << 2) | ((r >> 2) & 3)
-  //      (the 4 rows x 64 bytes of one transposing read land in 4 distinct 64-byte bank
-  //      groups).  A wave fills rows 4*wave + lane/16 of each 16-row half, so its keys do not
-  //      depend on the half.  Rows past the last valid one of a segment re-read that last
-  //      row: finite data that the mask discards (K) or that meets a zero weight (V);
-  //      padding is never touched.
-  const int ld_row = 4 * wave + (lane >> 4);
-  const int k_lane_chunk = ((lane & 15) ^ ld_row) << 4;
-  const int v_lane_chunk = ((lane & 15) ^ (((lane >> 4) << 2) | wave)) << 4;
+  //      c ^ key(r) of the global row.  A wave fills kLdRows consecutive rows per load, of each
+  //      block of 4 * kLdRows rows; its keys do not depend on the block.  Rows past the last
+  //      valid one of a segment re-read that last row: finite data that the mask discards (K) or
+  //      that meets a zero weight (V); padding is never touched.
+  constexpr int kLdRows = G_::kLdRows;
+  const int ld_row = kLdRows * wave + lane / G_::kChunks;
+  const int k_lane_chunk = ((lane % G_::kChunks) ^ G_::k_key(ld_row)) << 4;
+  const int v_lane_chunk = ((lane % G_::kChunks) ^ G_::v_key(ld_row)) << 4;
   Walk lw = cp;  // the next stage to issue
   int ld_rows;                       // rows left in the segment, from the next stage to issue
   const unsigned char *ld_k, *ld_v;  // first row of the next stage to issue
@@ -453,21 +572,21 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnPar
     __builtin_amdgcn_global_load_lds((global_void *)src, (lds_void *)dst, 16, 0, 2 /* nt */);
   };
   auto issue = [&](int slot) {
-    unsigned char *dst = smem + slot * kStageBytes + (4 * wave) * kRowBytes;
+    unsigned char *dst = smem + slot * kStageBytes + wave * 1024;
     if (ld_rows >= kStageRows) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int ro = (16 * i + ld_row) * kRowBytes;
-        dma16(ld_k + (ro + k_lane_chunk), dst + i * 16 * kRowBytes);
-        dma16(ld_v + (ro + v_lane_chunk), dst + kHalfStage + i * 16 * kRowBytes);
+      for (int i = 0; i < kLoads; ++i) {
+        const int ro = (4 * kLdRows * i + ld_row) * kRowBytes;
+        dma16(ld_k + (ro + k_lane_chunk), dst + i * 4096);
+        dma16(ld_v + (ro + v_lane_chunk), dst + kHalfStage + i * 4096);
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        int row = 16 * i + ld_row;
+      for (int i = 0; i < kLoads; ++i) {
+        int row = 4 * kLdRows * i + ld_row;
         row = row < ld_rows ? row : ld_rows - 1;
-        dma16(ld_k + (row * kRowBytes + k_lane_chunk), dst + i * 16 * kRowBytes);
-        dma16(ld_v + (row * kRowBytes + v_lane_chunk), dst + kHalfStage + i * 16 * kRowBytes);
+        dma16(ld_k + (row * kRowBytes + k_lane_chunk), dst + i * 4096);
+        dma16(ld_v + (row * kRowBytes + v_lane_chunk), dst + kHalfStage + i * 4096);
       }
     }
     lw.advance(map, G, 1);
@@ -482,28 +601,27 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnPar
 
   // ---- per-lane LDS read offsets within a stage
   // K as the A operand of S^T: lane = row l32, 8 consecutive d from 16*ks + 8*g (chunk 2*ks + g)
-  uint32_t k_rd[8];
+  uint32_t k_rd[kKs];
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks)
-    k_rd[ks] = smem_base + l32 * kRowBytes + (((2 * ks + g) ^ (l32 & 15)) << 4);
+  for (int ks = 0; ks < kKs; ++ks)
+    k_rd[ks] = smem_base + l32 * kRowBytes + (((2 * ks + g) ^ G_::k_key(l32)) << 4);
   // V^T as the A operand of O^T: transposing read; in each group of 16 lanes, lane i points at
   // row i/4, 4 columns from 4*(i%4), and receives column i of those 4 rows.  Per MFMA k-step
   // (16 rows): slots 0..3 = rows 4g + 0..3, slots 4..7 = those rows + 8.
-  uint32_t v_rd[4][2];
+  uint32_t v_rd[kMb][2];
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
+  for (int mb = 0; mb < kMb; ++mb)
 #pragma unroll
     for (int hi = 0; hi < 2; ++hi) {
       const int r = 4 * g + ((lane & 15) >> 2) + 8 * hi;
-      const int key = ((r & 3) << 2) | ((r >> 2) & 3);
       const int chunk = mb * 4 + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-      v_rd[mb][hi] = smem_base + kHalfStage + r * kRowBytes + ((chunk ^ key) << 4) + 8 * (lane & 1);
+      v_rd[mb][hi] = smem_base + kHalfStage + r * kRowBytes + ((chunk ^ G_::v_key(r)) << 4) + 8 * (lane & 1);
     }
 
   // ---- ring bookkeeping.  acquire() is called once per stage of the range, in order, by
   //      every wave: it waits for the stage's loads, meets the other waves, and refills the
   //      slot whose stage every wave finished two acquires ago.  Vector memory loads of a
-  //      wave complete in issue order, so "stage x has landed" is "at most 4 operations
+  //      wave complete in issue order, so "stage x has landed" is "at most one stage's operations
   //      outstanding": the loads of stage x+1.  Query loads and output stores that the wave
   //      issued since then are waited for as well (loads and stores are not ordered against
   //      each other, so the stores cannot be counted off).
@@ -519,7 +637,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnPar
       slot_ld = next_slot(slot_ld);
     }
   auto acquire = [&]() -> int {
-    if (n_acq + 1 < n_my) wait_vmem<4>(); else wait_vmem<0>();
+    if (n_acq + 1 < n_my) wait_vmem<2 * kLoads>(); else wait_vmem<0>();
     __builtin_amdgcn_s_barrier();
     if (n_acq + kAhead < n_my) {
       issue(slot_ld);
@@ -561,19 +679,26 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnPar
   // Q^T fragments (B operand: lane = query column, 8 consecutive d per K step) and the
   // ancestor set of this lane's node.  Lanes past the tree take node 0: valid memory, and
   // their columns are never stored.
-  u32x4 qf[8], ancv;
+  u32x4 qf[kKs], ancv;
+  // D = 64: left to the compiler, since code that it may move registers in (redo_not_finite) runs
+  // while they are in flight; its waits come where wait_queries() waits for everything anyway
+  auto load16 = [](const void *ptr) {
+    if constexpr (kTwoPart) return *reinterpret_cast<const u32x4 *>(ptr);
+    else return global_load16_untracked(ptr);
+  };
   auto load_queries = [&](const Piece &pc) {
     const int tq = t < pc.T ? t : 0;
-    const uint16_t *qrow = p.q + ((size_t)pc.unit * p.T_max + tq) * kD + g * 8;
+    const uint16_t *qrow = p.q + ((size_t)pc.unit * p.T_max + tq) * D + g * 8;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qf[ks] = global_load16_untracked(qrow + ks * 16);
-    ancv = global_load16_untracked(p.anc + ((size_t)pc.b * p.T_max + tq) * 2);
+    for (int ks = 0; ks < kKs; ++ks) qf[ks] = load16(qrow + ks * 16);
+    ancv = load16(p.anc + ((size_t)pc.b * p.T_max + tq) * 2);
   };
   auto wait_queries = [&]() {
     // the registers are named so that their uses cannot be scheduled above the wait
     auto tie = [&]() {
-      asm volatile("" : "+v"(qf[0]), "+v"(qf[1]), "+v"(qf[2]), "+v"(qf[3]), "+v"(qf[4]), "+v"(qf[5]),
-                        "+v"(qf[6]), "+v"(qf[7]), "+v"(ancv));
+#pragma unroll
+      for (int ks = 0; ks < kKs; ++ks) asm volatile("" : "+v"(qf[ks]));
+      asm volatile("" : "+v"(ancv));
     };
     tie();
     wait_vmem<0>();
@@ -581,8 +706,8 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnPar
   };
 
   float m_run, l_run;
-  f32x16 o_acc[4];
-  u32x2 vt[2][8];
+  f32x16 o_acc[kMb];
+  u32x2 vt[2][2 * kMb];
   // S^T = K . Q^T of one stage
   auto scores = [&](int sl) -> f32x16 {
     const uint32_t so = (uint32_t)sl * kStageBytes;
@@ -590,7 +715,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnPar
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
+    for (int ks = 0; ks < kKs; ++ks) {
       const bf16x8 a = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8 *>(
           (uintptr_t)(k_rd[ks] + so));
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, qf[ks]), acc, 0, 0, 0);
@@ -601,30 +726,33 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnPar
   auto read_v = [&](int sl) {
     const uint32_t so = (uint32_t)sl * kStageBytes;
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
+    for (int mb = 0; mb < kMb; ++mb) {
       vt[0][2 * mb] = lds_read_tr16<0>(v_rd[mb][0] + so);
       vt[0][2 * mb + 1] = lds_read_tr16<0>(v_rd[mb][1] + so);
     }
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
+    for (int mb = 0; mb < kMb; ++mb) {
       vt[1][2 * mb] = lds_read_tr16<16 * kRowBytes>(v_rd[mb][0] + so);
       vt[1][2 * mb + 1] = lds_read_tr16<16 * kRowBytes>(v_rd[mb][1] + so);
     }
   };
   // O^T += V^T . P^T with the V registers read last and the given weights
-  auto weighted_sum = [&](const uint32_t (&pw)[8]) {
+  auto weighted_sum = [&](const uint32_t (&pw)[kParts][8]) {
     wait_lds<0>(vt[0]);
     wait_lds<0>(vt[1]);
 #pragma unroll
     for (int ks2 = 0; ks2 < 2; ++ks2) {
-      const u32x4 pv = {pw[4 * ks2], pw[4 * ks2 + 1], pw[4 * ks2 + 2], pw[4 * ks2 + 3]};
-      const bf16x8 pf = __builtin_bit_cast(bf16x8, pv);
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        const u32x4 aw = {vt[ks2][2 * mb].x, vt[ks2][2 * mb].y, vt[ks2][2 * mb + 1].x,
-                          vt[ks2][2 * mb + 1].y};
-        o_acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, aw), pf,
-                                                            o_acc[mb], 0, 0, 0);
+      for (int part = kParts - 1; part >= 0; --part) {  // the small part first
+        const u32x4 pv = {pw[part][4 * ks2], pw[part][4 * ks2 + 1], pw[part][4 * ks2 + 2], pw[part][4 * ks2 + 3]};
+        const bf16x8 pf = __builtin_bit_cast(bf16x8, pv);
+#pragma unroll
+        for (int mb = 0; mb < kMb; ++mb) {
+          const u32x4 aw = {vt[ks2][2 * mb].x, vt[ks2][2 * mb].y, vt[ks2][2 * mb + 1].x,
+                            vt[ks2][2 * mb + 1].y};
+          o_acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, aw), pf,
+                                                              o_acc[mb], 0, 0, 0);
+        }
       }
     }
   };
@@ -641,7 +769,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnPar
     m_run = -INFINITY;
     l_run = 0.f;
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int mb = 0; mb < kMb; ++mb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o_acc[mb][r] = 0.f;
 
@@ -653,9 +781,14 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnPar
       wait_queries();
       const uint64_t anc_lo = ((uint64_t)ancv.y << 32) | ancv.x, anc_hi = ((uint64_t)ancv.w << 32) | ancv.z;
       f32x16 sc = scores(sl_cur);
-      uint32_t pw_prev[8];
+      uint32_t pw_prev[kParts][8];
+      auto clear_prev = [&]() {
 #pragma unroll
-      for (int r = 0; r < 8; ++r) pw_prev[r] = 0u;
+        for (int part = 0; part < kParts; ++part)
+#pragma unroll
+          for (int r = 0; r < 8; ++r) pw_prev[part][r] = 0u;
+      };
+      clear_prev();
 
       auto stage = [&](int i, auto has_next, auto has_prev) {
         constexpr bool kNext = decltype(has_next)::value, kPrev = decltype(has_prev)::value;
@@ -696,8 +829,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnPar
           // weights are relative to the old reference.
           if (kPrev) {
             weighted_sum(pw_prev);
-#pragma unroll
-            for (int r = 0; r < 8; ++r) pw_prev[r] = 0u;
+            clear_prev();
             mfma_settle();
           }
           const float m_new = fmaxf(m_run, m_blk);
@@ -705,7 +837,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnPar
           const float alpha = fast_exp2((m_run - m_safe) * p.scale_log2e);
           l_run *= alpha;
 #pragma unroll
-          for (int mb = 0; mb < 4; ++mb)
+          for (int mb = 0; mb < kMb; ++mb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) o_acc[mb][r] *= alpha;
           m_run = m_new;
@@ -715,20 +847,28 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnPar
         // ---- one block: scores of the next stage, weights of this one, O update of the last
         f32x16 sc_next;
         if (kNext) sc_next = scores(sl_next);
-        uint32_t pw[8];
+        uint32_t pw[kParts][8];
 #pragma unroll
         for (int r = 0; r < 16; r += 2) {
           const float p0 = fast_exp2(fmaf(sc[r], p.scale_log2e, neg_m));
           const float p1 = fast_exp2(fmaf(sc[r + 1], p.scale_log2e, neg_m));
-          pw[r >> 1] = cvt_pk_bf16(p0, p1);
-          // the row sums are taken over the rounded bf16 weights, the values the MFMA multiplies
-          l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pw[r >> 1]), ones,
-                                                  l_run, false);
+          pw[0][r >> 1] = cvt_pk_bf16(p0, p1);
+          if constexpr (kTwoPart) {
+            pw[1][r >> 1] = cvt_pk_bf16(p0 - __uint_as_float(pw[0][r >> 1] << 16),
+                                        p1 - __uint_as_float(pw[0][r >> 1] & 0xffff0000u));
+            l_run += p0 + p1;
+          } else {
+            // the row sums are taken over the rounded bf16 weights, the values the MFMA multiplies
+            l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pw[0][r >> 1]), ones,
+                                                    l_run, false);
+          }
         }
         if (kPrev) weighted_sum(pw_prev);
         read_v(sl_cur);  // V of this stage, used by the next iteration or the drain
 #pragma unroll
-        for (int r = 0; r < 8; ++r) pw_prev[r] = pw[r];
+        for (int part = 0; part < kParts; ++part)
+#pragma unroll
+          for (int r = 0; r < 8; ++r) pw_prev[part][r] = pw[part][r];
         if (kNext) {
           sc = sc_next;
           sl_cur = sl_next;
@@ -763,8 +903,14 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnPar
     m_run *= p.scale_log2e;  // from here on the maximum is in the exponent's (log2) domain
     if (wave * 32 < T) {
       if (done.whole) {
-        if (t < T)
-          store_out_row<true>(p.out + ((size_t)done.unit * p.T_max + t) * kD, o_acc, 1.f / l_run, g);
+        const float inv = 1.f / l_run;
+        bool mine = t < T;
+        if constexpr (kTwoPart) {
+          const bool bad = mine && (has_nan(o_acc) || inv != inv);
+          if (redo_not_finite(p, bad, done.unit, wave * 32, D, 0, D)) mine = false;
+        }
+        if (mine)
+          store_out_row<true>(p.out + ((size_t)done.unit * p.T_max + t) * D, o_acc, inv, g);
       } else {
         // a range starts inside at most one unit and ends inside at most one
         const size_t ps = 2 * (size_t)w + (s0 > 0 ? 0 : 1);
@@ -777,7 +923,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnPar
         }
         if (t < T) {
 #pragma unroll
-          for (int mb = 0; mb < 4; ++mb)
+          for (int mb = 0; mb < kMb; ++mb)
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
               const f32x4 w4 = {o_acc[mb][4 * q4], o_acc[mb][4 * q4 + 1], o_acc[mb][4 * q4 + 2],
@@ -802,8 +948,10 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_bf16_kernel(AttnPar
 // Lanes map to (query, d) exactly as in the main kernel; a wave owns one 32-wide block mb of d.
 constexpr int kCombinePieces = 4;
 
+template <int D>
 __global__ __launch_bounds__(kWave) void tree_attn_combine_kernel(AttnParams p) {
-  const int w = blockIdx.x >> 4, dw = (blockIdx.x >> 2) & 3, mb = blockIdx.x & 3;
+  constexpr int kMb = Geo<D>::kMb;
+  const int w = blockIdx.x / (4 * kMb), dw = (blockIdx.x / kMb) & 3, mb = blockIdx.x % kMb;
   const CutRecord cut = *reinterpret_cast<const CutRecord *>(p.cuts + 4 * w);
   if (cut.unit < 0) return;
   const int T = cut.w_last_and_nodes >> 16, w_last = cut.w_last_and_nodes & 0xffff;
@@ -844,13 +992,20 @@ __global__ __launch_bounds__(kWave) void tree_attn_combine_kernel(AttnParams p) 
     }
   }
   // the two lanes of an exchange pair hold the same query, so they are active together
-  if (t < T) store_out_block<false>(p.out + ((size_t)cut.unit * p.T_max + t) * kD, acc, 1.f / lsum, g, mb);
+  const float inv = 1.f / lsum;
+  bool mine = t < T;
+  if constexpr (D == 64) {
+    const f32x16 (&block)[1] = reinterpret_cast<const f32x16 (&)[1]>(acc);
+    const bool bad = mine && (has_nan(block) || inv != inv);
+    if (redo_not_finite(p, bad, cut.unit, dw * 32, D, 32 * mb, 32 * mb + 32)) mine = false;
+  }
+  if (mine) store_out_block<false>(p.out + ((size_t)cut.unit * p.T_max + t) * D, acc, inv, g, mb);
 }
 
 // ------------------------------------------------------------------------------------
 // Plain path: one wave per (sequence, head, node); products, softmax and output sums in fp32.
-// Serves fp32 operands (d = 64 or 128) and bf16 operands with d = 64, the head size the
-// tiled kernel above is not written for; the result is stored in the operands' type.
+// Serves fp32 operands (d = 64 or 128) and bf16 operands with d = 64 that come without the
+// workspace or the alignment of the tiled kernel; the result is stored in the operands' type.
 // ------------------------------------------------------------------------------------
 template <typename E>
 struct AttnParamsPlain {
@@ -862,64 +1017,13 @@ struct AttnParamsPlain {
   float scale;
 };
 
-__device__ __forceinline__ float plain_load(const float *p) { return *p; }
-__device__ __forceinline__ float plain_load(const uint16_t *p) { return bf16_bits_to_f32(*p); }
-__device__ __forceinline__ void plain_store(float *p, float x) { *p = x; }
-__device__ __forceinline__ void plain_store(uint16_t *p, float x) { *p = (uint16_t)f32_to_bf16_bits(x); }
-
 template <typename E>
 __global__ __launch_bounds__(kWave) void tree_attn_plain_kernel(AttnParamsPlain<E> p) {
   const int unit = blockIdx.x / p.T_max, i = blockIdx.x - unit * p.T_max;
-  const int b = unit / p.H;
-  int L = p.seq_lens[b];
-  L = L < 0 ? 0 : (L > p.L_max ? p.L_max : L);
-  int T = p.n_nodes[b];
+  int T = p.n_nodes[unit / p.H];
   T = T < 1 ? 1 : (T > p.T_max ? p.T_max : T);
   if (i >= T) return;
-  const int lane = threadIdx.x, d = p.d;
-  const uint64_t a_lo = p.anc[((size_t)b * p.T_max + i) * 2];
-  const uint64_t a_hi = p.anc[((size_t)b * p.T_max + i) * 2 + 1];
-  const E *q = p.q + ((size_t)unit * p.T_max + i) * d;
-  const E *kc = p.k_cache + (size_t)unit * p.L_max * d;
-  const E *vc = p.v_cache + (size_t)unit * p.L_max * d;
-  const E *kt = p.k_tree + (size_t)unit * p.T_max * d;
-  const E *vt = p.v_tree + (size_t)unit * p.T_max * d;
-
-  float m_run = -INFINITY, l_run = 0.f, o0 = 0.f, o1 = 0.f;  // lane owns columns lane, lane+64
-  const int total = L + T;
-  for (int j0 = 0; j0 < total; j0 += kWave) {
-    const int j = j0 + lane;
-    const bool in_cache = j < L;
-    const int jt = j - L;
-    const bool ok = in_cache || (j < total && test_bit128(a_lo, a_hi, jt));
-    float s = -INFINITY;
-    if (ok) {
-      const E *kr = in_cache ? kc + (size_t)j * d : kt + (size_t)jt * d;
-      float acc = 0.f;
-      for (int x = 0; x < d; ++x) acc = fmaf(plain_load(q + x), plain_load(kr + x), acc);
-      s = acc * p.scale;
-    }
-    const float m_new = fmaxf(m_run, wave_reduce_max(s));
-    if (m_new == -INFINITY) continue;  // nothing visible in this chunk (uniform across the wave)
-    const float alpha = expf(m_run - m_new);
-    const float w = ok ? expf(s - m_new) : 0.f;
-    l_run = l_run * alpha + wave_reduce_sum(w);
-    o0 *= alpha;
-    o1 *= alpha;
-    m_run = m_new;
-    const uint64_t live = __ballot(w != 0.f);
-    for (uint64_t rest = live; rest; rest &= rest - 1) {
-      const int src = __ffsll((long long)rest) - 1;
-      const float wj = __shfl(w, src, kWave);
-      const int jj = j0 + src;
-      const E *vr = jj < L ? vc + (size_t)jj * d : vt + (size_t)(jj - L) * d;
-      if (lane < d) o0 = fmaf(wj, plain_load(vr + lane), o0);
-      if (lane + 64 < d) o1 = fmaf(wj, plain_load(vr + lane + 64), o1);
-    }
-  }
-  E *o = p.out + ((size_t)unit * p.T_max + i) * d;
-  if (lane < d) plain_store(o + lane, o0 / l_run);
-  if (lane + 64 < d) plain_store(o + lane + 64, o1 / l_run);
+  plain_query(p, unit, i, p.d, 0, p.d);
 }
 
 template <typename E>
@@ -971,9 +1075,9 @@ static int grid_bound(int B, int H, int L_max, int T_max) {
   return (int)(grid < 1 ? 1 : grid);
 }
 
-// ... and two per compute unit (what LDS allows to be resident).
-static int pick_grid(int B, int H, int L_max, int T_max) {
-  const int bound = grid_bound(B, H, L_max, T_max), resident = 2 * compute_units();
+// ... and as many as are resident on the chip.
+static int pick_grid(int per_cu, int B, int H, int L_max, int T_max) {
+  const int bound = grid_bound(B, H, L_max, T_max), resident = per_cu * compute_units();
   return bound < resident ? bound : resident;
 }
 
@@ -985,19 +1089,20 @@ size_t tree_attention_workspace_bytes(int B, int H, int L_max, int T_max) {
          align_up(grid * sizeof(CutRecord), 256);
 }
 
+template <int D>
 static bool launch_bf16(const AttnParams &p, int grid, hipStream_t st) {
-  constexpr int lds_bytes = kRingStages * kStageBytes;
+  constexpr int lds_bytes = kRingStages * Geo<D>::kStageBytes;
   static bool attr_set = false;
   if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_bf16_kernel<kRingStages>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_bf16_kernel<kRingStages, D>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes) != hipSuccess)
       return false;
     attr_set = true;
   }
-  hipLaunchKernelGGL(tree_attn_bf16_kernel<kRingStages>, dim3((unsigned)grid), dim3(kAttnThreads),
+  hipLaunchKernelGGL((tree_attn_bf16_kernel<kRingStages, D>), dim3((unsigned)grid), dim3(kAttnThreads),
                      lds_bytes, st, p);
   if (!launch_ok()) return false;
-  hipLaunchKernelGGL(tree_attn_combine_kernel, dim3((unsigned)grid * 16), dim3(kWave), 0, st, p);
+  hipLaunchKernelGGL(tree_attn_combine_kernel<D>, dim3((unsigned)grid * 4 * Geo<D>::kMb), dim3(kWave), 0, st, p);
   return launch_ok();
 }
 
@@ -1027,18 +1132,20 @@ extern "C" propd_status propd_tree_attention(const propd_tree *tree, propd_dtype
                ? PROPD_OK
                : PROPD_ERR_DEVICE;
   }
-  if (d == 64)  // bf16, the smaller head: no workspace is used
+  if (d != 64 && d != 128) return PROPD_ERR_UNSUPPORTED;
+  // rows are moved 16 bytes per lane, by direct loads to LDS and four-dword loads and stores
+  bool aligned = true;
+  for (const void *ptr : {q, k_cache, v_cache, k_tree, v_tree, (const void *)out, (const void *)tree->anc,
+                          (const void *)workspace})
+    aligned = aligned && reinterpret_cast<uintptr_t>(ptr) % 16 == 0;
+  const size_t need = tree_attention_workspace_bytes(tree->B, H, L_max, tree->T_max);
+  const bool scratch = workspace && workspace_bytes >= need;
+  if (d == 64 && !(aligned && scratch))  // the smaller head may come without either: one wave per query
     return launch_plain<uint16_t>(tree, H, d, scale, q, k_cache, v_cache, k_tree, v_tree, seq_lens, L_max, out, st)
                ? PROPD_OK
                : PROPD_ERR_DEVICE;
-
-  if (d != kD) return PROPD_ERR_UNSUPPORTED;
-  // rows are moved 16 bytes per lane, by direct loads to LDS and four-dword loads and stores
-  for (const void *ptr : {q, k_cache, v_cache, k_tree, v_tree, (const void *)out, (const void *)tree->anc,
-                          (const void *)workspace})
-    if (reinterpret_cast<uintptr_t>(ptr) % 16 != 0) return PROPD_ERR_INVALID_ARG;
-  const size_t need = tree_attention_workspace_bytes(tree->B, H, L_max, tree->T_max);
-  if (!workspace || workspace_bytes < need) return PROPD_ERR_WORKSPACE;
+  if (!aligned) return PROPD_ERR_INVALID_ARG;
+  if (!scratch) return PROPD_ERR_WORKSPACE;
   AttnParams p;
   p.q = reinterpret_cast<const uint16_t *>(q);
   p.k_cache = reinterpret_cast<const uint16_t *>(k_cache);
@@ -1053,8 +1160,9 @@ extern "C" propd_status propd_tree_attention(const propd_tree *tree, propd_dtype
   p.T_max = tree->T_max;
   p.L_max = L_max;
   p.B = tree->B;
+  p.scale = scale;
   p.scale_log2e = scale * 1.4426950408889634f;
-  const int grid = pick_grid(tree->B, H, L_max, tree->T_max);
+  const int grid = pick_grid(d == 64 ? Geo<64>::kPerCu : Geo<128>::kPerCu, tree->B, H, L_max, tree->T_max);
   const size_t slots = 2 * (size_t)grid_bound(tree->B, H, L_max, tree->T_max);
   char *ws = reinterpret_cast<char *>(workspace);
   p.part_o = reinterpret_cast<float *>(ws);
@@ -1062,7 +1170,7 @@ extern "C" propd_status propd_tree_attention(const propd_tree *tree, propd_dtype
   p.part_ml = reinterpret_cast<float *>(ws);
   ws += align_up(slots * kPartMlFloats * 4, 256);
   p.cuts = reinterpret_cast<int32_t *>(ws);
-  if (!launch_bf16(p, grid, st)) return PROPD_ERR_DEVICE;
+  if (!(d == 64 ? launch_bf16<64>(p, grid, st) : launch_bf16<128>(p, grid, st))) return PROPD_ERR_DEVICE;
   return PROPD_OK;
 }
 

@@ -57,3 +57,116 @@ def test_prune_f32_rows_at_any_float(pb, oracle, Hd, offset):
     res = pb.propd_early_prune(tree, shifted(x["hidden_states"]), shifted(x["head_weight"]), x["top_k"],
                                want_rank=True)
     check_prune(oracle, x, res)
+
+
+# ------------------------------------------------------------------ attention, head size 64
+
+
+def d64_case(seed, T_max, shapes, lens, H=3):
+    w = synth.Workload(82, "case", "bf16", len(shapes), H, 64, T_max, 0, 0, 0, 1e-3)
+    return synth.make_attention_inputs(w, seq_lens=np.asarray(lens, np.int32), trees=shapes)
+
+
+def relative_error(oracle, x, out):
+    ref = oracle.tree_attention(x["n_nodes"], x["parent"], x["seq_lens"], x["q"], x["k_cache"],
+                                x["v_cache"], x["k_tree"], x["v_tree"], x["scale"])
+    got, d2, r2 = host_f64(out), 0.0, 0.0
+    for b in range(x["B"]):
+        T = int(x["n_nodes"][b])
+        d2 += ((got[b, :, :T] - ref[b, :, :T]) ** 2).sum()
+        r2 += (ref[b, :, :T] ** 2).sum()
+    return float(np.sqrt(d2 / r2))
+
+
+@pytest.mark.parametrize("T_max,lens", [(1, [0, 1, 33]), (8, [31, 32, 2000]), (33, [64, 0, 65]),
+                                        (64, [129, 700, 5]), (97, [1, 1000, 31]), (128, [300, 4096, 95])])
+def test_attention_d64_matches_oracle(pb, oracle, T_max, lens):
+    """The tiled kernel at head size 64: empty and ragged caches, one to four query groups, whole and
+    cut units.  Its weights keep fp32 precision, so rounding the result to bf16 (at most 2^-9
+    relative) is all the error there is, up to fp32 sums (1e-5)."""
+    rng = np.random.default_rng(T_max)
+    shapes = [synth.random_tree(rng, T_max), synth.chain_tree(max(1, T_max // 2)), synth.random_tree(rng, max(1, T_max - 1))]
+    x = d64_case(T_max, T_max, shapes, lens)
+    out, sent = run_attention(pb, x)
+    check_attention(oracle, x, out, sent)
+    assert relative_error(oracle, x, out) <= 2.0 ** -9 + 1e-5
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("direction", ["rising", "late_spike"])
+def test_attention_moving_maximum_other_kernels(pb, oracle, dtype, direction):
+    """Scores that grow along the cache move the reference of the online softmax again and again."""
+    shapes = [synth.rank_product_tree(40, 4)] * 2
+    w = synth.Workload(83, "case", dtype, 2, 2, 64, 40, 0, 0, 0, 1e-3)
+    x = synth.make_attention_inputs(w, seq_lens=np.array([700, 333], np.int32), trees=shapes, poison=False)
+    k = synth.as_float(x["k_cache"]).copy()
+    L = k.shape[2]
+    ramp = np.linspace(0.1, 6.0, L) if direction == "rising" else np.where(np.arange(L) == 321, 9.0, 0.3)
+    x["k_cache"] = synth.from_float((k * ramp[None, None, :, None]).astype(np.float32), dtype)
+    out, sent = run_attention(pb, x)
+    check_attention(oracle, x, out, sent)
+
+
+def raw_attention(pb, x, shift=0, workspace="full"):
+    """The C entry point itself: tensors `shift` bytes off the 16-byte grid, any workspace."""
+    import ctypes
+    B, H, T_max, d = x["q"].shape
+    es = 2 if x["dtype"] == "bf16" else 4
+
+    def place(a):
+        t = to_dev(a)
+        buf = torch.empty(t.numel() + 16, dtype=t.dtype, device="cuda")
+        v = buf[shift // es:shift // es + t.numel()].view(t.shape)
+        v.copy_(t)
+        return v
+
+    tree = dev_tree(pb, x["n_nodes"], x["parent"])
+    sent = sentinel_like(x["q"])
+    q, kc, vc, kt, vt, out = (place(a) for a in (x["q"], x["k_cache"], x["v_cache"], x["k_tree"], x["v_tree"], sent))
+    seq = to_dev(x["seq_lens"])
+    need = pb.workspace_bytes(pb.WS_TREE_ATTENTION, B, T_max, H, d, kc.shape[2])
+    size = {"full": need, "short": need - 1, "none": 0}[workspace]
+    ws = torch.empty(max(size, 1), dtype=torch.uint8, device="cuda")
+    c_tree = tree._c()
+    st = pb.load_library().propd_tree_attention(
+        ctypes.byref(c_tree), pb.PROPD_BF16 if x["dtype"] == "bf16" else pb.PROPD_F32, H, d, x["scale"],
+        q.data_ptr(), kc.data_ptr(), vc.data_ptr(), kt.data_ptr(), vt.data_ptr(), seq.data_ptr(), kc.shape[2],
+        out.data_ptr(), ws.data_ptr() if workspace != "none" else None, size, None)
+    torch.cuda.synchronize()
+    return st, out, sent
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("shift,workspace", [(0, "none"), (0, "short"), (4, "full"), (0, "full")])
+def test_attention_without_workspace_or_alignment(pb, oracle, dtype, d, shift, workspace):
+    """fp32 tensors and bf16 tensors with head size 64 are served whatever the workspace is and
+    wherever the tensors lie."""
+    rng = np.random.default_rng(3)
+    shapes = [synth.random_tree(rng, 37), synth.random_tree(rng, 50)]
+    w = synth.Workload(84, "case", dtype, 2, 2, d, 50, 0, 0, 0, 1e-3)
+    x = synth.make_attention_inputs(w, seq_lens=np.array([257, 70], np.int32), trees=shapes)
+    st, out, sent = raw_attention(pb, x, shift, workspace)
+    assert st == 0
+    check_attention(oracle, x, out, sent)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("L", [5, 600])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_attention_not_finite_values_stay_where_they_are_seen(pb, oracle, dtype, d, L, value):
+    """V rows of a leaf that hold NaN or an infinity reach the leaf's own result and no other."""
+    shapes = [synth.rank_product_tree(70, 4)] * 2
+    w = synth.Workload(85, "case", dtype, 2, 2, d, 70, 0, 0, 0, 1e-3)
+    x = synth.make_attention_inputs(w, seq_lens=np.array([L, L], np.int32), trees=shapes)
+    clean, _ = run_attention(pb, x)
+    leaf = 69
+    assert not (x["parent"][1] == leaf).any()
+    y = dict(x, v_tree=x["v_tree"].copy())
+    y["v_tree"][1, :, leaf, 3:40:7] = synth.from_float(np.array([value], np.float32), dtype)[0]
+    got = host_f64(run_attention(pb, y)[0])
+    want = host_f64(clean)
+    assert not np.isfinite(got[1, :, leaf, 3:40:7]).any()
+    got[1, :, leaf, 3:40:7] = want[1, :, leaf, 3:40:7]
+    tol = 2.0 ** -8 if dtype == "bf16" else 1e-5   # one bf16 rounding either way; fp32 sums
+    row = np.abs(want[:, :, :70]).max(axis=-1, keepdims=True)
+    assert (np.abs(got - want)[:, :, :70] <= tol * row).all()
