@@ -28,8 +28,8 @@
 //     cut; a second kernel merges the pieces of every recorded cut, in their order.
 // Both head sizes run the same kernel.  d = 64 came from one wave per query (each lane walking K rows
 // of its own): 8 x 16 units of 64 queries x 2048 keys, 4150 -> 28 us + 5.5 us merge (67 MB of K/V).
-// fp32 path, and d = 64 without a workspace or 16-byte alignment: a plain one-wave-per-query
-// kernel, fp32 throughout.
+// Without a workspace or 16-byte alignment d = 64 runs a plain one-wave-per-query kernel.
+// fp32 path: tree_attention_f32.h.
 #include <type_traits>
 
 #include "common.h"
@@ -1004,8 +1004,8 @@ __global__ __launch_bounds__(kWave) void tree_attn_combine_kernel(AttnParams p) 
 
 // ------------------------------------------------------------------------------------
 // Plain path: one wave per (sequence, head, node); products, softmax and output sums in fp32.
-// Serves fp32 operands (d = 64 or 128) and bf16 operands with d = 64 that come without the
-// workspace or the alignment of the tiled kernel; the result is stored in the operands' type.
+// Serves bf16 operands with d = 64 that come without the workspace or the alignment of the tiled
+// kernel; its per-query function also redoes results with a NaN in them for the other kernels.
 // ------------------------------------------------------------------------------------
 template <typename E>
 struct AttnParamsPlain {
@@ -1026,11 +1026,12 @@ __global__ __launch_bounds__(kWave) void tree_attn_plain_kernel(AttnParamsPlain<
   plain_query(p, unit, i, p.d, 0, p.d);
 }
 
+#include "tree_attention_f32.h"
+
 template <typename E>
-static bool launch_plain(const propd_tree *tree, int H, int d, float scale, const void *q, const void *k_cache,
-                         const void *v_cache, const void *k_tree, const void *v_tree, const int32_t *seq_lens,
-                         int L_max, void *out, hipStream_t st) {
-  AttnParamsPlain<E> p;
+static void fill_plain(AttnParamsPlain<E> &p, const propd_tree *tree, int H, int d, float scale, const void *q,
+                       const void *k_cache, const void *v_cache, const void *k_tree, const void *v_tree,
+                       const int32_t *seq_lens, int L_max, void *out) {
   p.q = reinterpret_cast<const E *>(q);
   p.k_cache = reinterpret_cast<const E *>(k_cache);
   p.v_cache = reinterpret_cast<const E *>(v_cache);
@@ -1045,9 +1046,6 @@ static bool launch_plain(const propd_tree *tree, int H, int d, float scale, cons
   p.L_max = L_max;
   p.d = d;
   p.scale = scale;
-  const long long units = (long long)tree->B * H;
-  hipLaunchKernelGGL(tree_attn_plain_kernel<E>, dim3((unsigned)(units * tree->T_max)), dim3(kWave), 0, st, p);
-  return launch_ok();
 }
 
 // ------------------------------------------------------------------------------------
@@ -1128,7 +1126,12 @@ extern "C" propd_status propd_tree_attention(const propd_tree *tree, propd_dtype
 
   if (dt == PROPD_F32) {
     if (d != 64 && d != 128) return PROPD_ERR_UNSUPPORTED;
-    return launch_plain<float>(tree, H, d, scale, q, k_cache, v_cache, k_tree, v_tree, seq_lens, L_max, out, st)
+    AttnParamsF32 p;
+    fill_plain<float>(p, tree, H, d, scale, q, k_cache, v_cache, k_tree, v_tree, seq_lens, L_max, out);
+    p.units = (int)units;
+    p.scale_log2e = scale * 1.4426950408889634f;
+    return (d == 64 ? launch_f32<64>(p, compute_units(), workspace, workspace_bytes, st)
+                    : launch_f32<128>(p, compute_units(), workspace, workspace_bytes, st))
                ? PROPD_OK
                : PROPD_ERR_DEVICE;
   }
@@ -1140,10 +1143,12 @@ extern "C" propd_status propd_tree_attention(const propd_tree *tree, propd_dtype
     aligned = aligned && reinterpret_cast<uintptr_t>(ptr) % 16 == 0;
   const size_t need = tree_attention_workspace_bytes(tree->B, H, L_max, tree->T_max);
   const bool scratch = workspace && workspace_bytes >= need;
-  if (d == 64 && !(aligned && scratch))  // the smaller head may come without either: one wave per query
-    return launch_plain<uint16_t>(tree, H, d, scale, q, k_cache, v_cache, k_tree, v_tree, seq_lens, L_max, out, st)
-               ? PROPD_OK
-               : PROPD_ERR_DEVICE;
+  if (d == 64 && !(aligned && scratch)) {  // the smaller head may come without either: one wave per query
+    AttnParamsPlain<uint16_t> p;
+    fill_plain<uint16_t>(p, tree, H, d, scale, q, k_cache, v_cache, k_tree, v_tree, seq_lens, L_max, out);
+    hipLaunchKernelGGL(tree_attn_plain_kernel<uint16_t>, dim3((unsigned)(units * tree->T_max)), dim3(kWave), 0, st, p);
+    return launch_ok() ? PROPD_OK : PROPD_ERR_DEVICE;
+  }
   if (!aligned) return PROPD_ERR_INVALID_ARG;
   if (!scratch) return PROPD_ERR_WORKSPACE;
   AttnParams p;

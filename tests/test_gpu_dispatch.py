@@ -170,3 +170,20 @@ def test_attention_not_finite_values_stay_where_they_are_seen(pb, oracle, dtype,
     tol = 2.0 ** -8 if dtype == "bf16" else 1e-5   # one bf16 rounding either way; fp32 sums
     row = np.abs(want[:, :, :70]).max(axis=-1, keepdims=True)
     assert (np.abs(got - want)[:, :, :70] <= tol * row).all()
+
+
+# ------------------------------------------------------------------ attention, fp32
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("T_max,H,lens", [(1, 1, [0, 1]), (16, 2, [128, 17]), (17, 1, [15, 3000]), (33, 2, [700, 0]),
+                                          (70, 3, [16, 1025]), (128, 1, [500, 4100])])
+def test_attention_f32_matches_oracle(pb, oracle, d, T_max, H, lens):
+    """One and two query groups per wave, one to several query groups per unit, keys of a unit in
+    one workgroup or split over up to 16, empty and ragged caches, tiles of one row."""
+    rng = np.random.default_rng(T_max + d)
+    shapes = [synth.random_tree(rng, T_max), synth.random_tree(rng, max(1, T_max - 1))]
+    w = synth.Workload(86, "case", "f32", 2, H, d, T_max, 0, 0, 0, 1e-5)
+    x = synth.make_attention_inputs(w, seq_lens=np.asarray(lens, np.int32), trees=shapes)
+    out, sent = run_attention(pb, x)
+    check_attention(oracle, x, out, sent)
