@@ -19,7 +19,7 @@
 //   - The waves' results are merged through LDS; a unit split over workgroups leaves (O, max, sum)
 //     per workgroup for tree_attn_f32_combine_kernel.
 // Against one wave per query with every lane walking K rows of its own (2 x 16 units, 48 queries,
-// up to 1024 keys, d = 128): 868 -> NEW us.
+// up to 1024 keys, d = 128): 868 -> 21 us, merge kernel 4 us.
 #pragma once
 
 constexpr int kF32AttnWaves = 4, kF32AttnThreads = kF32AttnWaves * kWave;
@@ -52,24 +52,15 @@ __device__ __forceinline__ bool redo_rows(const AttnParamsF32 &p, bool bad, int 
   return taken;
 }
 
+// QG groups of 16 queries of one key range of one unit; s_o, s_ml: the workgroup's LDS.
 template <int D, int QG>
-__global__ __launch_bounds__(kF32AttnThreads, 2) void tree_attn_f32_kernel(AttnParamsF32 p) {
+__device__ __forceinline__ void f32_attn_range(const AttnParamsF32 &p, int unit, int pair, int split, int b, int q0,
+                                               int L, int T, float *s_o, float *s_ml) {
   constexpr int kC = D / 16, kH = D / 64, kRow = D + 4;  // chunks of 16 floats; LDS row, padded
-  __shared__ __attribute__((aligned(16))) float s_o[kF32AttnWaves][16 * QG][kRow];
-  __shared__ float s_m[kF32AttnWaves][32], s_l[kF32AttnWaves][32];
+  constexpr int kRows = 16 * QG;
+  float *s_m = s_ml, *s_l = s_ml + kF32AttnWaves * 32;  // [wave][32]
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15, kq = lane >> 4;
-  // the query groups of one key range run on one XCD where the counts allow (its L2 holds the rows)
-  const unsigned per_pair = (unsigned)p.units * (unsigned)p.splits;
-  const int pair = (int)(blockIdx.x / per_pair);
-  const unsigned us = blockIdx.x - (unsigned)pair * per_pair;
-  const int unit = (int)(us / (unsigned)p.splits), split = (int)(us - (unsigned)unit * (unsigned)p.splits);
-  const int b = unit / p.H, q0 = 16 * QG * pair;
-  int T = p.n_nodes[b];
-  T = T < 1 ? 1 : (T > p.T_max ? p.T_max : T);
-  if (q0 >= T) return;
-  int L = p.seq_lens[b];
-  L = L < 0 ? 0 : (L > p.L_max ? p.L_max : L);
   const int n_cache = (L + 15) / 16, n_tiles = n_cache + (T + 15) / 16;
   const int lo = (int)((long long)n_tiles * split / p.splits), hi = (int)((long long)n_tiles * (split + 1) / p.splits);
   const float *kc = p.k_cache + (size_t)unit * p.L_max * D, *vc = p.v_cache + (size_t)unit * p.L_max * D;
@@ -192,14 +183,14 @@ __global__ __launch_bounds__(kF32AttnThreads, 2) void tree_attn_f32_kernel(AttnP
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const f32x4 v = {o[g][h][0][r], o[g][h][1][r], o[g][h][2][r], o[g][h][3][r]};
-        *reinterpret_cast<f32x4 *>(&s_o[wave][16 * g + c16][64 * h + 16 * kq + 4 * r]) = v;
+        *reinterpret_cast<f32x4 *>(s_o + (wave * kRows + 16 * g + c16) * kRow + 64 * h + 16 * kq + 4 * r) = v;
       }
     float l = l_run[g];
     l += __shfl_xor(l, 16, kWave);
     l += __shfl_xor(l, 32, kWave);
     if (kq == 0) {
-      s_m[wave][16 * g + c16] = m_run[g];
-      s_l[wave][16 * g + c16] = l;
+      s_m[wave * 32 + 16 * g + c16] = m_run[g];
+      s_l[wave * 32 + 16 * g + c16] = l;
     }
   }
   __syncthreads();
@@ -208,12 +199,12 @@ __global__ __launch_bounds__(kF32AttnThreads, 2) void tree_attn_f32_kernel(AttnP
   const int row = threadIdx.x / LPQ, part = threadIdx.x % LPQ, t = q0 + row;
   float M = -INFINITY, lsum = 0.f, f[kF32AttnWaves];
 #pragma unroll
-  for (int w = 0; w < kF32AttnWaves; ++w) M = fmaxf(M, s_m[w][row]);
+  for (int w = 0; w < kF32AttnWaves; ++w) M = fmaxf(M, s_m[w * 32 + row]);
   const float m_safe = M == -INFINITY ? 0.f : M;
 #pragma unroll
   for (int w = 0; w < kF32AttnWaves; ++w) {
-    f[w] = fast_exp2(s_m[w][row] - m_safe);
-    lsum += s_l[w][row] * f[w];
+    f[w] = fast_exp2(s_m[w * 32 + row] - m_safe);
+    lsum += s_l[w * 32 + row] * f[w];
   }
   f32x4 acc[kPieces];
 #pragma unroll
@@ -221,7 +212,7 @@ __global__ __launch_bounds__(kF32AttnThreads, 2) void tree_attn_f32_kernel(AttnP
     acc[x] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < kF32AttnWaves; ++w) {
-      const f32x4 v = *reinterpret_cast<const f32x4 *>(&s_o[w][row][4 * (part + LPQ * x)]);
+      const f32x4 v = *reinterpret_cast<const f32x4 *>(s_o + (w * kRows + row) * kRow + 4 * (part + LPQ * x));
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[x][j] += v[j] * f[w];
     }
@@ -244,7 +235,7 @@ __global__ __launch_bounds__(kF32AttnThreads, 2) void tree_attn_f32_kernel(AttnP
       if (mine) *reinterpret_cast<f32x4_a4 *>(dst + 4 * (part + LPQ * x)) = acc[x];
     return;
   }
-  float *rec = p.part + (((size_t)unit * ((p.T_max + 16 * QG - 1) / (16 * QG)) + pair) * p.splits + split) * f32_part_floats(D);
+  float *rec = p.part + (((size_t)unit * ((p.T_max + 31) / 32) + pair) * p.splits + split) * f32_part_floats(D);
 #pragma unroll
   for (int x = 0; x < kPieces; ++x) *reinterpret_cast<f32x4 *>(rec + row * D + 4 * (part + LPQ * x)) = acc[x];
   if (part == 0) {
@@ -253,7 +244,26 @@ __global__ __launch_bounds__(kF32AttnThreads, 2) void tree_attn_f32_kernel(AttnP
   }
 }
 
-// Units split over workgroups (QG = 2): out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s, always in
+// One workgroup per (unit, 32 queries, split).  MQ: groups of 16 queries it may find (1 when T_max <= 16).
+template <int D, int MQ>
+__global__ __launch_bounds__(kF32AttnThreads, 2) void tree_attn_f32_kernel(AttnParamsF32 p) {
+  __shared__ __attribute__((aligned(16))) float s_o[kF32AttnWaves * 16 * MQ * (D + 4)];
+  __shared__ float s_ml[2 * kF32AttnWaves * 32];
+  // the query groups of one key range run on one XCD where the counts allow (its L2 holds the rows)
+  const unsigned per_pair = (unsigned)p.units * (unsigned)p.splits;
+  const int pair = (int)(blockIdx.x / per_pair);
+  const unsigned us = blockIdx.x - (unsigned)pair * per_pair;
+  const int unit = (int)(us / (unsigned)p.splits), split = (int)(us - (unsigned)unit * (unsigned)p.splits);
+  const int b = unit / p.H, q0 = 32 * pair;
+  int T = p.n_nodes[b], L = p.seq_lens[b];
+  T = T < 1 ? 1 : (T > p.T_max ? p.T_max : T);
+  L = L < 0 ? 0 : (L > p.L_max ? p.L_max : L);
+  if (q0 >= T) return;
+  if (MQ == 1 || q0 + 16 >= T) f32_attn_range<D, 1>(p, unit, pair, split, b, q0, L, T, s_o, s_ml);
+  else f32_attn_range<D, MQ>(p, unit, pair, split, b, q0, L, T, s_o, s_ml);
+}
+
+// Units split over workgroups: out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s, always in
 // the order of the splits, all of a thread's pieces requested before the first is used.  One
 // thread per 16 bytes of the result.
 template <int D>
@@ -319,14 +329,12 @@ static bool launch_f32(AttnParamsF32 p, int cus, void *workspace, size_t workspa
   // records are read and written 16 bytes at a time
   if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 16 != 0) workspace_bytes = 0;
   p.part = reinterpret_cast<float *>(workspace);
-  p.splits = 1;
-  if (p.T_max <= 16) {
-    hipLaunchKernelGGL((tree_attn_f32_kernel<D, 1>), dim3((unsigned)p.units), dim3(kF32AttnThreads), 0, st, p);
-    return launch_ok();
-  }
   p.splits = f32_splits((long long)p.units * pairs, (p.L_max + 15) / 16 + (p.T_max + 15) / 16, cus, workspace_bytes, D);
-  hipLaunchKernelGGL((tree_attn_f32_kernel<D, 2>), dim3((unsigned)p.units * (unsigned)pairs * (unsigned)p.splits),
-                     dim3(kF32AttnThreads), 0, st, p);
+  const dim3 grid((unsigned)p.units * (unsigned)pairs * (unsigned)p.splits);
+  if (p.T_max <= 16)
+    hipLaunchKernelGGL((tree_attn_f32_kernel<D, 1>), grid, dim3(kF32AttnThreads), 0, st, p);
+  else
+    hipLaunchKernelGGL((tree_attn_f32_kernel<D, 2>), grid, dim3(kF32AttnThreads), 0, st, p);
   if (!launch_ok()) return false;
   if (p.splits == 1) return true;
   constexpr unsigned kBlocks = 32 / (kF32AttnThreads / (D / 4));
