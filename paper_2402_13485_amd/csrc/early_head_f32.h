@@ -17,9 +17,7 @@
 //   - Every element is ONE chain over k in rising chunks, starting from zero; a row's tail is
 //     filled with zeros, which leave the sum as it is.  own_scores in prune_prepare_kernel runs
 //     the same chain, so a child's own score is the same bits as its element here.
-//   - The scores pass through LDS once (rows x columns of the tile), so that a wave can take a
-//     whole row against all children of its node, whose tokens and own scores were fetched
-//     before the K loop, one child per lane.
+//   - The scores pass through LDS once, see rows_epilogue.
 // Against one thread per score (every lane walking a weight row of its own, each row fetched
 // once per score row): 22 rows x 1024 x 32000, 4186 -> 37 us (131 MB of weights,
 // 3.6 TB/s); 704 rows x 2048 x 32000 runs at 95 TFLOP/s.
@@ -43,8 +41,8 @@ __host__ __device__ inline F32Plan f32_plan(int m_total, int vocab) {
   return pl;
 }
 
-constexpr int kF32Threads = 512, kF32Waves = kF32Threads / kWave;
-constexpr int kF32MaxRows = 64, kF32Cols = 16 * kF32Waves;
+constexpr int kF32Threads = kGemmThreads, kF32Waves = kF32Threads / kWave;
+constexpr int kF32MaxRows = 64, kF32Cols = kRowsCols;
 constexpr int kF32Block = 128, kF32Chunks = kF32Block / 16;  // floats of a row per block, chunks of 16
 constexpr int kF32RowBytes = kF32Block * 4 + 16;             // padded: 16 rows start 4 banks apart
 // two blocks of the score rows, then (the operands are done with it) the tile's scores
@@ -129,30 +127,17 @@ __device__ __forceinline__ void early_head_f32_tile(int hidden, int vocab, int m
 #pragma unroll
       for (int i = 0; i < MT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j], wk[j], acc[i], 0, 0, 0);
   };
+  RowChildren<kRowsPerWave> ch;
+  if (KIND == 0) {
+    ch.rows(wave, m0, m_total, tb);
+    ch.list(lane, tb);
+  }
   if (n_blocks > 0) load_a(0);
   static_for<R - 1>([&](auto i) {
     if (i < n_blocks) load_w(i, i);
   });
 
-  // children of this wave's rows (row = wave + 8 r), one per lane, while the first block is on
-  // its way; a row's children past the 64th are fetched in the epilogue
-  int cc[kRowsPerWave], pos[kRowsPerWave], child[kRowsPerWave], tok[kRowsPerWave];
-  float own[kRowsPerWave];
-  if (KIND == 0) {
-#pragma unroll
-    for (int r = 0; r < kRowsPerWave; ++r) {
-      const int m = m0 + wave + kF32Waves * r;
-      pos[r] = __builtin_amdgcn_readfirstlane(m < m_total ? tb.row_info[2 * m] : 0);
-      cc[r] = __builtin_amdgcn_readfirstlane(m < m_total ? tb.row_info[2 * m + 1] : 0);
-    }
-#pragma unroll
-    for (int r = 0; r < kRowsPerWave; ++r) child[r] = lane < cc[r] ? tb.child_list[pos[r] + lane] : -1;
-#pragma unroll
-    for (int r = 0; r < kRowsPerWave; ++r) {
-      tok[r] = child[r] >= 0 ? tb.token[child[r]] : -1;
-      own[r] = child[r] >= 0 ? tb.own[child[r]] : INFINITY;
-    }
-  }
+  if (KIND == 0) ch.values(lane, tb);  // while the first blocks are on their way
 
   meet();  // the tile before this one has been read
   for (int b0 = 0; b0 < n_blocks; b0 += R)
@@ -178,62 +163,15 @@ __device__ __forceinline__ void early_head_f32_tile(int hidden, int vocab, int m
   }
   mfma_settle();
 
-  // element (row, col) of a 16 x 16 tile: lane col + 16 * (row / 4), register row % 4.  Columns
-  // past the vocabulary can beat nothing and add nothing to a sum of exponentials.
   float *s_z = reinterpret_cast<float *>(smem);
   __syncthreads();  // the score rows have been read
-  const bool in = v0 + col < vocab;
+  // element (row, col) of a 16 x 16 tile: lane col + 16 * (row / 4), register row % 4
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) s_z[(16 * i + 4 * kq + r) * BN + col] = in ? acc[i][r] : -INFINITY;
+    for (int r = 0; r < 4; ++r) s_z[(16 * i + 4 * kq + r) * BN + col] = acc[i][r];
   __syncthreads();
-#pragma unroll
-  for (int r = 0; r < kRowsPerWave; ++r) {
-    const int row = wave + kF32Waves * r, m = m0 + row;
-    if (m >= m_total) break;  // uniform
-    float z[BN / kWave];
-#pragma unroll
-    for (int x = 0; x < BN / kWave; ++x) z[x] = s_z[row * BN + kWave * x + lane];
-    if (KIND == 0) {
-      const int n_cc = cc[r];
-      for (int e0 = 0; e0 < n_cc; e0 += kWave) {
-        if (e0 > 0) {
-          child[r] = e0 + lane < n_cc ? tb.child_list[pos[r] + e0 + lane] : -1;
-          tok[r] = child[r] >= 0 ? tb.token[child[r]] : -1;
-          own[r] = child[r] >= 0 ? tb.own[child[r]] : INFINITY;
-        }
-        const int n = n_cc - e0 < kWave ? n_cc - e0 : kWave;
-        int count = 0;
-        for (int e = 0; e < n; ++e) {
-          const float zo = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(own[r]), e));
-          const int t = __builtin_amdgcn_readlane(tok[r], e);
-          int c = 0;
-#pragma unroll
-          for (int x = 0; x < BN / kWave; ++x) {
-            const int v = v0 + kWave * x + lane;  // the token's own column never counts
-            c += __popcll(__ballot(v != t && (z[x] > zo || (z[x] == zo && v < t))));
-          }
-          count = lane == e ? c : count;
-        }
-        if (lane < n) tb.cnt_part[(size_t)n_tile * tb.cnt_stride + child[r]] = count;
-      }
-    } else {
-      float mx = z[0];
-#pragma unroll
-      for (int x = 1; x < BN / kWave; ++x) mx = fmaxf(mx, z[x]);
-      mx = wave_reduce_max(mx);
-      float sum = 0.f;
-#pragma unroll
-      for (int x = 0; x < BN / kWave; ++x) sum += (v0 + kWave * x + lane < vocab && mx != -INFINITY) ? expf(z[x] - mx) : 0.f;
-      sum = wave_reduce_sum(sum);
-      if (lane == 0) {
-        float *dst = tb.lse_part + ((size_t)m * tb.parts + n_tile) * 2;
-        dst[0] = mx;
-        dst[1] = sum;
-      }
-    }
-  }
+  rows_epilogue<KIND, kRowsPerWave, 1>(ch, s_z, wave, lane, m0, m_total, v0, vocab, n_tile, tb);
 }
 
 // Persistent over the tiles, XCD-aware like the bf16 kernel: the row tiles of one column tile are

@@ -443,7 +443,7 @@ constexpr int kEpiChildren = 16;
 constexpr int kBK = 32;
 constexpr int kGemmBM = 256;
 constexpr int kGemmMinFN = 2, kGemmMaxFN = 4;
-constexpr int kGemmThreads = 512;
+constexpr int kGemmThreads = 512, kGemmWaves = kGemmThreads / kWave;
 // ring depth: five stages where they fit into the 160 KB of LDS, four for the widest tile
 __host__ __device__ constexpr int gemm_stages(int fn) { return fn == 4 ? 4 : 5; }
 __host__ __device__ constexpr int gemm_stage_bytes(int fn) { return (256 + 64 * fn) * 64; }
@@ -452,17 +452,24 @@ constexpr int kGemmWOffset = kGemmBM * kGemmRowBytes;                           
 constexpr int kGemmLdsBytes = 5 * gemm_stage_bytes(3);  // the largest ring: 140 KB (4 x 32 KB for FN = 4)
 static_assert(gemm_stages(4) * gemm_stage_bytes(4) <= kGemmLdsBytes && gemm_stages(2) * gemm_stage_bytes(2) <= kGemmLdsBytes, "ring");
 constexpr int kXcds = 8;
+constexpr int kHeadLdsBytes = 155648;  // dynamic LDS of the scoring kernel: the largest ring of its tile shapes
 
 // Tile width (in units of 64 vocabulary entries) for m_tiles row tiles: the time of a
 // launch goes as rounds of workgroups over the compute units times the width; ties go to
 // the wider tile.
+// (A 64-bit division is a long sequence of scalar instructions, several of which in front of every
+// workgroup's first load are felt in the short calls: the counts fit 32 bits in all but extreme ones.)
+__host__ __device__ inline long long div_up(long long a, int b) {
+  if (a < (1ll << 31) - b) return (uint32_t)((uint32_t)a + (uint32_t)b - 1u) / (uint32_t)b;
+  return (a + b - 1) / b;
+}
 __host__ __device__ inline int gemm_pick_fn(int m_tiles, int vocab, int cus) {
   int best = kGemmMaxFN;
   long long best_cost = -1;
+#pragma unroll
   for (int fn = kGemmMaxFN; fn >= kGemmMinFN; --fn) {
-    const long long n_tiles = (vocab + 64 * fn - 1) / (64 * fn);
-    const long long rounds = (n_tiles * m_tiles + cus - 1) / cus;
-    const long long cost = rounds * fn;
+    const long long n_tiles = (vocab - 1) / (64 * fn) + 1;
+    const long long cost = div_up(n_tiles * m_tiles, cus) * fn;
     if (best_cost < 0 || cost < best_cost) {
       best = fn;
       best_cost = cost;
@@ -736,6 +743,96 @@ __device__ __forceinline__ void lse_merge(float &m, float &s, float m2, float s2
   m = mm;
 }
 
+// ---- epilogues over whole rows, for the tiles of few score rows (the fp32 tiles and the bf16 tile
+//      of at most 128 rows): the scores of the tile, rows x 128 columns, pass through LDS, and a wave
+//      takes a whole row (row = wave + 8 r of the workgroup's eight waves) against all children
+//      of its node.  The children's tokens and own scores were fetched before the K loop, one
+//      child per lane, so that nothing is waited for here.
+constexpr int kRowsCols = 128;
+
+template <int R>
+struct RowChildren {
+  int cc[R], pos[R], child[R], tok[R];
+  float own[R];
+  // A row's first 64 children (the epilogue fetches the rest), in three steps that depend on each
+  // other, so that the tile's first operand loads can be issued between them.  Lanes without a
+  // child read slot 0 and drop it.
+  __device__ __forceinline__ void rows(int wave, int m0, int m_total, const HeadTables &tb) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int m = m0 + wave + kGemmWaves * r;
+      pos[r] = __builtin_amdgcn_readfirstlane(m < m_total ? tb.row_info[2 * m] : 0);
+      cc[r] = __builtin_amdgcn_readfirstlane(m < m_total ? tb.row_info[2 * m + 1] : 0);
+    }
+  }
+  __device__ __forceinline__ void list(int lane, const HeadTables &tb) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) child[r] = tb.child_list[lane < cc[r] ? pos[r] + lane : 0];
+  }
+  __device__ __forceinline__ void values(int lane, const HeadTables &tb) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      child[r] = lane < cc[r] ? child[r] : -1;
+      const int c = child[r] >= 0 ? child[r] : 0;
+      tok[r] = tb.token[c];
+      own[r] = tb.own[c];
+    }
+  }
+};
+
+// PARTS: column parts per tile in lse_part's layout; the first takes the tile, the others nothing.
+template <int KIND, int R, int PARTS>
+__device__ __forceinline__ void rows_epilogue(RowChildren<R> &ch, const float *s_z, int wave, int lane, int m0,
+                                              int m_total, int v0, int vocab, int n_tile, const HeadTables &tb) {
+  constexpr int kX = kRowsCols / kWave;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int row = wave + kGemmWaves * r, m = m0 + row;
+    if (m >= m_total) break;  // uniform
+    // columns past the vocabulary beat nothing and add nothing to a sum of exponentials
+    float z[kX];
+#pragma unroll
+    for (int x = 0; x < kX; ++x) z[x] = v0 + kWave * x + lane < vocab ? s_z[row * kRowsCols + kWave * x + lane] : -INFINITY;
+    if (KIND == 0) {
+      for (int e0 = 0; e0 < ch.cc[r]; e0 += kWave) {
+        if (e0 > 0) {
+          ch.child[r] = e0 + lane < ch.cc[r] ? tb.child_list[ch.pos[r] + e0 + lane] : -1;
+          ch.tok[r] = ch.child[r] >= 0 ? tb.token[ch.child[r]] : -1;
+          ch.own[r] = ch.child[r] >= 0 ? tb.own[ch.child[r]] : INFINITY;
+        }
+        const int n = ch.cc[r] - e0 < kWave ? ch.cc[r] - e0 : kWave;
+        int count = 0;
+        for (int e = 0; e < n; ++e) {
+          const float zo = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(ch.own[r]), e));
+          const int t = __builtin_amdgcn_readlane(ch.tok[r], e);
+          int c = 0;
+#pragma unroll
+          for (int x = 0; x < kX; ++x) {
+            const int v = v0 + kWave * x + lane;  // the token's own column never counts
+            c += __popcll(__ballot(v != t && (z[x] > zo || (z[x] == zo && v < t))));
+          }
+          count = lane == e ? c : count;
+        }
+        if (lane < n) tb.cnt_part[(size_t)n_tile * tb.cnt_stride + ch.child[r]] = count;
+      }
+    } else {
+      float mx = z[0];
+#pragma unroll
+      for (int x = 1; x < kX; ++x) mx = fmaxf(mx, z[x]);
+      mx = wave_reduce_max(mx);
+      float sum = 0.f;
+#pragma unroll
+      for (int x = 0; x < kX; ++x) sum += (v0 + kWave * x + lane < vocab && mx != -INFINITY) ? expf(z[x] - mx) : 0.f;
+      sum = wave_reduce_sum(sum);
+      if (lane < PARTS) {
+        float *dst = tb.lse_part + ((size_t)m * tb.parts + PARTS * n_tile + lane) * 2;
+        dst[0] = lane == 0 ? mx : -INFINITY;
+        dst[1] = lane == 0 ? sum : 0.f;
+      }
+    }
+  }
+}
+
 // Probability criterion: (max, sum of exponentials) of this wave's columns for every row of
 // the tile, one pair per row and column part, merged later by row_lse_kernel.
 template <int FN>
@@ -937,24 +1034,32 @@ __device__ __forceinline__ void early_head_tile(
 // scoring kernel is then a stream of the weight matrix through the compute units, and a step
 // (a barrier, fragment reads whose latency a handful of matrix instructions cannot hide)
 // costs more than its bytes.  This tile takes 64-deep steps: half as many steps for the same
-// bytes, whole 128-byte lines from every row.  Same 128-wide column tile, wave layout, accumulator layout and epilogues as the
-// 256 x 128 tile above, of which only the upper 128 rows exist; LDS rows are 128 bytes, their
-// eight 16-byte chunks XOR-swizzled with key(row) = (row >> 1) & 7 (a fragment read takes rows
-// r .. r + 15 of one chunk column in one pass: two rows share a 256-byte bank line, eight keys
-// spread the eight pairs).
+// bytes, whole 128-byte lines from every row.  Same 128-wide column tile, wave layout,
+// accumulator layout and epilogues as the 256 x 128 tile above, of which only the upper RA rows
+// exist; LDS rows are 128 bytes, their eight 16-byte chunks XOR-swizzled with key(row) =
+// (row >> 1) & 7 (a fragment read takes rows r .. r + 15 of one chunk column in one pass: two rows
+// share a 256-byte bank line, eight keys spread the eight pairs).
+// One workgroup runs per compute unit, so what bounds the stream is the weight bytes it has in
+// flight: the ring is as deep as LDS allows for the score rows there are (RA = 32, 64 or 128:
+// 7, 6 or 4 stages, 96, 80 or 48 KB of weights in flight).  22 rows x 4096 x 32000 (262 MB): 72.8 us
+// with four stages whatever the row count, NEW us with seven.
 // ------------------------------------------------------------------------------------
-constexpr int kSmallBM = 128, kSmallBK = 64, kSmallStages = 4;
+constexpr int kSmallBM = 128, kSmallBK = 64;
 constexpr int kSmallRowBytes = kSmallBK * 2;                          // 128
-constexpr int kSmallWOffset = kSmallBM * kSmallRowBytes;              // 16 KB of score rows, then 16 KB of weight rows
-constexpr int kSmallStageBytes = 2 * kSmallWOffset;                   // 32 KB
-static_assert(kSmallStages * kSmallStageBytes <= kGemmLdsBytes, "ring");
+constexpr int kSmallWBytes = 128 * kSmallRowBytes;                    // 16 KB of weight rows per stage
+__host__ __device__ constexpr int small_stage_bytes(int ra) { return ra * kSmallRowBytes + kSmallWBytes; }
+__host__ __device__ constexpr int small_stages(int ra) { return ra == 32 ? 7 : (ra == 64 ? 6 : 4); }
 
-template <int KIND>
+template <int KIND, int RA>
 __device__ __forceinline__ void early_head_small_tile(
     int hidden, int vocab, int m_total, int v0, int n_tile,
     const uint16_t *__restrict__ hidden_states, const uint16_t *__restrict__ head_weight,
     const HeadTables &tb, unsigned char *gemm_smem) {
-  constexpr int FN = 2, BM = kGemmBM;
+  constexpr int FN = 2;
+  constexpr int kStages = small_stages(RA), kStageBytes = small_stage_bytes(RA), kWOffset = RA * kSmallRowBytes;
+  static_assert(kStages * kStageBytes <= kHeadLdsBytes, "ring");
+  constexpr int kALoads = RA / 8 > 8 ? 2 : 1;  // 8-row groups of score rows a wave may have to fetch
+  constexpr int kX = RA == 32 ? 1 : 2;         // 32-row blocks of a wave's 64 rows that exist
   typedef __attribute__((address_space(3))) void lds_void;
   typedef const __attribute__((address_space(1))) void global_void;
   const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void *)gemm_smem;
@@ -967,38 +1072,42 @@ __device__ __forceinline__ void early_head_small_tile(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int l32 = lane & 31, g = lane >> 5;
-  int my_pos = 0, my_cc = 0;
-  if (KIND == 0 && tid < BM && tid < m_total) {
-    my_pos = tb.row_info[2 * tid];
-    my_cc = tb.row_info[2 * tid + 1];
-  }
-
-  // ---- loader: a load instruction fills 8 rows of 128 bytes (1 KB).  A stage has 16 such
-  //      groups of score rows and 16 of weight rows; wave w takes groups 2w and 2w + 1 of each.
-  //      Groups of score rows wholly past the last row are not fetched.
+  RowChildren<RA / kGemmWaves> ch;
+  if (KIND == 0) ch.rows(wave, 0, m_total, tb);
+  // ---- loader: a load instruction fills 8 rows of 128 bytes (1 KB).  A stage has RA / 8 such
+  //      groups of score rows, fetched by wave g / kALoads, and 16 of weight rows; wave w takes
+  //      groups 2w and 2w + 1 of those.  Groups of score rows wholly past the last are not fetched.
   const int ld_row = lane >> 3, ld_pos = lane & 7;
-  const unsigned char *a_src[2], *b_src[2];
-  bool a_on[2];
+  const unsigned char *a_src[kALoads], *b_src[2];
+  bool a_on[kALoads];
+  int per_step = 2;  // loads of this wave per K step
+#pragma unroll
+  for (int j = 0; j < kALoads; ++j) {
+    const int r = 8 * (kALoads * wave + j) + ld_row;  // row of the tile = LDS row
+    a_on[j] = kALoads * wave + j < RA / 8 && 8 * (kALoads * wave + j) < m_total;
+    per_step += a_on[j] ? 1 : 0;
+    const int m = r < m_total ? r : m_total - 1;
+    a_src[j] = reinterpret_cast<const unsigned char *>(hidden_states + (size_t)tb.row_src[m] * hidden) +
+               ((ld_pos ^ ((r >> 1) & 7)) << 4);
+  }
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int r = 8 * (2 * wave + j) + ld_row;  // row of the tile = LDS row
-    const int chunk = (ld_pos ^ ((r >> 1) & 7)) << 4;
-    a_on[j] = 8 * (2 * wave + j) < m_total;
-    const int m = r < m_total ? r : m_total - 1;
-    a_src[j] = reinterpret_cast<const unsigned char *>(hidden_states + (size_t)tb.row_src[m] * hidden) + chunk;
-    int v = v0 + r;
-    v = v < vocab ? v : vocab - 1;
-    b_src[j] = reinterpret_cast<const unsigned char *>(head_weight + (size_t)v * hidden) + chunk;
+    const int r = 8 * (2 * wave + j) + ld_row;
+    const int v = v0 + r < vocab ? v0 + r : vocab - 1;
+    b_src[j] = reinterpret_cast<const unsigned char *>(head_weight + (size_t)v * hidden) + ((ld_pos ^ ((r >> 1) & 7)) << 4);
   }
-  const int per_step = (a_on[0] ? 1 : 0) + (a_on[1] ? 1 : 0) + 2;  // loads of this wave per K step
-  const bool w_on = wm * 64 < m_total;                             // this wave's 64 rows hold score rows
+  const bool w_on = wm * 64 < m_total;  // this wave's 64 rows hold score rows
   auto issue = [&](int slot) {
-    unsigned char *dst = gemm_smem + slot * kSmallStageBytes + wave * 2048;
+    unsigned char *dst = gemm_smem + slot * kStageBytes;
+#pragma unroll
+    for (int j = 0; j < kALoads; ++j) {
+      if (a_on[j])
+        __builtin_amdgcn_global_load_lds((global_void *)a_src[j], (lds_void *)(dst + (kALoads * wave + j) * 1024), 16, 0, 0);
+      a_src[j] += kSmallRowBytes;
+    }
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      if (a_on[j]) __builtin_amdgcn_global_load_lds((global_void *)a_src[j], (lds_void *)(dst + j * 1024), 16, 0, 0);
-      a_src[j] += kSmallRowBytes;
-      __builtin_amdgcn_global_load_lds((global_void *)b_src[j], (lds_void *)(dst + kSmallWOffset + j * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((global_void *)b_src[j], (lds_void *)(dst + kWOffset + (2 * wave + j) * 1024), 16, 0, 2 /* nt */);
       b_src[j] += kSmallRowBytes;
     }
   };
@@ -1012,14 +1121,15 @@ __device__ __forceinline__ void early_head_small_tile(
     for (int ks = 0; ks < 4; ++ks) {
       const int off = l32 * kSmallRowBytes + (((2 * ks + g) ^ key) << 4);
       a_rd[ks] = smem_base + wm * 64 * kSmallRowBytes + off;
-      b_rd[ks] = smem_base + kSmallWOffset + wn * 64 * kSmallRowBytes + off;
+      b_rd[ks] = smem_base + kWOffset + wn * 64 * kSmallRowBytes + off;
     }
   }
   typedef GemmFrag<FN> Frag;
   auto read = [&](Frag &f, uint32_t so, int ks) {
     const uint32_t pa = a_rd[ks] + so, pb = b_rd[ks] + so;
     f.a[0] = gemm_lds_read16<0>(pa);
-    f.a[1] = gemm_lds_read16<32 * kSmallRowBytes>(pa);
+    if constexpr (kX == 2) f.a[1] = gemm_lds_read16<32 * kSmallRowBytes>(pa);
+    else f.a[1] = u32x4{0u, 0u, 0u, 0u};
     f.b[0] = gemm_lds_read16<0>(pb);
     f.b[1] = gemm_lds_read16<32 * kSmallRowBytes>(pb);
   };
@@ -1032,7 +1142,7 @@ __device__ __forceinline__ void early_head_small_tile(
       for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
   auto mma = [&](const Frag &f) {
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < kX; ++x)
 #pragma unroll
       for (int y = 0; y < FN; ++y)
         acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
@@ -1040,16 +1150,19 @@ __device__ __forceinline__ void early_head_small_tile(
   };
 
   const int n_steps = hidden / kSmallBK;
-  const int n_pro = n_steps < kSmallStages ? n_steps : kSmallStages;
-  constexpr int kMaxOutstanding = (kSmallStages - 1) * 4;
+  const int n_pro = n_steps < kStages ? n_steps : kStages;
+  constexpr int kMaxOutstanding = (kStages - 1) * 4;
   int slot_ld = 0;
+  if (KIND == 0) ch.list(lane, tb);
   for (int i = 0; i < n_pro; ++i) {
     issue(slot_ld);
-    slot_ld = slot_ld + 1 == kSmallStages ? 0 : slot_ld + 1;
+    slot_ld = slot_ld + 1 == kStages ? 0 : slot_ld + 1;
   }
+  // (loads younger than the ring's only make the counted waits below stricter)
+  if (KIND == 0) ch.values(lane, tb);
   gemm_wait_outstanding<kMaxOutstanding>((n_pro - 1) * per_step);
   __builtin_amdgcn_s_barrier();
-  constexpr int kReads = 2 + FN;  // LDS reads of one K sub-step
+  constexpr int kReads = kX + FN;  // LDS reads of one K sub-step
   Frag f0, f1;
   if (w_on) read(f0, 0, 0);
   uint32_t so = 0;  // byte offset of the stage being multiplied
@@ -1068,25 +1181,43 @@ __device__ __forceinline__ void early_head_small_tile(
     __builtin_amdgcn_sched_barrier(0);
     if (w_on) gemm_wait_frag<0>(f1);  // this wave is done with the slot of this step
     if (step + 1 < n_steps) {
-      const int issued_after = n_steps - 2 - step < kSmallStages - 2 ? n_steps - 2 - step : kSmallStages - 2;
-      gemm_wait_outstanding<kMaxOutstanding>(issued_after * per_step);
-      __builtin_amdgcn_s_barrier();  // it is visible; every wave is done with this step's slot
-      if (step + kSmallStages < n_steps) {
-        issue(slot_ld);  // into the slot of this step
-        slot_ld = slot_ld + 1 == kSmallStages ? 0 : slot_ld + 1;
+      const int issued_after = n_steps - 2 - step;  // steps after the next that have been issued, if not more than fit
+      if (issued_after >= kStages - 2) {
+        if (per_step == 2) gemm_wait_vmem<2 * (kStages - 2)>();
+        else if (per_step == 3) gemm_wait_vmem<3 * (kStages - 2)>();
+        else gemm_wait_vmem<4 * (kStages - 2)>();
+      } else {
+        gemm_wait_outstanding<kMaxOutstanding>(issued_after * per_step);
       }
-      so = so + kSmallStageBytes == kSmallStages * kSmallStageBytes ? 0 : so + kSmallStageBytes;
+      __builtin_amdgcn_s_barrier();  // it is visible; every wave is done with this step's slot
+      if (step + kStages < n_steps) {
+        issue(slot_ld);  // into the slot of this step
+        slot_ld = slot_ld + 1 == kStages ? 0 : slot_ld + 1;
+      }
+      so = so + kStageBytes == kStages * kStageBytes ? 0 : so + kStageBytes;
       if (w_on) read(f0, so, 0);
     }
     if (w_on) mma(f1);
     __builtin_amdgcn_sched_barrier(0);
   }
   mfma_settle();
-  if (KIND == 0)
-    epilogue_count<FN>(acc, 0, v0, n_tile, vocab, tid, my_pos, my_cc, tb, gemm_smem);
-  else
-    epilogue_lse<FN>(acc, 0, v0, m_total, vocab, n_tile, wm, wn, lane, tb);
+  // element (row, col) of a 32 x 32 tile: lane col + 32 * (row / 4 % 2), register 4 * (row / 8) + row % 4
+  float *s_z = reinterpret_cast<float *>(gemm_smem);
+  __syncthreads();  // every wave is done with the ring
+  if (w_on) {
+#pragma unroll
+    for (int x = 0; x < kX; ++x)
+#pragma unroll
+      for (int y = 0; y < FN; ++y)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          s_z[(wm * 64 + 32 * x + 8 * (r >> 2) + 4 * g + (r & 3)) * kRowsCols + wn * 64 + 32 * y + l32] = acc[x][y][r];
+  }
+  __syncthreads();
+  rows_epilogue<KIND, RA / kGemmWaves, 2>(ch, s_z, wave, lane, 0, m_total, v0, vocab, n_tile, tb);
+  __syncthreads();  // the next tile's loads reuse this memory
 }
+
 
 #include "early_head_tall.h"
 
@@ -1107,13 +1238,13 @@ __host__ __device__ inline HeadPlan head_plan(int m_total, int vocab, int cus, i
   pl.tall = 0;
   pl.m_tiles = (m_total + kGemmBM - 1) / kGemmBM;
   pl.fn = gemm_pick_fn(pl.m_tiles > 0 ? pl.m_tiles : 1, vocab, cus);
-  pl.n_tiles = (vocab + 64 * pl.fn - 1) / (64 * pl.fn);
+  pl.n_tiles = (vocab - 1) / (64 * pl.fn) + 1;
   pl.n_parts = 2 * pl.n_tiles;
   if (m_total <= 0) return pl;
-  const long long rounds = ((long long)pl.m_tiles * pl.n_tiles + cus - 1) / cus;
+  const long long rounds = div_up((long long)pl.m_tiles * pl.n_tiles, cus);
   const long long cost = rounds * kGemmBM * 64 * pl.fn * 100;
   const int mt = (m_total + kTallBM - 1) / kTallBM, nt = (vocab + kTallBN - 1) / kTallBN;
-  const long long rounds_tall = ((long long)mt * nt + cus - 1) / cus;
+  const long long rounds_tall = div_up((long long)mt * nt, cus);
   const long long cost_tall = rounds_tall * kTallBM * kTallBN * kTallCostPercent;
   if (force == 2 || (force == 0 && cost_tall < cost)) {
     pl.tall = 1;
@@ -1124,7 +1255,7 @@ __host__ __device__ inline HeadPlan head_plan(int m_total, int vocab, int cus, i
   return pl;
 }
 
-constexpr int kHeadLdsBytes = kTallLdsBytes > kGemmLdsBytes ? kTallLdsBytes : kGemmLdsBytes;
+static_assert(kTallLdsBytes <= kHeadLdsBytes && kGemmLdsBytes <= kHeadLdsBytes, "rings");
 
 // Persistent over the tiles: tile -> (xcd, slot) as described above, a workgroup takes tiles
 // blockIdx.x, blockIdx.x + gridDim.x, ... (the grid is a multiple of the XCD count).
@@ -1141,18 +1272,24 @@ __global__ __launch_bounds__(kGemmThreads, 1) void early_head_bf16_kernel(
   for (long long tile = blockIdx.x; tile < total; tile += gridDim.x) {
     const int xcd = (int)(tile % kXcds);
     const long long slot = tile / kXcds;
-    const int n_tile = (int)(slot / m_tiles) * kXcds + xcd;
+    const int group = slot < (1ll << 31) ? (int)((uint32_t)slot / (uint32_t)m_tiles) : (int)(slot / m_tiles);
+    const int n_tile = group * kXcds + xcd;
     if (n_tile >= n_tiles) continue;
-    const int m_tile = (int)(slot % m_tiles);
+    const int m_tile = (int)(slot - (long long)group * m_tiles);
     if (pl.tall) {
       early_head_tall_tile<KIND>(hidden, vocab, m_total, m_tile * kTallBM, n_tile * kTallBN, n_tile,
                                  hidden_states, head_weight, tb, gemm_smem);
       continue;
     }
     const int m0 = m_tile * kGemmBM, v0 = n_tile * 64 * pl.fn;
-    if (pl.fn == 2 && m_total <= kSmallBM && hidden % kSmallBK == 0)
-      early_head_small_tile<KIND>(hidden, vocab, m_total, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
-    else if (pl.fn == 2)
+    if (pl.fn == 2 && m_total <= kSmallBM && hidden % kSmallBK == 0) {
+      if (m_total <= 32)
+        early_head_small_tile<KIND, 32>(hidden, vocab, m_total, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
+      else if (m_total <= 64)
+        early_head_small_tile<KIND, 64>(hidden, vocab, m_total, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
+      else
+        early_head_small_tile<KIND, 128>(hidden, vocab, m_total, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
+    } else if (pl.fn == 2)
       early_head_tile<2, KIND>(hidden, vocab, m_total, m0, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
     else if (pl.fn == 3)
       early_head_tile<3, KIND>(hidden, vocab, m_total, m0, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);

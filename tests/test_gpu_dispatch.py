@@ -187,3 +187,17 @@ def test_attention_f32_matches_oracle(pb, oracle, d, T_max, H, lens):
     x = synth.make_attention_inputs(w, seq_lens=np.asarray(lens, np.int32), trees=shapes)
     out, sent = run_attention(pb, x)
     check_attention(oracle, x, out, sent)
+
+
+# ------------------------------------------------------------------ bf16 scoring, few rows
+
+
+@pytest.mark.parametrize("T", [2, 9, 33, 34, 65, 66, 127, 128])
+@pytest.mark.parametrize("Hd,V", [(64, 300), (192, 1003), (640, 257)])
+def test_prune_bf16_few_rows_edges(pb, oracle, T, Hd, V):
+    """One chain of T nodes has T - 1 score rows: both sides of every ring of the tile for few rows
+    (32, 64 and 128 rows), fewer K steps than ring stages and more, ragged column tiles."""
+    w = synth.Workload(73, "case", "bf16", 1, 1, 128, T, Hd, V, 4, 1e-3)
+    x = synth.make_prune_inputs(w, trees=[synth.chain_tree(T)])
+    res, sents = run_prune(pb, x, [x["hidden_states"]])
+    check_prune(oracle, x, res, [x["hidden_states"]], sents)
