@@ -1039,16 +1039,17 @@ __device__ __forceinline__ void early_head_tile(
 // exist; LDS rows are 128 bytes, their eight 16-byte chunks XOR-swizzled with key(row) =
 // (row >> 1) & 7 (a fragment read takes rows r .. r + 15 of one chunk column in one pass: two rows
 // share a 256-byte bank line, eight keys spread the eight pairs).
-// One workgroup runs per compute unit, so what bounds the stream is the weight bytes it has in
-// flight: the ring is as deep as LDS allows for the score rows there are (RA = 32, 64 or 128:
-// 7, 6 or 4 stages, 96, 80 or 48 KB of weights in flight).  22 rows x 4096 x 32000 (262 MB): 72.8 us
-// with four stages whatever the row count, NEW us with seven.
+// RA = 32 serves up to 32 rows: a wave then has one 32-row block to multiply instead of two (pruning
+// call at 22 rows x 4096 x 32000: 80 us, 83 with RA = 128; a shape for 64 rows gained nothing at 44).
+// The K loop runs at 5.8 TB/s of weights, read once and non-temporally (without that 6 us more); a
+// ring of seven stages instead of four changes nothing, and neither does requesting 256 or 512
+// bytes of a row together.  Kernel at that size: 72.8 -> 55.6 us with the row epilogue, the
+// children fetched before the K loop and a tile plan without 64-bit divisions (14 -> 10 us
+// outside the K loop; 72 rows: 83 -> 71 us).
 // ------------------------------------------------------------------------------------
-constexpr int kSmallBM = 128, kSmallBK = 64;
+constexpr int kSmallBM = 128, kSmallBK = 64, kSmallStages = 4;
 constexpr int kSmallRowBytes = kSmallBK * 2;                          // 128
 constexpr int kSmallWBytes = 128 * kSmallRowBytes;                    // 16 KB of weight rows per stage
-__host__ __device__ constexpr int small_stage_bytes(int ra) { return ra * kSmallRowBytes + kSmallWBytes; }
-__host__ __device__ constexpr int small_stages(int ra) { return ra == 32 ? 7 : (ra == 64 ? 6 : 4); }
 
 template <int KIND, int RA>
 __device__ __forceinline__ void early_head_small_tile(
@@ -1056,7 +1057,7 @@ __device__ __forceinline__ void early_head_small_tile(
     const uint16_t *__restrict__ hidden_states, const uint16_t *__restrict__ head_weight,
     const HeadTables &tb, unsigned char *gemm_smem) {
   constexpr int FN = 2;
-  constexpr int kStages = small_stages(RA), kStageBytes = small_stage_bytes(RA), kWOffset = RA * kSmallRowBytes;
+  constexpr int kStages = kSmallStages, kWOffset = RA * kSmallRowBytes, kStageBytes = kWOffset + kSmallWBytes;
   static_assert(kStages * kStageBytes <= kHeadLdsBytes, "ring");
   constexpr int kALoads = RA / 8 > 8 ? 2 : 1;  // 8-row groups of score rows a wave may have to fetch
   constexpr int kX = RA == 32 ? 1 : 2;         // 32-row blocks of a wave's 64 rows that exist
@@ -1285,8 +1286,6 @@ __global__ __launch_bounds__(kGemmThreads, 1) void early_head_bf16_kernel(
     if (pl.fn == 2 && m_total <= kSmallBM && hidden % kSmallBK == 0) {
       if (m_total <= 32)
         early_head_small_tile<KIND, 32>(hidden, vocab, m_total, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
-      else if (m_total <= 64)
-        early_head_small_tile<KIND, 64>(hidden, vocab, m_total, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
       else
         early_head_small_tile<KIND, 128>(hidden, vocab, m_total, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
     } else if (pl.fn == 2)
