@@ -74,7 +74,8 @@ struct AttnParams {
   float scale, scale_log2e;
   float *part_o;   // [2 * grid][4 waves][16 blocks][64 lanes][4]
   float *part_ml;  // [2 * grid][4 waves][m | l][64 lanes]
-  int32_t *cuts;   // [grid][4] per workgroup: the unit whose first piece it holds (CutRecord)
+  int32_t *cuts;   // CutRecords: [units] by unit, or [grid] by the workgroup that holds the first piece
+  int by_unit;     // 1 where there are no more units than workgroups
 };
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -309,14 +310,17 @@ struct Schedule {
   }
 };
 
-// What the workgroup that holds the FIRST piece of a cut unit leaves for the merge kernel
-// (every workgroup of the grid writes its record in every call; unit < 0: none).  The pieces
-// of the unit lie in workgroups w .. w_last: the first in the second partial slot of w, the
-// others in the first slot of theirs.
+// What the workgroup that holds the FIRST piece of a unit leaves for the merge kernel.  With no
+// more units than workgroups the records go by unit, and every unit gets one in every call;
+// otherwise by workgroup (a workgroup holds the first piece of at most one cut unit), and every
+// workgroup of the grid writes its own in every call (unit < 0: none).  The pieces of the unit
+// lie in workgroups w_first .. w_last: the first in the second partial slot of w_first, the others in
+// the first slot of theirs.
 struct CutRecord {
   int32_t unit;
   int32_t w_last_and_nodes;  // w_last | (tree nodes of the unit's sequence << 16)
-  int32_t pad[2];
+  int32_t w_first;
+  int32_t pad;
 };
 
 __device__ __forceinline__ Schedule make_schedule(const StageMap &m, long long G) {
@@ -535,12 +539,12 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
   const Schedule sch = make_schedule(map, G);
   Walk cp;
   const int n_my = cp.start(map, sch, w, G);
-  CutRecord cut = {-1, 0, {0, 0}};
-  auto leave_record = [&]() {
-    if (tid == 0) *reinterpret_cast<CutRecord *>(p.cuts + 4 * w) = cut;
+  CutRecord cut = {-1, 0, (int32_t)w, 0};
+  auto leave_record = [&](long long at) {
+    if (tid == 0) *reinterpret_cast<CutRecord *>(p.cuts + 4 * at) = cut;
   };
   if (n_my <= 0) {
-    leave_record();
+    if (!p.by_unit) leave_record(w);
     return;
   }
 
@@ -898,6 +902,15 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
       if (pc.n_cmp > 0) load_queries(pc);
     }
 
+    if (s0 == 0 && !done.whole) {
+      // the unit starts here and runs past the end of this range, which is the end of
+      // this workgroup's work: its last stage lies us - n_st stages further
+      const int us = n_cache + (T + kStageRows - 1) / kStageRows;
+      cut.unit = done.unit;
+      cut.w_last_and_nodes = (int32_t)sch.range_owner(cp.x_end - 1 + (us - done.n_st)) | (T << 16);
+    }
+    if (s0 == 0 && p.by_unit) leave_record(done.unit);
+
     // ---- write: lane holds d = mb*32 + 8*(r/4) + 4*g + r%4 for its query t
     l_run += __shfl_xor(l_run, 32, kWave);
     m_run *= p.scale_log2e;  // from here on the maximum is in the exponent's (log2) domain
@@ -914,13 +927,6 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
       } else {
         // a range starts inside at most one unit and ends inside at most one
         const size_t ps = 2 * (size_t)w + (s0 > 0 ? 0 : 1);
-        if (s0 == 0) {
-          // the unit starts here and runs past the end of this range, which is the end of
-          // this workgroup's work: its last stage lies us - n_st stages further
-          const int us = n_cache + (T + kStageRows - 1) / kStageRows;
-          cut.unit = done.unit;
-          cut.w_last_and_nodes = (int32_t)sch.range_owner(cp.x_end - 1 + (us - done.n_st)) | (T << 16);
-        }
         if (t < T) {
 #pragma unroll
           for (int mb = 0; mb < kMb; ++mb)
@@ -937,21 +943,27 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
       }
     }
   }
-  leave_record();
+  if (!p.by_unit) leave_record(w);
 }
 
 // Finish the units that a range boundary cut: out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s
-// over the pieces s of the unit, always in the order of the pieces.  One wave per (workgroup of
-// the main kernel, group of 32 queries, quarter of the head dimension): it reads that
-// workgroup's record, returns at once when it names no unit, and otherwise merges the partials
-// of workgroups w .. w_last, four pieces at a time with all their loads in flight together.
-// Lanes map to (query, d) exactly as in the main kernel; a wave owns one 32-wide block mb of d.
-constexpr int kCombinePieces = 4;
+// over the pieces s of the unit, always in the order of the pieces.  Lanes map to (query, d) exactly
+// as in the main kernel: register block 4 mb + q4 of a wave's 32 queries.
+// What it costs is waves that find nothing to do and the chain of dependent reads (record,
+// partials: written by other XCDs, so each comes from beyond the L2), not bytes.  Two kernels:
+//   by unit (no more units than workgroups: few units, each in many pieces): one workgroup per
+//     (unit, 32 queries, 32-wide block mb of d), one wave per q4, 16 pieces requested together.
+//     1 x 32 units of 1088 rows, 17 pieces each: 11.2 us by workgroup, 6.5 us by unit.
+//   by workgroup (many units in a few pieces each): one wave per (workgroup of the main kernel, 32
+//     queries, block mb), four pieces of the whole block together.  640 units of 4224 rows on 512
+//     workgroups: 12 us; four such waves to a workgroup, or one wave per q4, cost 14 to 18 us.
+constexpr int kCombinePieces = 4, kCombineManyPieces = 16;
 
 template <int D>
 __global__ __launch_bounds__(kWave) void tree_attn_combine_kernel(AttnParams p) {
   constexpr int kMb = Geo<D>::kMb;
-  const int w = blockIdx.x / (4 * kMb), dw = (blockIdx.x / kMb) & 3, mb = blockIdx.x % kMb;
+  const int groups = (p.T_max + 31) / 32;
+  const int mb = blockIdx.x % kMb, item = blockIdx.x / kMb, w = item / groups, dw = item - w * groups;
   const CutRecord cut = *reinterpret_cast<const CutRecord *>(p.cuts + 4 * w);
   if (cut.unit < 0) return;
   const int T = cut.w_last_and_nodes >> 16, w_last = cut.w_last_and_nodes & 0xffff;
@@ -1000,6 +1012,60 @@ __global__ __launch_bounds__(kWave) void tree_attn_combine_kernel(AttnParams p) 
     if (redo_not_finite(p, bad, cut.unit, dw * 32, D, 32 * mb, 32 * mb + 32)) mine = false;
   }
   if (mine) store_out_block<false>(p.out + ((size_t)cut.unit * p.T_max + t) * D, acc, inv, g, mb);
+}
+
+template <int D>
+__global__ __launch_bounds__(4 * kWave) void tree_attn_combine_unit_kernel(AttnParams p) {
+  constexpr int kMb = Geo<D>::kMb, N = kCombineManyPieces;
+  const int groups = (p.T_max + 31) / 32;
+  const int mb = blockIdx.x % kMb, item = blockIdx.x / kMb, unit = item / groups, dw = item - unit * groups;
+  const CutRecord cut = *reinterpret_cast<const CutRecord *>(p.cuts + 4 * (size_t)unit);
+  if (cut.unit < 0) return;
+  const int T = cut.w_last_and_nodes >> 16, w_last = cut.w_last_and_nodes & 0xffff, w = cut.w_first;
+  if (dw * 32 >= T) return;
+  const int lane = threadIdx.x & 63, q4 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int t = dw * 32 + (lane & 31), g = lane >> 5;
+  const int ln = t < T ? lane : 0;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  float M = -INFINITY, lsum = 0.f;
+  for (int w0 = w; w0 <= w_last; w0 += N) {
+    f32x4 o[N];
+    float m[N], l[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const int wg = w0 + k <= w_last ? w0 + k : w_last;  // past the last piece: re-read it, weight 0
+      const size_t ps = 2 * (size_t)wg + (wg == w ? 1 : 0);
+      m[k] = p.part_ml[part_ml_index(ps, dw, 0, ln)];
+      l[k] = p.part_ml[part_ml_index(ps, dw, 1, ln)];
+      o[k] = *reinterpret_cast<const f32x4 *>(p.part_o + part_o_index(ps, dw, 4 * mb + q4, ln));
+    }
+    float M_new = M;
+#pragma unroll
+    for (int k = 0; k < N; ++k) M_new = fmaxf(M_new, m[k]);
+    const float M_safe = M_new == -INFINITY ? 0.f : M_new, a_old = fast_exp2(M - M_safe);
+    lsum *= a_old;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] *= a_old;
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if (w0 + k <= w_last) {  // uniform
+        const float a_new = fast_exp2(m[k] - M_safe);
+        lsum += l[k] * a_new;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j] += o[k][j] * a_new;
+      }
+    M = M_new;
+  }
+  const float inv = 1.f / lsum;
+  const int d0 = 32 * mb + 8 * q4;  // the wave's 8 columns; the lane's four start at d0 + 4 g
+  bool mine = t < T;
+  if constexpr (D == 64) {
+    const float sum = (acc[0] + acc[1] + acc[2] + acc[3]) * inv;
+    if (redo_not_finite(p, mine && sum != sum, cut.unit, dw * 32, D, d0, d0 + 8)) mine = false;
+  }
+  if (mine)
+    *reinterpret_cast<u32x2 *>(p.out + ((size_t)cut.unit * p.T_max + t) * D + d0 + 4 * g) =
+        u32x2{cvt_pk_bf16(acc[0] * inv, acc[1] * inv), cvt_pk_bf16(acc[2] * inv, acc[3] * inv)};
 }
 
 // ------------------------------------------------------------------------------------
@@ -1100,7 +1166,11 @@ static bool launch_bf16(const AttnParams &p, int grid, hipStream_t st) {
   hipLaunchKernelGGL((tree_attn_bf16_kernel<kRingStages, D>), dim3((unsigned)grid), dim3(kAttnThreads),
                      lds_bytes, st, p);
   if (!launch_ok()) return false;
-  hipLaunchKernelGGL(tree_attn_combine_kernel<D>, dim3((unsigned)grid * 4 * Geo<D>::kMb), dim3(kWave), 0, st, p);
+  const unsigned blocks = (unsigned)(p.T_max + 31) / 32 * Geo<D>::kMb;
+  if (p.by_unit)
+    hipLaunchKernelGGL(tree_attn_combine_unit_kernel<D>, dim3((unsigned)(p.B * p.H) * blocks), dim3(4 * kWave), 0, st, p);
+  else
+    hipLaunchKernelGGL(tree_attn_combine_kernel<D>, dim3((unsigned)grid * blocks), dim3(kWave), 0, st, p);
   return launch_ok();
 }
 
@@ -1175,6 +1245,7 @@ extern "C" propd_status propd_tree_attention(const propd_tree *tree, propd_dtype
   p.part_ml = reinterpret_cast<float *>(ws);
   ws += align_up(slots * kPartMlFloats * 4, 256);
   p.cuts = reinterpret_cast<int32_t *>(ws);
+  p.by_unit = units <= grid ? 1 : 0;
   if (!(d == 64 ? launch_bf16<64>(p, grid, st) : launch_bf16<128>(p, grid, st))) return PROPD_ERR_DEVICE;
   return PROPD_OK;
 }

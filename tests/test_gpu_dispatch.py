@@ -196,8 +196,29 @@ def test_attention_f32_matches_oracle(pb, oracle, d, T_max, H, lens):
 @pytest.mark.parametrize("Hd,V", [(64, 300), (192, 1003), (640, 257)])
 def test_prune_bf16_few_rows_edges(pb, oracle, T, Hd, V):
     """One chain of T nodes has T - 1 score rows: both sides of every ring of the tile for few rows
-    (32, 64 and 128 rows), fewer K steps than ring stages and more, ragged column tiles."""
+    (32 and 128 rows), fewer K steps than ring stages and more, ragged column tiles."""
     w = synth.Workload(73, "case", "bf16", 1, 1, 128, T, Hd, V, 4, 1e-3)
     x = synth.make_prune_inputs(w, trees=[synth.chain_tree(T)])
     res, sents = run_prune(pb, x, [x["hidden_states"]])
     check_prune(oracle, x, res, [x["hidden_states"]], sents)
+
+
+# ------------------------------------------------------------------ attention: merge of cut units
+
+
+@pytest.mark.parametrize("B,H,T_max,L", [(1, 1, 40, 4000), (1, 3, 128, 2500), (2, 100, 20, 60), (3, 171, 33, 64),
+                                         (9, 57, 16, 100), (1, 600, 33, 90), (2, 130, 100, 700)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_attention_bf16_merge_of_cut_units(pb, oracle, B, H, T_max, L, d):
+    """Units cut into many pieces and into few, records by unit (no more units than workgroups)
+    and by workgroup (513 and 600 units: on the chip's 512 workgroups the one or the 88 units left
+    after the whole ones are cut into a piece per workgroup), equal lengths and ragged ones."""
+    rng = np.random.default_rng(B * 1000 + H)
+    shapes = [synth.random_tree(rng, T_max)] + [synth.random_tree(rng, max(1, T_max - 3 * b)) for b in range(1, B)]
+    lens = np.full(B, L, np.int32)
+    if B == 9:
+        lens = rng.integers(0, L + 1, B).astype(np.int32)
+    w = synth.Workload(87, "case", "bf16", B, H, d, T_max, 0, 0, 0, 1e-3)
+    x = synth.make_attention_inputs(w, seq_lens=lens, trees=shapes)
+    out, sent = run_attention(pb, x)
+    check_attention(oracle, x, out, sent)
