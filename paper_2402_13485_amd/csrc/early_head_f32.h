@@ -171,7 +171,7 @@ __device__ __forceinline__ void early_head_f32_tile(int hidden, int vocab, int m
 #pragma unroll
     for (int r = 0; r < 4; ++r) s_z[(16 * i + 4 * kq + r) * BN + col] = acc[i][r];
   __syncthreads();
-  rows_epilogue<KIND, kRowsPerWave, 1>(ch, s_z, wave, lane, m0, m_total, v0, vocab, n_tile, tb);
+  rows_epilogue<KIND, kRowsPerWave>(ch, s_z, wave, lane, m0, m_total, v0, vocab, n_tile, tb);
 }
 
 // Persistent over the tiles, XCD-aware like the bf16 kernel: the row tiles of one column tile are

@@ -1,60 +1,61 @@
-// Early-head scoring, second tile shape: 352 rows x 256 vocabulary entries per workgroup.
+// Early-head scoring, more than 256 score rows: tiles of 32*MI rows x 64*NJ vocabulary entries.
 // Included by early_prune.hip inside namespace propd, after the helpers it uses.
 //
-// Why a second shape.  The scoring GEMM has few rows (the nodes that have children: 704 at
-// B = 16, T = 128) against a wide vocabulary, and it is bound by operand delivery, not by the
-// matrix cores.  With 256-row tiles those 704 rows need three row tiles (8 % padding) and
-// 501 workgroups, two rounds of the chip.  Two 352-row tiles have no padding, 250 workgroups
-// of 352 x 256 fill the 256 compute units in ONE round, every weight tile is fetched by two
-// workgroups instead of three, and a workgroup moves (352 + 256) / (352 * 256) operand
-// bytes per output instead of (256 + 192) / (256 * 192): 26 % fewer bytes into LDS and 18 %
-// fewer out of it per FLOP.  The accumulators (352 x 256 fp32 = 360 KB) take 176 registers
-// in each of the 8 waves, which leaves room for operands only if they are streamed.
-//   - 8 waves as 2 (rows) x 4 (columns), a wave owns 176 x 64 as 11 x 4 tiles of the
-//     16x16x32 bf16 MFMA (176 = 11 x 16 is no multiple of 32);
-//   - K advances 32 per step through a ring of four 38 KB LDS stages (352 + 256 rows of 64
-//     bytes), filled by direct global->LDS loads three steps ahead.  The 16-byte chunks of a
+// The scoring GEMM has few rows (the nodes that have children: 704 at B = 16, T = 128) against a
+// wide vocabulary.  A round of workgroups costs about 10 + MI * NJ (head_plan), so the shape
+// is the one whose row tiles hold the rows with little padding in the fewest rounds:
+// 704 rows are two tiles of 352 and 250 workgroups, ONE round of the 256 compute units; 832 rows
+// are four tiles of 224 in two rounds (three of 352 would need as many rounds of larger tiles).
+// With 256-row tiles of the 32x32x16 instruction and one shape for rows like 704 only, the
+// pruning calls at 264, 352, 528, 832 and 1056 rows x 4096 took 181, 181, 212, 293 and 395 us; now
+// 142, 155, 186, 265 and 329.
+//   - 8 waves as 2 (rows) x 4 (columns), a wave owns 16*MI x 16*NJ as MI x NJ tiles of the
+//     16x16x32 bf16 MFMA: up to 176 accumulator registers (11 x 4) of the 256 a wave may have at
+//     two waves per SIMD, which leaves room for operands only if they are streamed;
+//   - K advances 32 per step through a ring of four LDS stages (64-byte rows, 38 KB for 11 x 4),
+//     filled by direct global->LDS loads three steps ahead.  The 16-byte chunks of a
 //     row are XOR-swizzled with key(row) = (row >> 1) & 3: a fragment read of this MFMA has
-//     lane -> (row lane % 16, chunk lane / 16), and with the other shape's key (row >> 2) & 3
+//     lane -> (row lane % 16, chunk lane / 16), and with the key (row >> 2) & 3
 //     every such read took twice its time in bank conflicts (measured: 64 against 38 ticks);
-//   - per step a wave reads its four B fragments and then streams the eleven A fragments
-//     through a four-deep register ring: the read of fragment i + 3 is issued behind the four
-//     MFMAs of fragment i, waits are placed by hand (LDS reads return in order);
-//   - the epilogues are the same two as for the other shape, on this accumulator layout: a
+//   - per step a wave reads its B fragments and then streams the A fragments
+//     through a four-deep register ring: the read of fragment i + 3 is issued behind the
+//     MFMAs of fragment i, waits are placed by hand (LDS reads return in order).  Meeting in the
+//     middle of a step and reading the next step's first fragments behind the last products of
+//     this one, so that no wave waits after a barrier, changed nothing at 224 x 256 and cost 3 % at
+//     352 x 256: loads and products compete, not reads (704 x 5120: 279 us whole, 211 without loads,
+//     210 without products, 270 without fragment reads);
+//   - epilogues: rank counts or log-sum-exp partials on this accumulator layout: a
 //     row of the tile lives in the 16 lanes of a quarter wave (column = lane % 16 + 16 j), a
 //     lane holds rows 16 i + 4 (lane / 16) + r.
 #pragma once
 
-constexpr int kTallBM = 352, kTallBN = 256, kTallStages = 4;
-constexpr int kTallWaveRows = kTallBM / 2, kTallWaveCols = kTallBN / 4;  // 176 x 64
-constexpr int kTallMI = kTallWaveRows / 16, kTallNJ = kTallWaveCols / 16;  // 11 x 4 MFMA tiles
-constexpr int kTallRows = kTallBM + kTallBN;                 // LDS rows of a stage
-constexpr int kTallStageBytes = kTallRows * kGemmRowBytes;   // 38912
-constexpr int kTallLdsBytes = kTallStages * kTallStageBytes; // 155648
-constexpr int kTallGroups = kTallRows / 16;                  // 16-row groups, one load instruction each
-constexpr int kTallAGroups = kTallBM / 16;
-constexpr int kTallEpiChildren = 12;                         // children of a row per epilogue pass
-static_assert(kTallLdsBytes <= 160 * 1024, "ring");
+constexpr int kTallStages = 4;
+constexpr int kTallEpiChildren = 12;  // children of a row per epilogue pass
+
+// What depends on the wave tile of MI x NJ matrix tiles.
+template <int MI, int NJ>
+struct Tall {
+  static constexpr int kWaveRows = 16 * MI, kWaveCols = 16 * NJ;
+  static constexpr int kBM = 2 * kWaveRows, kBN = 4 * kWaveCols;
+  static constexpr int kRows = kBM + kBN;                       // LDS rows of a stage
+  static constexpr int kStageBytes = kRows * kGemmRowBytes;     // 38912 for 11 x 4
+  static constexpr int kGroups = kRows / 16, kAGroups = kBM / 16;  // 16-row groups, one load instruction each
+  static constexpr int kLoads = (kGroups + 7) / 8;              // of a wave per K step, at most
+  static constexpr int kIssueAt = MI / 2 - 1;  // the loads of a later step are issued behind this fragment's products
+  static_assert(kTallStages * kStageBytes <= kHeadLdsBytes, "ring of stages");
+};
 
 template <int N>
 __device__ __forceinline__ void tall_wait_lds(u32x4 &a) {
   asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(a) : "n"(N));
 }
 template <int N>
-__device__ __forceinline__ void tall_wait_lds5(u32x4 &a, u32x4 &b0, u32x4 &b1, u32x4 &b2, u32x4 &b3) {
-  asm volatile("s_waitcnt lgkmcnt(%5)" : "+v"(a), "+v"(b0), "+v"(b1), "+v"(b2), "+v"(b3) : "n"(N));
+__device__ __forceinline__ void tall_wait_lds2(u32x4 &a, u32x4 &b) {
+  asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N));
 }
 
-// Waits until at most n of this wave's loads are outstanding (n = whole steps of 4 or 5 loads).
-__device__ __forceinline__ void tall_wait_outstanding(int n) {
-  if (n >= 10) gemm_wait_vmem<10>();
-  else if (n >= 8) gemm_wait_vmem<8>();
-  else if (n >= 5) gemm_wait_vmem<5>();
-  else if (n >= 4) gemm_wait_vmem<4>();
-  else gemm_wait_vmem<0>();
-}
-
-typedef f32x4 TallAcc[kTallMI][kTallNJ];
+template <int MI, int NJ>
+using TallAcc = f32x4[MI][NJ];
 
 // LDS accesses with the row's offset as an immediate of the instruction: one address register
 // serves all rows of a lane.  (Left to itself the compiler materialises an address per row,
@@ -86,13 +87,29 @@ __device__ __forceinline__ int quarter_wave_sum_to_last(int v) {
   return v;
 }
 
-// Counting epilogue on the 16x16 accumulator layout; the method is that of epilogue_count.
-__device__ __forceinline__ void tall_epilogue_count(TallAcc &acc, int m0, int v0, int n_tile, int vocab,
+// Top-k membership by counting (Section 4.1, "Pruning Criterion"): for every child c of the
+// row's node, the scores of the row that beat the child's own score (a higher score, or the
+// same score at a lower id) are counted; the count of this column tile goes to the child's
+// slot of the tile in cnt_part, and the decision kernel adds the tiles up.
+//
+// The children of the tile's rows are staged in LDS (the ring is free by now), kTallEpiChildren
+// per row and pass.  "Beats" is turned into one comparison per score: for the columns of a
+// wave that all lie above the child's token the threshold is the own score (z > own), for
+// columns that all lie below it the next smaller float (z > pred(own), i.e. z >= own); only
+// the one wave whose columns contain the token compares per lane, on a side path marked by
+// a NaN threshold, which the main comparison counts as nothing.  A lane counts its own columns
+// in a byte per child, and one cross-lane sum per row and four children (DPP) leaves the row's
+// counts in the last lane of each quarter wave.
+template <int MI, int NJ>
+__device__ __forceinline__ void tall_epilogue_count(TallAcc<MI, NJ> &acc, int m0, int v0, int n_tile, int vocab,
                                                     int tid_in, int my_pos, int my_cc,
                                                     const HeadTables &tb, unsigned char *smem) {
-  constexpr int BM = kTallBM, WN = kTallWaveCols, E = kTallEpiChildren, NW = 4;
+  using G = Tall<MI, NJ>;
+  constexpr int BM = G::kBM, WN = G::kWaveCols, E = kTallEpiChildren, NW = 4;
   static_assert(E % 4 == 0 && WN < 256, "four byte-sized counts per word");
-  int tid = tid_in;  // see epilogue_count: keeps the addresses below out of the K loop
+  // everything below is derived from this copy of the thread id, which the compiler cannot see
+  // through: otherwise it computes the dozens of LDS addresses of this epilogue before the K loop
+  int tid = tid_in;
   asm volatile("" : "+v"(tid));
   const int lane = tid & 63, c16 = lane & 15, q = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 2, wn = wave & 3;
@@ -104,13 +121,13 @@ __device__ __forceinline__ void tall_epilogue_count(TallAcc &acc, int m0, int v0
   int *s_tok = reinterpret_cast<int *>(s_own + BM * E);  // [BM][E]
   int *s_node = s_tok + BM * E;                          // [BM][E]
   int *s_count = s_node + BM * E;                        // [NW][BM][E/4]
-  static_assert((64 + 2 * BM + (NW + 3) * BM * E + NW * BM * (E / 4)) * 4 <= kTallLdsBytes, "epilogue tables");
-  if (v0 + kTallBN > vocab) {  // columns past the vocabulary can beat nothing
+  static_assert((64 + 2 * BM + (NW + 3) * BM * E + NW * BM * (E / 4)) * 4 <= kHeadLdsBytes, "epilogue tables");
+  if (v0 + G::kBN > vocab) {  // columns past the vocabulary can beat nothing
 #pragma unroll
-    for (int j = 0; j < kTallNJ; ++j) {
+    for (int j = 0; j < NJ; ++j) {
       const bool out = v0 + wn * WN + 16 * j + c16 >= vocab;
 #pragma unroll
-      for (int i = 0; i < kTallMI; ++i)
+      for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[i][j][r] = out ? -INFINITY : acc[i][j][r];
     }
@@ -124,7 +141,7 @@ __device__ __forceinline__ void tall_epilogue_count(TallAcc &acc, int m0, int v0
   }
   __syncthreads();
   const int max_cc = *s_max;
-  const int row0 = wm * kTallWaveRows + 4 * q;  // this lane's rows: row0 + 16 i + r
+  const int row0 = wm * G::kWaveRows + 4 * q;  // this lane's rows: row0 + 16 i + r
   for (int e0 = 0; e0 < max_cc; e0 += E) {
     if (tid < BM) {
       int n = my_cc - e0;
@@ -133,9 +150,10 @@ __device__ __forceinline__ void tall_epilogue_count(TallAcc &acc, int m0, int v0
     }
     __syncthreads();
     {
-      constexpr int kSlots = (BM * E + kGemmThreads - 1) / kGemmThreads, kChunk = 3;
-      static_assert(kSlots % kChunk == 0, "slots per thread");
-#pragma unroll 1  // three slots at a time: more would not fit beside the accumulators
+      // The slots of a thread in two goes, all reads of one in flight together: a go is two dependent
+      // reads long whatever its size, and the operand registers of the K loop are free by now.
+      constexpr int kSlots = (BM * E + kGemmThreads - 1) / kGemmThreads, kChunk = (kSlots + 1) / 2;
+#pragma unroll 1
       for (int j0 = 0; j0 < kSlots; j0 += kChunk) {
         int c[kChunk], t[kChunk];
         float o[kChunk];
@@ -173,12 +191,12 @@ __device__ __forceinline__ void tall_epilogue_count(TallAcc &acc, int m0, int v0
       }
     }
     __syncthreads();
-    // this lane's 44 rows in the order (i, r)
+    // this lane's rows in the order (i, r)
     typedef __attribute__((address_space(3))) void lds_void;
     const uint32_t cc_addr = (uint32_t)(uintptr_t)(lds_void *)(s_cc + row0);
     const uint32_t thr_addr = (uint32_t)(uintptr_t)(lds_void *)(s_thr + wn * BM * E + row0 * E);
     const uint32_t count_addr = (uint32_t)(uintptr_t)(lds_void *)(s_count + wn * BM * (E / 4) + row0 * (E / 4));
-    static_for<kTallMI * 4>([&](auto idx_c) {
+    static_for<MI * 4>([&](auto idx_c) {
       constexpr int idx = decltype(idx_c)::value;
       constexpr int i = idx >> 2, r = idx & 3, off = 16 * i + r;
       uint32_t meta = tall_lds_read4<off * 4>(cc_addr);
@@ -192,27 +210,38 @@ __device__ __forceinline__ void tall_epilogue_count(TallAcc &acc, int m0, int v0
       n_all = (m2q & 255) > n_all ? (m2q & 255) : n_all;
       n_all = (m3q & 255) > n_all ? (m3q & 255) : n_all;
       const bool side_path = (((m0q | m1q | m2q | m3q) >> (8 + wn)) & 1) != 0;
+      // This body stands in the code once per row of a lane, so it is kept short: unrolled over e4, with
+      // the side path's reads per child, the epilogue of one shape was 300 KB of instructions, fetched
+      // once per tile (the pruning call at 704 rows x 5120: 288 us then, 266 now).
+#pragma unroll 1
       for (int e4 = 0; e4 < n_all; e4 += 4) {
-        if (e4 > 0) thr4 = *reinterpret_cast<const f32x4 *>(s_thr + wn * BM * E + (row0 + opaque(off)) * E + e4);
+        const int ent0 = (row0 + opaque(off)) * E + e4;
+        if (e4 > 0) thr4 = *reinterpret_cast<const f32x4 *>(s_thr + wn * BM * E + ent0);
         int packed = 0;
 #pragma unroll
         for (int j4 = 0; j4 < 4; ++j4) {
-          const float thr = thr4[j4];
           int cnt = 0;
 #pragma unroll
-          for (int j = 0; j < kTallNJ; ++j) cnt += acc[i][j][r] > thr ? 1 : 0;
-          if (side_path && thr != thr) {
-            const int ent = (row0 + opaque(off)) * E + e4 + j4;
-            const float own = s_own[ent];
-            const int tok = s_tok[ent];
-#pragma unroll
-            for (int j = 0; j < kTallNJ; ++j) {
-              const int col = v0 + wn * WN + 16 * j + c16;
-              const float z = acc[i][j][r];
-              cnt += (col != tok && (z > own || (z == own && col < tok))) ? 1 : 0;
-            }
-          }
+          for (int j = 0; j < NJ; ++j) cnt += acc[i][j][r] > thr4[j4] ? 1 : 0;
           packed += cnt << (8 * j4);
+        }
+        if (side_path) {
+          const f32x4 own4 = *reinterpret_cast<const f32x4 *>(s_own + ent0);
+          const i32x4 tok4 = *reinterpret_cast<const i32x4 *>(s_tok + ent0);
+#pragma unroll
+          for (int j4 = 0; j4 < 4; ++j4) {
+            const bool mine = thr4[j4] != thr4[j4];
+            if (__ballot(mine) == 0) continue;  // uniform; one child of four rows as a rule
+            const float own = mine ? own4[j4] : INFINITY;
+            int cnt = 0;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+              const int before_tok = tok4[j4] - (v0 + wn * WN + 16 * j + c16);  // > 0: the column lies below the token
+              const float z = acc[i][j][r];
+              cnt += ((z > own || (z == own && before_tok > 0 && mine)) && before_tok != 0) ? 1 : 0;
+            }
+            packed += cnt << (8 * j4);
+          }
         }
         packed = quarter_wave_sum_to_last(packed);
         if (c16 == 15) {
@@ -236,48 +265,65 @@ __device__ __forceinline__ void tall_epilogue_count(TallAcc &acc, int m0, int v0
   }
 }
 
-// (max, sum of exponentials) per row and wave column, four column parts per tile
-__device__ __forceinline__ void tall_epilogue_lse(const TallAcc &acc, int m0, int v0, int m_total, int vocab,
-                                                  int n_tile, int wm, int wn, int lane, const HeadTables &tb) {
-  const int c16 = lane & 15, q = lane >> 4;
+// (max, sum of exponentials) per row: every wave its columns, the four wave columns merged through
+// LDS, one pair per row and tile.
+template <int MI, int NJ>
+__device__ __forceinline__ void tall_epilogue_lse(const TallAcc<MI, NJ> &acc, int m0, int v0, int m_total, int vocab,
+                                                  int n_tile, int tid, const HeadTables &tb, unsigned char *smem) {
+  using G = Tall<MI, NJ>;
+  const int lane = tid & 63, c16 = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 2, wn = wave & 3;
+  float *s_part = reinterpret_cast<float *>(smem);  // [BM][4][2]
+  __syncthreads();                                  // every wave is done with the ring
 #pragma unroll
-  for (int i = 0; i < kTallMI; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       float mx = -INFINITY;
 #pragma unroll
-      for (int j = 0; j < kTallNJ; ++j)
-        if (v0 + wn * kTallWaveCols + 16 * j + c16 < vocab) mx = fmaxf(mx, acc[i][j][r]);
+      for (int j = 0; j < NJ; ++j)
+        if (v0 + wn * G::kWaveCols + 16 * j + c16 < vocab) mx = fmaxf(mx, acc[i][j][r]);
 #pragma unroll
       for (int o = 8; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, kWave));
       float sum = 0.f;
 #pragma unroll
-      for (int j = 0; j < kTallNJ; ++j)
-        if (v0 + wn * kTallWaveCols + 16 * j + c16 < vocab) sum += expf(acc[i][j][r] - mx);
+      for (int j = 0; j < NJ; ++j)
+        if (v0 + wn * G::kWaveCols + 16 * j + c16 < vocab && mx != -INFINITY) sum += expf(acc[i][j][r] - mx);
 #pragma unroll
       for (int o = 8; o > 0; o >>= 1) sum += __shfl_xor(sum, o, kWave);
-      const int m = m0 + wm * kTallWaveRows + 16 * i + 4 * q + r;
-      if (c16 == 0 && m < m_total) {
-        float *dst = tb.lse_part + ((size_t)m * tb.parts + 4 * n_tile + wn) * 2;
+      if (c16 == 0) {
+        float *dst = s_part + ((wm * G::kWaveRows + 16 * i + 4 * q + r) * 4 + wn) * 2;
         dst[0] = mx;
         dst[1] = sum;
       }
     }
+  __syncthreads();
+  if (tid < G::kBM && m0 + tid < m_total) {
+    float mx = s_part[8 * tid], sum = s_part[8 * tid + 1];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) lse_merge(mx, sum, s_part[8 * tid + 2 * w], s_part[8 * tid + 2 * w + 1]);
+    float *dst = tb.lse_part + ((size_t)(m0 + tid) * tb.parts + n_tile) * 2;
+    dst[0] = mx;
+    dst[1] = sum;
+  }
 }
 
-template <int KIND>
+template <int MI, int NJ, int KIND>
 __device__ __forceinline__ void early_head_tall_tile(
     int hidden, int vocab, int m_total, int m0, int v0, int n_tile,
     const uint16_t *__restrict__ hidden_states, const uint16_t *__restrict__ head_weight,
     const HeadTables &tb, unsigned char *smem) {
+  using G = Tall<MI, NJ>;
   typedef __attribute__((address_space(3))) void lds_void;
   typedef const __attribute__((address_space(1))) void global_void;
   const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void *)smem;
-  const int tid = threadIdx.x, lane = tid & 63;
+  int tid = threadIdx.x;  // opaque: see early_head_small_tile
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
   int my_pos = 0, my_cc = 0;
-  if (KIND == 0 && tid < kTallBM && m0 + tid < m_total) {
+  if (KIND == 0 && tid < G::kBM && m0 + tid < m_total) {
     my_pos = tb.row_info[2 * (m0 + tid)];
     my_cc = tb.row_info[2 * (m0 + tid) + 1];
   }
@@ -285,48 +331,52 @@ __device__ __forceinline__ void early_head_tall_tile(
   // ---- loader: group gi = wave + 8 j (16 rows, 1 KB) for j = 0 .. n_groups - 1
   const int ld_row = lane >> 2;
   const int ld_chunk = ((lane & 3) ^ ((lane >> 3) & 3)) << 4;  // byte offset in the global row: chunk ^ key(row)
-  const int n_groups = wave + 32 < kTallGroups ? 5 : 4;         // loads of this wave per K step
-  const unsigned char *src[5];
+  const bool all_groups = wave + 8 * (G::kLoads - 1) < G::kGroups;  // kLoads groups, else one fewer
+  const unsigned char *src[G::kLoads];
 #pragma unroll
-  for (int j = 0; j < 5; ++j) {
+  for (int j = 0; j < G::kLoads; ++j) {
     const int gi = wave + 8 * j;
-    if (gi < kTallAGroups) {
+    if (gi < G::kAGroups) {
       int m = m0 + 16 * gi + ld_row;
       m = m < m_total ? m : m_total - 1;
       src[j] = reinterpret_cast<const unsigned char *>(hidden_states + (size_t)tb.row_src[m] * hidden) + ld_chunk;
     } else {
-      int v = v0 + 16 * (gi - kTallAGroups) + ld_row;
+      int v = v0 + 16 * (gi - G::kAGroups) + ld_row;
       v = v < vocab ? v : vocab - 1;
       src[j] = reinterpret_cast<const unsigned char *>(head_weight + (size_t)v * hidden) + ld_chunk;
     }
   }
   int k_off = 0;  // bytes into the rows of the next step to issue
   auto issue = [&](int slot) {
-    unsigned char *dst = smem + slot * kTallStageBytes + wave * 1024;
+    unsigned char *dst = smem + slot * G::kStageBytes + wave * 1024;
 #pragma unroll
-    for (int j = 0; j < 5; ++j)
-      if (j < n_groups)
+    for (int j = 0; j < G::kLoads; ++j)
+      if (j + 1 < G::kLoads || all_groups)
         __builtin_amdgcn_global_load_lds((global_void *)(src[j] + k_off), (lds_void *)(dst + j * 8192), 16, 0, 0);
     k_off += kGemmRowBytes;
   };
+  // until at most STEPS steps' loads of this wave are outstanding
+  auto wait_steps = [&](auto steps) {
+    constexpr int N = decltype(steps)::value;
+    if (all_groups) gemm_wait_vmem<N * G::kLoads>();
+    else gemm_wait_vmem<N * (G::kLoads - 1)>();
+  };
+  using none = std::integral_constant<int, 0>;
+  using one_step = std::integral_constant<int, 1>;
+  using two_steps = std::integral_constant<int, 2>;
 
   // ---- per-lane LDS read addresses: row lane % 16 of a 16-row block, chunk lane / 16 (swizzled)
   const int c16 = lane & 15, kq = lane >> 4;
   const uint32_t frag_off = c16 * kGemmRowBytes + ((kq ^ ((c16 >> 1) & 3)) << 4);
-  const uint32_t a_rd = smem_base + wm * kTallWaveRows * kGemmRowBytes + frag_off;
-  const uint32_t b_rd = smem_base + (kTallBM + wn * kTallWaveCols) * kGemmRowBytes + frag_off;
+  const uint32_t a_rd = smem_base + wm * G::kWaveRows * kGemmRowBytes + frag_off;
+  const uint32_t b_rd = smem_base + (G::kBM + wn * G::kWaveCols) * kGemmRowBytes + frag_off;
 
-  TallAcc acc;
+  TallAcc<MI, NJ> acc;
 #pragma unroll
-  for (int i = 0; i < kTallMI; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < kTallNJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // The ring: the step being multiplied, the next one (landed or landing) and one or two more
-  // in flight.  The loads of step s + 3 are issued in the MIDDLE of step s, into the slot that
-  // step s - 1 left at the last barrier: the address arithmetic and the issue then run in the
-  // shadow of this wave's queued MFMAs instead of right after the barrier, where every wave
-  // of the workgroup would do them at the same time with the matrix cores idle.
   const int n_steps = hidden / kBK;
   const int n_pro = n_steps < kTallStages - 1 ? n_steps : kTallStages - 1;
   int slot_ld = 0;
@@ -334,34 +384,36 @@ __device__ __forceinline__ void early_head_tall_tile(
     issue(slot_ld);
     slot_ld = slot_ld + 1 == kTallStages ? 0 : slot_ld + 1;
   }
-  tall_wait_outstanding((n_pro - 1) * n_groups);
+  if (n_pro == 3) wait_steps(two_steps{});
+  else if (n_pro == 2) wait_steps(one_step{});
+  else wait_steps(none{});
   __builtin_amdgcn_s_barrier();
   uint32_t so = 0;  // byte offset of the stage being multiplied
   for (int step = 0; step < n_steps; ++step) {
     const uint32_t pa = a_rd + so, pb = b_rd + so;
-    u32x4 bf[kTallNJ], af[4];
+    u32x4 bf[NJ], af[4];
     // the first product needs only A0 and B0: they are read first
     af[0] = gemm_lds_read16<0>(pa);
-    bf[0] = gemm_lds_read16<0>(pb);
-    bf[1] = gemm_lds_read16<1024>(pb);
-    bf[2] = gemm_lds_read16<2048>(pb);
-    bf[3] = gemm_lds_read16<3072>(pb);
+    static_for<NJ>([&](auto j) { bf[j] = gemm_lds_read16<j * 1024>(pb); });
     af[1] = gemm_lds_read16<1024>(pa);
     af[2] = gemm_lds_read16<2048>(pa);
-    tall_wait_lds5<5>(af[0], bf[0], bf[1], bf[2], bf[3]);  // A0, B0 (the B registers are only named)
-    acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[0]),
-                                                        __builtin_bit_cast(bf16x8, bf[0]), acc[0][0], 0, 0, 0);
-    static_for<kTallMI>([&](auto ic) {
+    static_for<MI>([&](auto ic) {
       constexpr int i = decltype(ic)::value;
-      constexpr int allowed = kTallMI - 1 - i < 2 ? kTallMI - 1 - i : 2;  // younger A reads in flight
-      if (i == 0) tall_wait_lds5<allowed>(af[0], bf[0], bf[1], bf[2], bf[3]);
-      else tall_wait_lds<allowed>(af[i & 3]);
+      constexpr int allowed = MI - 1 - i < 2 ? MI - 1 - i : 2;  // younger A reads in flight
+      if constexpr (i == 0) {
+        tall_wait_lds2<NJ + 1>(af[0], bf[0]);
+        acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[0]),
+                                                            __builtin_bit_cast(bf16x8, bf[0]), acc[0][0], 0, 0, 0);
+        static_for<NJ>([&](auto j) { tall_wait_lds2<2>(af[0], bf[j]); });
+      } else {
+        tall_wait_lds<allowed>(af[i & 3]);
+      }
 #pragma unroll
-      for (int j = (i == 0 ? 1 : 0); j < kTallNJ; ++j)
+      for (int j = (i == 0 ? 1 : 0); j < NJ; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[i & 3]),
                                                             __builtin_bit_cast(bf16x8, bf[j]), acc[i][j], 0, 0, 0);
-      if (i + 3 < kTallMI) af[(i + 3) & 3] = gemm_lds_read16<(i + 3) * 1024>(pa);
-      if (i == 4 && step + kTallStages - 1 < n_steps) {
+      if constexpr (i + 3 < MI) af[(i + 3) & 3] = gemm_lds_read16<(i + 3) * 1024>(pa);
+      if (i == G::kIssueAt && step + kTallStages - 1 < n_steps) {
         issue(slot_ld);  // step + 3, into the slot of step - 1
         slot_ld = slot_ld + 1 == kTallStages ? 0 : slot_ld + 1;
       }
@@ -369,13 +421,14 @@ __device__ __forceinline__ void early_head_tall_tile(
     if (step + 1 < n_steps) {
       // this wave has read everything of this step's slot; the next step has landed once at
       // most the steps after it that were issued (up to two) are outstanding
-      const int issued_after = n_steps - 2 - step < kTallStages - 2 ? n_steps - 2 - step : kTallStages - 2;
-      tall_wait_outstanding(issued_after * n_groups);
+      if (step + 3 < n_steps) wait_steps(two_steps{});
+      else if (step + 2 < n_steps) wait_steps(one_step{});
+      else wait_steps(none{});
       __builtin_amdgcn_s_barrier();  // it is visible; every wave is done with this step's slot
-      so = so + kTallStageBytes == kTallStages * kTallStageBytes ? 0 : so + kTallStageBytes;
+      so = so + G::kStageBytes == kTallStages * G::kStageBytes ? 0 : so + G::kStageBytes;
     }
   }
   mfma_settle();
-  if (KIND == 0) tall_epilogue_count(acc, m0, v0, n_tile, vocab, tid, my_pos, my_cc, tb, smem);
-  else tall_epilogue_lse(acc, m0, v0, m_total, vocab, n_tile, wm, wn, lane, tb);
+  if (KIND == 0) tall_epilogue_count<MI, NJ>(acc, m0, v0, n_tile, vocab, tid, my_pos, my_cc, tb, smem);
+  else tall_epilogue_lse<MI, NJ>(acc, m0, v0, m_total, vocab, n_tile, tid, tb, smem);
 }

@@ -69,8 +69,7 @@ static PruneScratch carve_scratch(void *base, int B, int T_max, int vocab) {
   s.own = reinterpret_cast<float *>(take(nt * 4));
   s.logq = reinterpret_cast<float *>(take(nt * 4));
   s.row_cap = (size_t)B * (T_max > 1 ? T_max - 1 : 1);  // a node with children is not a leaf
-  // column parts of a row: one per wave column of a tile, at most four per 256 columns (two
-  // per 128-wide tile, four per 256-wide tile; the fp32 kernel has one per tile)
+  // column parts of a row: one per tile, of at least 128 columns
   s.parts = 4 * (((size_t)vocab + 255) / 256);
   s.lse_part = reinterpret_cast<float *>(take(s.row_cap * s.parts * 8));
   s.cnt_part = reinterpret_cast<int32_t *>(take((((size_t)vocab + 127) / 128) * nt * 4));
@@ -270,9 +269,9 @@ __device__ void prepare_tables(const PrepareArgs &a, int g) {
 // 0..7).  All four waves fetch (coalesced, eight 512-byte steps ahead, through registers into
 // a padded double buffer in LDS); wave 0 runs the chain of matrix instructions over
 // K in rising order, starting from zero.
-//   bf16: the chain of 16x16x32 instructions that the 352-row tiles of the scoring kernel run
-//     for every element (the 32x32x16 chain of the 256-row tiles, two instructions per 32 of K,
-//     gives the same bits: measured, and held to it by the test of equal scores on both shapes).
+//   bf16: the chain of 16x16x32 instructions that the tiles of many rows of the scoring kernel run
+//     for every element (the 32x32x16 chain of the tile of few rows, two instructions per 32 of K,
+//     gives the same bits: measured, and held to it by the test of equal scores on both).
 //   fp32: the chain of 16x16x4 instructions of the fp32 scoring kernel: the four floats of a
 //     lane's 16-byte piece one after the other.  (One lane per node walking its two rows took
 //     78 us for 62 nodes of 1024 floats, a chain of 1024 dependent loads.)
@@ -405,34 +404,25 @@ struct HeadTables {
   int parts;  // column parts per row in lse_part
 };
 
-// children of a row taken per pass of the counting epilogue
-constexpr int kEpiChildren = 16;
-
 // ------------------------------------------------------------------------------------
 // early head, bf16 MFMA
 // ------------------------------------------------------------------------------------
-// C[m][v] = sum_x A[m][x] * W[v][x].  Both operands are contiguous along x, which is
-// the layout the 32x32x16 MFMA wants (8 consecutive x per lane), so tiles go
-// global -> LDS -> MFMA operands without any transpose.
-//   - workgroup tile 256 rows x 64*FN vocabulary entries with FN = 2, 3 or 4, eight waves
-//     in a 4 x 2 arrangement, each owning 64 x 32*FN as 2 x FN MFMA tiles of 32 x 32.
-//     Wider tiles move fewer operand bytes per FLOP (the kernel is bound by operand
-//     delivery, not by the matrix cores); FN is the width with the fewest
-//     rounds-of-workgroups x width on this chip, computed by every workgroup from the row
-//     count on the device, so the host never needs that count;
-//   - K advances 32 per step through a ring of LDS stages filled by direct global->LDS loads
-//     (no staging registers, no LDS stores), up to three steps ahead of the math; one barrier
-//     per K step.  A row of a stage is 64 bytes (4 chunks of 16); the lane that fills chunk c
-//     of LDS row r fetches chunk c ^ key(r) of the global row, with key(r) = (r >> 2) & 3, so
-//     that the 16 rows one quarter-wave reads for a chunk column fall into 16 different bank
-//     groups;
-//   - operand fragments are double-buffered in registers: the LDS reads of one half step
-//     are issued before the MFMAs of the half step before it, and the barrier sits between
-//     two MFMA groups whose operands are already in registers, so the matrix core has work
-//     queued while waves meet;
+// C[m][v] = sum_x A[m][x] * W[v][x].  Both operands are contiguous along x, which is the layout the
+// matrix instructions want (8 consecutive x per lane), so tiles go global -> LDS -> operands
+// without any transpose.  Two kinds of tiles, chosen on the device from the row count (head_plan):
+//   - at most 256 rows: early_head_small_tile, a stream of the weights;
+//   - more: the tiles of early_head_tall.h, 32*MI rows x 64*NJ vocabulary entries in several
+//     shapes.  They are bound by operand delivery and the matrix cores together.
+// Common to all:
+//   - K advances through a ring of LDS stages filled by direct global->LDS loads (no staging
+//     registers, no LDS stores), whose 16-byte chunks are XOR-swizzled on the global side so that
+//     fragment reads are free of bank conflicts;
 //   - the A rows are gathered through the row table by the loads themselves; rows past
 //     the last one and vocabulary entries past the last re-read the last valid one and
 //     are left out by the epilogue;
+//   - every element is one chain of products in rising K, started from zero, the same bits
+//     whatever the tile (two 32x32x16 products sum 32 of K as one 16x16x32 does: measured, and held
+//     to it by the test of equal scores), so that a child's own score can be compared with any;
 //   - the scores stay in the accumulators: the epilogue turns them into rank counts (or
 //     log-sum-exp partials) and nothing of size rows x vocabulary ever reaches memory;
 //   - the grid is one-dimensional, persistent and XCD-aware.  Workgroups are handed to the 8
@@ -441,43 +431,17 @@ constexpr int kEpiChildren = 16;
 //     so a weight tile is fetched from HBM once and hits in that XCD's L2 for the other
 //     row tiles.
 constexpr int kBK = 32;
-constexpr int kGemmBM = 256;
-constexpr int kGemmMinFN = 2, kGemmMaxFN = 4;
 constexpr int kGemmThreads = 512, kGemmWaves = kGemmThreads / kWave;
-// ring depth: five stages where they fit into the 160 KB of LDS, four for the widest tile
-__host__ __device__ constexpr int gemm_stages(int fn) { return fn == 4 ? 4 : 5; }
-__host__ __device__ constexpr int gemm_stage_bytes(int fn) { return (256 + 64 * fn) * 64; }
 constexpr int kGemmRowBytes = kBK * 2;                                           // 64
-constexpr int kGemmWOffset = kGemmBM * kGemmRowBytes;                            // W rows follow the A rows
-constexpr int kGemmLdsBytes = 5 * gemm_stage_bytes(3);  // the largest ring: 140 KB (4 x 32 KB for FN = 4)
-static_assert(gemm_stages(4) * gemm_stage_bytes(4) <= kGemmLdsBytes && gemm_stages(2) * gemm_stage_bytes(2) <= kGemmLdsBytes, "ring");
 constexpr int kXcds = 8;
 constexpr int kHeadLdsBytes = 155648;  // dynamic LDS of the scoring kernel: the largest ring of its tile shapes
 
-// Tile width (in units of 64 vocabulary entries) for m_tiles row tiles: the time of a
-// launch goes as rounds of workgroups over the compute units times the width; ties go to
-// the wider tile.
 // (A 64-bit division is a long sequence of scalar instructions, several of which in front of every
 // workgroup's first load are felt in the short calls: the counts fit 32 bits in all but extreme ones.)
 __host__ __device__ inline long long div_up(long long a, int b) {
   if (a < (1ll << 31) - b) return (uint32_t)((uint32_t)a + (uint32_t)b - 1u) / (uint32_t)b;
   return (a + b - 1) / b;
 }
-__host__ __device__ inline int gemm_pick_fn(int m_tiles, int vocab, int cus) {
-  int best = kGemmMaxFN;
-  long long best_cost = -1;
-#pragma unroll
-  for (int fn = kGemmMaxFN; fn >= kGemmMinFN; --fn) {
-    const long long n_tiles = (vocab - 1) / (64 * fn) + 1;
-    const long long cost = div_up(n_tiles * m_tiles, cus) * fn;
-    if (best_cost < 0 || cost < best_cost) {
-      best = fn;
-      best_cost = cost;
-    }
-  }
-  return best;
-}
-
 template <int N>
 __device__ __forceinline__ void gemm_wait_vmem() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
@@ -506,45 +470,6 @@ __device__ __forceinline__ u32x4 gemm_lds_read16(uint32_t addr) {
   return r;
 }
 
-template <int FN>
-struct GemmFrag {
-  u32x4 a[2], b[FN];
-};
-
-// Waits until at most N LDS reads of this wave are outstanding (they return in order); the
-// fragment named is the one waited for, so that its uses stay below the wait.
-template <int N, int FN>
-__device__ __forceinline__ void gemm_wait_frag(GemmFrag<FN> &f) {
-  if constexpr (FN == 2)
-    asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.b[0]), "+v"(f.b[1]) : "n"(N));
-  else if constexpr (FN == 3)
-    asm volatile("s_waitcnt lgkmcnt(%5)"
-                 : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.b[0]), "+v"(f.b[1]), "+v"(f.b[2])
-                 : "n"(N));
-  else
-    asm volatile("s_waitcnt lgkmcnt(%6)"
-                 : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.b[0]), "+v"(f.b[1]), "+v"(f.b[2]), "+v"(f.b[3])
-                 : "n"(N));
-}
-
-// ---- epilogues.  Accumulator layout of the 32x32 MFMA: lane -> column l32 (+ 32 y), register
-//      r -> row 8*(r/4) + 4*g + r%4 (+ 32 x): a row of the tile lives in the 32 lanes of one
-//      half of a wave, so a ballot over a comparison counts two rows at once.
-
-// Top-k membership by counting (Section 4.1, "Pruning Criterion"): for every child c of the
-// row's node, the scores of the row that beat the child's own score (a higher score, or the
-// same score at a lower id) are counted; the count of this column tile goes to the child's
-// slot of the tile in cnt_part, and the decision kernel adds the tiles up.
-//
-// The children of the tile's rows are staged in LDS (the ring is free by now), kEpiChildren
-// per row and pass.  "Beats" is turned into one comparison per score: for the columns of a
-// wave that all lie above the child's token the threshold is the own score (z > own), for
-// columns that all lie below it the next smaller float (z > pred(own), i.e. z >= own); only
-// the one wave whose columns contain the token compares per lane, on a side path marked by
-// a NaN threshold, which the main comparison counts as nothing.  A lane walks its 32 rows
-// with the thresholds of the next row already requested, four per LDS read, counts its own
-// columns in a byte per child, and one cross-lane sum per row and four children (DPP)
-// leaves the row's counts in the last lane of each half wave.
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 
 // A loop whose index is a compile-time constant in every iteration: accumulator registers can
@@ -565,175 +490,6 @@ __device__ __forceinline__ float float_pred(float x) {
   if (x == 0.f) return __uint_as_float(0x80000001u);
   if (x < 0.f && x > -INFINITY) return __uint_as_float(u + 1u);
   return x;
-}
-
-// Sum over the 32 lanes of each half wave, left in lanes 31 and 63.
-__device__ __forceinline__ int half_wave_sum_to_last(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);  // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);  // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);  // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);  // row_shr:8: lane 15 of a row = its sum
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
-  return v;
-}
-
-template <int FN>
-__device__ __forceinline__ void epilogue_count(f32x16 (&acc)[2][FN], int m0, int v0, int n_tile, int vocab,
-                                               int tid_in, int my_pos, int my_cc,
-                                               const HeadTables &tb, unsigned char *smem) {
-  constexpr int BM = kGemmBM, WN = 32 * FN, E = kEpiChildren;
-  static_assert(E % 4 == 0 && FN * 32 < 256 && kGemmThreads % E == 0, "four byte-sized counts per word");
-  // Everything below is derived from this copy of the thread id, which the compiler cannot
-  // see through: otherwise it computes the dozens of LDS addresses of this epilogue before the
-  // K loop and keeps them in scratch memory across it.
-  int tid = tid_in;
-  asm volatile("" : "+v"(tid));
-  const int lane = tid & 63, l32 = lane & 31, g = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
-  int *s_max = reinterpret_cast<int *>(smem);
-  int *s_cc = s_max + 64;                                // [BM] children of the row in this pass | flags << 8
-  int *s_pos = s_cc + BM;                                // [BM] first position in child_list
-  float *s_thr = reinterpret_cast<float *>(s_pos + BM);  // [2][BM][E] threshold per wave column
-  float *s_own = s_thr + 2 * BM * E;                     // [BM][E]
-  int *s_tok = reinterpret_cast<int *>(s_own + BM * E);  // [BM][E]
-  int *s_node = s_tok + BM * E;                          // [BM][E]
-  int *s_count = s_node + BM * E;                        // [2][BM][E/4] packed counts per wave column
-  // columns past the vocabulary (last column tile only) can beat nothing
-  if (v0 + 2 * WN > vocab) {
-#pragma unroll
-    for (int y = 0; y < FN; ++y) {
-      const bool out = v0 + wn * WN + y * 32 + l32 >= vocab;
-#pragma unroll
-      for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[x][y][r] = out ? -INFINITY : acc[x][y][r];
-    }
-  }
-  __syncthreads();  // every wave is done with the ring
-  if (tid == 0) *s_max = 0;
-  __syncthreads();
-  {
-    const int wave_max = wave_reduce_max(tid < BM ? my_cc : 0);
-    if (lane == 0 && wave_max > 0) atomicMax(s_max, wave_max);
-  }
-  __syncthreads();
-  const int max_cc = *s_max;
-  // this lane's rows: row0 + a constant per (x, r)
-  const int row0 = wm * 64 + 4 * g;
-  const int *cc_base = s_cc + row0;
-  const float *thr_base = s_thr + wn * BM * E + row0 * E;
-  const float *own_base = s_own + row0 * E;
-  const int *tok_base = s_tok + row0 * E;
-  int *count_base = s_count + wn * BM * (E / 4) + row0 * (E / 4);
-  // staging: this thread's slots are (row = tid / E + 32 j, child = tid % E)
-  const int st_row = tid / E, st_e = tid % E;
-  for (int e0 = 0; e0 < max_cc; e0 += E) {
-    if (tid < BM) {
-      int n = my_cc - e0;
-      s_cc[tid] = n < 0 ? 0 : (n > E ? E : n);
-      s_pos[tid] = my_pos + e0;
-    }
-    __syncthreads();
-    {
-      // all threads stage the (row, child) slots of the pass: the loads of a thread's slots
-      // are in flight together, first the children's ids, then their tokens and own scores
-      constexpr int kSlots = BM * E / kGemmThreads, kRowStep = kGemmThreads / E, kChunk = 4;
-#pragma unroll
-      for (int j0 = 0; j0 < kSlots; j0 += kChunk) {
-        int c[kChunk], t[kChunk];
-        float o[kChunk];
-#pragma unroll
-        for (int j = 0; j < kChunk; ++j) {
-          const int row = st_row + kRowStep * (j0 + j);
-          c[j] = st_e < (s_cc[row] & 255) ? tb.child_list[s_pos[row] + st_e] : -1;
-        }
-#pragma unroll
-        for (int j = 0; j < kChunk; ++j) {
-          t[j] = c[j] >= 0 ? tb.token[c[j]] : -1;
-          o[j] = c[j] >= 0 ? tb.own[c[j]] : INFINITY;
-        }
-#pragma unroll
-        for (int j = 0; j < kChunk; ++j) {
-          const int row = st_row + kRowStep * (j0 + j), slot = row * E + st_e;
-          // an id outside the vocabulary is beaten by nothing here (the decision kernel fails it)
-          const bool ok = t[j] >= 0 && t[j] < vocab;
-          s_own[slot] = ok ? o[j] : INFINITY;
-          s_tok[slot] = ok ? t[j] : -1;
-          s_node[slot] = c[j];
-#pragma unroll
-          for (int half = 0; half < 2; ++half) {
-            const int c0 = v0 + half * WN;
-            float thr = INFINITY;
-            if (ok) {
-              const bool inside = t[j] >= c0 && t[j] < c0 + WN;
-              thr = t[j] < c0 ? o[j] : (inside ? __uint_as_float(0x7fc00000u) : float_pred(o[j]));
-              if (inside) atomicOr(&s_cc[row], 256 << half);  // this row has a side-path entry
-            }
-            s_thr[(half * BM * E) + slot] = thr;
-          }
-        }
-      }
-    }
-    __syncthreads();
-    // this lane's 32 rows, in the order (x, r); the thresholds of the next row are requested
-    // before the current row is counted
-    auto row_off = [](int idx) { return (idx >> 4) * 32 + 8 * ((idx & 15) >> 2) + (idx & 3); };
-    int meta_cur = cc_base[row_off(0)];  // children | side-path flags of the two wave columns << 8
-    f32x4 thr_cur = *reinterpret_cast<const f32x4 *>(thr_base + row_off(0) * E);
-    static_for<32>([&](auto idx_c) {
-      constexpr int idx = decltype(idx_c)::value;
-      constexpr int x = idx >> 4, r = idx & 15;
-      constexpr int off = (idx >> 4) * 32 + 8 * ((idx & 15) >> 2) + (idx & 3);
-      int meta_nxt = 0;
-      f32x4 thr_nxt = {0.f, 0.f, 0.f, 0.f};
-      if (idx + 1 < 32) {
-        meta_nxt = cc_base[row_off(idx + 1)];
-        thr_nxt = *reinterpret_cast<const f32x4 *>(thr_base + row_off(idx + 1) * E);
-      }
-      const int m_lo = __builtin_amdgcn_readlane(meta_cur, 0), m_hi = __builtin_amdgcn_readlane(meta_cur, 32);
-      const int n_both = (m_lo & 255) > (m_hi & 255) ? (m_lo & 255) : (m_hi & 255);
-      const bool side_path = (((m_lo | m_hi) >> (8 + wn)) & 1) != 0;  // rare: the token's own columns
-      for (int e4 = 0; e4 < n_both; e4 += 4) {
-        if (e4 > 0) thr_cur = *reinterpret_cast<const f32x4 *>(thr_base + off * E + e4);  // more than four children
-        int packed = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float thr = thr_cur[j];
-          int cnt = 0;
-#pragma unroll
-          for (int y = 0; y < FN; ++y) cnt += acc[x][y][r] > thr ? 1 : 0;
-          if (side_path && thr != thr) {
-            const float own = own_base[off * E + e4 + j];
-            const int tok = tok_base[off * E + e4 + j];
-#pragma unroll
-            for (int y = 0; y < FN; ++y) {
-              const int col = v0 + wn * WN + y * 32 + l32;
-              const float z = acc[x][y][r];
-              cnt += (col != tok && (z > own || (z == own && col < tok))) ? 1 : 0;
-            }
-          }
-          packed += cnt << (8 * j);
-        }
-        packed = half_wave_sum_to_last(packed);
-        if (l32 == 31) count_base[off * (E / 4) + (e4 >> 2)] = packed;
-      }
-      meta_cur = meta_nxt;
-      thr_cur = thr_nxt;
-    });
-    __syncthreads();
-    // every (child, column tile) slot is written by exactly one workgroup, zero counts too
-#pragma unroll
-    for (int j = 0; j < BM * E / kGemmThreads; ++j) {
-      const int row = st_row + (kGemmThreads / E) * j, slot = row * E + st_e;
-      const int c = s_node[slot];
-      if (c >= 0) {
-        const int word = slot >> 2, sh = 8 * (slot & 3);
-        tb.cnt_part[(size_t)n_tile * tb.cnt_stride + c] =
-            ((s_count[word] >> sh) & 255) + ((s_count[BM * (E / 4) + word] >> sh) & 255);
-      }
-    }
-    __syncthreads();  // the next pass, or the next tile's loads, reuse this memory
-  }
 }
 
 // (max, sum of exp(z - max)) of two parts of a row, merged
@@ -780,8 +536,7 @@ struct RowChildren {
   }
 };
 
-// PARTS: column parts per tile in lse_part's layout; the first takes the tile, the others nothing.
-template <int KIND, int R, int PARTS>
+template <int KIND, int R>
 __device__ __forceinline__ void rows_epilogue(RowChildren<R> &ch, const float *s_z, int wave, int lane, int m0,
                                               int m_total, int v0, int vocab, int n_tile, const HeadTables &tb) {
   constexpr int kX = kRowsCols / kWave;
@@ -824,222 +579,27 @@ __device__ __forceinline__ void rows_epilogue(RowChildren<R> &ch, const float *s
 #pragma unroll
       for (int x = 0; x < kX; ++x) sum += (v0 + kWave * x + lane < vocab && mx != -INFINITY) ? expf(z[x] - mx) : 0.f;
       sum = wave_reduce_sum(sum);
-      if (lane < PARTS) {
-        float *dst = tb.lse_part + ((size_t)m * tb.parts + PARTS * n_tile + lane) * 2;
-        dst[0] = lane == 0 ? mx : -INFINITY;
-        dst[1] = lane == 0 ? sum : 0.f;
-      }
-    }
-  }
-}
-
-// Probability criterion: (max, sum of exponentials) of this wave's columns for every row of
-// the tile, one pair per row and column part, merged later by row_lse_kernel.
-template <int FN>
-__device__ __forceinline__ void epilogue_lse(const f32x16 (&acc)[2][FN], int m0, int v0, int m_total,
-                                             int vocab, int n_tile, int wm, int wn, int lane,
-                                             const HeadTables &tb) {
-  constexpr int WN = 32 * FN;
-  const int l32 = lane & 31, g = lane >> 5;
-#pragma unroll
-  for (int x = 0; x < 2; ++x)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float mx = -INFINITY;
-#pragma unroll
-      for (int y = 0; y < FN; ++y)
-        if (v0 + wn * WN + y * 32 + l32 < vocab) mx = fmaxf(mx, acc[x][y][r]);
-#pragma unroll
-      for (int o = 16; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, kWave));
-      float sum = 0.f;
-#pragma unroll
-      for (int y = 0; y < FN; ++y)
-        if (v0 + wn * WN + y * 32 + l32 < vocab) sum += expf(acc[x][y][r] - mx);
-#pragma unroll
-      for (int o = 16; o > 0; o >>= 1) sum += __shfl_xor(sum, o, kWave);
-      const int m = m0 + wm * 64 + x * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-      if (l32 == 0 && m < m_total) {
-        float *dst = tb.lse_part + ((size_t)m * tb.parts + 2 * n_tile + wn) * 2;
+      if (lane == 0) {
+        float *dst = tb.lse_part + ((size_t)m * tb.parts + n_tile) * 2;
         dst[0] = mx;
         dst[1] = sum;
       }
     }
+  }
 }
-
-template <int FN, int KIND>
-__device__ __forceinline__ void early_head_tile(
-    int hidden, int vocab, int m_total, int m0, int v0, int n_tile,
-    const uint16_t *__restrict__ hidden_states, const uint16_t *__restrict__ head_weight,
-    const HeadTables &tb, unsigned char *gemm_smem) {
-  constexpr int BM = kGemmBM, WN = 32 * FN;
-  constexpr int kStages = gemm_stages(FN), kStageBytes = gemm_stage_bytes(FN);
-  typedef __attribute__((address_space(3))) void lds_void;
-  typedef const __attribute__((address_space(1))) void global_void;
-  const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void *)gemm_smem;
-
-  // The thread id is made opaque: what is derived from it (addresses, row and chunk numbers)
-  // is then computed here, inside the loop over tiles, and not hoisted out of that loop into
-  // registers that stay occupied while the other tile shapes run.
-  int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
-  const int l32 = lane & 31, g = lane >> 5;
-  // children of the tile's rows (thread t < 256 looks after row m0 + t), fetched early
-  int my_pos = 0, my_cc = 0;
-  if (KIND == 0 && tid < BM && m0 + tid < m_total) {
-    my_pos = tb.row_info[2 * (m0 + tid)];
-    my_cc = tb.row_info[2 * (m0 + tid) + 1];
-  }
-
-  // ---- loader: a load instruction fills 16 rows (1 KB).  A stage has 16 such groups of A
-  //      rows and 4*FN of W rows; wave w takes groups w and w+8 of each (the second W group
-  //      only where it exists).
-  const int ld_row = lane >> 2;
-  const int ld_chunk = ((lane & 3) ^ ((lane >> 4) & 3)) << 4;  // byte offset in the global row
-  const bool second_w = FN == 4 ? true : (FN == 2 ? false : wave < 4);
-  // Few score rows (a small batch): groups of 16 rows that lie wholly past the last row are
-  // not fetched at all, and a wave whose 64 rows lie past it neither reads fragments nor
-  // multiplies.  What such rows hold in LDS and in the accumulators is never looked at.
-  const bool a_on[2] = {m0 + 16 * wave < m_total, m0 + 16 * (wave + 8) < m_total};
-  const bool w_on = m0 + wm * 64 < m_total;
-  const int per_step = (a_on[0] ? 1 : 0) + (a_on[1] ? 1 : 0) + (second_w ? 2 : 1);  // loads of this wave per K step
-  const unsigned char *a_src[2], *b_src[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    int m = m0 + 16 * (wave + 8 * j) + ld_row;
-    m = m < m_total ? m : m_total - 1;
-    a_src[j] = reinterpret_cast<const unsigned char *>(hidden_states + (size_t)tb.row_src[m] * hidden) + ld_chunk;
-    int v = v0 + 16 * (wave + 8 * j) + ld_row;
-    v = v < vocab ? v : vocab - 1;
-    b_src[j] = reinterpret_cast<const unsigned char *>(head_weight + (size_t)v * hidden) + ld_chunk;
-  }
-  auto issue = [&](int slot) {  // the next K step of every source pointer
-    unsigned char *dst = gemm_smem + slot * kStageBytes + wave * 1024;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (a_on[j]) __builtin_amdgcn_global_load_lds((global_void *)a_src[j], (lds_void *)(dst + j * 8192), 16, 0, 0);
-      a_src[j] += kGemmRowBytes;
-    }
-    __builtin_amdgcn_global_load_lds((global_void *)b_src[0], (lds_void *)(dst + kGemmWOffset), 16, 0, 0);
-    b_src[0] += kGemmRowBytes;
-    if (second_w) {
-      __builtin_amdgcn_global_load_lds((global_void *)b_src[1], (lds_void *)(dst + kGemmWOffset + 8192), 16, 0, 0);
-      b_src[1] += kGemmRowBytes;
-    }
-  };
-
-  // ---- per-lane LDS read offsets: operand row l32 of a 32-row block, chunk 2*ks + g
-  uint32_t a_rd[2], b_rd[2];
-  {
-    const int key = (l32 >> 2) & 3;
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const int off = l32 * kGemmRowBytes + (((2 * ks + g) ^ key) << 4);
-      a_rd[ks] = smem_base + wm * 64 * kGemmRowBytes + off;
-      b_rd[ks] = smem_base + kGemmWOffset + wn * WN * kGemmRowBytes + off;
-    }
-  }
-  typedef GemmFrag<FN> Frag;
-  auto read = [&](Frag &f, uint32_t so, int ks) {
-    const uint32_t pa = a_rd[ks] + so, pb = b_rd[ks] + so;
-    f.a[0] = gemm_lds_read16<0>(pa);
-    f.a[1] = gemm_lds_read16<32 * kGemmRowBytes>(pa);
-    f.b[0] = gemm_lds_read16<0>(pb);
-    f.b[1] = gemm_lds_read16<32 * kGemmRowBytes>(pb);
-    if constexpr (FN >= 3) f.b[2] = gemm_lds_read16<64 * kGemmRowBytes>(pb);
-    if constexpr (FN >= 4) f.b[3] = gemm_lds_read16<96 * kGemmRowBytes>(pb);
-  };
-
-  f32x16 acc[2][FN];
-#pragma unroll
-  for (int x = 0; x < 2; ++x)
-#pragma unroll
-    for (int y = 0; y < FN; ++y)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
-  auto mma = [&](const Frag &f) {
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-      for (int y = 0; y < FN; ++y)
-        acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-            __builtin_bit_cast(bf16x8, f.a[x]), __builtin_bit_cast(bf16x8, f.b[y]), acc[x][y], 0, 0, 0);
-  };
-
-  const int n_steps = hidden / kBK;
-  // The ring: the step being multiplied, the next one (already landed, its first fragments
-  // are read before this step ends) and kStages-2 steps in flight; the slot of the step
-  // being multiplied is handed back to the loads as soon as its last fragments are in
-  // registers, half a step before the step ends.
-  const int n_pro = n_steps < kStages ? n_steps : kStages;
-  int slot_ld = 0;
-  for (int i = 0; i < n_pro; ++i) {
-    issue(slot_ld);
-    slot_ld = slot_ld + 1 == kStages ? 0 : slot_ld + 1;
-  }
-  constexpr int kMaxOutstanding = (kStages - 1) * 4;
-  gemm_wait_outstanding<kMaxOutstanding>((n_pro - 1) * per_step);
-  __builtin_amdgcn_s_barrier();
-  constexpr int kReads = 2 + FN;  // LDS reads of one half step
-  Frag f0, f1;
-  if (w_on) read(f0, 0, 0);
-  uint32_t so = 0;  // byte offset of the stage being multiplied
-  for (int step = 0; step + 1 < n_steps; ++step) {
-    if (w_on) {
-      read(f1, so, 1);
-      gemm_wait_frag<kReads>(f0);  // the reads just issued fly while the MFMAs below run
-      mma(f0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if (w_on) gemm_wait_frag<0>(f1);  // this wave is done with the slot of this step
-    // the next step has landed once at most the steps after it (kStages-2 of them were
-    // issued) are outstanding
-    {
-      const int issued_after = n_steps - 2 - step < kStages - 2 ? n_steps - 2 - step : kStages - 2;
-      gemm_wait_outstanding<kMaxOutstanding>(issued_after * per_step);
-    }
-    __builtin_amdgcn_s_barrier();  // it is visible; every wave is done with this step's slot
-    if (step + kStages < n_steps) {
-      issue(slot_ld);  // into the slot of this step
-      slot_ld = slot_ld + 1 == kStages ? 0 : slot_ld + 1;
-    }
-    so = so + kStageBytes == kStages * kStageBytes ? 0 : so + kStageBytes;
-    if (w_on) {
-      read(f0, so, 0);
-      mma(f1);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  if (w_on) {
-    read(f1, so, 1);
-    gemm_wait_frag<kReads>(f0);
-    mma(f0);
-    gemm_wait_frag<0>(f1);
-    mma(f1);
-  }
-
-  mfma_settle();
-  if (KIND == 0)
-    epilogue_count<FN>(acc, m0, v0, n_tile, vocab, tid, my_pos, my_cc, tb, gemm_smem);
-  else
-    epilogue_lse<FN>(acc, m0, v0, m_total, vocab, n_tile, wm, wn, lane, tb);
-}
-
-
 
 // ------------------------------------------------------------------------------------
-// Few score rows (at most 128 in the whole batch: a small batch or small trees).  The
+// Few score rows (at most 256 in the whole batch: a small batch or small trees).  The
 // scoring kernel is then a stream of the weight matrix through the compute units, and a step
 // (a barrier, fragment reads whose latency a handful of matrix instructions cannot hide)
 // costs more than its bytes.  This tile takes 64-deep steps: half as many steps for the same
-// bytes, whole 128-byte lines from every row.  Same 128-wide column tile, wave layout,
-// accumulator layout and epilogues as the 256 x 128 tile above, of which only the upper RA rows
-// exist; LDS rows are 128 bytes, their eight 16-byte chunks XOR-swizzled with key(row) =
-// (row >> 1) & 7 (a fragment read takes rows r .. r + 15 of one chunk column in one pass: two rows
-// share a 256-byte bank line, eight keys spread the eight pairs).
-// RA = 32 serves up to 32 rows: a wave then has one 32-row block to multiply instead of two (pruning
+// bytes, whole 128-byte lines from every row (the last step of a row of an odd number of 32s fetches
+// its half twice and multiplies it once).  128 vocabulary entries x RA rows per workgroup, eight
+// waves as 4 (rows) x 2 (columns) blocks of 64 x 64 where the rows exist, 32x32x16 instructions; LDS
+// rows are 128 bytes, their eight 16-byte chunks XOR-swizzled with key(row) = (row >> 1) & 7 (a
+// fragment read takes rows r .. r + 15 of one chunk column in one pass: two rows share a 256-byte
+// bank line, eight keys spread the eight pairs).
+// RA = 32, 128 or 256 rows have room.  RA = 32: a wave then has one 32-row block to multiply instead of two (pruning
 // call at 22 rows x 4096 x 32000: 80 us, 83 with RA = 128; a shape for 64 rows gained nothing at 44).
 // The K loop runs at 5.8 TB/s of weights, read once and non-temporally (without that 6 us more); a
 // ring of seven stages instead of four changes nothing, and neither does requesting 256 or 512
@@ -1047,7 +607,17 @@ __device__ __forceinline__ void early_head_tile(
 // children fetched before the K loop and a tile plan without 64-bit divisions (14 -> 10 us
 // outside the K loop; 72 rows: 83 -> 71 us).
 // ------------------------------------------------------------------------------------
-constexpr int kSmallBM = 128, kSmallBK = 64, kSmallStages = 4;
+struct GemmFrag {
+  u32x4 a[2], b[2];
+};
+// Waits until at most N LDS reads of this wave are outstanding (they return in order); the
+// fragment named is the one waited for, so that its uses stay below the wait.
+template <int N>
+__device__ __forceinline__ void gemm_wait_frag(GemmFrag &f) {
+  asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.b[0]), "+v"(f.b[1]) : "n"(N));
+}
+
+constexpr int kSmallBM = 256, kSmallBK = 64;
 constexpr int kSmallRowBytes = kSmallBK * 2;                          // 128
 constexpr int kSmallWBytes = 128 * kSmallRowBytes;                    // 16 KB of weight rows per stage
 
@@ -1057,9 +627,9 @@ __device__ __forceinline__ void early_head_small_tile(
     const uint16_t *__restrict__ hidden_states, const uint16_t *__restrict__ head_weight,
     const HeadTables &tb, unsigned char *gemm_smem) {
   constexpr int FN = 2;
-  constexpr int kStages = kSmallStages, kWOffset = RA * kSmallRowBytes, kStageBytes = kWOffset + kSmallWBytes;
+  constexpr int kStages = RA == 256 ? 3 : 4, kWOffset = RA * kSmallRowBytes, kStageBytes = kWOffset + kSmallWBytes;
   static_assert(kStages * kStageBytes <= kHeadLdsBytes, "ring");
-  constexpr int kALoads = RA / 8 > 8 ? 2 : 1;  // 8-row groups of score rows a wave may have to fetch
+  constexpr int kALoads = RA > 64 ? RA / 64 : 1;  // 8-row groups of score rows a wave may have to fetch
   constexpr int kX = RA == 32 ? 1 : 2;         // 32-row blocks of a wave's 64 rows that exist
   typedef __attribute__((address_space(3))) void lds_void;
   typedef const __attribute__((address_space(1))) void global_void;
@@ -1073,7 +643,8 @@ __device__ __forceinline__ void early_head_small_tile(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int l32 = lane & 31, g = lane >> 5;
-  RowChildren<RA / kGemmWaves> ch;
+  constexpr int kRows = RA > 128 ? 128 : RA;  // of the epilogue at a time
+  RowChildren<kRows / kGemmWaves> ch;
   if (KIND == 0) ch.rows(wave, 0, m_total, tb);
   // ---- loader: a load instruction fills 8 rows of 128 bytes (1 KB).  A stage has RA / 8 such
   //      groups of score rows, fetched by wave g / kALoads, and 16 of weight rows; wave w takes
@@ -1081,6 +652,8 @@ __device__ __forceinline__ void early_head_small_tile(
   const int ld_row = lane >> 3, ld_pos = lane & 7;
   const unsigned char *a_src[kALoads], *b_src[2];
   bool a_on[kALoads];
+  // the lane's chunk lies in the second half of the 128 bytes: a half step fetches the first instead
+  int a_back[kALoads], b_back[2];
   int per_step = 2;  // loads of this wave per K step
 #pragma unroll
   for (int j = 0; j < kALoads; ++j) {
@@ -1088,17 +661,28 @@ __device__ __forceinline__ void early_head_small_tile(
     a_on[j] = kALoads * wave + j < RA / 8 && 8 * (kALoads * wave + j) < m_total;
     per_step += a_on[j] ? 1 : 0;
     const int m = r < m_total ? r : m_total - 1;
-    a_src[j] = reinterpret_cast<const unsigned char *>(hidden_states + (size_t)tb.row_src[m] * hidden) +
-               ((ld_pos ^ ((r >> 1) & 7)) << 4);
+    const int chunk = ld_pos ^ ((r >> 1) & 7);
+    a_back[j] = chunk & 4 ? 64 : 0;
+    a_src[j] = reinterpret_cast<const unsigned char *>(hidden_states + (size_t)tb.row_src[m] * hidden) + (chunk << 4);
   }
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int r = 8 * (2 * wave + j) + ld_row;
     const int v = v0 + r < vocab ? v0 + r : vocab - 1;
-    b_src[j] = reinterpret_cast<const unsigned char *>(head_weight + (size_t)v * hidden) + ((ld_pos ^ ((r >> 1) & 7)) << 4);
+    const int chunk = ld_pos ^ ((r >> 1) & 7);
+    b_back[j] = chunk & 4 ? 64 : 0;
+    b_src[j] = reinterpret_cast<const unsigned char *>(head_weight + (size_t)v * hidden) + (chunk << 4);
   }
   const bool w_on = wm * 64 < m_total;  // this wave's 64 rows hold score rows
-  auto issue = [&](int slot) {
+  const int n_steps = (hidden + kSmallBK - 1) / kSmallBK;
+  const bool half_end = hidden % kSmallBK != 0;  // the last step is 32 deep
+  auto issue = [&](int slot, int step) {
+    if (half_end && step + 1 == n_steps) {
+#pragma unroll
+      for (int j = 0; j < kALoads; ++j) a_src[j] -= a_back[j];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) b_src[j] -= b_back[j];
+    }
     unsigned char *dst = gemm_smem + slot * kStageBytes;
 #pragma unroll
     for (int j = 0; j < kALoads; ++j) {
@@ -1125,7 +709,7 @@ __device__ __forceinline__ void early_head_small_tile(
       b_rd[ks] = smem_base + kWOffset + wn * 64 * kSmallRowBytes + off;
     }
   }
-  typedef GemmFrag<FN> Frag;
+  typedef GemmFrag Frag;
   auto read = [&](Frag &f, uint32_t so, int ks) {
     const uint32_t pa = a_rd[ks] + so, pb = b_rd[ks] + so;
     f.a[0] = gemm_lds_read16<0>(pa);
@@ -1150,13 +734,12 @@ __device__ __forceinline__ void early_head_small_tile(
             __builtin_bit_cast(bf16x8, f.a[x]), __builtin_bit_cast(bf16x8, f.b[y]), acc[x][y], 0, 0, 0);
   };
 
-  const int n_steps = hidden / kSmallBK;
   const int n_pro = n_steps < kStages ? n_steps : kStages;
-  constexpr int kMaxOutstanding = (kStages - 1) * 4;
+  constexpr int kMaxOutstanding = (kStages - 1) * (kALoads + 2);
   int slot_ld = 0;
   if (KIND == 0) ch.list(lane, tb);
   for (int i = 0; i < n_pro; ++i) {
-    issue(slot_ld);
+    issue(slot_ld, i);
     slot_ld = slot_ld + 1 == kStages ? 0 : slot_ld + 1;
   }
   // (loads younger than the ring's only make the counted waits below stricter)
@@ -1172,27 +755,29 @@ __device__ __forceinline__ void early_head_small_tile(
       read(f1, so, 1);
       gemm_wait_frag<kReads>(f0);  // the reads just issued fly while the MFMAs below run
       mma(f0);
-      read(f0, so, 2);
-      gemm_wait_frag<kReads>(f1);
-      mma(f1);
-      read(f1, so, 3);
-      gemm_wait_frag<kReads>(f0);
-      mma(f0);
+      if (!half_end || step + 1 < n_steps) {
+        read(f0, so, 2);
+        gemm_wait_frag<kReads>(f1);
+        mma(f1);
+        read(f1, so, 3);
+        gemm_wait_frag<kReads>(f0);
+        mma(f0);
+      }
     }
     __builtin_amdgcn_sched_barrier(0);
     if (w_on) gemm_wait_frag<0>(f1);  // this wave is done with the slot of this step
     if (step + 1 < n_steps) {
       const int issued_after = n_steps - 2 - step;  // steps after the next that have been issued, if not more than fit
       if (issued_after >= kStages - 2) {
-        if (per_step == 2) gemm_wait_vmem<2 * (kStages - 2)>();
-        else if (per_step == 3) gemm_wait_vmem<3 * (kStages - 2)>();
-        else gemm_wait_vmem<4 * (kStages - 2)>();
+        static_for<kALoads + 1>([&](auto a) {  // 2 .. kALoads + 2 loads per step
+          if (per_step == 2 + a) gemm_wait_vmem<(2 + a) * (kStages - 2)>();
+        });
       } else {
         gemm_wait_outstanding<kMaxOutstanding>(issued_after * per_step);
       }
       __builtin_amdgcn_s_barrier();  // it is visible; every wave is done with this step's slot
       if (step + kStages < n_steps) {
-        issue(slot_ld);  // into the slot of this step
+        issue(slot_ld, step + kStages);  // into the slot of this step
         slot_ld = slot_ld + 1 == kStages ? 0 : slot_ld + 1;
       }
       so = so + kStageBytes == kStages * kStageBytes ? 0 : so + kStageBytes;
@@ -1215,48 +800,61 @@ __device__ __forceinline__ void early_head_small_tile(
           s_z[(wm * 64 + 32 * x + 8 * (r >> 2) + 4 * g + (r & 3)) * kRowsCols + wn * 64 + 32 * y + l32] = acc[x][y][r];
   }
   __syncthreads();
-  rows_epilogue<KIND, RA / kGemmWaves, 2>(ch, s_z, wave, lane, 0, m_total, v0, vocab, n_tile, tb);
+  if constexpr (RA > kRows) {
+    // the second half's children are on their way while the first half is counted
+    RowChildren<kRows / kGemmWaves> ch2;
+    if (KIND == 0) {
+      ch2.rows(wave, kRows, m_total, tb);
+      ch2.list(lane, tb);
+    }
+    rows_epilogue<KIND, kRows / kGemmWaves>(ch, s_z, wave, lane, 0, m_total, v0, vocab, n_tile, tb);
+    if (KIND == 0) ch2.values(lane, tb);
+    rows_epilogue<KIND, kRows / kGemmWaves>(ch2, s_z + kRows * kRowsCols, wave, lane, kRows, m_total, v0, vocab, n_tile, tb);
+  } else {
+    rows_epilogue<KIND, kRows / kGemmWaves>(ch, s_z, wave, lane, 0, m_total, v0, vocab, n_tile, tb);
+  }
   __syncthreads();  // the next tile's loads reuse this memory
 }
 
 
 #include "early_head_tall.h"
 
-// Which tile shape a call uses: decided on the device by every workgroup (and by the kernels
-// that read the per-tile results) from the row count, which the host never sees.  The cost of
-// a shape is rounds of workgroups over the compute units x tile area, the tall shape's area
-// weighted by what it was measured to cost per output relative to the other.
+// Which tile a call uses: decided on the device by every workgroup (and by the kernels
+// that read the per-tile results) from the row count, which the host never sees.
+//   - At most 256 rows: the tile of few rows, one row tile, 128 entries wide (32000 entries: 250
+//     workgroups).  220 rows x 4096 x 32000, pruning call: 131 us; 138 with 256 x 128 tiles of
+//     32-deep steps, 146 with two row tiles of 160 x 256.
+//   - More: the shape of the least cost = rounds of workgroups over the compute units x
+//     (10 + mi * nj).  Measured per round, us at 4096 x 32000: 92 for 160 x 256, 105 for 192, 119 for
+//     224, 127 for 256, 141 for 288, 167 for 352 x 256, i.e. 3.1 us per matrix tile of a wave and 30
+//     beside them.  Tiles of 192 columns were no better (288 x 192: 106 us), of 128 columns worse.
 struct HeadPlan {
-  int tall;     // 1: 352 x 256 tiles, 0: 256 x 64*fn tiles
-  int fn;
+  int mi, nj;  // tile of 32*mi x 64*nj; mi = 0: the tile of few rows
   int m_tiles, n_tiles;
-  int n_parts;  // column parts per row that the epilogue writes
 };
-constexpr int kTallCostPercent = 85;
+
+#ifndef PROPD_TALL_SHAPES
+#define PROPD_TALL_SHAPES(X) X(11, 4) X(10, 4) X(9, 4) X(8, 4) X(7, 4) X(6, 4) X(5, 4)
+#endif
 
 __host__ __device__ inline HeadPlan head_plan(int m_total, int vocab, int cus, int force) {
-  HeadPlan pl;
-  pl.tall = 0;
-  pl.m_tiles = (m_total + kGemmBM - 1) / kGemmBM;
-  pl.fn = gemm_pick_fn(pl.m_tiles > 0 ? pl.m_tiles : 1, vocab, cus);
-  pl.n_tiles = (vocab - 1) / (64 * pl.fn) + 1;
-  pl.n_parts = 2 * pl.n_tiles;
-  if (m_total <= 0) return pl;
-  const long long rounds = div_up((long long)pl.m_tiles * pl.n_tiles, cus);
-  const long long cost = rounds * kGemmBM * 64 * pl.fn * 100;
-  const int mt = (m_total + kTallBM - 1) / kTallBM, nt = (vocab + kTallBN - 1) / kTallBN;
-  const long long rounds_tall = div_up((long long)mt * nt, cus);
-  const long long cost_tall = rounds_tall * kTallBM * kTallBN * kTallCostPercent;
-  if (force == 2 || (force == 0 && cost_tall < cost)) {
-    pl.tall = 1;
-    pl.m_tiles = mt;
-    pl.n_tiles = nt;
-    pl.n_parts = 4 * nt;
-  }
+  HeadPlan pl = {0, 2, 1, (vocab - 1) / 128 + 1};
+  if (m_total <= kSmallBM && force == 0) return pl;
+  const int rows = m_total > 0 ? m_total : 1;
+  long long best = -1;
+  auto take = [&](int mi, int nj, int mt, int nt) {
+    const long long cost = div_up((long long)mt * nt, cus) * (10 + mi * nj);
+    if (best >= 0 && cost >= best) return;
+    best = cost;
+    pl = HeadPlan{mi, nj, mt, nt};
+  };
+#define X(MI, NJ)                                                          \
+  if (force == 0 || (force == 1 && MI == 8) || (force == 2 && MI == 11))   \
+    take(MI, NJ, (rows - 1) / (32 * MI) + 1, (vocab - 1) / (64 * NJ) + 1);
+  PROPD_TALL_SHAPES(X)
+#undef X
   return pl;
 }
-
-static_assert(kTallLdsBytes <= kHeadLdsBytes && kGemmLdsBytes <= kHeadLdsBytes, "rings");
 
 // Persistent over the tiles: tile -> (xcd, slot) as described above, a workgroup takes tiles
 // blockIdx.x, blockIdx.x + gridDim.x, ... (the grid is a multiple of the XCD count).
@@ -1277,23 +875,24 @@ __global__ __launch_bounds__(kGemmThreads, 1) void early_head_bf16_kernel(
     const int n_tile = group * kXcds + xcd;
     if (n_tile >= n_tiles) continue;
     const int m_tile = (int)(slot - (long long)group * m_tiles);
-    if (pl.tall) {
-      early_head_tall_tile<KIND>(hidden, vocab, m_total, m_tile * kTallBM, n_tile * kTallBN, n_tile,
-                                 hidden_states, head_weight, tb, gemm_smem);
-      continue;
-    }
-    const int m0 = m_tile * kGemmBM, v0 = n_tile * 64 * pl.fn;
-    if (pl.fn == 2 && m_total <= kSmallBM && hidden % kSmallBK == 0) {
+    // a wave may be here while another still reads the last stage of the tile before this one
+    if (tile != blockIdx.x) __syncthreads();
+    if (pl.mi == 0) {
+      const int v0 = n_tile * 128;
       if (m_total <= 32)
         early_head_small_tile<KIND, 32>(hidden, vocab, m_total, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
-      else
+      else if (m_total <= 128)
         early_head_small_tile<KIND, 128>(hidden, vocab, m_total, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
-    } else if (pl.fn == 2)
-      early_head_tile<2, KIND>(hidden, vocab, m_total, m0, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
-    else if (pl.fn == 3)
-      early_head_tile<3, KIND>(hidden, vocab, m_total, m0, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
-    else
-      early_head_tile<4, KIND>(hidden, vocab, m_total, m0, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
+      else
+        early_head_small_tile<KIND, 256>(hidden, vocab, m_total, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
+      continue;
+    }
+#define X(MI, NJ)                                                                                              \
+  if (pl.mi == MI && pl.nj == NJ)                                                                              \
+    early_head_tall_tile<MI, NJ, KIND>(hidden, vocab, m_total, m_tile * 32 * MI, n_tile * 64 * NJ, n_tile,      \
+                                       hidden_states, head_weight, tb, gemm_smem);
+    PROPD_TALL_SHAPES(X)
+#undef X
   }
 }
 
@@ -1312,7 +911,7 @@ __global__ __launch_bounds__(kWave) void row_lse_kernel(int B, int vocab, int cu
   if (m >= m_total) return;
   int n_parts;
   if (bf16) {
-    n_parts = head_plan(m_total, vocab, cus, force).n_parts;
+    n_parts = head_plan(m_total, vocab, cus, force).n_tiles;
   } else {
     n_parts = f32_plan(m_total, vocab).n_tiles;
   }
@@ -1735,7 +1334,6 @@ static propd_status prune_impl(
     tb.lse_part = ws.lse_part;
     tb.parts = (int)ws.parts;
     if (dt == PROPD_BF16) {
-      constexpr int BM = kGemmBM, BN = 64 * kGemmMinFN;  // the tile count is largest for the narrowest tiles
       static bool attr_set = false;
       if (!attr_set) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(&early_head_bf16_kernel<0>),
@@ -1747,8 +1345,8 @@ static propd_status prune_impl(
       }
       // one workgroup per compute unit and round, two rounds resident in the queue; fewer when
       // even the largest row count has fewer tiles
-      const long long m_tiles_cap = (ws.row_cap + BM - 1) / BM;
-      const long long n_groups = ((vocab + BN - 1) / BN + kXcds - 1) / kXcds;
+      const long long m_tiles_cap = ws.row_cap <= kSmallBM ? 1 : (ws.row_cap + 159) / 160;  // no tile is smaller than 160 x 256
+      const long long n_groups = ((vocab + 127) / 128 + kXcds - 1) / kXcds;          // or narrower than 128
       long long grid = kXcds * n_groups * m_tiles_cap;
       const long long persistent = (2ll * cus + kXcds - 1) / kXcds * kXcds;
       grid = grid < persistent ? grid : persistent;

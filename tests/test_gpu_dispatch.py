@@ -222,3 +222,39 @@ def test_attention_bf16_merge_of_cut_units(pb, oracle, B, H, T_max, L, d):
     x = synth.make_attention_inputs(w, seq_lens=lens, trees=shapes)
     out, sent = run_attention(pb, x)
     check_attention(oracle, x, out, sent)
+
+
+# ------------------------------------------------------------------ bf16 scoring, many rows
+
+
+@pytest.mark.parametrize("Hd", [32, 96, 160, 288])
+def test_prob_prune_several_tiles_per_workgroup(pb, oracle, Hd):
+    """More tiles than workgroups under the criterion whose epilogue passes nothing through LDS: a
+    workgroup starts its next tile's loads only when all its waves have left the tile before (the
+    last stage lies in another slot of the ring for every count of K steps modulo four)."""
+    B, T_max, V = 9, 128, 32000
+    w = synth.Workload(74, "case", "bf16", B, 1, 128, T_max, Hd, V, 8, 1e-3)
+    x = synth.make_prune_inputs(w, trees=[synth.rank_product_tree(128, 5)] * B)
+    logm, _, _ = prob_reference(oracle, x, threshold=0.5)
+    thr = float(np.float32(threshold_in_a_gap(logm, x["n_nodes"], 1e-3, 0.6)))
+    _, _, ref = prob_reference(oracle, x, threshold=thr)
+    res, sents = run_prob(pb, x, [x["hidden_states"]], threshold=thr)
+    check_prob(pb, oracle, x, res, ref, logm, [x["hidden_states"]], sents)
+
+
+@pytest.mark.parametrize("B,T,V", [(1, 128, 32000), (2, 66, 32000), (2, 128, 4001), (3, 87, 32000), (3, 128, 32000),
+                                   (4, 112, 32000), (4, 128, 32000), (5, 116, 32000), (5, 128, 32000), (6, 118, 32000),
+                                   (7, 120, 32001), (7, 120, 700)])
+def test_prune_bf16_every_tile_shape(pb, oracle, B, T, V):
+    """B chains of T nodes have B * (T - 1) score rows.  Against 32000 entries on 256 compute units the
+    counts 127, 130, 254, 261, 381, 444, 508, 575, 635, 702 and 833 take every tile there is, with
+    its last rows missing; both criteria, rows of an odd number of 32s."""
+    w = synth.Workload(76, "case", "bf16", B, 1, 128, T, 96, V, 6, 1e-3)
+    x = synth.make_prune_inputs(w, trees=[synth.chain_tree(T)] * B, p_pass=0.8)
+    res, sents = run_prune(pb, x, [x["hidden_states"]])
+    check_prune(oracle, x, res, [x["hidden_states"]], sents)
+    logm, _, _ = prob_reference(oracle, x, threshold=0.5)
+    thr = float(np.float32(threshold_in_a_gap(logm, x["n_nodes"], 1e-3, 0.95)))
+    _, _, ref = prob_reference(oracle, x, threshold=thr)
+    res, sents = run_prob(pb, x, [x["hidden_states"]], threshold=thr)
+    check_prob(pb, oracle, x, res, ref, logm, [x["hidden_states"]], sents)
