@@ -148,8 +148,15 @@ def _dev(t: torch.Tensor, dtype: torch.dtype, name: str) -> torch.Tensor:
     return t
 
 
+# The current stream's handle without the Stream object around it, which costs about 4 us of host
+# time per call, as much as everything else a small call does (a torch without it gets the object).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dt(t: torch.Tensor) -> int:
@@ -297,15 +304,17 @@ def _early_prune(crit, tree, hidden_states, head_weight, payloads, payload_out, 
     if tree.B != B or tree.T_max != T_max:
         raise ValueError("tree and hidden_states disagree on B or T_max")
     dev = hidden_states.device
+    # per-node and per-sequence outputs come out of one allocation each: an allocation per output
+    # was a third of the host's time for the call
     i32 = dict(dtype=torch.int32, device=dev)
+    nodes = torch.empty((6 if want_rank else 5, B, T_max), **i32).unbind(0)
+    n_kept, n_nodes = torch.empty((2, B), **i32).unbind(0)
     res = PruneResult(
         keep_bits=torch.empty((B, 2), dtype=torch.int64, device=dev),
-        new_index=torch.empty((B, T_max), **i32), orig_index=torch.empty((B, T_max), **i32),
-        n_kept=torch.empty(B, **i32), cu_nodes=torch.empty(B + 1, **i32),
-        tree=Tree(n_nodes=torch.empty(B, **i32), parent=torch.empty((B, T_max), **i32),
-                  token=torch.empty((B, T_max), **i32), depth=torch.empty((B, T_max), **i32),
+        new_index=nodes[0], orig_index=nodes[1], n_kept=n_kept, cu_nodes=torch.empty(B + 1, **i32),
+        tree=Tree(n_nodes=n_nodes, parent=nodes[2], token=nodes[3], depth=nodes[4],
                   anc=torch.empty((B, T_max, 2), dtype=torch.int64, device=dev)),
-        rank=torch.empty((B, T_max), **i32) if want_rank else None, payloads=[])
+        rank=nodes[5] if want_rank else None, payloads=[])
     descs = (_Payload * max(len(payloads), 1))()
     for n, src in enumerate(payloads):
         if not src.is_cuda or not src.is_contiguous() or src.dim() not in (3, 4):
