@@ -436,12 +436,6 @@ constexpr int kGemmRowBytes = kBK * 2;                                          
 constexpr int kXcds = 8;
 constexpr int kHeadLdsBytes = 155648;  // dynamic LDS of the scoring kernel: the largest ring of its tile shapes
 
-// (A 64-bit division is a long sequence of scalar instructions, several of which in front of every
-// workgroup's first load are felt in the short calls: the counts fit 32 bits in all but extreme ones.)
-__host__ __device__ inline long long div_up(long long a, int b) {
-  if (a < (1ll << 31) - b) return (uint32_t)((uint32_t)a + (uint32_t)b - 1u) / (uint32_t)b;
-  return (a + b - 1) / b;
-}
 template <int N>
 __device__ __forceinline__ void gemm_wait_vmem() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
@@ -841,9 +835,21 @@ __host__ __device__ inline HeadPlan head_plan(int m_total, int vocab, int cus, i
   HeadPlan pl = {0, 2, 1, (vocab - 1) / 128 + 1};
   if (m_total <= kSmallBM && force == 0) return pl;
   const int rows = m_total > 0 ? m_total : 1;
+  const float inv = 1.f / (float)cus;  // a division per shape is felt in front of a small kernel's first load
   long long best = -1;
   auto take = [&](int mi, int nj, int mt, int nt) {
-    const long long cost = div_up((long long)mt * nt, cus) * (10 + mi * nj);
+    const long long tiles = (long long)mt * nt;
+    long long rounds;
+    if (tiles < (1ll << 24)) {  // by the reciprocal, off by one at most
+      const int t = (int)tiles;
+      int q = (int)((float)t * inv);
+      q -= q * cus > t ? 1 : 0;
+      q += (q + 1) * cus <= t ? 1 : 0;  // q = t / cus
+      rounds = q * cus < t ? q + 1 : q;
+    } else {
+      rounds = (tiles + cus - 1) / cus;
+    }
+    const long long cost = rounds * (10 + mi * nj);
     if (best >= 0 && cost >= best) return;
     best = cost;
     pl = HeadPlan{mi, nj, mt, nt};
