@@ -402,6 +402,7 @@ struct HeadTables {
   int cnt_stride;     // B * T_max
   float *lse_part;
   int parts;  // column parts per row in lse_part
+  int32_t *n_tiles;  // top-k criterion, bf16: the column tiles of the plan, left for the decision kernel
 };
 
 // ------------------------------------------------------------------------------------
@@ -872,6 +873,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void early_head_bf16_kernel(
   if (m_total <= 0) return;
   const HeadPlan pl = head_plan(m_total, vocab, cus, force);
   const int m_tiles = pl.m_tiles, n_tiles = pl.n_tiles;
+  if (KIND == 0 && blockIdx.x == 0 && threadIdx.x == 0) *tb.n_tiles = n_tiles;
   const long long total = (long long)kXcds * ((n_tiles + kXcds - 1) / kXcds) * m_tiles;
   extern __shared__ __attribute__((aligned(1024))) unsigned char gemm_smem[];
   for (long long tile = blockIdx.x; tile < total; tile += gridDim.x) {
@@ -962,7 +964,7 @@ struct Criterion {
 constexpr int kCompactSplit = 4;  // threads that add up one node's per-tile counts
 
 __global__ __launch_bounds__(PROPD_MAX_TREE * kCompactSplit) void prune_compact_kernel(
-    int B, int T_max, int vocab, int cus, int force, int bf16, Criterion crit, const int32_t *__restrict__ n_nodes,
+    int B, int T_max, int vocab, int bf16, Criterion crit, const int32_t *__restrict__ plan_tiles, const int32_t *__restrict__ n_nodes,
     const int32_t *__restrict__ parent, const int32_t *__restrict__ token,
     const int32_t *__restrict__ depth, const uint64_t *__restrict__ anc,
     const int32_t *__restrict__ row_base, const int32_t *__restrict__ cnt_part,
@@ -995,7 +997,10 @@ __global__ __launch_bounds__(PROPD_MAX_TREE * kCompactSplit) void prune_compact_
     if (row_base) {
       const int m_total = row_base[B];
       if (bf16) {
-        if (m_total > 0) n_tiles = head_plan(m_total, vocab, cus, force).n_tiles;
+        // left by the scoring kernel (which has nothing to do without rows): worked out here it stood
+        // 2 us in front of the first count
+        const int left = *plan_tiles;
+        if (m_total > 0) n_tiles = left;
       } else if (m_total > 0) {
         n_tiles = f32_plan(m_total, vocab).n_tiles;
       }
@@ -1339,6 +1344,7 @@ static propd_status prune_impl(
     tb.cnt_stride = B * T_max;
     tb.lse_part = ws.lse_part;
     tb.parts = (int)ws.parts;
+    tb.n_tiles = reinterpret_cast<int32_t *>(ws.logq);  // unused by the top-k criterion otherwise
     if (dt == PROPD_BF16) {
       static bool attr_set = false;
       if (!attr_set) {
@@ -1386,7 +1392,8 @@ static propd_status prune_impl(
   }
   if (!launch_ok()) return PROPD_ERR_DEVICE;
   hipLaunchKernelGGL(prune_compact_kernel, dim3(B), dim3(PROPD_MAX_TREE * kCompactSplit), 0, st, B, T_max,
-                     vocab, cus, force, dt == PROPD_BF16 ? 1 : 0, crit, tree->n_nodes, tree->parent, tree->token,
+                     vocab, dt == PROPD_BF16 ? 1 : 0, crit, reinterpret_cast<const int32_t *>(ws.logq),
+                     tree->n_nodes, tree->parent, tree->token,
                      tree->depth, tree->anc, scored ? ws.row_base : nullptr, ws.cnt_part, ws.logq,
                      keep_bits, new_index, orig_index, n_kept, tree_out->n_nodes, tree_out->parent,
                      tree_out->token, tree_out->depth, tree_out->anc, rank_out);
