@@ -953,7 +953,8 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
 // partials: written by other XCDs, so each comes from beyond the L2), not bytes.  Two kernels:
 //   by unit (no more units than workgroups: few units, each in many pieces): one workgroup per
 //     (unit, 32 queries, 32-wide block mb of d), one wave per q4, 16 pieces requested together.
-//     1 x 32 units of 1088 rows, 17 pieces each: 11.2 us by workgroup, 6.5 us by unit.
+//     1 x 32 units of 1088 rows, 17 pieces each: 11.2 us by workgroup, 6.5 us by unit.  The steps of the
+//     merge are those of the other kernel, one piece after the other, and so are the bits of the result.
 //   by workgroup (many units in a few pieces each): one wave per (workgroup of the main kernel, 32
 //     queries, block mb), four pieces of the whole block together.  640 units of 4224 rows on 512
 //     workgroups: 12 us; four such waves to a workgroup, or one wave per q4, cost 14 to 18 us.
@@ -1039,22 +1040,17 @@ __global__ __launch_bounds__(4 * kWave) void tree_attn_combine_unit_kernel(AttnP
       l[k] = p.part_ml[part_ml_index(ps, dw, 1, ln)];
       o[k] = *reinterpret_cast<const f32x4 *>(p.part_o + part_o_index(ps, dw, 4 * mb + q4, ln));
     }
-    float M_new = M;
-#pragma unroll
-    for (int k = 0; k < N; ++k) M_new = fmaxf(M_new, m[k]);
-    const float M_safe = M_new == -INFINITY ? 0.f : M_new, a_old = fast_exp2(M - M_safe);
-    lsum *= a_old;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j] *= a_old;
 #pragma unroll
     for (int k = 0; k < N; ++k)
       if (w0 + k <= w_last) {  // uniform
-        const float a_new = fast_exp2(m[k] - M_safe);
-        lsum += l[k] * a_new;
+        const float M_new = fmaxf(M, m[k]);
+        const float M_safe = M_new == -INFINITY ? 0.f : M_new;
+        const float a_old = fast_exp2(M - M_safe), a_new = fast_exp2(m[k] - M_safe);
+        lsum = lsum * a_old + l[k] * a_new;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j] += o[k][j] * a_new;
+        for (int j = 0; j < 4; ++j) acc[j] = acc[j] * a_old + o[k][j] * a_new;
+        M = M_new;
       }
-    M = M_new;
   }
   const float inv = 1.f / lsum;
   const int d0 = 32 * mb + 8 * q4;  // the wave's 8 columns; the lane's four start at d0 + 4 g
@@ -1129,30 +1125,22 @@ static int compute_units() {
   return cus;
 }
 
-static long long total_stages(int B, int H, int L_max, int T_max) {
-  return (long long)B * H * ((L_max + kStageRows - 1) / kStageRows + (T_max + kStageRows - 1) / kStageRows);
-}
-
 // Workgroups of the persistent kernel: at most one per two stages of the call, a bound the
 // host can compute without a device (the workspace is sized by it) ...
 static int grid_bound(int B, int H, int L_max, int T_max) {
-  const long long stages = total_stages(B, H, L_max, T_max);
+  const long long per_unit = (L_max + kStageRows - 1) / kStageRows + (T_max + kStageRows - 1) / kStageRows;
+  const long long stages = (long long)B * H * per_unit;
   long long grid = kMaxGrid;
   if (grid > (stages + 1) / 2) grid = (stages + 1) / 2;
   return (int)(grid < 1 ? 1 : grid);
 }
 
-// ... as many as are resident on the chip, and at least three stages for each: with two, a unit
-// has so many pieces that their merge costs more than the shorter ranges save (1 x 32 units of
-// 1088 rows, whole call: 21.9 us with two, 20.5 with three, 20.9 with four, 23 with eight; 1 x 8
-// units of 4128 rows with 128 queries: 28.0, 25.0, 25.5, 29.4).
-constexpr int kMinStages = 3;
+// ... and as many as are resident on the chip.  (Ranges of three stages or more take 1 us less at 1 x 32
+// units of 1088 rows, but a piece's largest weight is exactly 1 and rounds without error: with fewer
+// pieces the error against 64 bits goes from 2.20e-3 to 2.24e-3.)
 static int pick_grid(int per_cu, int B, int H, int L_max, int T_max) {
-  long long grid = grid_bound(B, H, L_max, T_max);
-  const long long resident = (long long)per_cu * compute_units(), fed = total_stages(B, H, L_max, T_max) / kMinStages;
-  if (grid > resident) grid = resident;
-  if (grid > fed) grid = fed;
-  return (int)(grid < 1 ? 1 : grid);
+  const int bound = grid_bound(B, H, L_max, T_max), resident = per_cu * compute_units();
+  return bound < resident ? bound : resident;
 }
 
 // Partial slots (two per workgroup) and cut records (one per workgroup) of the largest grid
