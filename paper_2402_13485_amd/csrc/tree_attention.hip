@@ -514,16 +514,16 @@ __device__ __forceinline__ bool has_nan(const f32x16 (&o)[MB]) {
   return sum != sum;
 }
 
-// D = 128 multiplies bf16 weights with V.  D = 64 keeps them in fp32 precision: a weight is the
-// sum of two bf16 values, both of which are multiplied, and the row sums are taken over the fp32
-// weights.  (The extra products are free, a stage is bound by its K/V bytes.)
+// D = 128 multiplies bf16 weights with V.  D = 64 keeps them in fp32: a weight is the sum of three
+// bf16 values, 8 of its 24 bits each, all of which are multiplied.  (With two of them a weight
+// is off by up to 2^-17.  8 x 16 units of 64 queries x 2048 keys, whole call: 33.8 us, 30.7 with two.)
 template <int NS, int D>
 __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_kernel(AttnParams p) {
   using G_ = Geo<D>;
   constexpr int kRowBytes = G_::kRowBytes, kHalfStage = G_::kHalfStage, kStageBytes = G_::kStageBytes;
   constexpr int kKs = G_::kKs, kMb = G_::kMb, kLoads = G_::kLoads;
-  constexpr bool kTwoPart = D == 64;  // weights as two bf16 values
-  constexpr int kParts = kTwoPart ? 2 : 1;
+  constexpr bool kExact = D == 64;  // weights of fp32 precision, in several bf16 values
+  constexpr int kParts = kExact ? 3 : 1;
   static_assert(NS >= 4, "three stages are in use by the math, the rest is in flight");
   constexpr int kAhead = NS - 3;  // stages in flight beyond the newest one the math uses
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -687,7 +687,7 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
   // D = 64: left to the compiler, since code that it may move registers in (redo_not_finite) runs
   // while they are in flight; its waits come where wait_queries() waits for everything anyway
   auto load16 = [](const void *ptr) {
-    if constexpr (kTwoPart) return *reinterpret_cast<const u32x4 *>(ptr);
+    if constexpr (kExact) return *reinterpret_cast<const u32x4 *>(ptr);
     else return global_load16_untracked(ptr);
   };
   auto load_queries = [&](const Piece &pc) {
@@ -747,7 +747,7 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
 #pragma unroll
     for (int ks2 = 0; ks2 < 2; ++ks2) {
 #pragma unroll
-      for (int part = kParts - 1; part >= 0; --part) {  // the small part first
+      for (int part = kParts - 1; part >= 0; --part) {  // the small parts first
         const u32x4 pv = {pw[part][4 * ks2], pw[part][4 * ks2 + 1], pw[part][4 * ks2 + 2], pw[part][4 * ks2 + 3]};
         const bf16x8 pf = __builtin_bit_cast(bf16x8, pv);
 #pragma unroll
@@ -856,12 +856,17 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
         for (int r = 0; r < 16; r += 2) {
           const float p0 = fast_exp2(fmaf(sc[r], p.scale_log2e, neg_m));
           const float p1 = fast_exp2(fmaf(sc[r + 1], p.scale_log2e, neg_m));
-          pw[0][r >> 1] = cvt_pk_bf16(p0, p1);
-          if constexpr (kTwoPart) {
-            pw[1][r >> 1] = cvt_pk_bf16(p0 - __uint_as_float(pw[0][r >> 1] << 16),
-                                        p1 - __uint_as_float(pw[0][r >> 1] & 0xffff0000u));
+          if constexpr (kExact) {
+            uint32_t rest0 = __float_as_uint(p0), rest1 = __float_as_uint(p1);
+#pragma unroll
+            for (int part = 0; part < kParts; ++part) {  // upper halves, and what they leave (without rounding)
+              pw[part][r >> 1] = __builtin_amdgcn_perm(rest1, rest0, 0x07060302u);
+              rest0 = __float_as_uint(__uint_as_float(rest0) - __uint_as_float(rest0 & 0xffff0000u));
+              rest1 = __float_as_uint(__uint_as_float(rest1) - __uint_as_float(rest1 & 0xffff0000u));
+            }
             l_run += p0 + p1;
           } else {
+            pw[0][r >> 1] = cvt_pk_bf16(p0, p1);
             // the row sums are taken over the rounded bf16 weights, the values the MFMA multiplies
             l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pw[0][r >> 1]), ones,
                                                     l_run, false);
@@ -918,7 +923,7 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
       if (done.whole) {
         const float inv = 1.f / l_run;
         bool mine = t < T;
-        if constexpr (kTwoPart) {
+        if constexpr (kExact) {
           const bool bad = mine && (has_nan(o_acc) || inv != inv);
           if (redo_not_finite(p, bad, done.unit, wave * 32, D, 0, D)) mine = false;
         }

@@ -58,3 +58,22 @@ def test_attention_short_cache_keeps_two_stages_to_a_piece(pb, oracle, d):
     ref = reference(oracle, x)
     got = host_f64(run_attention(pb, x)[0])
     assert (np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 8e-6).all(), np.abs(got - ref).max()
+
+
+def test_attention_d64_weights_keep_fp32_precision(pb, oracle):
+    """Two keys per column of V with values +1 and -1 and weights w and w (1 + 2^-11): what is left is
+    2^-11 w, so an error of the weights of 2^-18 would be one of 2^-7 in the result.  fp32 weights: the
+    rounding of the exponents (2^-23 and less), of the exponentials and of the sums, 2e-3 of the
+    result together; then the result is rounded to bf16 (2^-9)."""
+    rng = np.random.default_rng(6)
+    H, d, L, T = 4, 64, 129, 9
+    score, second, v = np.full((H, L), 0.0), np.zeros((H, L)), np.zeros((H, L, d))
+    s = bf16(rng.uniform(-2.0, -0.05, (H, d)))
+    score[:, 1::2], score[:, 2::2] = s, s
+    second[:, 2::2] = 2.0 ** -11
+    for i in range(d):
+        v[:, 1 + 2 * i, i], v[:, 2 + 2 * i, i] = -1.0, 1.0
+    x = hand_made("bf16", H, d, T, score, second, v)
+    ref = reference(oracle, x)
+    got = host_f64(run_attention(pb, x)[0])
+    assert (np.abs(got - ref) <= (2.0 ** -9 + 2e-3) * np.abs(ref)).all(), (np.abs(got - ref) / np.abs(ref)).max()
