@@ -764,7 +764,10 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
   const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3f803f80u);
   // a new running maximum is adopted only when it exceeds the reference by 2^8 in the
   // exponent; below that the weights simply exceed 1, by a factor fp32 sums and bf16 hold
-  const float tau = 8.f / p.scale_log2e;
+  // D = 64: the reference is put 2^4 above the maximum instead, and adopted anew when that is
+  // exceeded, so that weights are at most 1 and no product leaves the range of its V value
+  // (finite, also where the scale is next to nothing)
+  const float tau = kExact ? fminf(4.f / p.scale_log2e, 1e38f) : 8.f / p.scale_log2e;
 
   Piece pc = piece_at(cp, 0);
   if (pc.n_cmp > 0) load_queries(pc);
@@ -828,7 +831,7 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
           swap_halves(lo, hi);
           m_blk = fmaxf(__uint_as_float(lo), __uint_as_float(hi));
         }
-        if (__builtin_amdgcn_ballot_w64(m_blk > m_run + tau) != 0) {
+        if (__builtin_amdgcn_ballot_w64(m_blk > (kExact ? m_run : m_run + tau)) != 0) {
           // rare: move the reference.  O must first receive the stage still pending, whose
           // weights are relative to the old reference.
           if (kPrev) {
@@ -836,7 +839,7 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
             clear_prev();
             mfma_settle();
           }
-          const float m_new = fmaxf(m_run, m_blk);
+          const float m_new = fmaxf(m_run, kExact ? m_blk + tau : m_blk);
           const float m_safe = m_new == -INFINITY ? 0.f : m_new;
           const float alpha = fast_exp2((m_run - m_safe) * p.scale_log2e);
           l_run *= alpha;

@@ -77,3 +77,32 @@ def test_attention_d64_weights_keep_fp32_precision(pb, oracle):
     ref = reference(oracle, x)
     got = host_f64(run_attention(pb, x)[0])
     assert (np.abs(got - ref) <= (2.0 ** -9 + 2e-3) * np.abs(ref)).all(), (np.abs(got - ref) / np.abs(ref)).max()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_attention_d64_values_near_the_largest(pb, oracle, dtype):
+    """A maximum that rises after the first rows, and V values within a factor of four of the
+    largest float: products of weights above 1 would overflow where the result does not."""
+    rng = np.random.default_rng(7)
+    H, d, L = 3, 64, 200
+    score = rng.uniform(-3.0, -1.0, (H, L))
+    score[:, 40], score[:, 130] = 3.0, 4.5
+    v = bf16(rng.uniform(-1.0, 1.0, (H, L, d)))
+    v[:, 40], v[:, 130] = 1e38, -5e37
+    x = hand_made(dtype, H, d, 2, bf16(score), np.zeros((H, L)), v)
+    ref = reference(oracle, x)
+    got = host_f64(run_attention(pb, x)[0])
+    assert np.isfinite(ref).all() and np.isfinite(got).all()
+    assert (np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref)).all()
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64)])
+def test_attention_with_next_to_no_scale(pb, oracle, dtype, d):
+    """A scale of 2^-130 makes all weights equal."""
+    rng = np.random.default_rng(9)
+    x = hand_made(dtype, 2, d, 3, bf16(rng.uniform(-3.0, 3.0, (2, 100))), np.zeros((2, 100)),
+                  bf16(rng.uniform(0.5, 1.0, (2, 100, d))))
+    x["scale"] = 2.0 ** -130
+    ref = reference(oracle, x)
+    got = host_f64(run_attention(pb, x)[0])
+    assert (np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref)).all()
