@@ -428,85 +428,40 @@ struct Walk {
   }
 };
 
-__device__ __forceinline__ float plain_load(const float *p) { return *p; }
-__device__ __forceinline__ float plain_load(const uint16_t *p) { return bf16_bits_to_f32(*p); }
-__device__ __forceinline__ void plain_store(float *p, float x) { *p = x; }
-__device__ __forceinline__ void plain_store(uint16_t *p, float x) { *p = (uint16_t)f32_to_bf16_bits(x); }
-
-// One query by one wave, products, softmax and output sums in fp32; columns [c_lo, c_hi) of its
-// row are stored.  Rows of V with weight zero are not looked at, so a value that is not finite
-// reaches the queries that see it and no others.
-template <typename P>
-__device__ __forceinline__ void plain_query(const P &p, int unit, int i, int d, int c_lo, int c_hi) {
-  const int b = unit / p.H;
-  int L = p.seq_lens[b];
-  L = L < 0 ? 0 : (L > p.L_max ? p.L_max : L);
-  int T = p.n_nodes[b];
-  T = T < 1 ? 1 : (T > p.T_max ? p.T_max : T);
-  const int lane = threadIdx.x & (kWave - 1);
-  const uint64_t a_lo = p.anc[((size_t)b * p.T_max + i) * 2];
-  const uint64_t a_hi = p.anc[((size_t)b * p.T_max + i) * 2 + 1];
-  const auto *q = p.q + ((size_t)unit * p.T_max + i) * d;
-  const auto *kc = p.k_cache + (size_t)unit * p.L_max * d;
-  const auto *vc = p.v_cache + (size_t)unit * p.L_max * d;
-  const auto *kt = p.k_tree + (size_t)unit * p.T_max * d;
-  const auto *vt = p.v_tree + (size_t)unit * p.T_max * d;
-
-  float m_run = -INFINITY, l_run = 0.f, o0 = 0.f, o1 = 0.f;  // lane owns columns lane, lane+64
-  const int total = L + T;
-  for (int j0 = 0; j0 < total; j0 += kWave) {
-    const int j = j0 + lane;
-    const bool in_cache = j < L;
-    const int jt = j - L;
-    const bool ok = in_cache || (j < total && test_bit128(a_lo, a_hi, jt));
-    float s = -INFINITY;
-    if (ok) {
-      const auto *kr = in_cache ? kc + (size_t)j * d : kt + (size_t)jt * d;
-      float acc = 0.f;
-      for (int x = 0; x < d; ++x) acc = fmaf(plain_load(q + x), plain_load(kr + x), acc);
-      s = acc * p.scale;
-    }
-    const float m_new = fmaxf(m_run, wave_reduce_max(s));
-    if (m_new == -INFINITY) continue;  // nothing visible in this chunk (uniform across the wave)
-    const float alpha = expf(m_run - m_new);
-    const float w = ok ? expf(s - m_new) : 0.f;
-    l_run = l_run * alpha + wave_reduce_sum(w);
-    o0 *= alpha;
-    o1 *= alpha;
-    m_run = m_new;
-    const uint64_t live = __ballot(w != 0.f);
-    for (uint64_t rest = live; rest; rest &= rest - 1) {
-      const int src = __ffsll((long long)rest) - 1;
-      const float wj = __shfl(w, src, kWave);
-      const int jj = j0 + src;
-      const auto *vr = jj < L ? vc + (size_t)jj * d : vt + (size_t)(jj - L) * d;
-      if (lane < d) o0 = fmaf(wj, plain_load(vr + lane), o0);
-      if (lane + 64 < d) o1 = fmaf(wj, plain_load(vr + lane + 64), o1);
-    }
-  }
-  auto *o = p.out + ((size_t)unit * p.T_max + i) * d;
-  if (lane >= c_lo && lane < c_hi) plain_store(o + lane, o0 / l_run);
-  if (lane + 64 >= c_lo && lane + 64 < c_hi) plain_store(o + lane + 64, o1 / l_run);
+// Values of V that are not finite.  The tiled kernels multiply every row of a tile by a weight,
+// zero for the rows that a query does not see (or that weigh less than the smallest number), and zero
+// times such a value is NaN.  D = 64 and fp32 operands keep these values to the queries that give them
+// weight: a tile is multiplied with zeros in the place of such values, and with a code in their place and
+// zero for all others by weights of 0 and 1.  The sum of the codes tells how many +inf, -inf and NaN
+// (at most 32 of each) the query sees in that column, and what to add to its result.
+//   fp32: tiles that have weights of zero (tree rows; hardly any other) and such a value.  With a NaN in
+//     every unit 2 x 16 units of 48 queries x 1024 keys take 31 us instead of 28, by HIP events.
+//   D = 64: a weight of three parts has zeros among them in any tile, and looking through every
+//     tile costs 1 us of 34, so a piece whose results hold a NaN is done once more: 83 us instead
+//     of 38 where every unit of 8 x 16 has one (64 queries x 2048 keys; 0.6 us for the question).
+constexpr float kCodePlus = 1.f, kCodeMinus = 64.f, kCodeNan = 4096.f;  // exact in bf16, sums exact in fp32
+__device__ __forceinline__ float not_finite_sum(float codes) {
+  const int n = (int)codes;
+  float x = (n & 63) != 0 ? INFINITY : 0.f;
+  x -= ((n >> 6) & 63) != 0 ? INFINITY : 0.f;
+  return (n >> 12) != 0 ? __uint_as_float(0x7fc00000u) : x;
 }
-
-// The tiled kernels multiply masked rows by a weight of zero, which a value that is not finite
-// turns into NaN for every query of the tile.  D = 64 and fp32 operands keep such values to the
-// queries that see them: a result with a NaN in it is computed once more, query by query, by
-// plain_query.  `bad`: the lane's part of its query's row (query l32, both lane halves) holds
-// a NaN.  Returns whether the lane's query was taken over.
-template <typename P>
-__device__ __forceinline__ bool redo_not_finite(const P &p, bool bad, int unit, int t0, int d, int c_lo, int c_hi) {
-  const uint64_t both = __ballot(bad);
-  if (both == 0) return false;
-  const uint32_t queries = (uint32_t)both | (uint32_t)(both >> 32);
-  for (uint32_t rest = queries; rest; rest &= rest - 1)
-    plain_query(p, unit, t0 + __ffs((int)rest) - 1, d, c_lo, c_hi);
-  return ((queries >> (threadIdx.x & 31)) & 1u) != 0;
+// the code of a value, 0 for a finite one
+__device__ __forceinline__ float not_finite_code(uint32_t bits) {
+  const uint32_t mag = bits & 0x7fffffffu;
+  return mag < 0x7f800000u ? 0.f : mag > 0x7f800000u ? kCodeNan : bits >> 31 ? kCodeMinus : kCodePlus;
+}
+// both halves of a bf16 pair: their codes as a pair; the halves that have one become zero
+__device__ __forceinline__ uint32_t take_not_finite(uint32_t &pair) {
+  const uint32_t lo = __float_as_uint(not_finite_code(pair << 16)) >> 16;
+  const uint32_t hi = __float_as_uint(not_finite_code(pair & 0xffff0000u)) & 0xffff0000u;
+  pair &= (lo ? 0u : 0xffffu) | (hi ? 0u : 0xffff0000u);
+  return lo | hi;
 }
 
 template <int MB>
 __device__ __forceinline__ bool has_nan(const f32x16 (&o)[MB]) {
-  float sum = 0.f;  // NaN as soon as a term is (and for +inf - inf, which then is done twice for nothing)
+  float sum = 0.f;  // NaN as soon as a term is (and for +inf - inf)
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -634,12 +589,15 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
   int slot_acq = 0;           // slot of the next stage to acquire
   int slot_ld = 0;            // slot of the next stage to issue
   auto next_slot = [](int sl) { return sl + 1 == NS ? 0 : sl + 1; };
+  auto fill_ring = [&]() {
 #pragma unroll
-  for (int i = 0; i < kAhead; ++i)
-    if (i < n_my) {
-      issue(slot_ld);
-      slot_ld = next_slot(slot_ld);
-    }
+    for (int i = 0; i < kAhead; ++i)
+      if (n_acq + i < n_my) {
+        issue(slot_ld);
+        slot_ld = next_slot(slot_ld);
+      }
+  };
+  fill_ring();
   auto acquire = [&]() -> int {
     if (n_acq + 1 < n_my) wait_vmem<2 * kLoads>(); else wait_vmem<0>();
     __builtin_amdgcn_s_barrier();
@@ -684,8 +642,7 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
   // ancestor set of this lane's node.  Lanes past the tree take node 0: valid memory, and
   // their columns are never stored.
   u32x4 qf[kKs], ancv;
-  // D = 64: left to the compiler, since code that it may move registers in (redo_not_finite) runs
-  // while they are in flight; its waits come where wait_queries() waits for everything anyway
+  // D = 64: left to the compiler, whose waits come where wait_queries() waits for everything anyway
   auto load16 = [](const void *ptr) {
     if constexpr (kExact) return *reinterpret_cast<const u32x4 *>(ptr);
     else return global_load16_untracked(ptr);
@@ -740,6 +697,38 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
       vt[1][2 * mb + 1] = lds_read_tr16<16 * kRowBytes>(v_rd[mb][1] + so);
     }
   };
+  // D = 64, a piece done for the second time: V values that are not finite are taken out of the V
+  // registers read last, and what they add to O is added
+  bool careful = false;
+  auto take_out = [&](const uint32_t (&pw)[kParts][8]) __attribute__((always_inline)) {
+    if (!kExact || !careful) return;
+    wait_lds<0>(vt[0]);
+    wait_lds<0>(vt[1]);
+#pragma unroll
+    for (int mb = 0; mb < kMb; ++mb) {
+      f32x16 codes;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) codes[r] = 0.f;
+#pragma unroll
+      for (int ks2 = 0; ks2 < 2; ++ks2) {
+        uint32_t v4[4] = {vt[ks2][2 * mb].x, vt[ks2][2 * mb].y, vt[ks2][2 * mb + 1].x, vt[ks2][2 * mb + 1].y};
+        u32x4 code, seen;  // seen: 1 for a weight
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          const uint32_t w2 = pw[0][4 * ks2 + x];
+          seen[x] = (w2 & 0xffffu ? 0x3f80u : 0u) | (w2 >> 16 ? 0x3f800000u : 0u);
+          code[x] = take_not_finite(v4[x]);
+        }
+        vt[ks2][2 * mb] = u32x2{v4[0], v4[1]};
+        vt[ks2][2 * mb + 1] = u32x2{v4[2], v4[3]};
+        codes = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, code),
+                                                        __builtin_bit_cast(bf16x8, seen), codes, 0, 0, 0);
+      }
+      mfma_settle();  // O too: its last products came before
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o_acc[mb][r] += not_finite_sum(codes[r]);
+    }
+  };
   // O^T += V^T . P^T with the V registers read last and the given weights
   auto weighted_sum = [&](const uint32_t (&pw)[kParts][8]) {
     wait_lds<0>(vt[0]);
@@ -759,6 +748,23 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
         }
       }
     }
+  };
+
+  // whether `mine` holds in any wave of the workgroup (which all come here)
+  __shared__ int s_any[2];
+  int n_any = 0;  // calls so far: a call leaves its number, the one before it is then no longer looked at
+  if constexpr (kExact) {
+    if (tid < 2) s_any[tid] = 0;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // seen by all after the first stage's barrier
+  }
+  auto any_wave = [&](bool mine) {
+    ++n_any;
+    int *word = s_any + (n_any & 1);
+    if (mine) *word = n_any;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    return __builtin_amdgcn_readfirstlane(*word) == n_any;
   };
 
   const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3f803f80u);
@@ -835,6 +841,7 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
           // rare: move the reference.  O must first receive the stage still pending, whose
           // weights are relative to the old reference.
           if (kPrev) {
+            take_out(pw_prev);
             weighted_sum(pw_prev);
             clear_prev();
             mfma_settle();
@@ -850,6 +857,8 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
           m_run = m_new;
         }
         const float neg_m = -(m_run == -INFINITY ? 0.f : m_run) * p.scale_log2e;
+
+        if (kPrev) take_out(pw_prev);
 
         // ---- one block: scores of the next stage, weights of this one, O update of the last
         f32x16 sc_next;
@@ -895,11 +904,29 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
         for (int i = 1; i < pc.n_cmp - 1; ++i) stage(i, yes{}, yes{});
         stage(pc.n_cmp - 1, no{}, yes{});
       }
+      take_out(pw_prev);
       weighted_sum(pw_prev);  // drain
       mfma_settle();
     }
     // stages of the piece without math for this wave: keep the ring and the barriers going
     for (int i = pc.n_cmp; i < pc.n_st; ++i) acquire();
+
+    if constexpr (kExact) {
+      // a NaN in any wave's results: the piece once more, from its first stage, for all waves.
+      // (No loads but the ring's are in flight here, and none of it is left behind.)
+      const bool again = !careful && any_wave(__builtin_amdgcn_ballot_w64(has_nan(o_acc)) != 0);
+      careful = again;
+      if (again) {
+        wait_vmem<0>();
+        __builtin_amdgcn_s_barrier();
+        lw = cp;
+        ld_segment();
+        n_acq -= pc.n_st;
+        slot_acq = slot_ld = 0;
+        fill_ring();
+        continue;
+      }
+    }
 
     // ---- the next piece's queries are requested before this piece's results are stored:
     //      waiting for them later then does not wait for the stores
@@ -924,14 +951,8 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
     m_run *= p.scale_log2e;  // from here on the maximum is in the exponent's (log2) domain
     if (wave * 32 < T) {
       if (done.whole) {
-        const float inv = 1.f / l_run;
-        bool mine = t < T;
-        if constexpr (kExact) {
-          const bool bad = mine && (has_nan(o_acc) || inv != inv);
-          if (redo_not_finite(p, bad, done.unit, wave * 32, D, 0, D)) mine = false;
-        }
-        if (mine)
-          store_out_row<true>(p.out + ((size_t)done.unit * p.T_max + t) * D, o_acc, inv, g);
+        if (t < T)
+          store_out_row<true>(p.out + ((size_t)done.unit * p.T_max + t) * D, o_acc, 1.f / l_run, g);
       } else {
         // a range starts inside at most one unit and ends inside at most one
         const size_t ps = 2 * (size_t)w + (s0 > 0 ? 0 : 1);
@@ -967,6 +988,16 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
 //     queries, block mb), four pieces of the whole block together.  640 units of 4224 rows on 512
 //     workgroups: 12 us; four such waves to a workgroup, or one wave per q4, cost 14 to 18 us.
 constexpr int kCombinePieces = 4, kCombineManyPieces = 16;
+
+// x * a + y * b; D = 64: an infinity in a piece that counts for nothing is left out
+template <int D>
+__device__ __forceinline__ float merge_add(float x, float a, float y, float b) {
+  if constexpr (D == 64) {
+    x = a == 0.f ? 0.f : x;
+    y = b == 0.f ? 0.f : y;
+  }
+  return x * a + y * b;
+}
 
 template <int D>
 __global__ __launch_bounds__(kWave) void tree_attn_combine_kernel(AttnParams p) {
@@ -1008,19 +1039,13 @@ __global__ __launch_bounds__(kWave) void tree_attn_combine_kernel(AttnParams p) 
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[4 * q4 + j] = acc[4 * q4 + j] * a_old + o[k][q4][j] * a_new;
+        for (int j = 0; j < 4; ++j)
+          acc[4 * q4 + j] = merge_add<D>(acc[4 * q4 + j], a_old, o[k][q4][j], a_new);
       M = M_new;
     }
   }
   // the two lanes of an exchange pair hold the same query, so they are active together
-  const float inv = 1.f / lsum;
-  bool mine = t < T;
-  if constexpr (D == 64) {
-    const f32x16 (&block)[1] = reinterpret_cast<const f32x16 (&)[1]>(acc);
-    const bool bad = mine && (has_nan(block) || inv != inv);
-    if (redo_not_finite(p, bad, cut.unit, dw * 32, D, 32 * mb, 32 * mb + 32)) mine = false;
-  }
-  if (mine) store_out_block<false>(p.out + ((size_t)cut.unit * p.T_max + t) * D, acc, inv, g, mb);
+  if (t < T) store_out_block<false>(p.out + ((size_t)cut.unit * p.T_max + t) * D, acc, 1.f / lsum, g, mb);
 }
 
 template <int D>
@@ -1056,18 +1081,13 @@ __global__ __launch_bounds__(4 * kWave) void tree_attn_combine_unit_kernel(AttnP
         const float a_old = fast_exp2(M - M_safe), a_new = fast_exp2(m[k] - M_safe);
         lsum = lsum * a_old + l[k] * a_new;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j] = acc[j] * a_old + o[k][j] * a_new;
+        for (int j = 0; j < 4; ++j) acc[j] = merge_add<D>(acc[j], a_old, o[k][j], a_new);
         M = M_new;
       }
   }
   const float inv = 1.f / lsum;
   const int d0 = 32 * mb + 8 * q4;  // the wave's 8 columns; the lane's four start at d0 + 4 g
-  bool mine = t < T;
-  if constexpr (D == 64) {
-    const float sum = (acc[0] + acc[1] + acc[2] + acc[3]) * inv;
-    if (redo_not_finite(p, mine && sum != sum, cut.unit, dw * 32, D, d0, d0 + 8)) mine = false;
-  }
-  if (mine)
+  if (t < T)
     *reinterpret_cast<u32x2 *>(p.out + ((size_t)cut.unit * p.T_max + t) * D + d0 + 4 * g) =
         u32x2{cvt_pk_bf16(acc[0] * inv, acc[1] * inv), cvt_pk_bf16(acc[2] * inv, acc[3] * inv)};
 }
@@ -1075,7 +1095,8 @@ __global__ __launch_bounds__(4 * kWave) void tree_attn_combine_unit_kernel(AttnP
 // ------------------------------------------------------------------------------------
 // Plain path: one wave per (sequence, head, node); products, softmax and output sums in fp32.
 // Serves bf16 operands with d = 64 that come without the workspace or the alignment of the tiled
-// kernel; its per-query function also redoes results with a NaN in them for the other kernels.
+// kernel.  Rows of V with weight zero are not looked at, so a value that is not finite reaches the
+// queries that see it and no others.
 // ------------------------------------------------------------------------------------
 template <typename E>
 struct AttnParamsPlain {
@@ -1083,23 +1104,65 @@ struct AttnParamsPlain {
   E *out;
   const int32_t *seq_lens, *n_nodes;
   const uint64_t *anc;
-  int H, T_max, L_max, d;
+  int H, T_max, L_max;
   float scale;
 };
 
-template <typename E>
-__global__ __launch_bounds__(kWave) void tree_attn_plain_kernel(AttnParamsPlain<E> p) {
+__global__ __launch_bounds__(kWave) void tree_attn_plain_kernel(AttnParamsPlain<uint16_t> p) {
+  constexpr int d = kWave;  // a lane owns a column of the result
   const int unit = blockIdx.x / p.T_max, i = blockIdx.x - unit * p.T_max;
-  int T = p.n_nodes[unit / p.H];
+  const int b = unit / p.H;
+  int L = p.seq_lens[b];
+  L = L < 0 ? 0 : (L > p.L_max ? p.L_max : L);
+  int T = p.n_nodes[b];
   T = T < 1 ? 1 : (T > p.T_max ? p.T_max : T);
   if (i >= T) return;
-  plain_query(p, unit, i, p.d, 0, p.d);
+  const int lane = threadIdx.x;
+  const uint64_t a_lo = p.anc[((size_t)b * p.T_max + i) * 2];
+  const uint64_t a_hi = p.anc[((size_t)b * p.T_max + i) * 2 + 1];
+  const uint16_t *q = p.q + ((size_t)unit * p.T_max + i) * d;
+  const uint16_t *kc = p.k_cache + (size_t)unit * p.L_max * d;
+  const uint16_t *vc = p.v_cache + (size_t)unit * p.L_max * d;
+  const uint16_t *kt = p.k_tree + (size_t)unit * p.T_max * d;
+  const uint16_t *vt = p.v_tree + (size_t)unit * p.T_max * d;
+
+  float m_run = -INFINITY, l_run = 0.f, o = 0.f;
+  const int total = L + T;
+  for (int j0 = 0; j0 < total; j0 += kWave) {
+    const int j = j0 + lane;
+    const bool in_cache = j < L;
+    const int jt = j - L;
+    const bool ok = in_cache || (j < total && test_bit128(a_lo, a_hi, jt));
+    float s = -INFINITY;
+    if (ok) {
+      const uint16_t *kr = in_cache ? kc + (size_t)j * d : kt + (size_t)jt * d;
+      float acc = 0.f;
+      for (int x = 0; x < d; ++x) acc = fmaf(bf16_bits_to_f32(q[x]), bf16_bits_to_f32(kr[x]), acc);
+      s = acc * p.scale;
+    }
+    const float m_new = fmaxf(m_run, wave_reduce_max(s));
+    if (m_new == -INFINITY) continue;  // nothing visible in this chunk (uniform across the wave)
+    const float alpha = expf(m_run - m_new);
+    const float w = ok ? expf(s - m_new) : 0.f;
+    l_run = l_run * alpha + wave_reduce_sum(w);
+    o *= alpha;
+    m_run = m_new;
+    const uint64_t live = __ballot(w != 0.f);
+    for (uint64_t rest = live; rest; rest &= rest - 1) {
+      const int src = __ffsll((long long)rest) - 1;
+      const float wj = __shfl(w, src, kWave);
+      const int jj = j0 + src;
+      const uint16_t *vr = jj < L ? vc + (size_t)jj * d : vt + (size_t)(jj - L) * d;
+      o = fmaf(wj, bf16_bits_to_f32(vr[lane]), o);
+    }
+  }
+  p.out[((size_t)unit * p.T_max + i) * d + lane] = (uint16_t)f32_to_bf16_bits(o / l_run);
 }
 
 #include "tree_attention_f32.h"
 
 template <typename E>
-static void fill_plain(AttnParamsPlain<E> &p, const propd_tree *tree, int H, int d, float scale, const void *q,
+static void fill_plain(AttnParamsPlain<E> &p, const propd_tree *tree, int H, float scale, const void *q,
                        const void *k_cache, const void *v_cache, const void *k_tree, const void *v_tree,
                        const int32_t *seq_lens, int L_max, void *out) {
   p.q = reinterpret_cast<const E *>(q);
@@ -1114,7 +1177,6 @@ static void fill_plain(AttnParamsPlain<E> &p, const propd_tree *tree, int H, int
   p.H = H;
   p.T_max = tree->T_max;
   p.L_max = L_max;
-  p.d = d;
   p.scale = scale;
 }
 
@@ -1203,7 +1265,7 @@ extern "C" propd_status propd_tree_attention(const propd_tree *tree, propd_dtype
   if (dt == PROPD_F32) {
     if (d != 64 && d != 128) return PROPD_ERR_UNSUPPORTED;
     AttnParamsF32 p;
-    fill_plain<float>(p, tree, H, d, scale, q, k_cache, v_cache, k_tree, v_tree, seq_lens, L_max, out);
+    fill_plain<float>(p, tree, H, scale, q, k_cache, v_cache, k_tree, v_tree, seq_lens, L_max, out);
     p.units = (int)units;
     p.scale_log2e = scale * 1.4426950408889634f;
     return (d == 64 ? launch_f32<64>(p, compute_units(), workspace, workspace_bytes, st)
@@ -1221,8 +1283,8 @@ extern "C" propd_status propd_tree_attention(const propd_tree *tree, propd_dtype
   const bool scratch = workspace && workspace_bytes >= need;
   if (d == 64 && !(aligned && scratch)) {  // the smaller head may come without either: one wave per query
     AttnParamsPlain<uint16_t> p;
-    fill_plain<uint16_t>(p, tree, H, d, scale, q, k_cache, v_cache, k_tree, v_tree, seq_lens, L_max, out);
-    hipLaunchKernelGGL(tree_attn_plain_kernel<uint16_t>, dim3((unsigned)(units * tree->T_max)), dim3(kWave), 0, st, p);
+    fill_plain<uint16_t>(p, tree, H, scale, q, k_cache, v_cache, k_tree, v_tree, seq_lens, L_max, out);
+    hipLaunchKernelGGL(tree_attn_plain_kernel, dim3((unsigned)(units * tree->T_max)), dim3(kWave), 0, st, p);
     return launch_ok() ? PROPD_OK : PROPD_ERR_DEVICE;
   }
   if (!aligned) return PROPD_ERR_INVALID_ARG;

@@ -35,22 +35,9 @@ struct AttnParamsF32 : AttnParamsPlain<float> {
 
 __host__ __device__ constexpr size_t f32_part_floats(int D) { return (size_t)32 * (D + 2); }
 
-// Queries whose result holds a NaN, LPQ consecutive lanes per query: done once more by
-// plain_query (see redo_not_finite).  `q0`: the first query of this wave.
-template <int LPQ>
-__device__ __forceinline__ bool redo_rows(const AttnParamsF32 &p, bool bad, int unit, int q0, int d) {
-  uint64_t rest = __ballot(bad);
-  if (rest == 0) return false;
-  const int lane = threadIdx.x & (kWave - 1), mine = lane / LPQ;
-  bool taken = false;
-  while (rest) {
-    const int q = (__ffsll((long long)rest) - 1) / LPQ;
-    plain_query(p, unit, q0 + q, d, 0, d);
-    taken = taken || q == mine;
-    rest &= ~(((LPQ == 64 ? 0ull : (1ull << LPQ)) - 1ull) << (q * LPQ));
-  }
-  return taken;
-}
+// Results of a group of waves or workgroups merged: o * f, nothing where that group counts for nothing
+// (an infinity there would be NaN).
+__device__ __forceinline__ float f32_part(float o, float f) { return f == 0.f ? 0.f : o * f; }
 
 // QG groups of 16 queries of one key range of one unit; s_o, s_ml: the workgroup's LDS.
 template <int D, int QG>
@@ -129,6 +116,7 @@ __device__ __forceinline__ void f32_attn_range(const AttnParamsF32 &p, int unit,
     if (tile + kF32AttnWaves < hi) load_k(tile + kF32AttnWaves);
     const bool tree = tile >= n_cache;
     const int j0 = 16 * (tree ? tile - n_cache : tile), n_valid = (tree ? T : L) - j0;
+    float least = INFINITY;
 #pragma unroll
     for (int g = 0; g < QG; ++g) {
 #pragma unroll
@@ -153,6 +141,7 @@ __device__ __forceinline__ void f32_attn_range(const AttnParamsF32 &p, int unit,
       for (int r = 0; r < 4; ++r) {
         sc[g][r] = fast_exp2(sc[g][r] - m_safe);
         sum += sc[g][r];
+        least = fminf(least, sc[g][r]);
       }
       l_run[g] = l_run[g] * alpha + sum;
 #pragma unroll
@@ -161,6 +150,39 @@ __device__ __forceinline__ void f32_attn_range(const AttnParamsF32 &p, int unit,
         for (int e = 0; e < 4; ++e)
 #pragma unroll
           for (int r = 0; r < 4; ++r) o[g][h][e][r] *= alpha;
+    }
+    if (__ballot(least < 0x1p-126f) != 0) {  // weights of zero: V is looked through, see not_finite_sum
+      uint32_t top = 0;  // of the bits without their signs, shifted (a masked copy would be kept for the use below)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int h = 0; h < kH; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t twice = __float_as_uint(vf[r][h][e]) << 1;
+            top = twice > top ? twice : top;
+          }
+      if (__ballot(top >= 0xff000000u) != 0) {
+#pragma unroll
+        for (int h = 0; h < kH; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+#pragma unroll
+            for (int g = 0; g < QG; ++g) {
+              f32x4 codes = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                codes = __builtin_amdgcn_mfma_f32_16x16x4f32(not_finite_code(__float_as_uint(vf[r][h][e])),
+                                                             sc[g][r] != 0.f ? 1.f : 0.f, codes, 0, 0, 0);
+              mfma_settle();
+#pragma unroll
+              for (int r = 0; r < 4; ++r) o[g][h][e][r] += not_finite_sum(codes[r]);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              vf[r][h][e] = not_finite_code(__float_as_uint(vf[r][h][e])) != 0.f ? 0.f : vf[r][h][e];
+          }
+      }
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r)
@@ -214,25 +236,18 @@ __device__ __forceinline__ void f32_attn_range(const AttnParamsF32 &p, int unit,
     for (int w = 0; w < kF32AttnWaves; ++w) {
       const f32x4 v = *reinterpret_cast<const f32x4 *>(s_o + (w * kRows + row) * kRow + 4 * (part + LPQ * x));
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[x][j] += v[j] * f[w];
+      for (int j = 0; j < 4; ++j) acc[x][j] += f32_part(v[j], f[w]);
     }
   }
   if (p.splits == 1) {
-    bool mine = t < T;
-    float sum = lsum;
+    if (t >= T) return;
+    float *dst = p.out + ((size_t)unit * p.T_max + t) * D;
 #pragma unroll
     for (int x = 0; x < kPieces; ++x) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        acc[x][j] /= lsum;
-        sum += acc[x][j];
-      }
+      for (int j = 0; j < 4; ++j) acc[x][j] /= lsum;
+      *reinterpret_cast<f32x4_a4 *>(dst + 4 * (part + LPQ * x)) = acc[x];
     }
-    if (redo_rows<LPQ>(p, mine && sum != sum, unit, q0 + (threadIdx.x & ~63) / LPQ, D)) mine = false;
-    float *dst = p.out + ((size_t)unit * p.T_max + t) * D;
-#pragma unroll
-    for (int x = 0; x < kPieces; ++x)
-      if (mine) *reinterpret_cast<f32x4_a4 *>(dst + 4 * (part + LPQ * x)) = acc[x];
     return;
   }
   float *rec = p.part + (((size_t)unit * ((p.T_max + 31) / 32) + pair) * p.splits + split) * f32_part_floats(D);
@@ -298,16 +313,12 @@ __global__ __launch_bounds__(kF32AttnThreads) void tree_attn_f32_combine_kernel(
       const float f = fast_exp2(m[s] - m_safe);
       lsum += l[s] * f;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j] += v[s][j] * f;
+      for (int j = 0; j < 4; ++j) acc[j] += f32_part(v[s][j], f);
     }
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) acc[j] /= lsum;
-  const float sum = acc[0] + acc[1] + acc[2] + acc[3] + lsum;
-  bool mine = t < T;
-  if (redo_rows<LPQ>(p, mine && sum != sum, unit, 32 * pair + (int)(blockIdx.x % kBlocks) * kRows + (threadIdx.x & ~63) / LPQ, D))
-    mine = false;
-  if (mine) *reinterpret_cast<f32x4_a4 *>(p.out + ((size_t)unit * p.T_max + t) * D + 4 * part) = acc;
+  if (t < T) *reinterpret_cast<f32x4_a4 *>(p.out + ((size_t)unit * p.T_max + t) * D + 4 * part) = acc;
 }
 
 // Workgroups per unit and 32 queries: as many as bring two workgroups to every compute unit, each

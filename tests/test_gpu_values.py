@@ -5,10 +5,12 @@ two entries, and the columns of V are chosen so that errors of the weights stay 
 itself is small."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2402_13485_amd import synth
-from gpu_util import host_f64
-from test_gpu_parity import pb, run_attention  # noqa: F401
+from gpu_util import host_f64, to_host
+from test_gpu_dispatch import raw_attention
+from test_gpu_parity import dev_tree, pb, run_attention  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -106,3 +108,116 @@ def test_attention_with_next_to_no_scale(pb, oracle, dtype, d):
     ref = reference(oracle, x)
     got = host_f64(run_attention(pb, x)[0])
     assert (np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref)).all()
+
+
+def timed(f):
+    times = []
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b))
+    return sorted(times)[2]
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("where", ["cache", "leaf"])
+def test_attention_not_finite_values_cost_no_more(pb, dtype, d, where):
+    """One V row per (sequence, head) that holds a NaN: the call takes as long as without (a factor
+    of four is allowed; work done query by query for such units takes a hundred times as long)."""
+    B, H, T, L = 2, 8, 64, 2048
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    normal = lambda *s: torch.randn(s, device="cuda", dtype=dt, generator=gen)
+    n_nodes, parent, _ = synth.pad_trees([synth.rank_product_tree(T, 4)] * B, T)
+    tree = dev_tree(pb, n_nodes, parent)
+    q, kt, vt, kc, vc = normal(B, H, T, d), normal(B, H, T, d), normal(B, H, T, d), normal(B, H, L, d), normal(B, H, L, d)
+    seq = torch.full((B,), L, dtype=torch.int32, device="cuda")
+    call = lambda: pb.propd_tree_attention(tree, q, kc, vc, kt, vt, seq, d ** -0.5)
+    clean_out = call()
+    clean = timed(call)
+    (vc if where == "cache" else vt)[:, :, T - 1, 5] = float("nan")
+    out = call()
+    seen = torch.zeros_like(out, dtype=torch.bool)
+    seen[:, :, (slice(None) if where == "cache" else T - 1), 5] = True  # the last node is a leaf
+    assert torch.isnan(out[seen]).all()
+    tol = 2.0 ** -8 if dtype == "bf16" else 1e-5
+    assert ((out - clean_out)[~seen].abs() <= tol * clean_out.abs().max()).all()
+    assert timed(call) <= 4 * clean + 0.05
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+def test_attention_not_finite_keys_stay_where_they_are_seen(pb, dtype, d, value):
+    """K entries of a leaf that are not finite reach the leaf's own row and no other."""
+    shapes = [synth.rank_product_tree(70, 4)] * 2
+    w = synth.Workload(92, "case", dtype, 2, 2, d, 70, 0, 0, 0, 1e-3)
+    x = synth.make_attention_inputs(w, seq_lens=np.array([600, 33], np.int32), trees=shapes)
+    want = host_f64(run_attention(pb, x)[0])
+    leaf = 69
+    y = dict(x, k_tree=x["k_tree"].copy())
+    y["k_tree"][:, :, leaf, 11] = synth.from_float(np.array([value], np.float32), dtype)[0]
+    got = host_f64(run_attention(pb, y)[0])
+    score = synth.as_float(x["q"])[:, :, leaf, 11] * value  # NaN and +inf: no softmax; -inf: a weight of zero
+    assert (np.isnan(got[:, :, leaf]).all(axis=-1) == ~(score < 0)).all()
+    rest = [t for t in range(70) if t != leaf]
+    tol = 2.0 ** -8 if dtype == "bf16" else 1e-5
+    assert (np.abs(got - want)[:, :, rest] <= tol * np.abs(want[:, :, rest]).max(axis=-1, keepdims=True)).all()
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("L", [5, 600])
+def test_attention_infinities_of_both_signs(pb, oracle, dtype, d, L):
+    """+inf and -inf in V, in one column, in two and in both signs of one column, in cached rows (the
+    last one too, which fills its stage) and in tree rows, seen by some nodes and not by others:
+    every result is the sum that the node sees."""
+    shapes = [synth.rank_product_tree(40, 4)]
+    w = synth.Workload(93, "case", dtype, 1, 2, d, 40, 0, 0, 0, 1e-3)
+    x = synth.make_attention_inputs(w, seq_lens=np.array([L], np.int32), trees=shapes)
+    inf = lambda s: synth.from_float(np.array([s * np.inf], np.float32), dtype)[0]
+    x["v_cache"][0, :, L - 1, 2] = inf(1)
+    x["v_cache"][0, :, 1, 3] = inf(-1)
+    x["v_cache"][0, :, 0, 4], x["v_cache"][0, :, L - 1, 4] = inf(1), inf(-1)
+    x["v_tree"][0, :, 7, 5], x["v_tree"][0, :, 39, 5], x["v_tree"][0, :, 12, 6] = inf(1), inf(-1), inf(-1)
+    with np.errstate(all="ignore"):
+        ref = reference(oracle, x)
+    got = host_f64(run_attention(pb, x)[0])
+    assert not np.isfinite(ref[..., 2:5]).any() and np.isfinite(ref[..., 5]).any() and np.isinf(ref[..., 5]).any()
+    same = np.isfinite(ref)
+    assert (np.isnan(got) == np.isnan(ref)).all() and (got[~same & ~np.isnan(ref)] == ref[~same & ~np.isnan(ref)]).all()
+    tol = 2e-2 if dtype == "bf16" else 1e-5
+    assert (np.abs(got[same] - ref[same]) <= tol * max(1.0, np.abs(ref[same]).max())).all()
+
+
+@pytest.mark.parametrize("T,L", [(1, 33), (20, 0), (70, 31), (128, 300), (64, 2000)])
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+def test_attention_d64_not_finite_like_the_plain_kernel(pb, T, L, value):
+    """With and without a workspace (tiled kernel, one wave per query): the same results are NaN, the
+    same are infinite, and the finite ones agree, whatever is not finite among V, and for infinities in
+    K (a NaN there is a NaN score, whose maximum the plain kernel does not define)."""
+    rng = np.random.default_rng(T + L)
+    w = synth.Workload(96, "case", "bf16", 2, 2, 64, T, 0, 0, 0, 1e-3)
+    x = synth.make_attention_inputs(w, seq_lens=np.array([L, L // 2], np.int32), L_max=max(L, 1),
+                                    trees=[synth.random_tree(rng, T), synth.random_tree(rng, max(1, T // 2))])
+    bad = synth.from_float(np.array([value], np.float32), "bf16")[0]
+    for name, n in (("v_tree", 3), ("v_cache", 2), ("k_tree", 0 if np.isnan(value) else 1)):
+        rows = x[name].shape[2]
+        for _ in range(n):
+            x[name][:, rng.integers(0, 2), rng.integers(0, rows), rng.integers(0, 64)] = bad
+    st, plain, sent = raw_attention(pb, x, workspace="none")
+    assert st == 0
+    st, tiled, _ = raw_attention(pb, x, workspace="full")
+    assert st == 0
+    a, b = host_f64(plain), host_f64(tiled)
+    for s in range(2):
+        n = int(x["n_nodes"][s])
+        assert np.array_equal(np.isnan(a[s, :, :n]), np.isnan(b[s, :, :n]))
+        assert np.array_equal(np.isposinf(a[s, :, :n]), np.isposinf(b[s, :, :n]))
+        assert np.array_equal(np.isneginf(a[s, :, :n]), np.isneginf(b[s, :, :n]))
+        fin = np.isfinite(a[s, :, :n])
+        one, other = a[s, :, :n][fin], b[s, :, :n][fin]
+        # both round a result that differs by fp32 sums only
+        assert (np.abs(one - other) <= 2.0 ** -7 * np.maximum(np.abs(one), 1e-3)).all()
+        assert (to_host(tiled)[s, :, n:] == sent[s, :, n:]).all()
