@@ -266,14 +266,15 @@ __global__ __launch_bounds__(kF32AttnThreads, 2) void tree_attn_f32_kernel(AttnP
   __shared__ float s_ml[2 * kF32AttnWaves * 32];
   // the query groups of one key range run on one XCD where the counts allow (its L2 holds the rows)
   const unsigned per_pair = (unsigned)p.units * (unsigned)p.splits;
-  const int pair = (int)(blockIdx.x / per_pair);
-  const unsigned us = blockIdx.x - (unsigned)pair * per_pair;
+  const unsigned block = blockIdx.y * gridDim.x + blockIdx.x;
+  const int pair = (int)(block / per_pair);
+  const unsigned us = block - (unsigned)pair * per_pair;
   const int unit = (int)(us / (unsigned)p.splits), split = (int)(us - (unsigned)unit * (unsigned)p.splits);
   const int b = unit / p.H, q0 = 32 * pair;
   int T = p.n_nodes[b], L = p.seq_lens[b];
   T = T < 1 ? 1 : (T > p.T_max ? p.T_max : T);
   L = L < 0 ? 0 : (L > p.L_max ? p.L_max : L);
-  if (q0 >= T) return;
+  if (q0 >= T) return;  // also where the last row of the grid is not full
   if (MQ == 1 || q0 + 16 >= T) f32_attn_range<D, 1>(p, unit, pair, split, b, q0, L, T, s_o, s_ml);
   else f32_attn_range<D, MQ>(p, unit, pair, split, b, q0, L, T, s_o, s_ml);
 }
@@ -341,7 +342,10 @@ static bool launch_f32(AttnParamsF32 p, int cus, void *workspace, size_t workspa
   if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 16 != 0) workspace_bytes = 0;
   p.part = reinterpret_cast<float *>(workspace);
   p.splits = f32_splits((long long)p.units * pairs, (p.L_max + 15) / 16 + (p.T_max + 15) / 16, cus, workspace_bytes, D);
-  const dim3 grid((unsigned)p.units * (unsigned)pairs * (unsigned)p.splits);
+  // a dimension of the grid holds fewer than 2^32 threads, and there may be 2^28 units
+  constexpr unsigned kGridX = 1u << 22;
+  const unsigned blocks = (unsigned)p.units * (unsigned)pairs * (unsigned)p.splits;
+  const dim3 grid(blocks < kGridX ? blocks : kGridX, (blocks + kGridX - 1) / kGridX);
   if (p.T_max <= 16)
     hipLaunchKernelGGL((tree_attn_f32_kernel<D, 1>), grid, dim3(kF32AttnThreads), 0, st, p);
   else

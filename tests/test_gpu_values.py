@@ -221,3 +221,18 @@ def test_attention_d64_not_finite_like_the_plain_kernel(pb, T, L, value):
         # both round a result that differs by fp32 sums only
         assert (np.abs(one - other) <= 2.0 ** -7 * np.maximum(np.abs(one), 1e-3)).all()
         assert (to_host(tiled)[s, :, n:] == sent[s, :, n:]).all()
+
+
+def test_attention_f32_many_units(pb):
+    """2^24 units of one node and no cache: more workgroups than one launch dimension takes in
+    threads (2^32 of them).  A node that sees itself alone returns its own V row."""
+    B, H, d = 1 << 14, 1 << 10, 64
+    nn = torch.ones(B, dtype=torch.int32, device="cuda")
+    par = torch.full((B, 1), -1, dtype=torch.int32, device="cuda")
+    depth, anc = pb.propd_tree_mask(nn, par)
+    tree = pb.Tree(n_nodes=nn, parent=par, depth=depth, anc=anc)
+    q = torch.empty((B, H, 1, d), device="cuda").normal_()
+    v = torch.empty((B, H, 1, d), device="cuda").normal_()
+    none = torch.empty((B, H, 0, d), device="cuda")
+    out = pb.propd_tree_attention(tree, q, none, none, q, v, torch.zeros(B, dtype=torch.int32, device="cuda"), 0.125)
+    assert torch.equal(out, v)
