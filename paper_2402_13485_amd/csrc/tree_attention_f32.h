@@ -35,9 +35,8 @@ struct AttnParamsF32 : AttnParamsPlain<float> {
 
 __host__ __device__ constexpr size_t f32_part_floats(int D) { return (size_t)32 * (D + 2); }
 
-// Results of a group of waves or workgroups merged: o * f, nothing where that group counts for nothing
-// (an infinity there would be NaN).
-__device__ __forceinline__ float f32_part(float o, float f) { return f == 0.f ? 0.f : o * f; }
+// A result to be merged with factor f: left out where the factor is zero (an infinity would be NaN).
+__device__ __forceinline__ float f32_part(float o, float f) { return f == 0.f ? 0.f : o; }
 
 // QG groups of 16 queries of one key range of one unit; s_o, s_ml: the workgroup's LDS.
 template <int D, int QG>
@@ -236,7 +235,7 @@ __device__ __forceinline__ void f32_attn_range(const AttnParamsF32 &p, int unit,
     for (int w = 0; w < kF32AttnWaves; ++w) {
       const f32x4 v = *reinterpret_cast<const f32x4 *>(s_o + (w * kRows + row) * kRow + 4 * (part + LPQ * x));
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[x][j] += f32_part(v[j], f[w]);
+      for (int j = 0; j < 4; ++j) acc[x][j] += f32_part(v[j], f[w]) * f[w];
     }
   }
   if (p.splits == 1) {
@@ -314,7 +313,7 @@ __global__ __launch_bounds__(kF32AttnThreads) void tree_attn_f32_combine_kernel(
       const float f = fast_exp2(m[s] - m_safe);
       lsum += l[s] * f;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j] += f32_part(v[s][j], f);
+      for (int j = 0; j < 4; ++j) acc[j] += f32_part(v[s][j], f) * f;
     }
   }
 #pragma unroll
