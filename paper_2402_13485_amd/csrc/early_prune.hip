@@ -1302,9 +1302,11 @@ static propd_status prune_impl(
   PruneScratch ws = carve_scratch(workspace, B, T_max, vocab);
   hipStream_t st = as_stream(hip_stream);
 
-  static const int force = [] {  // tile-shape override for tuning runs: 1 = 256-row tiles, 2 = 352-row tiles
+  // tile-shape override for tuning runs: 2 = 352-row tiles, 1 (and whatever else is no 0) = 256-row tiles
+  static const int force = [] {
     const char *e = getenv("PROPD_HEAD_PLAN");
-    return e ? atoi(e) : 0;
+    const int v = e ? atoi(e) : 0;
+    return v == 0 || v == 2 ? v : 1;
   }();
   const bool scored = !(crit.kind == 0 && crit.top_k >= vocab);
   // top_k >= vocab: every id of the vocabulary is inside the list, no scores are needed (ids

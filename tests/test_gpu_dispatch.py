@@ -1,6 +1,10 @@
 """GPU parity at the edges of the kernels' dispatch rules: row counts, lengths, alignments and
 types on both sides of every line where a call changes its kernel or tile shape, against the
 CPU oracle with the tolerances of test_gpu_parity."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -258,3 +262,29 @@ def test_prune_bf16_every_tile_shape(pb, oracle, B, T, V):
     _, _, ref = prob_reference(oracle, x, threshold=thr)
     res, sents = run_prob(pb, x, [x["hidden_states"]], threshold=thr)
     check_prob(pb, oracle, x, res, ref, logm, [x["hidden_states"]], sents)
+
+
+PLAN_CHILD = """
+import sys
+sys.path[:0] = {path!r}
+from oracle import oracle
+from paper_2402_13485_amd import binding, synth
+from test_gpu_parity import check_prune, run_prune
+binding.load_library()
+w = synth.Workload(95, "case", "bf16", 3, 1, 128, 128, 64, 700, 6, 1e-3)
+x = synth.make_prune_inputs(w, trees=[synth.chain_tree(128)] * 3)
+res, sents = run_prune(binding, x, [x["hidden_states"]])
+check_prune(oracle, x, res, [x["hidden_states"]], sents)
+print("same as the oracle")
+"""
+
+
+@pytest.mark.parametrize("value", ["1", "2", "7"])
+def test_prune_with_the_tile_shape_given(pb, oracle, value):
+    """PROPD_HEAD_PLAN takes the choice of the tile shape away: 381 score rows are scored
+    whatever it holds.  (It is read once per process, hence the child.)"""
+    child = PLAN_CHILD.format(path=[os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                                    os.path.dirname(os.path.abspath(__file__))])
+    done = subprocess.run([sys.executable, "-c", child], env=dict(os.environ, PROPD_HEAD_PLAN=value), timeout=100,
+                          capture_output=True, text=True)
+    assert done.returncode == 0 and "same as the oracle" in done.stdout, done.stderr[-2000:]
