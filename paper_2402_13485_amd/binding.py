@@ -305,10 +305,11 @@ def _early_prune(crit, tree, hidden_states, head_weight, payloads, payload_out, 
         raise ValueError("tree and hidden_states disagree on B or T_max")
     dev = hidden_states.device
     # per-node and per-sequence outputs come out of one allocation each: an allocation per output
-    # was a third of the host's time for the call
+    # was a third of the host's time for the call.  Each starts on a multiple of 16 bytes, as every
+    # call wants its tensors (and keeping one of them keeps the memory of all).
     i32 = dict(dtype=torch.int32, device=dev)
-    nodes = torch.empty((6 if want_rank else 5, B, T_max), **i32).unbind(0)
-    n_kept, n_nodes = torch.empty((2, B), **i32).unbind(0)
+    nodes = torch.empty_strided((6 if want_rank else 5, B, T_max), (-(-B * T_max // 4) * 4, T_max, 1), **i32).unbind(0)
+    n_kept, n_nodes = torch.empty_strided((2, B), (-(-B // 4) * 4, 1), **i32).unbind(0)
     res = PruneResult(
         keep_bits=torch.empty((B, 2), dtype=torch.int64, device=dev),
         new_index=nodes[0], orig_index=nodes[1], n_kept=n_kept, cu_nodes=torch.empty(B + 1, **i32),

@@ -288,3 +288,19 @@ def test_prune_with_the_tile_shape_given(pb, oracle, value):
     done = subprocess.run([sys.executable, "-c", child], env=dict(os.environ, PROPD_HEAD_PLAN=value), timeout=100,
                           capture_output=True, text=True)
     assert done.returncode == 0 and "same as the oracle" in done.stdout, done.stderr[-2000:]
+
+
+def test_prune_outputs_are_aligned(pb):
+    """Every output is a tensor that any call takes: bases on 16 bytes, also for one sequence and
+    for an odd number of nodes."""
+    for B, T in ((1, 33), (3, 5), (1, 1), (2, 64), (5, 7)):
+        shapes = [synth.chain_tree(T)] * B
+        w = synth.Workload(94, "case", "f32", B, 1, 64, T, 32, 100, 4, 1e-5)
+        x = synth.make_prune_inputs(w, trees=shapes)
+        tree = dev_tree(pb, x["n_nodes"], x["parent"], x["token"])
+        res = pb.propd_early_prune(tree, to_dev(x["hidden_states"]), to_dev(x["head_weight"]), 4, want_rank=True)
+        outs = [res.keep_bits, res.new_index, res.orig_index, res.n_kept, res.cu_nodes, res.rank, res.tree.n_nodes,
+                res.tree.parent, res.tree.token, res.tree.depth, res.tree.anc]
+        assert all(t.is_contiguous() and t.data_ptr() % 16 == 0 for t in outs), (B, T)
+        assert all(tuple(t.shape) == (B, T) for t in (res.new_index, res.rank, res.tree.parent))
+        assert (to_host(res.n_kept) == to_host(res.tree.n_nodes)).all()
