@@ -2,12 +2,14 @@
 from __future__ import annotations
 
 import os
+import re
 import subprocess
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libpropd.so")
+HEADER = os.path.join(HERE, os.pardir, "include", "propd.h")
 SOURCES = ["tree_mask.hip", "tree_attention.hip", "early_prune.hip", "accept_path.hip",
            "commit_path.hip", "tree_controller.hip"]
 FLAGS = [
@@ -17,13 +19,60 @@ FLAGS = [
 ]
 
 
+# Kernels with loads or LDS reads in flight that the compiler does not track (they are waited for
+# by hand).  A register that is saved to scratch memory or to an accumulation register while such a load
+# is on its way is saved before the value is there, and the load then lands in a register that
+# holds something else by that time, an address for instance.
+HAND_WAITED = ("tree_attn_bf16_kernel", "early_head_bf16_kernel")
+
+
+def unsafe_kernels(remarks: str) -> list:
+    """Kernels of HAND_WAITED that spill, from the compiler's remarks on resource usage."""
+    found, seen = [], set()
+    for block in remarks.split("Function Name: ")[1:]:
+        name = block.split()[0]
+        used = {key: int(value) for key, value in
+                re.findall(r"(AGPRs|ScratchSize \[bytes/lane\]|VGPRs Spill): (\d+)", block)}
+        for kernel in HAND_WAITED:
+            if kernel in name:
+                seen.add(kernel)
+                if len(used) != 3 or any(used.values()):
+                    found.append(f"{name}: {used}")
+    return found + [f"{kernel}: no resource usage reported" for kernel in HAND_WAITED if kernel not in seen]
+
+
+def stale() -> bool:
+    """Whether there is no library, or one that is older than a source."""
+    if not os.path.exists(LIB_PATH):
+        return True
+    sources = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [HEADER, os.path.abspath(__file__)]
+    return max(map(os.path.getmtime, sources)) > os.path.getmtime(LIB_PATH)
+
+
 def build(verbose: bool = False) -> str:
     srcs = [os.path.join(CSRC, s) for s in SOURCES]
     extra = os.environ.get("PROPD_EXTRA_HIPCC_FLAGS", "").split()  # tuning experiments only
-    cmd = ["hipcc", *FLAGS, *extra, "-DPROPD_BUILD", "-o", LIB_PATH, *srcs]
+    new = LIB_PATH + ".new"
+    cmd = ["hipcc", *FLAGS, *extra, "-DPROPD_BUILD", "-Rpass-analysis=kernel-resource-usage",
+           "-fno-caret-diagnostics", "-o", new, *srcs]
     if verbose:
         print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    done = subprocess.run(cmd, stderr=subprocess.PIPE, text=True)
+    context = []  # of the next line
+    for line in done.stderr.splitlines():
+        context.append(line)
+        if line.startswith("In file included from"):
+            continue
+        if "[-Rpass-analysis=kernel-resource-usage]" not in line and "'-packed-fp32-ops' is not a recognized" not in line:
+            print("\n".join(context), file=sys.stderr, flush=True)
+        context = []
+    if done.returncode != 0:
+        raise subprocess.CalledProcessError(done.returncode, cmd)
+    bad = unsafe_kernels(done.stderr)
+    if bad:
+        os.remove(new)
+        raise RuntimeError("these kernels must not spill, the library is not replaced:\n" + "\n".join(bad))
+    os.replace(new, LIB_PATH)
     return LIB_PATH
 
 

@@ -12,8 +12,8 @@ LLVM = "/opt/rocm/llvm/bin"
 
 
 def kernel_metadata(tmp_path):
-    """name -> bytes of scratch memory per work item, of every kernel in libpropd.so"""
-    if not os.path.exists(hip_build.LIB_PATH):
+    """name -> bytes of scratch memory per work item, of every kernel in libpropd.so as its sources are now"""
+    if hip_build.stale():
         hip_build.build()
     lib = shutil.copy(hip_build.LIB_PATH, tmp_path)
     subprocess.run([f"{LLVM}/llvm-objdump", "--offloading", lib], check=True, cwd=tmp_path, capture_output=True)
@@ -39,3 +39,52 @@ def test_no_kernel_uses_scratch_memory(tmp_path):
     scratch = kernel_metadata(tmp_path)
     assert any("tree_attn_bf16_kernel" in k for k in scratch) and any("early_head_bf16_kernel" in k for k in scratch)
     assert {k: v for k, v in scratch.items() if v} == {}
+
+
+SPILLING = """
+#include <hip/hip_runtime.h>
+// %d floats alive across the barrier, of 128 registers
+extern "C" __global__ __launch_bounds__(1024) void tree_attn_bf16_kernel(float *p) {
+  float v[%d];
+#pragma unroll
+  for (int i = 0; i < %d; ++i) v[i] = p[1024 * i + threadIdx.x];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < %d; ++i) p[1024 * i + (threadIdx.x ^ 1)] = v[i];
+}
+extern "C" __global__ void early_head_bf16_kernel(float *p) { p[threadIdx.x] = 0.f; }
+"""
+
+
+@pytest.mark.parametrize("live,spills", [(16, False), (200, True)])
+def test_build_refuses_a_kernel_that_spills(tmp_path, monkeypatch, live, spills):
+    """build() leaves the library alone when a kernel with hand-placed waits spills, with or without
+    LLVM's tools at hand.  (The kernel here is compiled, never run.)"""
+    (tmp_path / "one.hip").write_text(SPILLING % ((live,) * 4))
+    lib = tmp_path / "lib.so"
+    lib.write_text("the one before")
+    monkeypatch.setattr(hip_build, "CSRC", str(tmp_path))
+    monkeypatch.setattr(hip_build, "SOURCES", ["one.hip"])
+    monkeypatch.setattr(hip_build, "LIB_PATH", str(lib))
+    if spills:
+        with pytest.raises(RuntimeError, match="tree_attn_bf16_kernel"):
+            hip_build.build()
+        assert lib.read_text() == "the one before" and sorted(os.listdir(tmp_path)) == ["lib.so", "one.hip"]
+    else:
+        hip_build.build()
+        assert lib.read_bytes()[:4] == b"\x7fELF"
+
+
+def test_library_older_than_a_source_is_stale(tmp_path, monkeypatch):
+    for name in ("lib.so", "one.hip", "one.h"):
+        (tmp_path / name).write_text("")
+        os.utime(tmp_path / name, (1e9, 1e9))
+    monkeypatch.setattr(hip_build, "CSRC", str(tmp_path))
+    monkeypatch.setattr(hip_build, "LIB_PATH", str(tmp_path / "lib.so"))
+    now = 2e9 if os.path.getmtime(hip_build.__file__) < 2e9 else 4e9
+    os.utime(tmp_path / "lib.so", (now, now))
+    assert not hip_build.stale()
+    os.utime(tmp_path / "one.h", (now + 1, now + 1))
+    assert hip_build.stale()
+    os.remove(tmp_path / "lib.so")
+    assert hip_build.stale()
