@@ -1,18 +1,18 @@
-// Early-head scoring, more than 256 score rows: tiles of 32*MI rows x 64*NJ vocabulary entries.
+// Early-head scoring, more than 256 score rows: tiles of 32*MI rows x 256 vocabulary entries.
 // Included by early_prune.hip inside namespace propd, after the helpers it uses.
 //
 // The scoring GEMM has few rows (the nodes that have children: 704 at B = 16, T = 128) against a
-// wide vocabulary.  A round of workgroups costs about 10 + MI * NJ (head_plan), so the shape
+// wide vocabulary.  A round of workgroups costs about 10 + 4 * MI (head_plan), so the shape
 // is the one whose row tiles hold the rows with little padding in the fewest rounds:
 // 704 rows are two tiles of 352 and 250 workgroups, ONE round of the 256 compute units; 832 rows
 // are four tiles of 224 in two rounds (three of 352 would need as many rounds of larger tiles).
 // With 256-row tiles of the 32x32x16 instruction and one shape for rows like 704 only, the
 // pruning calls at 264, 352, 528, 832 and 1056 rows x 4096 took 181, 181, 212, 293 and 395 us; now
 // 142, 155, 186, 265 and 329.
-//   - 8 waves as 2 (rows) x 4 (columns), a wave owns 16*MI x 16*NJ as MI x NJ tiles of the
-//     16x16x32 bf16 MFMA: up to 176 accumulator registers (11 x 4) of the 256 a wave may have at
+//   - 8 waves as 2 (rows) x 4 (columns), a wave owns 16*MI x 64 as MI x 4 tiles of the
+//     16x16x32 bf16 MFMA: up to 176 accumulator registers (MI = 11) of the 256 a wave may have at
 //     two waves per SIMD, which leaves room for operands only if they are streamed;
-//   - K advances 32 per step through a ring of four LDS stages (64-byte rows, 38 KB for 11 x 4),
+//   - K advances 32 per step through a ring of four LDS stages (64-byte rows, 38 KB for MI = 11),
 //     filled by direct global->LDS loads three steps ahead.  The 16-byte chunks of a
 //     row are XOR-swizzled with key(row) = (row >> 1) & 3: a fragment read of this MFMA has
 //     lane -> (row lane % 16, chunk lane / 16), and with the key (row >> 2) & 3
@@ -32,13 +32,15 @@
 constexpr int kTallStages = 4;
 constexpr int kTallEpiChildren = 12;  // children of a row per epilogue pass
 
-// What depends on the wave tile of MI x NJ matrix tiles.
-template <int MI, int NJ>
+constexpr int kTallNJ = 4;  // matrix tiles of a wave side by side in the vocabulary
+
+// What depends on the wave tile of MI x kTallNJ matrix tiles.
+template <int MI>
 struct Tall {
-  static constexpr int kWaveRows = 16 * MI, kWaveCols = 16 * NJ;
+  static constexpr int kWaveRows = 16 * MI, kWaveCols = 16 * kTallNJ;
   static constexpr int kBM = 2 * kWaveRows, kBN = 4 * kWaveCols;
   static constexpr int kRows = kBM + kBN;                       // LDS rows of a stage
-  static constexpr int kStageBytes = kRows * kGemmRowBytes;     // 38912 for 11 x 4
+  static constexpr int kStageBytes = kRows * kGemmRowBytes;     // 38912 for MI = 11
   static constexpr int kGroups = kRows / 16, kAGroups = kBM / 16;  // 16-row groups, one load instruction each
   static constexpr int kLoads = (kGroups + 7) / 8;              // of a wave per K step, at most
   static constexpr int kIssueAt = MI / 2 - 1;  // the loads of a later step are issued behind this fragment's products
@@ -54,8 +56,8 @@ __device__ __forceinline__ void tall_wait_lds2(u32x4 &a, u32x4 &b) {
   asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N));
 }
 
-template <int MI, int NJ>
-using TallAcc = f32x4[MI][NJ];
+template <int MI>
+using TallAcc = f32x4[MI][kTallNJ];
 
 // LDS accesses with the row's offset as an immediate of the instruction: one address register
 // serves all rows of a lane.  (Left to itself the compiler materialises an address per row,
@@ -100,11 +102,12 @@ __device__ __forceinline__ int quarter_wave_sum_to_last(int v) {
 // a NaN threshold, which the main comparison counts as nothing.  A lane counts its own columns
 // in a byte per child, and one cross-lane sum per row and four children (DPP) leaves the row's
 // counts in the last lane of each quarter wave.
-template <int MI, int NJ>
-__device__ __forceinline__ void tall_epilogue_count(TallAcc<MI, NJ> &acc, int m0, int v0, int n_tile, int vocab,
+template <int MI>
+__device__ __forceinline__ void tall_epilogue_count(TallAcc<MI> &acc, int m0, int v0, int n_tile, int vocab,
                                                     int tid_in, int my_pos, int my_cc,
                                                     const HeadTables &tb, unsigned char *smem) {
-  using G = Tall<MI, NJ>;
+  using G = Tall<MI>;
+  constexpr int NJ = kTallNJ;
   constexpr int BM = G::kBM, WN = G::kWaveCols, E = kTallEpiChildren, NW = 4;
   static_assert(E % 4 == 0 && WN < 256, "four byte-sized counts per word");
   // everything below is derived from this copy of the thread id, which the compiler cannot see
@@ -267,10 +270,11 @@ __device__ __forceinline__ void tall_epilogue_count(TallAcc<MI, NJ> &acc, int m0
 
 // (max, sum of exponentials) per row: every wave its columns, the four wave columns merged through
 // LDS, one pair per row and tile.
-template <int MI, int NJ>
-__device__ __forceinline__ void tall_epilogue_lse(const TallAcc<MI, NJ> &acc, int m0, int v0, int m_total, int vocab,
+template <int MI>
+__device__ __forceinline__ void tall_epilogue_lse(const TallAcc<MI> &acc, int m0, int v0, int m_total, int vocab,
                                                   int n_tile, int tid, const HeadTables &tb, unsigned char *smem) {
-  using G = Tall<MI, NJ>;
+  using G = Tall<MI>;
+  constexpr int NJ = kTallNJ;
   const int lane = tid & 63, c16 = lane & 15, q = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 2, wn = wave & 3;
   float *s_part = reinterpret_cast<float *>(smem);  // [BM][4][2]
@@ -308,12 +312,13 @@ __device__ __forceinline__ void tall_epilogue_lse(const TallAcc<MI, NJ> &acc, in
   }
 }
 
-template <int MI, int NJ, int KIND>
+template <int MI, int KIND>
 __device__ __forceinline__ void early_head_tall_tile(
     int hidden, int vocab, int m_total, int m0, int v0, int n_tile,
     const uint16_t *__restrict__ hidden_states, const uint16_t *__restrict__ head_weight,
     const HeadTables &tb, unsigned char *smem) {
-  using G = Tall<MI, NJ>;
+  using G = Tall<MI>;
+  constexpr int NJ = kTallNJ;
   typedef __attribute__((address_space(3))) void lds_void;
   typedef const __attribute__((address_space(1))) void global_void;
   const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void *)smem;
@@ -371,7 +376,7 @@ __device__ __forceinline__ void early_head_tall_tile(
   const uint32_t a_rd = smem_base + wm * G::kWaveRows * kGemmRowBytes + frag_off;
   const uint32_t b_rd = smem_base + (G::kBM + wn * G::kWaveCols) * kGemmRowBytes + frag_off;
 
-  TallAcc<MI, NJ> acc;
+  TallAcc<MI> acc;
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -429,6 +434,6 @@ __device__ __forceinline__ void early_head_tall_tile(
     }
   }
   mfma_settle();
-  if (KIND == 0) tall_epilogue_count<MI, NJ>(acc, m0, v0, n_tile, vocab, tid, my_pos, my_cc, tb, smem);
-  else tall_epilogue_lse<MI, NJ>(acc, m0, v0, m_total, vocab, n_tile, tid, tb, smem);
+  if (KIND == 0) tall_epilogue_count<MI>(acc, m0, v0, n_tile, vocab, tid, my_pos, my_cc, tb, smem);
+  else tall_epilogue_lse<MI>(acc, m0, v0, m_total, vocab, n_tile, tid, tb, smem);
 }

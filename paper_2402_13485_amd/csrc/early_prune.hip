@@ -412,7 +412,7 @@ struct HeadTables {
 // matrix instructions want (8 consecutive x per lane), so tiles go global -> LDS -> operands
 // without any transpose.  Two kinds of tiles, chosen on the device from the row count (head_plan):
 //   - at most 256 rows: early_head_small_tile, a stream of the weights;
-//   - more: the tiles of early_head_tall.h, 32*MI rows x 64*NJ vocabulary entries in several
+//   - more: the tiles of early_head_tall.h, 32*MI rows x 256 vocabulary entries in several
 //     shapes.  They are bound by operand delivery and the matrix cores together.
 // Common to all:
 //   - K advances through a ring of LDS stages filled by direct global->LDS loads (no staging
@@ -820,25 +820,24 @@ __device__ __forceinline__ void early_head_small_tile(
 //     workgroups).  220 rows x 4096 x 32000, pruning call: 131 us; 138 with 256 x 128 tiles of
 //     32-deep steps, 146 with two row tiles of 160 x 256.
 //   - More: the shape of the least cost = rounds of workgroups over the compute units x
-//     (10 + mi * nj).  Measured per round, us at 4096 x 32000: 92 for 160 x 256, 105 for 192, 119 for
-//     224, 127 for 256, 141 for 288, 167 for 352 x 256, i.e. 3.1 us per matrix tile of a wave and 30
-//     beside them.  Tiles of 192 columns were no better (288 x 192: 106 us), of 128 columns worse.
+//     (10 + 4 * mi).  Measured per round, us at 4096 x 32000: 92 for 160 x 256, 105 for 192, 119 for
+//     224, 127 for 256, 141 for 288, 156 for 320, 167 for 352 x 256, i.e. 3.1 us per matrix tile of a wave
+//     and 30 beside them.  Tiles of 192 columns were no better (288 x 192: 106 us), of 128 columns worse.
 struct HeadPlan {
-  int mi, nj;  // tile of 32*mi x 64*nj; mi = 0: the tile of few rows
+  int mi;  // tile of 32*mi x 256; 0: the tile of few rows
   int m_tiles, n_tiles;
 };
 
-#ifndef PROPD_TALL_SHAPES
-#define PROPD_TALL_SHAPES(X) X(11, 4) X(10, 4) X(9, 4) X(8, 4) X(7, 4) X(6, 4) X(5, 4)
-#endif
+#define PROPD_TALL_SHAPES(X) X(11) X(10) X(9) X(8) X(7) X(6) X(5)  // the larger first: of equal cost the first is taken
 
 __host__ __device__ inline HeadPlan head_plan(int m_total, int vocab, int cus, int force) {
-  HeadPlan pl = {0, 2, 1, (vocab - 1) / 128 + 1};
+  HeadPlan pl = {0, 1, (vocab - 1) / 128 + 1};
   if (m_total <= kSmallBM && force == 0) return pl;
-  const int rows = m_total > 0 ? m_total : 1;
-  const float inv = 1.f / (float)cus;  // a division per shape is felt in front of a small kernel's first load
+  const int rows = m_total > 0 ? m_total : 1, nt = (vocab - 1) / 256 + 1;
+  const float inv = 1.f / (float)cus;  // instead of a 64-bit division per shape in front of the first load
   long long best = -1;
-  auto take = [&](int mi, int nj, int mt, int nt) {
+  auto take = [&](int mi) {
+    const int mt = (rows - 1) / (32 * mi) + 1;
     const long long tiles = (long long)mt * nt;
     long long rounds;
     if (tiles < (1ll << 24)) {  // by the reciprocal, off by one at most
@@ -850,14 +849,13 @@ __host__ __device__ inline HeadPlan head_plan(int m_total, int vocab, int cus, i
     } else {
       rounds = (tiles + cus - 1) / cus;
     }
-    const long long cost = rounds * (10 + mi * nj);
+    const long long cost = rounds * (10 + 4 * mi);
     if (best >= 0 && cost >= best) return;
     best = cost;
-    pl = HeadPlan{mi, nj, mt, nt};
+    pl = HeadPlan{mi, mt, nt};
   };
-#define X(MI, NJ)                                                          \
-  if (force == 0 || (force == 1 && MI == 8) || (force == 2 && MI == 11))   \
-    take(MI, NJ, (rows - 1) / (32 * MI) + 1, (vocab - 1) / (64 * NJ) + 1);
+#define X(MI) \
+  if (force == 0 || (force == 1 && MI == 8) || (force == 2 && MI == 11)) take(MI);
   PROPD_TALL_SHAPES(X)
 #undef X
   return pl;
@@ -895,10 +893,10 @@ __global__ __launch_bounds__(kGemmThreads, 1) void early_head_bf16_kernel(
         early_head_small_tile<KIND, 256>(hidden, vocab, m_total, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
       continue;
     }
-#define X(MI, NJ)                                                                                              \
-  if (pl.mi == MI && pl.nj == NJ)                                                                              \
-    early_head_tall_tile<MI, NJ, KIND>(hidden, vocab, m_total, m_tile * 32 * MI, n_tile * 64 * NJ, n_tile,      \
-                                       hidden_states, head_weight, tb, gemm_smem);
+#define X(MI)                                                                                              \
+  if (pl.mi == MI)                                                                                         \
+    early_head_tall_tile<MI, KIND>(hidden, vocab, m_total, m_tile * 32 * MI, n_tile * 256, n_tile,          \
+                                   hidden_states, head_weight, tb, gemm_smem);
     PROPD_TALL_SHAPES(X)
 #undef X
   }
