@@ -184,7 +184,7 @@ PROPD_API propd_status propd_tree_attention(const propd_tree *tree, propd_dtype 
  *              to row (b,o,j) of dst for j < n_kept[b]; other dst rows are untouched.
  *   workspace  propd_workspace_bytes(PROPD_WS_EARLY_PRUNE, ...) bytes, 16-byte aligned.  The
  *              scores themselves are never stored: the scratch holds per-node tables and,
- *              for the probability criterion, two floats per score row and 64 columns.
+ *              for the probability criterion, two floats per score row and 128 columns.
  * hidden_states and head_weight must be 16-byte aligned for PROPD_BF16
  * (PROPD_ERR_INVALID_ARG otherwise).
  * The bf16 scoring kernel chooses its tile shape on the device, from the number of score rows.  The

@@ -69,10 +69,9 @@ static PruneScratch carve_scratch(void *base, int B, int T_max, int vocab) {
   s.own = reinterpret_cast<float *>(take(nt * 4));
   s.logq = reinterpret_cast<float *>(take(nt * 4));
   s.row_cap = (size_t)B * (T_max > 1 ? T_max - 1 : 1);  // a node with children is not a leaf
-  // column parts of a row: one per tile, of at least 128 columns
-  s.parts = 4 * (((size_t)vocab + 255) / 256);
+  s.parts = ((size_t)vocab + 127) / 128;  // column parts of a row: one per tile, of at least 128 columns
   s.lse_part = reinterpret_cast<float *>(take(s.row_cap * s.parts * 8));
-  s.cnt_part = reinterpret_cast<int32_t *>(take((((size_t)vocab + 127) / 128) * nt * 4));
+  s.cnt_part = reinterpret_cast<int32_t *>(take(s.parts * nt * 4));
   s.total_bytes = off;
   return s;
 }

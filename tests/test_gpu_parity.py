@@ -112,7 +112,7 @@ def test_attention_fp32_ragged_d128(pb, oracle):
 
 @pytest.mark.parametrize("T_max", [16, 128])
 def test_attention_bf16_head_size_64(pb, oracle, T_max):
-    """bf16 tensors with the smaller head size (the plain kernel, no workspace): ragged
+    """bf16 tensors with the smaller head size (the tiled kernel): ragged
     lengths, an empty cache, a one-node tree, trees smaller than the slot."""
     rng = np.random.default_rng(64 + T_max)
     shapes = [synth.rank_product_tree(T_max, 3 if T_max == 16 else 5),
