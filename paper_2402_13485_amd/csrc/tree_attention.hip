@@ -75,7 +75,7 @@ struct AttnParams {
   float *part_o;   // [2 * grid][4 waves][16 blocks][64 lanes][4]
   float *part_ml;  // [2 * grid][4 waves][m | l][64 lanes]
   int32_t *cuts;   // CutRecords: [units] by unit, or [grid] by the workgroup that holds the first piece
-  int by_unit;     // 1 where there are no more units than workgroups
+  int by_unit;     // see merge_by_unit
 };
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -310,8 +310,8 @@ struct Schedule {
   }
 };
 
-// What the workgroup that holds the FIRST piece of a unit leaves for the merge kernel.  With no
-// more units than workgroups the records go by unit, and every unit gets one in every call;
+// What the workgroup that holds the FIRST piece of a unit leaves for the merge kernel.  With few
+// units (merge_by_unit) the records go by unit, and every unit gets one in every call;
 // otherwise by workgroup (a workgroup holds the first piece of at most one cut unit), and every
 // workgroup of the grid writes its own in every call (unit < 0: none).  The pieces of the unit
 // lie in workgroups w_first .. w_last: the first in the second partial slot of w_first, the others in
@@ -980,13 +980,18 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
 // as in the main kernel: register block 4 mb + q4 of a wave's 32 queries.
 // What it costs is waves that find nothing to do and the chain of dependent reads (record,
 // partials: written by other XCDs, so each comes from beyond the L2), not bytes.  Two kernels:
-//   by unit (no more units than workgroups: few units, each in many pieces): one workgroup per
-//     (unit, 32 queries, 32-wide block mb of d), one wave per q4, 16 pieces requested together.
-//     1 x 32 units of 1088 rows, 17 pieces each: 11.2 us by workgroup, 6.5 us by unit.  The steps of the
-//     merge are those of the other kernel, one piece after the other, and so are the bits of the result.
+//   by unit (few units, each in many pieces): one workgroup per (unit, 32 queries, 32-wide block mb
+//     of d), one wave per q4, up to 16 pieces requested together.
 //   by workgroup (many units in a few pieces each): one wave per (workgroup of the main kernel, 32
 //     queries, block mb), four pieces of the whole block together.  640 units of 4224 rows on 512
 //     workgroups: 12 us; four such waves to a workgroup, or one wave per q4, cost 14 to 18 us.
+// The steps of both are the same, one piece after the other, and so are the bits of the result.
+// Where the line lies (merge_by_unit): at four pieces per unit.  Whole calls by unit / by workgroup,
+// us, d = 128, equal lengths, on 512 workgroups: 32 units of 64 queries x 1024 keys 19.7 / 24.4, 40 x
+// 128 x 3000 36.4 / 39.4, 64 x 128 x 2000 38.1 / 39.1, 96 x 32 x 700 20.6 / 21.9, 128 x 64 x 2048 42.0 / 42.5 (d =
+// 64: 34.2 / 35.0), 160 x 128 x 1500 50.4 / 50.2, 256 x 64 x 1000 38.6 / 38.4, 256 x 128 x 4000 126.8 / 124.9, 480
+// x 70 x 300 41.1 / 38.4.
+static bool merge_by_unit(long long units, int grid) { return 4 * units <= grid; }
 constexpr int kCombinePieces = 4, kCombineManyPieces = 16;
 
 // x * a + y * b; D = 64: an infinity in a piece that counts for nothing is left out
@@ -1067,11 +1072,13 @@ __global__ __launch_bounds__(4 * kWave) void tree_attn_combine_unit_kernel(AttnP
     float m[N], l[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-      const int wg = w0 + k <= w_last ? w0 + k : w_last;  // past the last piece: re-read it, weight 0
-      const size_t ps = 2 * (size_t)wg + (wg == w ? 1 : 0);
-      m[k] = p.part_ml[part_ml_index(ps, dw, 0, ln)];
-      l[k] = p.part_ml[part_ml_index(ps, dw, 1, ln)];
-      o[k] = *reinterpret_cast<const f32x4 *>(p.part_o + part_o_index(ps, dw, 4 * mb + q4, ln));
+      if (w0 + k <= w_last) {  // uniform
+        const int wg = w0 + k;
+        const size_t ps = 2 * (size_t)wg + (wg == w ? 1 : 0);
+        m[k] = p.part_ml[part_ml_index(ps, dw, 0, ln)];
+        l[k] = p.part_ml[part_ml_index(ps, dw, 1, ln)];
+        o[k] = *reinterpret_cast<const f32x4 *>(p.part_o + part_o_index(ps, dw, 4 * mb + q4, ln));
+      }
     }
 #pragma unroll
     for (int k = 0; k < N; ++k)
@@ -1313,7 +1320,7 @@ extern "C" propd_status propd_tree_attention(const propd_tree *tree, propd_dtype
   p.part_ml = reinterpret_cast<float *>(ws);
   ws += align_up(slots * kPartMlFloats * 4, 256);
   p.cuts = reinterpret_cast<int32_t *>(ws);
-  p.by_unit = units <= grid ? 1 : 0;
+  p.by_unit = merge_by_unit(units, grid) ? 1 : 0;
   if (!(d == 64 ? launch_bf16<64>(p, grid, st) : launch_bf16<128>(p, grid, st))) return PROPD_ERR_DEVICE;
   return PROPD_OK;
 }

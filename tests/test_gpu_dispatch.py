@@ -214,7 +214,7 @@ def test_prune_bf16_few_rows_edges(pb, oracle, T, Hd, V):
                                          (9, 57, 16, 100), (1, 600, 33, 90), (2, 130, 100, 700)])
 @pytest.mark.parametrize("d", [64, 128])
 def test_attention_bf16_merge_of_cut_units(pb, oracle, B, H, T_max, L, d):
-    """Units cut into many pieces and into few, records by unit (no more units than workgroups)
+    """Units cut into many pieces and into few, records by unit (few units)
     and by workgroup (513 and 600 units: on the chip's 512 workgroups the one or the 88 units left
     after the whole ones are cut into a piece per workgroup), equal lengths and ragged ones."""
     rng = np.random.default_rng(B * 1000 + H)
@@ -224,6 +224,17 @@ def test_attention_bf16_merge_of_cut_units(pb, oracle, B, H, T_max, L, d):
         lens = rng.integers(0, L + 1, B).astype(np.int32)
     w = synth.Workload(87, "case", "bf16", B, H, d, T_max, 0, 0, 0, 1e-3)
     x = synth.make_attention_inputs(w, seq_lens=lens, trees=shapes)
+    out, sent = run_attention(pb, x)
+    check_attention(oracle, x, out, sent)
+
+
+@pytest.mark.parametrize("H", [127, 128, 129, 160])
+@pytest.mark.parametrize("d,T_max,L", [(64, 40, 500), (128, 33, 480)])
+def test_attention_bf16_merge_at_four_pieces(pb, oracle, H, d, T_max, L):
+    """18 and 17 stages per unit: at most 128 units are merged by unit on the chip's 512 workgroups, more by
+    workgroup."""
+    w = synth.Workload(88, "case", "bf16", 1, H, d, T_max, 0, 0, 0, 1e-3)
+    x = synth.make_attention_inputs(w, seq_lens=np.array([L], np.int32), trees=[synth.rank_product_tree(T_max, 4)])
     out, sent = run_attention(pb, x)
     check_attention(oracle, x, out, sent)
 
