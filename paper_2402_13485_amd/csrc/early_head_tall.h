@@ -1,4 +1,4 @@
-// Early-head scoring, more than 256 score rows: tiles of 32*MI rows x 256 vocabulary entries.
+// Early-head scoring, many score rows (see head_plan): tiles of 32*MI rows x 256 vocabulary entries.
 // Included by early_prune.hip inside namespace propd, after the helpers it uses.
 //
 // The scoring GEMM has few rows (the nodes that have children: 704 at B = 16, T = 128) against a

@@ -410,7 +410,7 @@ struct HeadTables {
 // C[m][v] = sum_x A[m][x] * W[v][x].  Both operands are contiguous along x, which is the layout the
 // matrix instructions want (8 consecutive x per lane), so tiles go global -> LDS -> operands
 // without any transpose.  Two kinds of tiles, chosen on the device from the row count (head_plan):
-//   - at most 256 rows: early_head_small_tile, a stream of the weights;
+//   - few (at most 128, or 256 in one round): early_head_small_tile, a stream of the weights;
 //   - more: the tiles of early_head_tall.h, 32*MI rows x 256 vocabulary entries in several
 //     shapes.  They are bound by operand delivery and the matrix cores together.
 // Common to all:
@@ -583,7 +583,7 @@ __device__ __forceinline__ void rows_epilogue(RowChildren<R> &ch, const float *s
 }
 
 // ------------------------------------------------------------------------------------
-// Few score rows (at most 256 in the whole batch: a small batch or small trees).  The
+// Few score rows (at most 256 in the whole batch, see head_plan: a small batch or small trees).  The
 // scoring kernel is then a stream of the weight matrix through the compute units, and a step
 // (a barrier, fragment reads whose latency a handful of matrix instructions cannot hide)
 // costs more than its bytes.  This tile takes 64-deep steps: half as many steps for the same
@@ -815,9 +815,14 @@ __device__ __forceinline__ void early_head_small_tile(
 
 // Which tile a call uses: decided on the device by every workgroup (and by the kernels
 // that read the per-tile results) from the row count, which the host never sees.
-//   - At most 256 rows: the tile of few rows, one row tile, 128 entries wide (32000 entries: 250
-//     workgroups).  220 rows x 4096 x 32000, pruning call: 131 us; 138 with 256 x 128 tiles of
-//     32-deep steps, 146 with two row tiles of 160 x 256.
+//   - At most 128 rows: the tile of few rows, one row tile, 128 entries wide (32000 entries: 250
+//     workgroups).
+//   - 129 to 256 rows: the same where a round of it, taken for 14 + rows / 16 (measured 61 us at 132
+//     rows x 4096, 67 at 176, 81 at 220), times its rounds costs no more than the best of the shapes below, whose
+//     rounds take a quarter less while a quarter of the compute units hold them.  Pruning call, us,
+//     few rows / best other: 176 rows x 4096 x 32000 114 / 124, 220 rows 127 / 130, 132 x 16001 103 / 129, 176 x 8192
+//     107.6 / 106.3, 220 x 8192 118 / 107, 176 x 64000 204 / 170, 176 x 128256 384 / 315, 132 x 3584 x 152064
+//     402 / 343, 176 x 1600 x 50257 123 / 89.
 //   - More: the shape of the least cost = rounds of workgroups over the compute units x
 //     (10 + 4 * mi).  Measured per round, us at 4096 x 32000: 92 for 160 x 256, 105 for 192, 119 for
 //     224, 127 for 256, 141 for 288, 156 for 320, 167 for 352 x 256, i.e. 3.1 us per matrix tile of a wave
@@ -830,25 +835,23 @@ struct HeadPlan {
 #define PROPD_TALL_SHAPES(X) X(11) X(10) X(9) X(8) X(7) X(6) X(5)  // the larger first: of equal cost the first is taken
 
 __host__ __device__ inline HeadPlan head_plan(int m_total, int vocab, int cus, int force) {
-  HeadPlan pl = {0, 1, (vocab - 1) / 128 + 1};
-  if (m_total <= kSmallBM && force == 0) return pl;
+  const HeadPlan few = {0, 1, (vocab - 1) / 128 + 1};
+  if (m_total <= kSmallBM / 2 && force == 0) return few;
   const int rows = m_total > 0 ? m_total : 1, nt = (vocab - 1) / 256 + 1;
   const float inv = 1.f / (float)cus;  // instead of a 64-bit division per shape in front of the first load
+  auto rounds = [&](long long tiles) -> long long {
+    if (tiles >= (1ll << 24)) return (tiles + cus - 1) / cus;
+    const int t = (int)tiles;  // by the reciprocal, off by one at most
+    int q = (int)((float)t * inv);
+    q -= q * cus > t ? 1 : 0;
+    q += (q + 1) * cus <= t ? 1 : 0;  // q = t / cus
+    return q * cus < t ? q + 1 : q;
+  };
+  HeadPlan pl = {};
   long long best = -1;
   auto take = [&](int mi) {
     const int mt = (rows - 1) / (32 * mi) + 1;
-    const long long tiles = (long long)mt * nt;
-    long long rounds;
-    if (tiles < (1ll << 24)) {  // by the reciprocal, off by one at most
-      const int t = (int)tiles;
-      int q = (int)((float)t * inv);
-      q -= q * cus > t ? 1 : 0;
-      q += (q + 1) * cus <= t ? 1 : 0;  // q = t / cus
-      rounds = q * cus < t ? q + 1 : q;
-    } else {
-      rounds = (tiles + cus - 1) / cus;
-    }
-    const long long cost = rounds * (10 + 4 * mi);
+    const long long cost = rounds((long long)mt * nt) * (10 + 4 * mi);
     if (best >= 0 && cost >= best) return;
     best = cost;
     pl = HeadPlan{mi, mt, nt};
@@ -857,6 +860,10 @@ __host__ __device__ inline HeadPlan head_plan(int m_total, int vocab, int cus, i
   if (force == 0 || (force == 1 && MI == 8) || (force == 2 && MI == 11)) take(MI);
   PROPD_TALL_SHAPES(X)
 #undef X
+  if (m_total <= kSmallBM && force == 0) {
+    const int quarters = 4 * pl.m_tiles * (long long)pl.n_tiles <= cus ? 3 : 4;
+    if (4 * rounds(few.n_tiles) * (14 + rows / 16) <= quarters * best) return few;
+  }
   return pl;
 }
 

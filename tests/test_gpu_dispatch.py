@@ -275,6 +275,21 @@ def test_prune_bf16_every_tile_shape(pb, oracle, B, T, V):
     check_prob(pb, oracle, x, res, ref, logm, [x["hidden_states"]], sents)
 
 
+@pytest.mark.parametrize("B,T,V", [(2, 66, 8192), (2, 66, 16001), (2, 128, 8192), (2, 128, 33001), (2, 89, 40000), (2, 65, 70000)])
+def test_prune_bf16_few_rows_or_tiles(pb, oracle, B, T, V):
+    """129 to 256 score rows take the tile of few rows in one round of workgroups and a shape for many
+    rows beyond that, or where the vocabulary is small: 130, 254, 176 and 128 rows, both criteria."""
+    w = synth.Workload(77, "case", "bf16", B, 1, 128, T, 64, V, 6, 1e-3)
+    x = synth.make_prune_inputs(w, trees=[synth.chain_tree(T)] * B, p_pass=0.8)
+    res, sents = run_prune(pb, x, [x["hidden_states"]])
+    check_prune(oracle, x, res, [x["hidden_states"]], sents)
+    logm, _, _ = prob_reference(oracle, x, threshold=0.5)
+    thr = float(np.float32(threshold_in_a_gap(logm, x["n_nodes"], 1e-3, 0.95)))
+    _, _, ref = prob_reference(oracle, x, threshold=thr)
+    res, sents = run_prob(pb, x, [x["hidden_states"]], threshold=thr)
+    check_prob(pb, oracle, x, res, ref, logm, [x["hidden_states"]], sents)
+
+
 PLAN_CHILD = """
 import sys
 sys.path[:0] = {path!r}
