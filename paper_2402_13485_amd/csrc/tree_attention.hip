@@ -27,7 +27,7 @@
 //     two per workgroup, and the workgroup holding its first piece leaves a record of the
 //     cut; a second kernel merges the pieces of every recorded cut, in their order.
 // Both head sizes run the same kernel.  d = 64 came from one wave per query (each lane walking K rows
-// of its own): 8 x 16 units of 64 queries x 2048 keys, 4150 -> 28 us + 5.5 us merge (67 MB of K/V).
+// of its own): 8 x 16 units of 64 queries x 2048 keys, 4150 -> 31 us + 5 us merge (67 MB of K/V).
 // Without a workspace or 16-byte alignment d = 64 runs a plain one-wave-per-query kernel.
 // fp32 path: tree_attention_f32.h.
 #include <type_traits>
