@@ -191,6 +191,20 @@ def test_attention_infinities_of_both_signs(pb, oracle, dtype, d, L):
     assert (np.abs(got[same] - ref[same]) <= tol * max(1.0, np.abs(ref[same]).max())).all()
 
 
+def same_kind_of_result(x, plain, tiled, sent):
+    a, b = host_f64(plain), host_f64(tiled)
+    for s in range(x["B"]):
+        n = int(x["n_nodes"][s])
+        one, other = a[s, :, :n], b[s, :, :n]
+        assert np.array_equal(np.isnan(one), np.isnan(other))
+        assert np.array_equal(np.isposinf(one), np.isposinf(other))
+        assert np.array_equal(np.isneginf(one), np.isneginf(other))
+        fin = np.isfinite(one)
+        # both round a result that differs by fp32 sums only
+        assert (np.abs(one[fin] - other[fin]) <= 2.0 ** -7 * np.maximum(np.abs(one[fin]), 1e-3)).all()
+        assert (to_host(tiled)[s, :, n:] == sent[s, :, n:]).all()
+
+
 @pytest.mark.parametrize("T,L", [(1, 33), (20, 0), (70, 31), (128, 300), (64, 2000)])
 @pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
 def test_attention_d64_not_finite_like_the_plain_kernel(pb, T, L, value):
@@ -210,17 +224,28 @@ def test_attention_d64_not_finite_like_the_plain_kernel(pb, T, L, value):
     assert st == 0
     st, tiled, _ = raw_attention(pb, x, workspace="full")
     assert st == 0
-    a, b = host_f64(plain), host_f64(tiled)
-    for s in range(2):
-        n = int(x["n_nodes"][s])
-        assert np.array_equal(np.isnan(a[s, :, :n]), np.isnan(b[s, :, :n]))
-        assert np.array_equal(np.isposinf(a[s, :, :n]), np.isposinf(b[s, :, :n]))
-        assert np.array_equal(np.isneginf(a[s, :, :n]), np.isneginf(b[s, :, :n]))
-        fin = np.isfinite(a[s, :, :n])
-        one, other = a[s, :, :n][fin], b[s, :, :n][fin]
-        # both round a result that differs by fp32 sums only
-        assert (np.abs(one - other) <= 2.0 ** -7 * np.maximum(np.abs(one), 1e-3)).all()
-        assert (to_host(tiled)[s, :, n:] == sent[s, :, n:]).all()
+    same_kind_of_result(x, plain, tiled, sent)
+
+
+@pytest.mark.parametrize("B,H,lens", [(1, 700, [90]), (3, 400, [64, 64, 64]), (5, 80, [300, 0, 1000, 33, 640])])
+def test_attention_d64_not_finite_in_the_middle_of_a_workgroup(pb, B, H, lens):
+    """Workgroups that do several units and parts of units, some of which are done a second time:
+    whole units first and the rest cut, and ranges over ragged units."""
+    rng = np.random.default_rng(B * H)
+    T = 40
+    w = synth.Workload(97, "case", "bf16", B, H, 64, T, 0, 0, 0, 1e-3)
+    x = synth.make_attention_inputs(w, seq_lens=np.array(lens, np.int32),
+                                    trees=[synth.random_tree(rng, T - 7 * (b % 2)) for b in range(B)])
+    for value in (np.nan, np.inf, -np.inf):
+        bad = synth.from_float(np.array([value], np.float32), "bf16")[0]
+        for name in ("v_tree", "v_cache"):
+            for _ in range(B * H // 8):
+                x[name][rng.integers(0, B), rng.integers(0, H), rng.integers(0, x[name].shape[2]), rng.integers(0, 64)] = bad
+    st, plain, sent = raw_attention(pb, x, workspace="none")
+    assert st == 0
+    st, tiled, _ = raw_attention(pb, x, workspace="full")
+    assert st == 0
+    same_kind_of_result(x, plain, tiled, sent)
 
 
 def test_attention_f32_many_units(pb):
