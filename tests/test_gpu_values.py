@@ -261,3 +261,35 @@ def test_attention_f32_many_units(pb):
     none = torch.empty((B, H, 0, d), device="cuda")
     out = pb.propd_tree_attention(tree, q, none, none, q, v, torch.zeros(B, dtype=torch.int32, device="cuda"), 0.125)
     assert torch.equal(out, v)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+def test_attention_replayed_with_values_that_come_and_go(pb, dtype, d):
+    """A captured call, replayed on inputs that are finite, hold a NaN and are finite again, with the
+    caller's own work between the replays: each replay gives the eager bits."""
+    B, H, T, L = 2, 4, 48, 700
+    gen = torch.Generator(device="cuda").manual_seed(10)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    normal = lambda *s: torch.randn(s, device="cuda", dtype=dt, generator=gen)
+    n_nodes, parent, _ = synth.pad_trees([synth.rank_product_tree(T, 4)] * B, T)
+    tree = dev_tree(pb, n_nodes, parent)
+    q, kt, vt, kc, vc = normal(B, H, T, d), normal(B, H, T, d), normal(B, H, T, d), normal(B, H, L, d), normal(B, H, L, d)
+    seq = torch.full((B,), L, dtype=torch.int32, device="cuda")
+    ws = torch.empty(pb.workspace_bytes(pb.WS_TREE_ATTENTION, B, T, H, d, L), dtype=torch.uint8, device="cuda")
+    out = torch.zeros_like(q)
+    call = lambda: pb.propd_tree_attention(tree, q, kc, vc, kt, vt, seq, d ** -0.5, out=out, workspace=ws)
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    kept = vt[1, 2, 30, 7].clone()
+    for value in (None, float("nan"), float("inf"), None):
+        vt[1, 2, 30, 7] = kept if value is None else value
+        call()
+        want = out.clone()
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16 if dtype == "bf16" else torch.int32),
+                           want.view(torch.int16 if dtype == "bf16" else torch.int32))
