@@ -2,34 +2,39 @@
 // Included by early_prune.hip inside namespace propd, after the helpers it uses.
 //
 // The scoring GEMM has few rows (the nodes that have children: 704 at B = 16, T = 128) against a
-// wide vocabulary.  A round of workgroups costs about 10 + 4 * MI (head_plan), so the shape
+// wide vocabulary.  A round of workgroups costs about 7 + 4 * MI (head_plan), so the shape
 // is the one whose row tiles hold the rows with little padding in the fewest rounds:
 // 704 rows are two tiles of 352 and 250 workgroups, ONE round of the 256 compute units; 832 rows
 // are four tiles of 224 in two rounds (three of 352 would need as many rounds of larger tiles).
-// With 256-row tiles of the 32x32x16 instruction and one shape for rows like 704 only, the
-// pruning calls at 264, 352, 528, 832 and 1056 rows x 4096 took 181, 181, 212, 293 and 395 us; now
-// 142, 155, 186, 265 and 329.
 //   - 8 waves as 2 (rows) x 4 (columns), a wave owns 16*MI x 64 as MI x 4 tiles of the
 //     16x16x32 bf16 MFMA: up to 176 accumulator registers (MI = 11) of the 256 a wave may have at
 //     two waves per SIMD, which leaves room for operands only if they are streamed;
-//   - K advances 32 per step through a ring of four LDS stages (64-byte rows, 38 KB for MI = 11),
-//     filled by direct global->LDS loads three steps ahead.  The 16-byte chunks of a
-//     row are XOR-swizzled with key(row) = (row >> 1) & 3: a fragment read of this MFMA has
-//     lane -> (row lane % 16, chunk lane / 16), and with the key (row >> 2) & 3
-//     every such read took twice its time in bank conflicts (measured: 64 against 38 ticks);
-//   - per step a wave reads its B fragments and then streams the A fragments
-//     through a four-deep register ring: the read of fragment i + 3 is issued behind the
-//     MFMAs of fragment i, waits are placed by hand (LDS reads return in order).  Meeting in the
-//     middle of a step and reading the next step's first fragments behind the last products of
-//     this one, so that no wave waits after a barrier, changed nothing at 224 x 256 and cost 3 % at
-//     352 x 256: loads and products compete, not reads (704 x 5120: 279 us whole, 211 without loads,
-//     210 without products, 270 without fragment reads);
+//   - K advances 64 per step, through a ring of LDS slots for each operand (128-byte rows), filled by
+//     direct global->LDS loads.  Every load takes whole 128-byte lines: the load path charges per line
+//     touched, and steps of 32 (half a line of a row per load, every line fetched twice) could not keep
+//     up with the products.  What a load has left to land matters as much: B, which comes from
+//     HBM, is requested two steps ahead; up to MI = 8 it has three slots for that, beyond it two,
+//     and its slot is handed back in the middle of a step, when every wave has its fragments in
+//     registers.  A, which comes from the L2, is requested one step ahead, two for MI = 5.
+//     Pruning call, us, steps of 32 in four stages / of 64 in two / as it is: 704 rows x 5120 x 32000
+//     250 / 235 / 235, 440 x 4096 159 / 155 / 146, 308 x 4096 139 / 142 / 122, 836 x 4096 276 / 266 / 258, 352 x 4096 x
+//     128256 446 / 451 / 417, 132 x 4096 x 128256 305 / 327 / 300, 176 x 1600 x 50257 90 / 90 / 82.  With B in two slots
+//     up to MI = 8 too: 176 x 4096 x 128256 344 instead of 321.
+//     704 x 5120 runs at 1.2 PFLOP/s, as fast as a large product of the library here; in two stages a
+//     call took 221 us without loads, 240 without products, without fragment reads and as it was;
+//   - the 16-byte chunks of a row are XOR-swizzled with key(row) = (row >> 1) & 7, so that the fragment
+//     reads of this MFMA (lane -> row lane % 16, chunk lane / 16) are free of bank conflicts;
+//   - per step a wave streams 2*MI fragments of A through a four-deep register ring: the read of
+//     fragment g + 3 is issued behind the MFMAs of fragment g, waits are placed by hand (LDS reads return in
+//     order).  Of the four B fragments of a step's second half two are read ahead into registers
+//     of their own; there is no room for more;
+//   - a row of an odd number of 32s ends in a step whose second half is zeros;
 //   - epilogues: rank counts or log-sum-exp partials on this accumulator layout: a
 //     row of the tile lives in the 16 lanes of a quarter wave (column = lane % 16 + 16 j), a
 //     lane holds rows 16 i + 4 (lane / 16) + r.
 #pragma once
 
-constexpr int kTallStages = 4;
+constexpr int kTallBK = 64, kTallRowBytes = 2 * kTallBK;  // depth of a step; bytes of a row in it
 constexpr int kTallEpiChildren = 12;  // children of a row per epilogue pass
 
 constexpr int kTallNJ = 4;  // matrix tiles of a wave side by side in the vocabulary
@@ -39,12 +44,24 @@ template <int MI>
 struct Tall {
   static constexpr int kWaveRows = 16 * MI, kWaveCols = 16 * kTallNJ;
   static constexpr int kBM = 2 * kWaveRows, kBN = 4 * kWaveCols;
-  static constexpr int kRows = kBM + kBN;                       // LDS rows of a stage
-  static constexpr int kStageBytes = kRows * kGemmRowBytes;     // 38912 for MI = 11
-  static constexpr int kGroups = kRows / 16, kAGroups = kBM / 16;  // 16-row groups, one load instruction each
-  static constexpr int kLoads = (kGroups + 7) / 8;              // of a wave per K step, at most
-  static constexpr int kIssueAt = MI / 2 - 1;  // the loads of a later step are issued behind this fragment's products
-  static_assert(kTallStages * kStageBytes <= kHeadLdsBytes, "ring of stages");
+  static constexpr int kABytes = kBM * kTallRowBytes, kBBytes = kBN * kTallRowBytes;  // of a step: 44 KB (MI = 11), 32 KB
+  // Slots of the two rings.  With three a load has two steps to land; where B has only two, its slot
+  // is handed back in the middle of a step, when its fragments are in registers.
+  static constexpr int kASlots = 3 * (kABytes + kBBytes) <= kHeadLdsBytes ? 3 : 2;           // 3: MI = 5
+  static constexpr int kBSlots = 2 * kABytes + 3 * kBBytes <= kHeadLdsBytes ? 3 : 2;         // 3: MI <= 8
+  static_assert(kASlots * kABytes + kBSlots * kBBytes <= kHeadLdsBytes, "rings");
+  static constexpr int kAGroups = kBM / 8;                      // 8-row groups, one load instruction each
+  static constexpr int kALoads = (kAGroups + 7) / 8, kBLoads = kBN / 64;  // of a wave per step (A: at most)
+  static constexpr bool kNarrow = MI > kTallWideMI;             // row addresses as 32-bit offsets
+  // fragment of A behind whose products fragment j of B of a step's second half is read: two of them
+  // early, into registers of their own, the others when their registers are free
+  static constexpr int b_at(int j) { return j < 2 ? MI - 5 + j : MI - 1; }
+  // such reads behind fragment g
+  static constexpr int b_behind(int g) {
+    int count = 0;
+    for (int j = 0; j < kTallNJ; ++j) count += b_at(j) == g ? 1 : 0;
+    return count;
+  }
 };
 
 template <int N>
@@ -327,54 +344,103 @@ __device__ __forceinline__ void early_head_tall_tile(
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
-  int my_pos = 0, my_cc = 0;
-  if (KIND == 0 && tid < G::kBM && m0 + tid < m_total) {
-    my_pos = tb.row_info[2 * (m0 + tid)];
-    my_cc = tb.row_info[2 * (m0 + tid) + 1];
-  }
+  // first position in child_list (24 bits) and children (at most 127) of the thread's row, in one
+  // register; where these are short it waits for the epilogue in LDS, behind the rings
+  int my_row = 0;
+  constexpr bool kParked = KIND == 0 && G::kNarrow;
+  static_assert(!kParked || G::kASlots * G::kABytes + G::kBSlots * G::kBBytes + 4 * kGemmThreads <= kHeadLdsBytes, "parked");
+  int *parked = reinterpret_cast<int *>(smem + G::kASlots * G::kABytes + G::kBSlots * G::kBBytes);
+  if (KIND == 0 && tid < G::kBM && m0 + tid < m_total)
+    my_row = tb.row_info[2 * (m0 + tid)] | tb.row_info[2 * (m0 + tid) + 1] << 24;
+  if constexpr (kParked) parked[tid] = my_row;
 
-  // ---- loader: group gi = wave + 8 j (16 rows, 1 KB) for j = 0 .. n_groups - 1
-  const int ld_row = lane >> 2;
-  const int ld_chunk = ((lane & 3) ^ ((lane >> 3) & 3)) << 4;  // byte offset in the global row: chunk ^ key(row)
-  const bool all_groups = wave + 8 * (G::kLoads - 1) < G::kGroups;  // kLoads groups, else one fewer
-  const unsigned char *src[G::kLoads];
+  // ---- loader: a load instruction fills 8 rows of 128 bytes (1 KB); wave w takes groups w + 8 j of
+  //      both operands
+  const int ld_row = 8 * wave + (lane >> 3);
+  // byte offset in the global row: chunk ^ key(row); a wave's groups are all even or all odd
+  const int ld_chunk = ((lane & 7) ^ ((4 * wave + (lane >> 4)) & 7)) << 4;
+  const bool all_a = wave + 8 * (G::kALoads - 1) < G::kAGroups;  // kALoads groups of A, else one fewer
+  // Where registers are short the rows are addressed by 32-bit offsets from the operand's first byte of
+  // this tile (head_plan takes such shapes only where they suffice), and those of B, at constant
+  // distances up to the last row of the vocabulary, from the first.
+  using Src = std::conditional_t<G::kNarrow, uint32_t, const unsigned char *>;
+  constexpr int kBOwn = G::kNarrow ? 1 : G::kBLoads;
+  Src a_src[G::kALoads], b_src[kBOwn];
+  const unsigned char *a_base = reinterpret_cast<const unsigned char *>(hidden_states);
+  const unsigned char *b_base = reinterpret_cast<const unsigned char *>(head_weight + (size_t)v0 * hidden);
+  const uint32_t b_last = (uint32_t)(vocab - 1 - v0) * (uint32_t)(2 * hidden);
 #pragma unroll
-  for (int j = 0; j < G::kLoads; ++j) {
-    const int gi = wave + 8 * j;
-    if (gi < G::kAGroups) {
-      int m = m0 + 16 * gi + ld_row;
-      m = m < m_total ? m : m_total - 1;
-      src[j] = reinterpret_cast<const unsigned char *>(hidden_states + (size_t)tb.row_src[m] * hidden) + ld_chunk;
-    } else {
-      int v = v0 + 16 * (gi - G::kAGroups) + ld_row;
-      v = v < vocab ? v : vocab - 1;
-      src[j] = reinterpret_cast<const unsigned char *>(head_weight + (size_t)v * hidden) + ld_chunk;
+  for (int j = 0; j < G::kALoads; ++j) {
+    const int m = m0 + ld_row + 64 * j, row = tb.row_src[m < m_total ? m : m_total - 1];
+    if constexpr (G::kNarrow) a_src[j] = (uint32_t)row * (uint32_t)(2 * hidden);
+    else a_src[j] = a_base + (size_t)row * (2 * (size_t)hidden);
+  }
+#pragma unroll
+  for (int j = 0; j < kBOwn; ++j) {
+    const int v = ld_row + 64 * j;
+    if constexpr (G::kNarrow) b_src[j] = (uint32_t)v * (uint32_t)(2 * hidden);
+    else b_src[j] = b_base + (size_t)(v0 + v < vocab ? v : vocab - 1 - v0) * (2 * (size_t)hidden);
+  }
+  unsigned char *a_smem = smem + wave * 1024, *b_smem = smem + G::kASlots * G::kABytes + wave * 1024;
+  // The last step of a row of an odd number of 32s: the lanes of its second half fetch the first again,
+  // and put zeros in its place once it has landed (products of zeros leave a sum as it is).
+  const int n_steps = (hidden + kTallBK - 1) / kTallBK;
+  const bool half_end = hidden % kTallBK != 0;
+  auto load_a = [&](int step, int slot, auto jc) {
+    constexpr int j = decltype(jc)::value;
+    if (j + 1 < G::kALoads || all_a) {
+      const int chunk = ld_chunk & (half_end && step + 1 == n_steps ? ~64 : ~0);
+      lds_void *dst = (lds_void *)(a_smem + slot * G::kABytes + j * 8192);
+      if constexpr (G::kNarrow)
+        __builtin_amdgcn_global_load_lds((global_void *)(a_base + (size_t)step * kTallRowBytes + (a_src[j] + chunk)), dst, 16, 0, 0);
+      else
+        __builtin_amdgcn_global_load_lds((global_void *)(a_src[j] + ((size_t)step * kTallRowBytes + chunk)), dst, 16, 0, 0);
     }
-  }
-  int k_off = 0;  // bytes into the rows of the next step to issue
-  auto issue = [&](int slot) {
-    unsigned char *dst = smem + slot * G::kStageBytes + wave * 1024;
+  };
+  auto load_b = [&](int step, int slot, auto jc) {
+    constexpr int j = decltype(jc)::value;
+    const int chunk = ld_chunk & (half_end && step + 1 == n_steps ? ~64 : ~0);
+    lds_void *dst = (lds_void *)(b_smem + slot * G::kBBytes + j * 8192);
+    if constexpr (G::kNarrow) {
+      uint32_t off = b_src[0] + (uint32_t)(j * 128) * (uint32_t)hidden;  // 64 rows each
+      off = off < b_last ? off : b_last;
+      __builtin_amdgcn_global_load_lds((global_void *)(b_base + (size_t)step * kTallRowBytes + (off + chunk)), dst, 16, 0, 0);
+    } else {
+      __builtin_amdgcn_global_load_lds((global_void *)(b_src[j] + ((size_t)step * kTallRowBytes + chunk)), dst, 16, 0, 0);
+    }
+  };
+  // Step `step`, in the given slots, is there for all waves.  Of this wave's loads those of B of the
+  // step after it (and of A where that has three slots) may be outstanding, if there is one.
+  auto landed = [&](int step, int slot_a, int slot_b) {
+    if (step + 1 >= n_steps) gemm_wait_vmem<0>();
+    else if (G::kASlots == 2) gemm_wait_vmem<G::kBLoads>();
+    else if (all_a) gemm_wait_vmem<G::kBLoads + G::kALoads>();
+    else gemm_wait_vmem<G::kBLoads + G::kALoads - 1>();
+    if (half_end && step + 1 == n_steps) {
+      if (ld_chunk & 64) {
+        // (opaque, so that no register holds it, or the lane, outside this branch)
+        const uint32_t zero = (uint32_t)opaque(0);
+        const u32x4 zeros = {zero, zero, zero, zero};
+        const int lane = opaque(threadIdx.x) & 63;
 #pragma unroll
-    for (int j = 0; j < G::kLoads; ++j)
-      if (j + 1 < G::kLoads || all_groups)
-        __builtin_amdgcn_global_load_lds((global_void *)(src[j] + k_off), (lds_void *)(dst + j * 8192), 16, 0, 0);
-    k_off += kGemmRowBytes;
+        for (int j = 0; j < G::kALoads; ++j)
+          if (j + 1 < G::kALoads || all_a)
+            *reinterpret_cast<u32x4 *>(a_smem + slot_a * G::kABytes + j * 8192 + 16 * lane) = zeros;
+#pragma unroll
+        for (int j = 0; j < G::kBLoads; ++j)
+          *reinterpret_cast<u32x4 *>(b_smem + slot_b * G::kBBytes + j * 8192 + 16 * lane) = zeros;
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+    __builtin_amdgcn_s_barrier();
   };
-  // until at most STEPS steps' loads of this wave are outstanding
-  auto wait_steps = [&](auto steps) {
-    constexpr int N = decltype(steps)::value;
-    if (all_groups) gemm_wait_vmem<N * G::kLoads>();
-    else gemm_wait_vmem<N * (G::kLoads - 1)>();
-  };
-  using none = std::integral_constant<int, 0>;
-  using one_step = std::integral_constant<int, 1>;
-  using two_steps = std::integral_constant<int, 2>;
 
-  // ---- per-lane LDS read addresses: row lane % 16 of a 16-row block, chunk lane / 16 (swizzled)
+  // ---- per-lane LDS read addresses: row lane % 16 of a 16-row block, chunk lane / 16 (swizzled);
+  //      the second 32 of K lie 64 bytes away, up or down
   const int c16 = lane & 15, kq = lane >> 4;
-  const uint32_t frag_off = c16 * kGemmRowBytes + ((kq ^ ((c16 >> 1) & 3)) << 4);
-  const uint32_t a_rd = smem_base + wm * G::kWaveRows * kGemmRowBytes + frag_off;
-  const uint32_t b_rd = smem_base + (G::kBM + wn * G::kWaveCols) * kGemmRowBytes + frag_off;
+  const uint32_t frag_off = c16 * kTallRowBytes + ((kq ^ ((c16 >> 1) & 7)) << 4);
+  const uint32_t a_rd = smem_base + wm * G::kWaveRows * kTallRowBytes + frag_off;
+  const uint32_t b_rd = smem_base + G::kASlots * G::kABytes + wn * G::kWaveCols * kTallRowBytes + frag_off;
 
   TallAcc<MI> acc;
 #pragma unroll
@@ -382,58 +448,80 @@ __device__ __forceinline__ void early_head_tall_tile(
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const int n_steps = hidden / kBK;
-  const int n_pro = n_steps < kTallStages - 1 ? n_steps : kTallStages - 1;
-  int slot_ld = 0;
-  for (int i = 0; i < n_pro; ++i) {
-    issue(slot_ld);
-    slot_ld = slot_ld + 1 == kTallStages ? 0 : slot_ld + 1;
-  }
-  if (n_pro == 3) wait_steps(two_steps{});
-  else if (n_pro == 2) wait_steps(one_step{});
-  else wait_steps(none{});
-  __builtin_amdgcn_s_barrier();
-  uint32_t so = 0;  // byte offset of the stage being multiplied
-  for (int step = 0; step < n_steps; ++step) {
-    const uint32_t pa = a_rd + so, pb = b_rd + so;
-    u32x4 bf[NJ], af[4];
+  constexpr int SA = G::kASlots, SB = G::kBSlots;
+  auto next_slot = [](int slot, int n) { return slot + 1 == n ? 0 : slot + 1; };
+  static_for<2>([&](auto i) {
+    if (i < n_steps) {
+      if constexpr (i < SA - 1) static_for<G::kALoads>([&](auto j) { load_a(i, i, j); });
+      static_for<G::kBLoads>([&](auto j) { load_b(i, i, j); });
+    }
+  });
+  landed(0, 0, 0);
+  // slots being multiplied and being filled
+  int slot_a = 0, slot_b = 0, fill_a = SA - 1, fill_b = SB - 1;
+  for (int step = 0;; ++step) {
+    const bool more_a = step + SA - 1 < n_steps, more_b = step + 2 < n_steps;
+    if constexpr (SB == 2) fill_b = slot_b;
+    constexpr int N = 2 * MI;  // fragments of A in a step
+    const uint32_t so_a = a_rd + slot_a * G::kABytes, so_b = b_rd + slot_b * G::kBBytes;
+    const uint32_t pa[2] = {so_a, so_a ^ 64u}, pb[2] = {so_b, so_b ^ 64u};
+    u32x4 bf[NJ + 2], af[4];
+    auto read_a = [&](auto gc) {
+      constexpr int g = decltype(gc)::value;
+      if constexpr (g < N) af[g & 3] = gemm_lds_read16<(g % MI) * 16 * kTallRowBytes>(pa[g / MI]);
+    };
     // the first product needs only A0 and B0: they are read first
-    af[0] = gemm_lds_read16<0>(pa);
-    static_for<NJ>([&](auto j) { bf[j] = gemm_lds_read16<j * 1024>(pb); });
-    af[1] = gemm_lds_read16<1024>(pa);
-    af[2] = gemm_lds_read16<2048>(pa);
-    static_for<MI>([&](auto ic) {
-      constexpr int i = decltype(ic)::value;
-      constexpr int allowed = MI - 1 - i < 2 ? MI - 1 - i : 2;  // younger A reads in flight
-      if constexpr (i == 0) {
+    read_a(std::integral_constant<int, 0>{});
+    static_for<NJ>([&](auto j) { bf[j] = gemm_lds_read16<j * 16 * kTallRowBytes>(pb[0]); });
+    read_a(std::integral_constant<int, 1>{});
+    read_a(std::integral_constant<int, 2>{});
+    static_for<N>([&](auto gc) {
+      constexpr int g = decltype(gc)::value, i = g % MI, ks = g / MI;
+      // reads younger than fragment g of A
+      constexpr int allowed = (g + 1 < N) + (g + 2 < N) + G::b_behind(g - 2) + G::b_behind(g - 1);
+      if constexpr (g == 0) {
         tall_wait_lds2<NJ + 1>(af[0], bf[0]);
         acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[0]),
                                                             __builtin_bit_cast(bf16x8, bf[0]), acc[0][0], 0, 0, 0);
         static_for<NJ>([&](auto j) { tall_wait_lds2<2>(af[0], bf[j]); });
       } else {
-        tall_wait_lds<allowed>(af[i & 3]);
+        tall_wait_lds<allowed>(af[g & 3]);
+        if constexpr (g == MI) tall_wait_lds2<allowed>(bf[NJ], bf[NJ + 1]);
       }
-#pragma unroll
-      for (int j = (i == 0 ? 1 : 0); j < NJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[i & 3]),
-                                                            __builtin_bit_cast(bf16x8, bf[j]), acc[i][j], 0, 0, 0);
-      if constexpr (i + 3 < MI) af[(i + 3) & 3] = gemm_lds_read16<(i + 3) * 1024>(pa);
-      if (i == G::kIssueAt && step + kTallStages - 1 < n_steps) {
-        issue(slot_ld);  // step + 3, into the slot of step - 1
-        slot_ld = slot_ld + 1 == kTallStages ? 0 : slot_ld + 1;
+      static_for<NJ>([&](auto j) {
+        if constexpr (g == MI && j == 2) tall_wait_lds2<1>(bf[2], bf[3]);
+        if constexpr (g > 0 || j > 0)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              __builtin_bit_cast(bf16x8, af[g & 3]), __builtin_bit_cast(bf16x8, bf[ks == 1 && j < 2 ? NJ + j : j]),
+              acc[i][j], 0, 0, 0);
+      });
+      static_for<NJ>([&](auto j) {
+        if constexpr (G::b_at(j) == g) bf[j < 2 ? NJ + j : j] = gemm_lds_read16<j * 16 * kTallRowBytes>(pb[1]);
+      });
+      read_a(std::integral_constant<int, g + 3>{});
+      // the loads: A first, then B, whose slot is free here
+      if constexpr (SB == 2 && g == MI) {
+        if (more_b) __builtin_amdgcn_s_barrier();
+      }
+      if constexpr (g < G::kALoads) {
+        if (more_a) load_a(step + SA - 1, fill_a, gc);
+      }
+      constexpr int jb = g - (SB == 2 ? MI + 1 : G::kALoads);
+      if constexpr (jb >= 0 && jb < G::kBLoads) {
+        if (more_b) load_b(step + 2, fill_b, std::integral_constant<int, jb>{});
       }
     });
-    if (step + 1 < n_steps) {
-      // this wave has read everything of this step's slot; the next step has landed once at
-      // most the steps after it that were issued (up to two) are outstanding
-      if (step + 3 < n_steps) wait_steps(two_steps{});
-      else if (step + 2 < n_steps) wait_steps(one_step{});
-      else wait_steps(none{});
-      __builtin_amdgcn_s_barrier();  // it is visible; every wave is done with this step's slot
-      so = so + G::kStageBytes == kTallStages * G::kStageBytes ? 0 : so + G::kStageBytes;
-    }
+    // this wave has read all of its slots
+    slot_a = next_slot(slot_a, SA);
+    fill_a = next_slot(fill_a, SA);
+    slot_b = next_slot(slot_b, SB);
+    fill_b = next_slot(fill_b, SB);
+    if (step + 1 >= n_steps) break;
+    landed(step + 1, slot_a, slot_b);
   }
   mfma_settle();
-  if (KIND == 0) tall_epilogue_count<MI>(acc, m0, v0, n_tile, vocab, tid, my_pos, my_cc, tb, smem);
+  tid = opaque(threadIdx.x);
+  if constexpr (kParked) my_row = parked[tid];
+  if (KIND == 0) tall_epilogue_count<MI>(acc, m0, v0, n_tile, vocab, tid, my_row & 0xffffff, my_row >> 24, tb, smem);
   else tall_epilogue_lse<MI>(acc, m0, v0, m_total, vocab, n_tile, tid, tb, smem);
 }

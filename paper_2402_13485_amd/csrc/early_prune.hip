@@ -410,7 +410,7 @@ struct HeadTables {
 // C[m][v] = sum_x A[m][x] * W[v][x].  Both operands are contiguous along x, which is the layout the
 // matrix instructions want (8 consecutive x per lane), so tiles go global -> LDS -> operands
 // without any transpose.  Two kinds of tiles, chosen on the device from the row count (head_plan):
-//   - few (at most 128, or 256 in one round): early_head_small_tile, a stream of the weights;
+//   - few (at most 128, or 160 in one round): early_head_small_tile, a stream of the weights;
 //   - more: the tiles of early_head_tall.h, 32*MI rows x 256 vocabulary entries in several
 //     shapes.  They are bound by operand delivery and the matrix cores together.
 // Common to all:
@@ -432,9 +432,9 @@ struct HeadTables {
 //     row tiles.
 constexpr int kBK = 32;
 constexpr int kGemmThreads = 512, kGemmWaves = kGemmThreads / kWave;
-constexpr int kGemmRowBytes = kBK * 2;                                           // 64
+constexpr int kTallWideMI = 8;  // the tallest tile whose registers have room for row addresses of 64 bits
 constexpr int kXcds = 8;
-constexpr int kHeadLdsBytes = 155648;  // dynamic LDS of the scoring kernel: the largest ring of its tile shapes
+constexpr int kHeadLdsBytes = 163840;  // dynamic LDS of the scoring kernel: the largest ring of its tile shapes
 
 template <int N>
 __device__ __forceinline__ void gemm_wait_vmem() {
@@ -583,7 +583,7 @@ __device__ __forceinline__ void rows_epilogue(RowChildren<R> &ch, const float *s
 }
 
 // ------------------------------------------------------------------------------------
-// Few score rows (at most 256 in the whole batch, see head_plan: a small batch or small trees).  The
+// Few score rows (at most 160 in the whole batch, see head_plan: a small batch or small trees).  The
 // scoring kernel is then a stream of the weight matrix through the compute units, and a step
 // (a barrier, fragment reads whose latency a handful of matrix instructions cannot hide)
 // costs more than its bytes.  This tile takes 64-deep steps: half as many steps for the same
@@ -611,7 +611,8 @@ __device__ __forceinline__ void gemm_wait_frag(GemmFrag &f) {
   asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.b[0]), "+v"(f.b[1]) : "n"(N));
 }
 
-constexpr int kSmallBM = 256, kSmallBK = 64;
+constexpr int kSmallBK = 64;
+constexpr int kSmallMaxRows = 160;  // rows that this tile is used for at most, see head_plan
 constexpr int kSmallRowBytes = kSmallBK * 2;                          // 128
 constexpr int kSmallWBytes = 128 * kSmallRowBytes;                    // 16 KB of weight rows per stage
 
@@ -817,26 +818,26 @@ __device__ __forceinline__ void early_head_small_tile(
 // that read the per-tile results) from the row count, which the host never sees.
 //   - At most 128 rows: the tile of few rows, one row tile, 128 entries wide (32000 entries: 250
 //     workgroups).
-//   - 129 to 256 rows: the same where a round of it, taken for 14 + rows / 16 (measured 61 us at 132
-//     rows x 4096, 67 at 176, 81 at 220), times its rounds costs no more than the best of the shapes below, whose
-//     rounds take a quarter less while a quarter of the compute units hold them.  Pruning call, us,
-//     few rows / best other: 176 rows x 4096 x 32000 114 / 124, 220 rows 127 / 130, 132 x 16001 103 / 129, 176 x 8192
-//     107.6 / 106.3, 220 x 8192 118 / 107, 176 x 64000 204 / 170, 176 x 128256 384 / 315, 132 x 3584 x 152064
-//     402 / 343, 176 x 1600 x 50257 123 / 89.
+//   - 129 to 160 rows: the same where one round of it covers the vocabulary and rows are long.  Pruning
+//     call, us, few rows / best other: 132 rows x 4096 x 32000 111 / 117, 132 x 4096 x 16001 104 / 107, 176 x
+//     4096 x 32000 115 / 115, 220 x 4096 x 32000 125 / 116, 176 x 4096 x 8192 109 / 105, 132 x 1024 x 32000 61 / 55, 220 x
+//     2048 x 32000 91 / 79; in two rounds 176 x 4096 x 64000 205 / 176, 132 x 3584 x 152064 391 / 294.
 //   - More: the shape of the least cost = rounds of workgroups over the compute units x
-//     (10 + 4 * mi).  Measured per round, us at 4096 x 32000: 92 for 160 x 256, 105 for 192, 119 for
-//     224, 127 for 256, 141 for 288, 156 for 320, 167 for 352 x 256, i.e. 3.1 us per matrix tile of a wave
-//     and 30 beside them.  Tiles of 192 columns were no better (288 x 192: 106 us), of 128 columns worse.
+//     (7 + 4 * mi).  Pruning call, us, one round at 4096 x 32000 (43 of it beside the kernel): 122 for 160 x 256,
+//     134 for 192, 146 for 224, 158 for 256, 170 for 288, 183 for 320, 200 for 352 x 256.  Tiles of 192 columns
+//     were no better, of 128 columns worse.
 struct HeadPlan {
   int mi;  // tile of 32*mi x 256; 0: the tile of few rows
   int m_tiles, n_tiles;
 };
 
+constexpr int kTallMaxMI = 11;
 #define PROPD_TALL_SHAPES(X) X(11) X(10) X(9) X(8) X(7) X(6) X(5)  // the larger first: of equal cost the first is taken
 
-__host__ __device__ inline HeadPlan head_plan(int m_total, int vocab, int cus, int force) {
+__host__ __device__ inline HeadPlan head_plan(int m_total, int hidden, int vocab, int cus, int force, int max_mi) {
   const HeadPlan few = {0, 1, (vocab - 1) / 128 + 1};
-  if (m_total <= kSmallBM / 2 && force == 0) return few;
+  if (force == 0 && (m_total <= 128 || (m_total <= kSmallMaxRows && few.n_tiles <= cus && hidden >= 3072)))
+    return few;
   const int rows = m_total > 0 ? m_total : 1, nt = (vocab - 1) / 256 + 1;
   const float inv = 1.f / (float)cus;  // instead of a 64-bit division per shape in front of the first load
   auto rounds = [&](long long tiles) -> long long {
@@ -851,19 +852,15 @@ __host__ __device__ inline HeadPlan head_plan(int m_total, int vocab, int cus, i
   long long best = -1;
   auto take = [&](int mi) {
     const int mt = (rows - 1) / (32 * mi) + 1;
-    const long long cost = rounds((long long)mt * nt) * (10 + 4 * mi);
+    const long long cost = rounds((long long)mt * nt) * (7 + 4 * mi);
     if (best >= 0 && cost >= best) return;
     best = cost;
     pl = HeadPlan{mi, mt, nt};
   };
 #define X(MI) \
-  if (force == 0 || (force == 1 && MI == 8) || (force == 2 && MI == 11)) take(MI);
+  if (MI <= max_mi && (force == 0 || (force == 1 && MI == 8) || (force == 2 && MI == (max_mi < 11 ? max_mi : 11)))) take(MI);
   PROPD_TALL_SHAPES(X)
 #undef X
-  if (m_total <= kSmallBM && force == 0) {
-    const int quarters = 4 * pl.m_tiles * (long long)pl.n_tiles <= cus ? 3 : 4;
-    if (4 * rounds(few.n_tiles) * (14 + rows / 16) <= quarters * best) return few;
-  }
   return pl;
 }
 
@@ -871,11 +868,11 @@ __host__ __device__ inline HeadPlan head_plan(int m_total, int vocab, int cus, i
 // blockIdx.x, blockIdx.x + gridDim.x, ... (the grid is a multiple of the XCD count).
 template <int KIND>
 __global__ __launch_bounds__(kGemmThreads, 1) void early_head_bf16_kernel(
-    int hidden, int vocab, int B, int cus, int force, const uint16_t *__restrict__ hidden_states,
+    int hidden, int vocab, int B, int cus, int force, int max_mi, const uint16_t *__restrict__ hidden_states,
     const uint16_t *__restrict__ head_weight, HeadTables tb) {
   const int m_total = tb.row_base[B];
   if (m_total <= 0) return;
-  const HeadPlan pl = head_plan(m_total, vocab, cus, force);
+  const HeadPlan pl = head_plan(m_total, hidden, vocab, cus, force, max_mi);
   const int m_tiles = pl.m_tiles, n_tiles = pl.n_tiles;
   if (KIND == 0 && blockIdx.x == 0 && threadIdx.x == 0) *tb.n_tiles = n_tiles;
   const long long total = (long long)kXcds * ((n_tiles + kXcds - 1) / kXcds) * m_tiles;
@@ -916,14 +913,14 @@ __global__ __launch_bounds__(kGemmThreads, 1) void early_head_bf16_kernel(
 // One wave per score row: log sum_v exp(z[v]) from the row's tile partials (the first
 // n_parts of them were written), then logq = own score - that for every child of the
 // row's node.  A token id outside the vocabulary has probability 0 (logq = -inf).
-__global__ __launch_bounds__(kWave) void row_lse_kernel(int B, int vocab, int cus, int force, int bf16,
+__global__ __launch_bounds__(kWave) void row_lse_kernel(int B, int hidden, int vocab, int cus, int force, int max_mi, int bf16,
                                                         HeadTables tb, float *__restrict__ logq) {
   const int m = blockIdx.x;
   const int m_total = tb.row_base[B];
   if (m >= m_total) return;
   int n_parts;
   if (bf16) {
-    n_parts = head_plan(m_total, vocab, cus, force).n_tiles;
+    n_parts = head_plan(m_total, hidden, vocab, cus, force, max_mi).n_tiles;
   } else {
     n_parts = f32_plan(m_total, vocab).n_tiles;
   }
@@ -1316,6 +1313,9 @@ static propd_status prune_impl(
   // top_k >= vocab: every id of the vocabulary is inside the list, no scores are needed (ids
   // outside the vocabulary still fail, in the decision kernel)
   const int cus = prune_compute_units();
+  // the tallest tiles address their operand rows by 32-bit offsets
+  const int max_mi = (unsigned long long)hidden * 2 * ((unsigned long long)B * T_max > 256 ? (unsigned long long)B * T_max : 256) <
+                             (1ull << 32) ? kTallMaxMI : kTallWideMI;
   if (scored) {
     PrepareArgs pr;
     pr.B = B;
@@ -1363,18 +1363,18 @@ static propd_status prune_impl(
       }
       // one workgroup per compute unit and round, two rounds resident in the queue; fewer when
       // even the largest row count has fewer tiles
-      const long long m_tiles_cap = ws.row_cap <= kSmallBM ? 1 : (ws.row_cap + 159) / 160;  // no tile is smaller than 160 x 256
+      const long long m_tiles_cap = (ws.row_cap + 159) / 160;  // no tile is smaller than 160 x 256
       const long long n_groups = ((vocab + 127) / 128 + kXcds - 1) / kXcds;          // or narrower than 128
       long long grid = kXcds * n_groups * m_tiles_cap;
       const long long persistent = (2ll * cus + kXcds - 1) / kXcds * kXcds;
       grid = grid < persistent ? grid : persistent;
       if (crit.kind == 0)
         hipLaunchKernelGGL(early_head_bf16_kernel<0>, dim3((unsigned)grid), dim3(kGemmThreads), kHeadLdsBytes, st,
-                           hidden, vocab, B, cus, force, reinterpret_cast<const uint16_t *>(hidden_states),
+                           hidden, vocab, B, cus, force, max_mi, reinterpret_cast<const uint16_t *>(hidden_states),
                            reinterpret_cast<const uint16_t *>(head_weight), tb);
       else
         hipLaunchKernelGGL(early_head_bf16_kernel<1>, dim3((unsigned)grid), dim3(kGemmThreads), kHeadLdsBytes, st,
-                           hidden, vocab, B, cus, force, reinterpret_cast<const uint16_t *>(hidden_states),
+                           hidden, vocab, B, cus, force, max_mi, reinterpret_cast<const uint16_t *>(hidden_states),
                            reinterpret_cast<const uint16_t *>(head_weight), tb);
     } else {
       // two workgroups per compute unit (their LDS), fewer when even the largest row count has
@@ -1393,7 +1393,7 @@ static propd_status prune_impl(
                            reinterpret_cast<const float *>(head_weight), tb);
     }
     if (crit.kind != 0)
-      hipLaunchKernelGGL(row_lse_kernel, dim3((unsigned)ws.row_cap), dim3(kWave), 0, st, B, vocab, cus, force,
+      hipLaunchKernelGGL(row_lse_kernel, dim3((unsigned)ws.row_cap), dim3(kWave), 0, st, B, hidden, vocab, cus, force, max_mi,
                          dt == PROPD_BF16 ? 1 : 0, tb, ws.logq);
   }
   if (!launch_ok()) return PROPD_ERR_DEVICE;

@@ -275,10 +275,30 @@ def test_prune_bf16_every_tile_shape(pb, oracle, B, T, V):
     check_prob(pb, oracle, x, res, ref, logm, [x["hidden_states"]], sents)
 
 
+@pytest.mark.parametrize("Hd", [32, 64, 160, 192])
+@pytest.mark.parametrize("B,T", [(3, 87), (6, 118)])
+def test_prune_bf16_tall_tiles_short_rows(pb, oracle, Hd, B, T):
+    """One half step, one step, a half step behind two, three steps, on a tile that addresses rows by
+    pointers (258 score rows) and on one that does by offsets (702); the last column tile not full."""
+    w = synth.Workload(78, "case", "bf16", B, 1, 128, T, Hd, 31990, 6, 1e-3)
+    x = synth.make_prune_inputs(w, trees=[synth.chain_tree(T)] * B, p_pass=0.8)
+    res, sents = run_prune(pb, x, [x["hidden_states"]])
+    check_prune(oracle, x, res, [x["hidden_states"]], sents)
+
+
+@pytest.mark.parametrize("B,T,Hd", [(2, 65, 3072), (2, 66, 3072), (2, 81, 3072), (2, 82, 3072), (2, 66, 3040)])
+def test_prune_bf16_few_rows_rule(pb, oracle, B, T, Hd):
+    """128, 130 and 160 score rows of 3072 take the tile of few rows, 162 rows, or rows of 3040, another."""
+    w = synth.Workload(79, "case", "bf16", B, 1, 128, T, Hd, 1000, 6, 1e-3)
+    x = synth.make_prune_inputs(w, trees=[synth.chain_tree(T)] * B, p_pass=0.8)
+    res, sents = run_prune(pb, x, [x["hidden_states"]])
+    check_prune(oracle, x, res, [x["hidden_states"]], sents)
+
+
 @pytest.mark.parametrize("B,T,V", [(2, 66, 8192), (2, 66, 16001), (2, 128, 8192), (2, 128, 33001), (2, 89, 40000), (2, 65, 70000)])
 def test_prune_bf16_few_rows_or_tiles(pb, oracle, B, T, V):
-    """129 to 256 score rows take the tile of few rows in one round of workgroups and a shape for many
-    rows beyond that, or where the vocabulary is small: 130, 254, 176 and 128 rows, both criteria."""
+    """More score rows than the tile of few rows takes, in little and in much vocabulary: 130, 254, 176
+    and 128 rows, both criteria."""
     w = synth.Workload(77, "case", "bf16", B, 1, 128, T, 64, V, 6, 1e-3)
     x = synth.make_prune_inputs(w, trees=[synth.chain_tree(T)] * B, p_pass=0.8)
     res, sents = run_prune(pb, x, [x["hidden_states"]])
@@ -314,6 +334,45 @@ def test_prune_with_the_tile_shape_given(pb, oracle, value):
     done = subprocess.run([sys.executable, "-c", child], env=dict(os.environ, PROPD_HEAD_PLAN=value), timeout=100,
                           capture_output=True, text=True)
     assert done.returncode == 0 and "same as the oracle" in done.stdout, done.stderr[-2000:]
+
+
+FAR_ROWS_CHILD = """
+import sys
+sys.path[:0] = {path!r}
+import numpy as np
+import torch
+from paper_2402_13485_amd import binding as pb
+from paper_2402_13485_amd import synth
+B, T, Hd, V = 128, 128, 1 << 17, 300
+gen = torch.Generator(device="cuda")
+gen.manual_seed(5)
+small = lambda *shape: torch.randint(-1, 2, shape, device="cuda", generator=gen, dtype=torch.int8).to(torch.bfloat16)
+n, parent, _ = synth.pad_trees([synth.chain_tree(T if b in (0, 64, 125, 127) else 1) for b in range(B)], T)
+token = np.random.default_rng(5).integers(0, V, (B, T)).astype(np.int32)
+token[np.arange(T)[None] >= n[:, None]] = -1
+hid = torch.zeros(B, T, Hd, device="cuda", dtype=torch.bfloat16)
+head = small(V, Hd)
+nn, par, tok = (torch.from_numpy(x.astype(np.int32)).cuda() for x in (n, parent, token))
+depth, anc = pb.propd_tree_mask(nn, par)
+for b in (0, 64, 125, 127):
+    hid[b] = small(T, Hd)
+rank = pb.propd_early_prune(pb.Tree(nn, par, tok, depth, anc), hid, head, 5, want_rank=True).rank.cpu().numpy()
+for b in (0, 64, 125, 127):
+    z = (hid[b].float().cpu() @ head.float().cpu().T).numpy()  # whole numbers: exact in any order
+    for i in range(1, T):
+        row, t = z[i - 1], token[b, i]
+        assert rank[b, i] == (row > row[t]).sum() + (row[:t] == row[t]).sum(), (b, i)
+print("ranks as counted")
+"""
+
+
+def test_prune_rows_further_apart_than_32_bits(pb):
+    """Hidden states of 4 GiB: the tallest tiles, which address rows by 32-bit offsets, are asked for
+    and give way to the tallest that does not; 508 score rows, the last ones beyond 4 GB."""
+    child = FAR_ROWS_CHILD.format(path=[os.path.dirname(os.path.dirname(os.path.abspath(__file__)))])
+    done = subprocess.run([sys.executable, "-c", child], env=dict(os.environ, PROPD_HEAD_PLAN="2"), timeout=100,
+                          capture_output=True, text=True)
+    assert done.returncode == 0 and "ranks as counted" in done.stdout, done.stderr[-2000:]
 
 
 def test_prune_outputs_are_aligned(pb):
