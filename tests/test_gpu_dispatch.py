@@ -336,6 +336,25 @@ def test_prune_with_the_tile_shape_given(pb, oracle, value):
     assert done.returncode == 0 and "same as the oracle" in done.stdout, done.stderr[-2000:]
 
 
+@pytest.mark.parametrize("C", [8, 24, 264, 2048, 2056, 5])
+@pytest.mark.parametrize("T,outer", [(1, 1), (33, 3), (128, 2)])
+def test_prune_payload_row_sizes(pb, C, T, outer):
+    """Payload rows of 1, 3, 33, 256 and 257 pieces of 16 bytes, and of 10 bytes: survivors in their
+    order, everything behind them as it was."""
+    B = 3
+    w = synth.Workload(93, "case", "f32", B, 1, 64, T, 32, 2000, 4, 1e-5)
+    x = synth.make_prune_inputs(w, trees=[synth.chain_tree(T), synth.star_tree(T), synth.chain_tree(max(1, T // 2))])
+    tree = dev_tree(pb, x["n_nodes"], x["parent"], x["token"])
+    src = torch.randint(0, 30000, (B, outer, T, C), device="cuda").to(torch.int16)
+    res = pb.propd_early_prune(tree, to_dev(x["hidden_states"]), to_dev(x["head_weight"]), 40, payloads=[src],
+                               payload_out=[torch.full_like(src, -5)])
+    origin, got, want = to_host(res.orig_index), to_host(res.payloads[0]), np.full(src.shape, -5, np.int16)
+    for b, o in enumerate(origin):
+        o = o[o >= 0]
+        want[b, :, :len(o)] = to_host(src)[b][:, o]
+    assert (got == want).all()
+
+
 FAR_ROWS_CHILD = """
 import sys
 sys.path[:0] = {path!r}
