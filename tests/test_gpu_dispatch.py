@@ -228,6 +228,21 @@ def test_attention_bf16_merge_of_cut_units(pb, oracle, B, H, T_max, L, d):
     check_attention(oracle, x, out, sent)
 
 
+@pytest.mark.parametrize("B", [1, 63, 64, 65, 130])
+@pytest.mark.parametrize("H,ragged", [(1, True), (9, True), (9, False), (17, False)])
+def test_attention_bf16_sequences_of_a_wave(pb, oracle, B, H, ragged):
+    """Up to 64 sequences are scheduled from one lane each, more by a loop: ragged lengths with empty
+    ones among them, and equal ones, of which the workgroups take one or more units whole."""
+    rng = np.random.default_rng(B * 100 + H)
+    lens = rng.integers(0, 150, B).astype(np.int32) if ragged else np.full(B, 70, np.int32)
+    lens[::7] = 0 if ragged else 70
+    trees = [synth.random_tree(rng, int(rng.integers(1, 41)) if ragged else 40) for _ in range(B)]
+    w = synth.Workload(86, "case", "bf16", B, H, 64, 40, 0, 0, 0, 1e-3)
+    x = synth.make_attention_inputs(w, seq_lens=lens, trees=trees)
+    out, sent = run_attention(pb, x)
+    check_attention(oracle, x, out, sent)
+
+
 @pytest.mark.parametrize("H", [127, 128, 129, 160])
 @pytest.mark.parametrize("d,T_max,L", [(64, 40, 500), (128, 33, 480)])
 def test_attention_bf16_merge_at_four_pieces(pb, oracle, H, d, T_max, L):
