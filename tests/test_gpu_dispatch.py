@@ -17,6 +17,36 @@ from test_gpu_parity import (check_attention, check_prob, check_prune, dev_tree,
 pytestmark = pytest.mark.gpu
 
 
+# ------------------------------------------------------------------ commit of the accepted path
+
+
+@pytest.mark.parametrize("H,stride", [(64, 8), (65, 8), (4, 128), (5, 128), (1, 1), (31, 16)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_commit_one_launch_or_two(pb, oracle, dtype, H, stride):
+    """Path buffers of up to 8192 pieces of 16 bytes per sequence are committed in one launch, larger
+    ones in two: both sides of the line, paths of every length, caches with and without room."""
+    rng = np.random.default_rng(H * 1000 + stride)
+    B, T, d, L_max = 5, 128, 128 if dtype == "bf16" else 64, 40
+    n_nodes = np.array([T, T, 1, 7, T], np.int32)
+    token = rng.integers(0, 1000, (B, T)).astype(np.int32)
+    alen = np.array([stride, max(1, stride // 2), 1, min(stride, 7), 1], np.int32)
+    path = np.full((B, stride), -1, np.int32)
+    for b in range(B):
+        path[b, :alen[b]] = np.sort(rng.choice(n_nodes[b], alen[b], replace=False))
+    nxt = rng.integers(0, 1000, B).astype(np.int32)
+    seq = np.array([0, L_max - 3, L_max, 20, L_max - 1], np.int32)
+    draw = lambda *s: (rng.integers(0, 1 << 15, s).astype(np.uint16) if dtype == "bf16"
+                       else rng.standard_normal(s).astype(np.float32))
+    kt, vt, kc, vc = draw(B, H, T, d), draw(B, H, T, d), draw(B, H, L_max, d), draw(B, H, L_max, d)
+    kc_r, vc_r, seq_r, out_r = oracle.commit_path(n_nodes, token, alen, path, nxt, kt, vt, kc, vc, seq, out_stride=stride + 1)
+    tree = dev_tree(pb, n_nodes, np.maximum(np.arange(T, dtype=np.int32)[None].repeat(B, 0) - 1, -1), token)
+    kc_d, vc_d, seq_d = to_dev(kc), to_dev(vc), to_dev(seq)
+    out = pb.propd_commit_path(tree, to_dev(alen), to_dev(path), to_dev(nxt), to_dev(kt), to_dev(vt), kc_d, vc_d, seq_d,
+                               out_stride=stride + 1)
+    assert (to_host(kc_d) == kc_r).all() and (to_host(vc_d) == vc_r).all()
+    assert (to_host(seq_d) == seq_r).all() and (to_host(out) == out_r).all()
+
+
 # ------------------------------------------------------------------ fp32 scoring
 
 
