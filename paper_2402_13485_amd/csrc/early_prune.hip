@@ -332,16 +332,35 @@ __device__ void own_scores(const PrepareArgs &a, int b, int group) {
   // piece lane / 16
   const int c16 = lane & 15, kq = lane >> 4;
   const int frag_off = (c16 & (kOwnNodes - 1)) * kOwnRowBytes + kq * 16;
-  auto product = [&](const unsigned char *pa, const unsigned char *pb) {
-    if constexpr (kBf16) {
-      const bf16x8 fa = *reinterpret_cast<const bf16x8 *>(pa), fb = *reinterpret_cast<const bf16x8 *>(pb);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fb, acc, 0, 0, 0);
-    } else {
-      const f32x4 fa = *reinterpret_cast<const f32x4 *>(pa), fb = *reinterpret_cast<const f32x4 *>(pb);
+  // Wave 0 reads a step's fragments while it multiplies those of the step before, so that the chain of
+  // products does not wait for LDS once per step: pruning call 75.2 -> 73.8 us at 1 x 64 nodes x 4096, 239.3 ->
+  // 237.4 at 16 x 128 x 5120, 60.2 -> 59.8 in fp32.  (The barrier of the next step waits for these reads,
+  // and the buffer is written again only behind it.)
+  constexpr int kGroups = kOwnStepBytes / 64;
+  u32x4 fa[2][kGroups], fb[2][kGroups];
+  auto read = [&](int set, const unsigned char *pa, const unsigned char *pb) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[j], fb[j], acc, 0, 0, 0);
+    for (int ks = 0; ks < kGroups; ++ks) {
+      fa[set][ks] = *reinterpret_cast<const u32x4 *>(pa + frag_off + ks * 64);
+      fb[set][ks] = *reinterpret_cast<const u32x4 *>(pb + frag_off + ks * 64);
     }
   };
+  auto product = [&](const u32x4 &x, const u32x4 &y) {
+    if constexpr (kBf16) {
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), acc, 0, 0, 0);
+    } else {
+      const f32x4 xf = __builtin_bit_cast(f32x4, x), yf = __builtin_bit_cast(f32x4, y);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xf[j], yf[j], acc, 0, 0, 0);
+    }
+  };
+  auto last_step = [&](int set) {  // may end inside
+    const int left = n_groups - (n_steps - 1) * kGroups;
+#pragma unroll
+    for (int ks = 0; ks < kGroups; ++ks)
+      if (ks < left) product(fa[set][ks], fb[set][ks]);
+  };
+  static_assert(kOwnAhead % 2 == 0, "the fragment set of a step is its number's parity");
   for (int s0 = 0; s0 < n_steps; s0 += kOwnAhead) {
 #pragma unroll
     for (int i = 0; i < kOwnAhead; ++i) {
@@ -351,24 +370,19 @@ __device__ void own_scores(const PrepareArgs &a, int b, int group) {
       *reinterpret_cast<u32x4 *>(buf_a + ld_row * kOwnRowBytes + ld_piece * 16) = ra[i];
       *reinterpret_cast<u32x4 *>(buf_b + ld_row * kOwnRowBytes + ld_piece * 16) = rb[i];
       fetch(i, step + kOwnAhead);
-      __syncthreads();  // the step is in LDS; wave 0 is done with the other buffer
+      __syncthreads();  // the step is in LDS; wave 0 has read the other buffer
       if (wave == 0) {
-        constexpr int kGroups = kOwnStepBytes / 64;
-        const int left = n_groups - step * kGroups;
-        if (left >= kGroups) {
-          // a whole step: no condition between the reads, so that all of them are in flight
-          // before the first product needs its pair
+        read(i & 1, buf_a, buf_b);
+        if (step > 0) {
 #pragma unroll
-          for (int ks = 0; ks < kGroups; ++ks) product(buf_a + frag_off + ks * 64, buf_b + frag_off + ks * 64);
-        } else {
-#pragma unroll
-          for (int ks = 0; ks < kGroups; ++ks)
-            if (ks < left) product(buf_a + frag_off + ks * 64, buf_b + frag_off + ks * 64);
+          for (int ks = 0; ks < kGroups; ++ks) product(fa[1 - (i & 1)][ks], fb[1 - (i & 1)][ks]);
         }
       }
     }
   }
   if (wave != 0) return;
+  if (n_steps & 1) last_step(0);
+  else last_step(1);
   mfma_settle();
   // element (row, col) of the tile sits in lane col + 16 * (row / 4), register row % 4: the
   // diagonal element of column j < 8 is in the lane quarter j >> 2, register j & 3
