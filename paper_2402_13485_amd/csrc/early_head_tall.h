@@ -361,14 +361,16 @@ __device__ __forceinline__ void early_head_tall_tile(
   const int ld_chunk = ((lane & 7) ^ ((4 * wave + (lane >> 4)) & 7)) << 4;
   const bool all_a = wave + 8 * (G::kALoads - 1) < G::kAGroups;  // kALoads groups of A, else one fewer
   // Where registers are short the rows are addressed by 32-bit offsets from the operand's first byte of
-  // this tile (head_plan takes such shapes only where they suffice), and those of B, at constant
-  // distances up to the last row of the vocabulary, from the first.
+  // this tile (head_plan takes such shapes only where all score rows, and the 256 weight rows of a tile,
+  // lie within 4 GiB), and those of B, at constant distances up to the tile's last row in the vocabulary,
+  // from the first.
   using Src = std::conditional_t<G::kNarrow, uint32_t, const unsigned char *>;
   constexpr int kBOwn = G::kNarrow ? 1 : G::kBLoads;
   Src a_src[G::kALoads], b_src[kBOwn];
   const unsigned char *a_base = reinterpret_cast<const unsigned char *>(hidden_states);
   const unsigned char *b_base = reinterpret_cast<const unsigned char *>(head_weight + (size_t)v0 * hidden);
-  const uint32_t b_last = (uint32_t)(vocab - 1 - v0) * (uint32_t)(2 * hidden);
+  // (within the tile: the distance to the last row of the vocabulary itself may pass 32 bits)
+  const uint32_t b_last = (uint32_t)min(vocab - 1 - v0, G::kBN - 1) * (uint32_t)(2 * hidden);
 #pragma unroll
   for (int j = 0; j < G::kALoads; ++j) {
     const int m = m0 + ld_row + 64 * j, row = tb.row_src[m < m_total ? m : m_total - 1];

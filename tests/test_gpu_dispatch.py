@@ -439,6 +439,37 @@ def test_prune_rows_further_apart_than_32_bits(pb):
     assert done.returncode == 0 and "ranks as counted" in done.stdout, done.stderr[-2000:]
 
 
+@pytest.mark.parametrize("B,T,Hd,V", [(3, 87, 8192, 262208), (4, 89, 16384, 151936), (1, 128, 8192, 262208)])
+def test_prune_head_weight_beyond_32_bits(pb, B, T, Hd, V):
+    """Head weights of 4 to 5 GiB: 258, 352 and 127 score rows take tiles of 288 and 352 rows, which address
+    rows by 32-bit offsets, and the tile of few rows.  In the tile whose distance to the end of the
+    weights lies just above 4 GiB (entries 0 to 255 of 262208, 20736 to 20991 of 151936) as in any other
+    every entry counts with its own score; the entries there are the only ones above zero."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(V)
+    hid = torch.randint(0, 3, (B, T, Hd), device="cuda", generator=gen, dtype=torch.int8).to(torch.bfloat16)
+    head = torch.empty(V, Hd, device="cuda", dtype=torch.bfloat16)
+    for v in range(0, V, 16384):  # -1 and 0: scores of at most 0, whole numbers that fp32 sums hold exactly
+        head[v:v + 16384] = torch.randint(-1, 1, (min(V - v, 16384), Hd), device="cuda", generator=gen, dtype=torch.int8)
+    first = V - 1 - ((1 << 32) // (2 * Hd))  # a distance of 4 GiB ends here
+    for v in range(max(0, first - 256), first + 1):
+        head[v] = -head[v]
+    n, parent, _ = synth.pad_trees([synth.chain_tree(T)] * B, T)
+    token = np.random.default_rng(V).integers(0, V, (B, T)).astype(np.int32)
+    token[:, 1::2] = np.random.default_rng(T).integers(max(0, first - 256), first + 1, token[:, 1::2].shape)
+    tree = dev_tree(pb, n, parent, token)
+    rank = to_host(pb.propd_early_prune(tree, hid, head, 5, want_rank=True).rank)
+    rows = hid[:, :-1].reshape(-1, Hd).double().cpu()  # node i - 1 is the parent of node i
+    child = torch.from_numpy(token[:, 1:].reshape(-1).astype(np.int64))
+    own = (rows * head[child.cuda()].double().cpu()).sum(1, keepdim=True).cuda()
+    ahead = torch.zeros(len(child), dtype=torch.int64, device="cuda")
+    for v in range(0, V, 16384):
+        z = rows.float().cuda() @ head[v:v + 16384].float().T
+        before = torch.arange(v, v + z.shape[1], device="cuda")[None] < child.cuda()[:, None]
+        ahead += ((z.double() > own) | ((z.double() == own) & before)).sum(1)
+    assert (rank[:, 1:].reshape(-1) == to_host(ahead)).all()
+
+
 def test_prune_outputs_are_aligned(pb):
     """Every output is a tensor that any call takes: bases on 16 bytes, also for one sequence and
     for an odd number of nodes."""
