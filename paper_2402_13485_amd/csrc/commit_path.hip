@@ -31,8 +31,7 @@ __device__ __forceinline__ void commit_tokens(int b, int tid, int threads, int T
 }
 
 // Short paths: one workgroup does all heads of a sequence, and then its length and tokens, so that the
-// call is one launch instead of two (kCommitOneMax below): a step of 1 sequence, 1
-// head, d = 64, fp32, which the host bounds, 103.9 -> 101.0 us; 4 x 32 heads 157.8 -> 157.6, 16 x 40 heads 290.0 -> 289.2.
+// call is one launch instead of two (see commit_one_threads).
 constexpr int kCommitOneThreads = 1024, kCommitOneItems = 4;  // pieces of K and of V of a thread requested together
 
 __global__ __launch_bounds__(kCommitOneThreads) void commit_one_kernel(
@@ -47,14 +46,14 @@ __global__ __launch_bounds__(kCommitOneThreads) void commit_one_kernel(
   L = L < 0 ? 0 : (L > L_max ? L_max : L);
   a = a < 0 ? 0 : (a > path_stride ? path_stride : a);
   const int rows = a > L_max - L ? L_max - L : a, pieces = row_bytes / 16;
-  const int items = rows * H * pieces;
-  for (int item0 = threadIdx.x; item0 < items; item0 += kCommitOneItems * kCommitOneThreads) {
+  const int items = rows * H * pieces, threads = blockDim.x;
+  for (int item0 = threadIdx.x; item0 < items; item0 += kCommitOneItems * threads) {
     u32x4 kv[kCommitOneItems][2];
     size_t dst[kCommitOneItems];
     bool on[kCommitOneItems];
 #pragma unroll
     for (int x = 0; x < kCommitOneItems; ++x) {
-      const int wanted = item0 + x * kCommitOneThreads, item = wanted < items ? wanted : item0;
+      const int wanted = item0 + x * threads, item = wanted < items ? wanted : item0;
       const int row = item / pieces, c = item - row * pieces, h = row / rows, j = row - h * rows;
       int node = accept_path[(size_t)b * path_stride + j];
       on[x] = wanted < items && node >= 0 && node < T;
@@ -72,7 +71,7 @@ __global__ __launch_bounds__(kCommitOneThreads) void commit_one_kernel(
       }
   }
   __syncthreads();  // every thread has read the old length
-  commit_tokens(b, threadIdx.x, kCommitOneThreads, T, L, a, L_max, T_max, token, accept_path, path_stride, next_token,
+  commit_tokens(b, threadIdx.x, threads, T, L, a, L_max, T_max, token, accept_path, path_stride, next_token,
                 seq_lens, out_tokens, out_stride);
 }
 
@@ -126,9 +125,32 @@ __global__ __launch_bounds__(kCommitThreads) void commit_tokens_kernel(
                 out_stride);
 }
 
-// Pieces of K that a full path buffer may stand for in the one-launch form: two rounds of a workgroup's
-// threads.
-constexpr long long kCommitOneMax = 2ll * kCommitOneThreads * kCommitOneItems;
+// Threads per sequence of the one-launch form, 0 where the call takes two launches.
+//   - The line.  One workgroup moves 4096 pieces of K and of V in a round of its threads, a launch less
+//     outweighs that.  What is left of a full buffer beyond a round costs more than the launch, unless
+//     the other form is slow too: its second kernel writes a sequence's tokens one by one (from 32 of
+//     them on), or its workgroups of a (sequence, head) each fill the chip more than twice.  Call, us, two launches / one,
+//     with 3 nodes accepted and with a full buffer:
+//       1 x 32 heads, 8 nodes of 256 bytes (4096 pieces)   7.1 / 6.5   7.6 / 7.3
+//       1 x 40, 8 (5120, within the third of a round)      7.2 / 6.6   7.5 / 9.1 (5 accepted: 7.4 / 6.9)
+//       1 x 64, 8 (8192)                                   7.2 / 6.9   7.7 / 10.0
+//       64 x 64, 8                                         9.8 / 8.7  12.3 / 13.0
+//       256 x 64, 8                                       17.6 / 12.1 28.0 / 23.1
+//       1 x 16, 32 (8192)                                  9.6 / 6.1  11.8 / 10.0
+//       1 x 4, 128 (8192)                                 17.5 / 5.1  31.5 / 9.9
+//     The host saves a launch besides.
+//   - The threads: one per piece, as long as those of all sequences fit the chip at once (2^19).  Beyond
+//     that each takes several: 4096 x 1 head, 1 node of 128 bytes 8.7 / 7.5 (26.2 with 1024 threads), 4096 x 8, 8
+//     of 256 bytes 59 / 49 (89), 1024 x 8, 8 19.0 / 16.0 (20.7).  It also keeps the threads of a
+//     launch, which may be fewer than 2^32, from bounding the batch: 64 of them from 8192 sequences on.
+static int commit_one_threads(int B, int H, int pieces, int path_stride) {
+  const long long full = (long long)path_stride * H * pieces, round = (long long)kCommitOneThreads * kCommitOneItems;
+  const bool others_slow = path_stride >= 32 || (long long)B * H > 4096;
+  if (full > (others_slow ? 2 * round : round + round / 3)) return 0;
+  int threads = kWave;
+  while (threads < full && threads < kCommitOneThreads && 2ll * B * threads <= (1 << 19)) threads *= 2;
+  return threads;
+}
 
 }  // namespace propd
 
@@ -153,8 +175,9 @@ extern "C" propd_status propd_commit_path(const propd_tree *tree, propd_dtype dt
   const long long units = (long long)tree->B * H;
   if (units > (1ll << 30)) return PROPD_ERR_UNSUPPORTED;
   hipStream_t st = as_stream(hip_stream);
-  if ((long long)path_stride * H <= kCommitOneMax / (row_bytes / 16)) {
-    hipLaunchKernelGGL(commit_one_kernel, dim3((unsigned)tree->B), dim3(kCommitOneThreads), 0, st, H, tree->T_max,
+  const int one = commit_one_threads(tree->B, H, (int)(row_bytes / 16), path_stride);
+  if (one > 0) {
+    hipLaunchKernelGGL(commit_one_kernel, dim3((unsigned)tree->B), dim3((unsigned)one), 0, st, H, tree->T_max,
                        L_max, (int)row_bytes, tree->n_nodes, tree->token, accept_len, accept_path, path_stride,
                        next_token, seq_lens, reinterpret_cast<const unsigned char *>(k_tree),
                        reinterpret_cast<const unsigned char *>(v_tree), reinterpret_cast<unsigned char *>(k_cache),

@@ -20,11 +20,13 @@ pytestmark = pytest.mark.gpu
 # ------------------------------------------------------------------ commit of the accepted path
 
 
-@pytest.mark.parametrize("H,stride", [(64, 8), (65, 8), (4, 128), (5, 128), (1, 1), (31, 16)])
+@pytest.mark.parametrize("H,stride", [(64, 8), (65, 8), (4, 128), (5, 128), (1, 1), (31, 16), (21, 16), (22, 16),
+                                      (11, 31), (16, 32), (17, 32), (33, 8)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_commit_one_launch_or_two(pb, oracle, dtype, H, stride):
-    """Path buffers of up to 8192 pieces of 16 bytes per sequence are committed in one launch, larger
-    ones in two: both sides of the line, paths of every length, caches with and without room."""
+    """Path buffers of up to 5461 pieces of 16 bytes per sequence, of 8192 from 32 nodes on, are committed
+    in one launch, larger ones in two: both sides of the lines, paths of every length, caches with and
+    without room."""
     rng = np.random.default_rng(H * 1000 + stride)
     B, T, d, L_max = 5, 128, 128 if dtype == "bf16" else 64, 40
     n_nodes = np.array([T, T, 1, 7, T], np.int32)
@@ -45,6 +47,35 @@ def test_commit_one_launch_or_two(pb, oracle, dtype, H, stride):
                                out_stride=stride + 1)
     assert (to_host(kc_d) == kc_r).all() and (to_host(vc_d) == vc_r).all()
     assert (to_host(seq_d) == seq_r).all() and (to_host(out) == out_r).all()
+
+
+@pytest.mark.parametrize("B,H,stride,d", [(1 << 22, 1, 1, 8), ((1 << 22) + 3, 1, 1, 8), (9000, 1, 128, 64), (700, 3, 8, 128),
+                                          (600, 7, 40, 32), (257, 16, 32, 64), (65, 63, 12, 64)])
+def test_commit_many_sequences(pb, B, H, stride, d):
+    """More sequences than a launch has room for with 1024 threads each, and batches whose threads
+    take several pieces, in one round and in several."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(B)
+    T, L_max = min(5, max(1, stride - 2)), 2 if B > 10000 else 130
+    draw = lambda low, high, *s: torch.randint(low, high, s, device="cuda", generator=gen, dtype=torch.int32)
+    rows = lambda n: draw(-30000, 30000, B, H, n, d).to(torch.int16).view(torch.bfloat16)
+    n_nodes = torch.full((B,), T, dtype=torch.int32, device="cuda")
+    token, nxt, path = draw(0, 1000, B, T), draw(0, 1000, B), draw(0, T, B, stride)
+    alen, seq = draw(1, stride + 1, B), draw(0, L_max + 1, B)
+    kt, vt, kc, vc = rows(T), rows(T), rows(L_max), rows(L_max)
+    old = seq.clone()
+    want = []
+    j = torch.arange(stride, device="cuda")
+    b, at = ((j[None] < alen[:, None]) & (old[:, None] + j[None] < L_max)).nonzero(as_tuple=True)
+    for tree_rows, cache in ((kt, kc), (vt, vc)):
+        want.append(cache.clone().view(torch.int16))
+        want[-1][b, :, old[b].long() + at] = tree_rows.view(torch.int16)[b, :, path[b, at].long()]
+    out = pb.propd_commit_path(pb.Tree(n_nodes, draw(0, 1, B, T), token), alen, path, nxt, kt, vt, kc, vc, seq)
+    assert torch.equal(kc.view(torch.int16), want[0]) and torch.equal(vc.view(torch.int16), want[1])
+    assert torch.equal(seq, torch.minimum(old + alen, torch.full_like(old, L_max)))
+    nodes = token.gather(1, torch.cat([path[:, 1:], path[:, :1]], 1).long())
+    last = j[None] == alen[:, None] - 1
+    assert torch.equal(out, torch.where(j[None] < alen[:, None] - 1, nodes, torch.where(last, nxt[:, None], -1)))
 
 
 # ------------------------------------------------------------------ fp32 scoring
