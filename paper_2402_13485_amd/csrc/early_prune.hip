@@ -424,7 +424,7 @@ struct HeadTables {
 // C[m][v] = sum_x A[m][x] * W[v][x].  Both operands are contiguous along x, which is the layout the
 // matrix instructions want (8 consecutive x per lane), so tiles go global -> LDS -> operands
 // without any transpose.  Two kinds of tiles, chosen on the device from the row count (head_plan):
-//   - few (at most 128, or 160 in one round): early_head_small_tile, a stream of the weights;
+//   - few (at most 128, or 192 in one round): early_head_small_tile, a stream of the weights;
 //   - more: the tiles of early_head_tall.h, 32*MI rows x 256 vocabulary entries in several
 //     shapes.  They are bound by operand delivery and the matrix cores together.
 // Common to all:
@@ -597,7 +597,7 @@ __device__ __forceinline__ void rows_epilogue(RowChildren<R> &ch, const float *s
 }
 
 // ------------------------------------------------------------------------------------
-// Few score rows (at most 160 in the whole batch, see head_plan: a small batch or small trees).  The
+// Few score rows (at most 192 in the whole batch, see head_plan: a small batch or small trees).  The
 // scoring kernel is then a stream of the weight matrix through the compute units, and a step
 // (a barrier, fragment reads whose latency a handful of matrix instructions cannot hide)
 // costs more than its bytes.  This tile takes 64-deep steps: half as many steps for the same
@@ -607,7 +607,8 @@ __device__ __forceinline__ void rows_epilogue(RowChildren<R> &ch, const float *s
 // rows are 128 bytes, their eight 16-byte chunks XOR-swizzled with key(row) = (row >> 1) & 7 (a
 // fragment read takes rows r .. r + 15 of one chunk column in one pass: two rows share a 256-byte
 // bank line, eight keys spread the eight pairs).
-// RA = 32, 128 or 256 rows have room.  RA = 32: a wave then has one 32-row block to multiply instead of two (pruning
+// RA = 32, 128 or 192 rows have room.  (With 192, four stages instead of three are 1 to 2 us slower. Pruning call with
+// room for 256 rows / 192, us: 130 rows x 4096 x 8192 83.0 / 78.7, 160 x 4096 x 8192 84.1 / 86.0.)  RA = 32: a wave then has one 32-row block to multiply instead of two (pruning
 // call at 22 rows x 4096 x 32000: 80 us, 83 with RA = 128; a shape for 64 rows gained nothing at 44).
 // The K loop runs at 5.8 TB/s of weights, read once and non-temporally (without that 6 us more); a
 // ring of seven stages instead of four changes nothing, and neither does requesting 256 or 512
@@ -626,7 +627,7 @@ __device__ __forceinline__ void gemm_wait_frag(GemmFrag &f) {
 }
 
 constexpr int kSmallBK = 64;
-constexpr int kSmallMaxRows = 160;  // rows that this tile is used for at most, see head_plan
+constexpr int kSmallMaxRows = 192;  // rows that this tile is used for at most, see head_plan
 constexpr int kSmallRowBytes = kSmallBK * 2;                          // 128
 constexpr int kSmallWBytes = 128 * kSmallRowBytes;                    // 16 KB of weight rows per stage
 
@@ -636,7 +637,7 @@ __device__ __forceinline__ void early_head_small_tile(
     const uint16_t *__restrict__ hidden_states, const uint16_t *__restrict__ head_weight,
     const HeadTables &tb, unsigned char *gemm_smem) {
   constexpr int FN = 2;
-  constexpr int kStages = RA == 256 ? 3 : 4, kWOffset = RA * kSmallRowBytes, kStageBytes = kWOffset + kSmallWBytes;
+  constexpr int kStages = RA == 192 ? 3 : 4, kWOffset = RA * kSmallRowBytes, kStageBytes = kWOffset + kSmallWBytes;
   static_assert(kStages * kStageBytes <= kHeadLdsBytes, "ring");
   constexpr int kALoads = RA > 64 ? RA / 64 : 1;  // 8-row groups of score rows a wave may have to fetch
   constexpr int kX = RA == 32 ? 1 : 2;         // 32-row blocks of a wave's 64 rows that exist
@@ -810,15 +811,16 @@ __device__ __forceinline__ void early_head_small_tile(
   }
   __syncthreads();
   if constexpr (RA > kRows) {
-    // the second half's children are on their way while the first half is counted
-    RowChildren<kRows / kGemmWaves> ch2;
+    // the children of the other rows are on their way while the first rows' are counted
+    constexpr int kMore = (RA - kRows) / kGemmWaves;
+    RowChildren<kMore> ch2;
     if (KIND == 0) {
       ch2.rows(wave, kRows, m_total, tb);
       ch2.list(lane, tb);
     }
     rows_epilogue<KIND, kRows / kGemmWaves>(ch, s_z, wave, lane, 0, m_total, v0, vocab, n_tile, tb);
     if (KIND == 0) ch2.values(lane, tb);
-    rows_epilogue<KIND, kRows / kGemmWaves>(ch2, s_z + kRows * kRowsCols, wave, lane, kRows, m_total, v0, vocab, n_tile, tb);
+    rows_epilogue<KIND, kMore>(ch2, s_z + kRows * kRowsCols, wave, lane, kRows, m_total, v0, vocab, n_tile, tb);
   } else {
     rows_epilogue<KIND, kRows / kGemmWaves>(ch, s_z, wave, lane, 0, m_total, v0, vocab, n_tile, tb);
   }
@@ -832,10 +834,12 @@ __device__ __forceinline__ void early_head_small_tile(
 // that read the per-tile results) from the row count, which the host never sees.
 //   - At most 128 rows: the tile of few rows, one row tile, 128 entries wide (32000 entries: 250
 //     workgroups).
-//   - 129 to 160 rows: the same where one round of it covers the vocabulary and rows are long.  Pruning
-//     call, us, few rows / best other: 132 rows x 4096 x 32000 111 / 117, 132 x 4096 x 16001 104 / 107, 176 x
-//     4096 x 32000 115 / 115, 220 x 4096 x 32000 125 / 116, 176 x 4096 x 8192 109 / 105, 132 x 1024 x 32000 61 / 55, 220 x
-//     2048 x 32000 91 / 79; in two rounds 176 x 4096 x 64000 205 / 176, 132 x 3584 x 152064 391 / 294.
+//   - 129 to 192 rows: the same where one round of it covers the vocabulary and rows have 64 elements
+//     for each score row beyond 112.  Pruning call, us, few rows / best other, at 8192 and 32000 entries on the
+//     two sides of that line: 130 rows x 2048 53.8 / 60.2, 59.8 / 60.3, x 1024 40.6 / 41.9, 43.1 / 45.1; 144 x 2048 56.3 / 60.1, 61.5 /
+//     61.2, x 1024 42.6 / 42.4, 45.1 / 46.4; 160 x 3072 72.1 / 76.1, 75.3 / 76.4, x 2048 58.2 / 61.2, 64.0 / 61.6; 176 x 4096
+//     86.7 / 90.2, 95.3 / 97.8, x 2048 59.0 / 60.9, 64.8 / 64.5; 192 x 5120 102.6 / 105.4, 108.3 / 117.6, x 4096 (24000 entries) 94.0 /
+//     90.9; in two rounds 176 x 4096 x 64000 205 / 176, 132 x 3584 x 152064 391 / 294.
 //   - More: the shape of the least cost = rounds of workgroups over the compute units x
 //     (7 + 4 * mi).  Pruning call, us, one round at 4096 x 32000 (43 of it beside the kernel): 122 for 160 x 256,
 //     134 for 192, 146 for 224, 158 for 256, 170 for 288, 183 for 320, 200 for 352 x 256.  Tiles of 192 columns
@@ -850,7 +854,7 @@ constexpr int kTallMaxMI = 11;
 
 __host__ __device__ inline HeadPlan head_plan(int m_total, int hidden, int vocab, int cus, int force, int max_mi) {
   const HeadPlan few = {0, 1, (vocab - 1) / 128 + 1};
-  if (force == 0 && (m_total <= 128 || (m_total <= kSmallMaxRows && few.n_tiles <= cus && hidden >= 3072)))
+  if (force == 0 && (m_total <= 128 || (m_total <= kSmallMaxRows && few.n_tiles <= cus && hidden >= 64 * (m_total - 112))))
     return few;
   const int rows = m_total > 0 ? m_total : 1, nt = (vocab - 1) / 256 + 1;
   const float inv = 1.f / (float)cus;  // instead of a 64-bit division per shape in front of the first load
@@ -907,7 +911,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void early_head_bf16_kernel(
       else if (m_total <= 128)
         early_head_small_tile<KIND, 128>(hidden, vocab, m_total, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
       else
-        early_head_small_tile<KIND, 256>(hidden, vocab, m_total, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
+        early_head_small_tile<KIND, 192>(hidden, vocab, m_total, v0, n_tile, hidden_states, head_weight, tb, gemm_smem);
       continue;
     }
 #define X(MI)                                                                                              \

@@ -362,13 +362,22 @@ def test_prune_bf16_tall_tiles_short_rows(pb, oracle, Hd, B, T):
     check_prune(oracle, x, res, [x["hidden_states"]], sents)
 
 
-@pytest.mark.parametrize("B,T,Hd", [(2, 65, 3072), (2, 66, 3072), (2, 81, 3072), (2, 82, 3072), (2, 66, 3040)])
-def test_prune_bf16_few_rows_rule(pb, oracle, B, T, Hd):
-    """128, 130 and 160 score rows of 3072 take the tile of few rows, 162 rows, or rows of 3040, another."""
-    w = synth.Workload(79, "case", "bf16", B, 1, 128, T, Hd, 1000, 6, 1e-3)
+@pytest.mark.parametrize("B,T,Hd,V", [(2, 65, 96, 1000), (2, 66, 1152, 1000), (2, 66, 1120, 1000), (2, 66, 1184, 32768),
+                                      (2, 66, 1184, 32769), (2, 81, 3072, 1000), (2, 81, 3104, 1000), (2, 81, 3040, 1000),
+                                      (2, 97, 5120, 1000), (2, 97, 5152, 300), (2, 97, 5088, 1000), (2, 98, 5280, 1000)])
+def test_prune_bf16_few_rows_rule(pb, oracle, B, T, Hd, V):
+    """128 score rows, and 130, 160 and 192 of at least 1152, 3072 and 5120, take the tile of few rows in one
+    round (32768 entries on 256 compute units); shorter rows, 194 of them or 32769 entries take another. Both
+    criteria, rows of an even and of an odd number of 32s."""
+    w = synth.Workload(79, "case", "bf16", B, 1, 128, T, Hd, V, 6, 1e-3)
     x = synth.make_prune_inputs(w, trees=[synth.chain_tree(T)] * B, p_pass=0.8)
     res, sents = run_prune(pb, x, [x["hidden_states"]])
     check_prune(oracle, x, res, [x["hidden_states"]], sents)
+    logm, _, _ = prob_reference(oracle, x, threshold=0.5)
+    thr = float(np.float32(threshold_in_a_gap(logm, x["n_nodes"], 1e-3, 0.95)))
+    _, _, ref = prob_reference(oracle, x, threshold=thr)
+    res, sents = run_prob(pb, x, [x["hidden_states"]], threshold=thr)
+    check_prob(pb, oracle, x, res, ref, logm, [x["hidden_states"]], sents)
 
 
 @pytest.mark.parametrize("B,T,V", [(2, 66, 8192), (2, 66, 16001), (2, 128, 8192), (2, 128, 33001), (2, 89, 40000), (2, 65, 70000)])
