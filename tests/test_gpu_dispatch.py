@@ -320,9 +320,8 @@ def test_attention_bf16_merge_at_four_pieces(pb, oracle, H, d, T_max, L):
 
 @pytest.mark.parametrize("Hd", [32, 96, 160, 288])
 def test_prob_prune_several_tiles_per_workgroup(pb, oracle, Hd):
-    """More tiles than workgroups under the criterion whose epilogue passes nothing through LDS: a
-    workgroup starts its next tile's loads only when all its waves have left the tile before (the
-    last stage lies in another slot of the ring for every count of K steps modulo four)."""
+    """The criterion whose epilogue passes nothing through LDS, with K loops of one step to five: 396 score
+    rows are 2 x 125 tiles, one for each workgroup."""
     B, T_max, V = 9, 128, 32000
     w = synth.Workload(74, "case", "bf16", B, 1, 128, T_max, Hd, V, 8, 1e-3)
     x = synth.make_prune_inputs(w, trees=[synth.rank_product_tree(128, 5)] * B)
@@ -331,6 +330,55 @@ def test_prob_prune_several_tiles_per_workgroup(pb, oracle, Hd):
     _, _, ref = prob_reference(oracle, x, threshold=thr)
     res, sents = run_prob(pb, x, [x["hidden_states"]], threshold=thr)
     check_prob(pb, oracle, x, res, ref, logm, [x["hidden_states"]], sents)
+
+
+def whole_number_scores(pb, parent, token, Hd, V, seed):
+    """Hidden states, head weight and what every rank and log-probability must be: operands of -1, 0 and 1
+    (weights in eighths), whose sums fp32 holds exactly in any order, scored by a plain product."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    draw = lambda *s: torch.randint(-1, 2, s, device="cuda", generator=gen, dtype=torch.int8).to(torch.bfloat16)
+    B, T = parent.shape
+    hid, head = draw(B, T, Hd), draw(V, Hd) / 8
+    rows, which = np.unique((np.arange(B)[:, None] * T + parent)[:, 1:].reshape(-1), return_inverse=True)
+    flat, tok = hid.view(-1, Hd)[torch.from_numpy(rows).cuda()].float(), torch.from_numpy(token[:, 1:].reshape(-1).astype(np.int64)).cuda()
+    which = torch.from_numpy(which.reshape(-1)).cuda()
+    chunks = [(v, flat @ head[v:v + 8192].float().T) for v in range(0, V, 8192)]
+    z = torch.cat([c for _, c in chunks], 1)
+    own = z[which, tok]
+    rank = torch.zeros_like(tok)
+    for v, c in chunks:
+        c, ids = c[which], torch.arange(v, v + c.shape[1], device="cuda")
+        rank += ((c > own[:, None]) | ((c == own[:, None]) & (ids[None] < tok[:, None]))).sum(1)
+    logq = own.double() - torch.logsumexp(z.double(), 1)[which]
+    shape = (B, T - 1)
+    return hid, head, to_host(rank).reshape(shape), to_host(logq).reshape(shape)
+
+
+@pytest.mark.parametrize("Hd", [32, 352, 384])
+@pytest.mark.parametrize("B", [1, 3, 4, 5, 11, 6, 14, 8])
+def test_prune_bf16_several_tiles_per_workgroup(pb, B, Hd):
+    """More column tiles than workgroups, for the tile of few rows and for every shape of many (32 * MI rows
+    with MI = 5, 6, 7, 8, 9, 10, 11 on 256 compute units), both criteria: a workgroup's next tile starts in
+    memory that its last one has used.  One step, and enough of them that every ring wraps, with a half
+    step at the end and without."""
+    groups = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    T, V = 128, 256 * (groups + 70) + 3
+    assert (V + 255) // 256 > (groups + 7) // 8 * 8
+    shape = synth.rank_product_tree(T, 5)  # 44 of its nodes have children
+    n, parent, _ = synth.pad_trees([shape] * B, T)
+    token = np.random.default_rng(B).integers(0, V, (B, T)).astype(np.int32)
+    hid, head, rank, logq = whole_number_scores(pb, parent, token, Hd, V, 100 * B + Hd)
+    tree = dev_tree(pb, n, parent, token)
+    got = to_host(pb.propd_early_prune(tree, hid, head, 8, want_rank=True).rank)
+    assert (got[:, 1:] == rank).all()
+    # a row's log-sum-exp is merged from at most V / 128 partials, one fp32 rounding each at worst, and a path
+    # has at most five nodes
+    lm = to_host(pb.propd_early_prune_prob(tree, hid, head, threshold=1e-30, want_log_marginal=True).log_marginal)
+    want = np.zeros((B, T))
+    for i in range(1, T):
+        want[:, i] = want[np.arange(B), parent[:, i]] + logq[:, i - 1]
+    assert np.abs(lm - want).max() <= 5 * (V / 128) * 2.0 ** -24 + 5 * 2.0 ** -24 * np.abs(want).max()
 
 
 @pytest.mark.parametrize("B,T,V", [(1, 128, 32000), (2, 66, 32000), (2, 128, 4001), (3, 87, 32000), (3, 128, 32000),
