@@ -189,7 +189,8 @@ PROPD_API propd_status propd_tree_attention(const propd_tree *tree, propd_dtype 
  * (PROPD_ERR_INVALID_ARG otherwise).
  * The bf16 scoring kernel chooses its tile shape on the device, from the number of score rows.  The
  * environment variable PROPD_HEAD_PLAN (read once per process; for tuning and
- * tests) overrides the choice: 1 = 256-row tiles, 2 = 352-row tiles, unset or 0 = no override (any
+ * tests) overrides the choice: 1 = 256-row tiles, 2 = 352-row tiles (256-row tiles where the hidden
+ * states, or 256 rows of the head weight, take 4 GiB or more), unset or 0 = no override (any
  * other value is taken for 1); which nodes survive does
  * not depend on it beyond the order of rounding noted for rank_out.
  */

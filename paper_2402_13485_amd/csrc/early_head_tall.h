@@ -20,7 +20,8 @@
 //     250 / 235 / 235, 440 x 4096 159 / 155 / 146, 308 x 4096 139 / 142 / 122, 836 x 4096 276 / 266 / 258, 352 x 4096 x
 //     128256 446 / 451 / 417, 132 x 4096 x 128256 305 / 327 / 300, 176 x 1600 x 50257 90 / 90 / 82.  With B in two slots
 //     up to MI = 8 too: 176 x 4096 x 128256 344 instead of 321.
-//     704 x 5120 runs at 1.2 PFLOP/s, as fast as a large product of the library here; in two stages a
+//     704 x 5120 multiplies at 1.2 PFLOP/s, as fast as a large product of the library here (1.06 for the
+//     kernel with its epilogue); in two stages a
 //     call took 221 us without loads, 240 without products, without fragment reads and as it was;
 //   - the 16-byte chunks of a row are XOR-swizzled with key(row) = (row >> 1) & 7, so that the fragment
 //     reads of this MFMA (lane -> row lane % 16, chunk lane / 16) are free of bank conflicts;

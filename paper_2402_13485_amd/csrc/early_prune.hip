@@ -334,7 +334,7 @@ __device__ void own_scores(const PrepareArgs &a, int b, int group) {
   const int frag_off = (c16 & (kOwnNodes - 1)) * kOwnRowBytes + kq * 16;
   // Wave 0 reads a step's fragments while it multiplies those of the step before, so that the chain of
   // products does not wait for LDS once per step: pruning call 75.2 -> 73.8 us at 1 x 64 nodes x 4096, 239.3 ->
-  // 237.4 at 16 x 128 x 5120, 60.2 -> 59.8 in fp32.  (The barrier of the next step waits for these reads,
+  // 237.4 at 16 x 128 x 5120; nothing in fp32.  (The barrier of the next step waits for these reads,
   // and the buffer is written again only behind it.)
   constexpr int kGroups = kOwnStepBytes / 64;
   u32x4 fa[2][kGroups], fb[2][kGroups];
@@ -607,9 +607,10 @@ __device__ __forceinline__ void rows_epilogue(RowChildren<R> &ch, const float *s
 // rows are 128 bytes, their eight 16-byte chunks XOR-swizzled with key(row) = (row >> 1) & 7 (a
 // fragment read takes rows r .. r + 15 of one chunk column in one pass: two rows share a 256-byte
 // bank line, eight keys spread the eight pairs).
-// RA = 32, 128 or 192 rows have room.  (With 192, four stages instead of three are 1 to 2 us slower. Pruning call with
-// room for 256 rows / 192, us: 130 rows x 4096 x 8192 83.0 / 78.7, 160 x 4096 x 8192 84.1 / 86.0.)  RA = 32: a wave then has one 32-row block to multiply instead of two (pruning
-// call at 22 rows x 4096 x 32000: 80 us, 83 with RA = 128; a shape for 64 rows gained nothing at 44).
+// RA = 32, 128 or 192 rows have room.  RA = 32: a wave then has one 32-row block to multiply instead of two (pruning
+// call at 22 rows x 4096 x 32000: 80 us, 83 with RA = 128; a shape for 64 rows gained nothing at 44).  RA = 192: four
+// stages instead of three are 1 to 2 us slower.  Call with room for 256 rows / 192, us: 130 rows x 4096 x
+// 8192 83.0 / 78.7, 160 x 4096 x 8192 84.1 / 86.0.
 // The K loop runs at 5.8 TB/s of weights, read once and non-temporally (without that 6 us more); a
 // ring of seven stages instead of four changes nothing, and neither does requesting 256 or 512
 // bytes of a row together.  Kernel at that size: 72.8 -> 55.6 us with the row epilogue, the
