@@ -22,7 +22,8 @@
 //   - the cached prefix needs no mask; tree stages keep a score only where the
 //     node's 128-bit ancestor set has the bit;
 //   - the four waves of a workgroup split the query columns (32 each); a wave whose
-//     columns lie beyond the tree only helps with the loads;
+//     columns lie beyond the tree only helps with the loads.  Trees of at most 64 nodes have two
+//     waves per 32 columns, each with half of a stage's rows (see KS);
 //   - a unit cut by a range boundary leaves fp32 partials (O, max, sum), at most
 //     two per workgroup, and the workgroup holding its first piece leaves a record of the
 //     cut; a second kernel merges the pieces of every recorded cut, in their order.
@@ -31,6 +32,7 @@
 // Without a workspace or 16-byte alignment d = 64 runs a plain one-wave-per-query kernel.
 // fp32 path: tree_attention_f32.h.
 #include <type_traits>
+#include <utility>
 
 #include "common.h"
 
@@ -50,7 +52,7 @@ struct Geo {
   static constexpr int kChunks = kRowBytes / 16;              // 16-byte chunks of a row
   static constexpr int kLdRows = 1024 / kRowBytes;            // rows that one direct load of a wave fills
   static constexpr int kLoads = kHalfStage / 4096;            // direct loads of a wave per half stage
-  static constexpr int kKs = D / 16, kMb = D / 32;            // MFMA steps over d of QK^T; 32-wide blocks of d of PV
+  static constexpr int kMb = D / 32;                          // 32-wide blocks of d of PV
   // Workgroups resident on a compute unit: what LDS (two rings of 80 KB at D = 128) and registers
   // (254; 195 at D = 64) allow.  A bound of more workgroups spills, which this kernel must not:
   // loads that it waits for by hand would land in registers given away meanwhile.
@@ -77,6 +79,7 @@ struct AttnParams {
   int32_t *cuts;   // CutRecords: [units] by unit, or [grid] by the workgroup that holds the first piece
   int by_unit;     // see merge_by_unit
   int one_pass;    // see begin_one_pass
+  int cus;         // compute units
 };
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -101,6 +104,23 @@ __device__ __forceinline__ u32x2 lds_read_tr16(uint32_t addr) {
   u32x2 r;
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "n"(OFFSET));
   return r;
+}
+
+// LDS traffic between the waves of a workgroup, for the same reason as assembly.
+template <int OFFSET>
+__device__ __forceinline__ void lds_write16(uint32_t addr, f32x4 v) {
+  asm volatile("ds_write_b128 %0, %1 offset:%2" ::"v"(addr), "v"(v), "n"(OFFSET) : "memory");
+}
+__device__ __forceinline__ void lds_write8(uint32_t addr, u32x2 v) {
+  asm volatile("ds_write_b64 %0, %1" ::"v"(addr), "v"(v) : "memory");
+}
+template <class F, int... I>
+__device__ __forceinline__ void static_for_i_impl(F &&f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for_i(F &&f) {
+  static_for_i_impl(f, std::make_integer_sequence<int, N>{});
 }
 
 // wait until at most N LDS operations of this wave are outstanding; the registers named
@@ -199,6 +219,8 @@ __device__ __forceinline__ size_t part_ml_index(size_t slot, int wave, int which
 //     units (all units when lengths differ, so that every workgroup streams the same number
 //     of rows whatever the mix); a unit cut by a range boundary is finished by the merge
 //     kernel from per-workgroup partial results.
+// With no more units than workgroups the ranges are cut so that none crosses a unit, where that
+// costs little (begin_one_pass).
 // A wave-uniform 32-bit load on the scalar path.  Issued as assembly: the compiler would
 // use a vector load here and wait for it with vmcnt(0), which drains the ring.  The
 // scalar cache is invalidated when a kernel starts, like the vector caches, so values
@@ -216,7 +238,7 @@ __device__ __forceinline__ int32_t uniform_load_i32(const int32_t *ptr) {
 struct StageMap {
   int B, H;
   const int32_t *seq_lens, *n_nodes;
-  int L_max, T_max;
+  int L_max, T_max, cus;
   __device__ __forceinline__ int len(int b) const {
     const int L = uniform_load_i32(seq_lens + b);
     return L < 0 ? 0 : (L > L_max ? L_max : L);
@@ -297,6 +319,13 @@ struct Schedule {
   // The split list is cut into G contiguous ranges: the first `rem` workgroups take
   // `quot` + 1 stages, the others `quot` (one division per kernel, none per range).
   long long quot, rem;
+  int pieces = 0;  // > 0: no range crosses a unit, and this workgroup's unit is cut into so many
+  // The softmax reference is set anew every so many stages (kernels with kAnew; the check alone costs 0.5 % of a long
+  // call).  The largest weight of such a stage is exactly 1 and rounds to bf16 without error, like that of
+  // a piece's first stage: with ranges that cross no unit there would be fewer of these, and the error against
+  // 64 bits up to 4 % larger than with ranges that do (6 x 8 ragged units of 107 queries: 1.887e-3, 1.965e-3 without
+  // this).  Set often enough that it is no larger; once per stage costs 1.1 us of 14.
+  int anew = 1 << 30;
   __device__ __forceinline__ long long range_start(long long w) const {
     return w * quot + (w < rem ? w : rem);
   }
@@ -429,7 +458,14 @@ struct Walk {
   // every sequence's sizes are read once, into a lane, and what follows from them is 32-bit
   // arithmetic on registers.  It stands in front of a workgroup's first load, and a small call is
   // little else: 1 x 32 units of 64 queries x 1024 keys 19.8 -> 18.2 us for the call, 8 x 16 x 64 x 2048 (d =
-  // 64) 35.0 -> 33.1, against loads per question, sums through LDS and 64-bit divisions.
+  // 64) 35.0 -> 33.1, against loads per question, sums through LDS and 64-bit divisions.  (With ranges
+  // that cross no unit and two waves per 32 queries these calls take 14.2 and 26.4 us now.)
+  // n / d rounded down, for whole n below 2^20 and inv = 1 / d to one unit in the last place: n + 1/2 is half a
+  // d-th away from the next whole quotient, the error of the product at most n / d / 2^22
+  static __device__ __forceinline__ float floor_quotient(float n, float inv) { return floorf((n + .5f) * inv); }
+  // n / d rounded up, up = (d - 1/2) / d
+  static __device__ __forceinline__ float ceil_quotient(float n, float inv, float up) { return floorf(fmaf(n, inv, up)); }
+  template <int KS>
   __device__ __forceinline__ int begin_one_pass(const StageMap &m, Schedule &sc, int w, int G) {
     const int lane = threadIdx.x & 63, H = m.H;
     int len_l = m.seq_lens[lane < m.B ? lane : 0], nodes_l = m.n_nodes[lane < m.B ? lane : 0];
@@ -437,11 +473,71 @@ struct Walk {
     nodes_l = nodes_l < 1 ? 1 : (nodes_l > m.T_max ? m.T_max : nodes_l);
     const int us_l = lane < m.B ? (len_l + kStageRows - 1) / kStageRows + (nodes_l + kStageRows - 1) / kStageRows : 0;
     const int incl = wave_scan_i32(us_l, 0, [](int x, int y) { return x + y; });
+    const uint32_t n_all = (uint32_t)(H * __builtin_amdgcn_readlane(incl, 63)), U = (uint32_t)(m.B * H);
+    auto take_sizes = [&](int at) {
+      b = at;
+      L = __builtin_amdgcn_readlane(len_l, at);
+      T = __builtin_amdgcn_readlane(nodes_l, at);
+      cs = (L + kStageRows - 1) / kStageRows;
+      ts = (T + kStageRows - 1) / kStageRows;
+    };
+    // ---- Ranges that cross no unit, where that makes the longest of them not much longer: a range of two
+    //      units waits for queries and stores partials twice, 3 to 4 us after the others are done, and a
+    //      unit in one piece needs no merge.  The longest range q is the least for which the pieces of
+    //      all units, ceil(stages / q) each, fit the grid (a candidate per lane).
+    if (U <= (uint32_t)G) {
+      const float mean = (float)n_all * __builtin_amdgcn_rcpf((float)G);
+      const uint32_t least_q = (n_all + (uint32_t)G - 1u) / (uint32_t)G, q = least_q + (uint32_t)lane;
+      const float inv = __builtin_amdgcn_rcpf((float)q), up = ((float)q - .5f) * inv;
+      float total = 0.f;  // beyond 2^24 not exact, and far beyond any grid
+      const float us_f = (float)us_l;
+      for (int i = 0; i < m.B; ++i)
+        total += ceil_quotient(__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(us_f), i)), inv, up);
+      total *= (float)H;
+      const uint64_t fit = __ballot(total <= (float)G), fit_cus = __ballot(total <= (float)m.cus);
+      int pick = -1;
+      if (fit != 0) {
+        pick = __builtin_ctzll(fit);
+        const float pieces = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(total), pick));
+        const float longest = (float)(least_q + (uint32_t)pick);
+        // How much longer: the more units there are for each workgroup, the more of them a range crosses.  Whole calls, us, at mean /
+        // longest stages, crossing / not: ragged lengths, 496 units 9.0 / 17 35.5 / 30.4, 352 11.9 / 19 38.9 / 31.1, 280 22.9 / 32
+        // 57.8 / 48.5, 256 32.8 / 46 64.3 / 60.0, 240 14.1 / 18 43.2 / 38.3, 160 44 / 60 70.3 / 73.9; equal ones, 80 7.3 / 8 29.8 /
+        // 26.8, 208 72 / 89 130.7 / 133.7, 176 6.2 / 9 22.1 / 23.6.  In one piece each: 312 units of 57 queries 28.6 / 47 59.5 /
+        // 53.7, 320 of 89 4.4 / 7 26.9 / 21.5, 320 of 104 86 / 137 153.8 / 165.4.
+        const float share = (float)U * __builtin_amdgcn_rcpf((float)G);
+        const float limit = pieces <= (float)U ? (KS == 2 ? 1.65f : 1.2f) * mean + 8.f
+                                               : (1.f + (share < .5f ? .8f : 1.1f) * share) * mean + 1.f;
+        // One wave per 32 queries and fewer workgroups left than half the chip: 16 units of 127 x 136 (d = 64) 12.5 / 13.9.
+        if (longest > limit || (KS == 1 && pieces < .5f * (float)m.cus && pick > 0)) pick = -1;
+        // Fewer, longer pieces, one workgroup per compute unit, where a unit would be cut into many: 32 units of 34 stages in 12 / 7
+        // pieces 15.5 / 14.2, 8 of 247 in 62 / 31 22.7 / 18.6; 64 units in 8 / 4 20.8 / 21.4.
+        if (pick >= 0 && pieces > 8.f * (float)U && fit_cus != 0 && least_q + (uint32_t)__builtin_ctzll(fit_cus) <= 8u)
+          pick = __builtin_ctzll(fit_cus);
+      }
+      if (pick >= 0) {
+        const float inv_q = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(inv), pick));
+        const float up_q = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(up), pick));
+        const int mine = lane < m.B ? (int)ceil_quotient(us_f, inv_q, up_q) : 0;
+        const int wgs_before = H * (wave_scan_i32(mine, 0, [](int x, int y) { return x + y; }) - mine);
+        whole_left = 0;
+        take_sizes(__popcll(__ballot(lane < m.B && wgs_before <= w)) - 1);
+        const uint32_t at = (uint32_t)(w - __builtin_amdgcn_readlane(wgs_before, b)), P = (uint32_t)__builtin_amdgcn_readlane(mine, b);
+        const float inv_p = __builtin_amdgcn_rcpf((float)P);
+        const uint32_t head = (uint32_t)floor_quotient((float)at, inv_p), piece = at - head * P;
+        sc.pieces = (int)P;
+        sc.anew = (int)fminf((KS == 1 ? (mean < 5.f ? .67f : .5f) : mean < 6.f ? 1.f : .6f) * mean, 32.f);
+        sc.anew = sc.anew > 1 ? sc.anew : 1;
+        unit = split_unit = (long long)(b * H) + (head < (uint32_t)H ? head : 0);
+        const uint32_t quot = (uint32_t)floor_quotient((float)(cs + ts), inv_p), rem = (uint32_t)(cs + ts) - quot * P;
+        s = split_s = (int)(piece * quot + (piece < rem ? piece : rem));
+        return head < (uint32_t)H ? (int)(quot + (piece < rem ? 1u : 0u)) : 0;  // 0: past the last unit
+      }
+    }
     const int most = wave_scan_i32(us_l, 0, [](int x, int y) { return x > y ? x : y; });
     const int least = wave_scan_i32(lane < m.B ? us_l : 1 << 30, 1 << 30, [](int x, int y) { return x < y ? x : y; });
     const int us_max = __builtin_amdgcn_readlane(most, 63), us_min = __builtin_amdgcn_readlane(least, 63);
     const int before_l = H * (incl - us_l);  // stages of the units of the sequences before
-    const uint32_t n_all = (uint32_t)(H * __builtin_amdgcn_readlane(incl, 63)), U = (uint32_t)(m.B * H);
     sc.k = (us_max - us_min) * 32 <= us_max ? (int)(U / (uint32_t)G) : 0;
     sc.first_split = sc.k * G;
     uint32_t split_base = 0;
@@ -461,13 +557,6 @@ struct Walk {
     x_end = x0 + (uint32_t)n_my;
     // the sequence that holds stage split_base + x0 is the last one that starts at or before it
     const uint32_t x = split_base + x0;
-    auto take_sizes = [&](int at) {
-      b = at;
-      L = __builtin_amdgcn_readlane(len_l, at);
-      T = __builtin_amdgcn_readlane(nodes_l, at);
-      cs = (L + kStageRows - 1) / kStageRows;
-      ts = (T + kStageRows - 1) / kStageRows;
-    };
     const uint64_t starts = __ballot(lane < m.B && (uint32_t)before_l <= x);
     take_sizes(__popcll(starts) - 1);
     const uint32_t in_seq = x - (uint32_t)__builtin_amdgcn_readlane(before_l, b), hh = in_seq / (uint32_t)(cs + ts);
@@ -546,14 +635,34 @@ __device__ __forceinline__ bool has_nan(const f32x16 (&o)[MB]) {
   return sum != sum;
 }
 
+// x * a + y * b; D = 64: an infinity in a piece that counts for nothing is left out
+template <int D>
+__device__ __forceinline__ float merge_add(float x, float a, float y, float b) {
+  if constexpr (D == 64) {
+    x = a == 0.f ? 0.f : x;
+    y = b == 0.f ? 0.f : y;
+  }
+  return x * a + y * b;
+}
+
+// KS: waves per 32 queries.  1: the four waves split up to 128 queries.  2 (trees of at most 64 nodes, where
+// half of the waves would only load): a wave takes 16 of a stage's 32 rows, with 16x16x32 products for the
+// scores and 32x32x16, 16 keys deep, for the weighted sum, and the two waves of a query group merge
+// their results through LDS at the end of a piece.  That halves the chain of a stage, which bounds
+// the kernel at D = 64 (8 x 16 units, 64 queries, 2048 keys: 29.2 -> 26.4 us for the call; 96 x 50 x 2135 26.4 ->
+// 23.4) and costs at D = 128 where pieces are short and many (800 ragged units of up to 834 keys 37.2 -> 37.9;
+// 372 units x 49 x 5383 187 -> 178).
+// kAnew: see Schedule::anew.
 // D = 128 multiplies bf16 weights with V.  D = 64 keeps them in fp32: a weight is the sum of three
 // bf16 values, 8 of its 24 bits each, all of which are multiplied.  (With two of them a weight
 // is off by up to 2^-17.  8 x 16 units of 64 queries x 2048 keys, whole call: 33.8 us, 30.7 with two.)
-template <int NS, int D>
+template <int NS, int D, int KS, bool kAnew>
 __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_kernel(AttnParams p) {
   using G_ = Geo<D>;
   constexpr int kRowBytes = G_::kRowBytes, kHalfStage = G_::kHalfStage, kStageBytes = G_::kStageBytes;
-  constexpr int kKs = G_::kKs, kMb = G_::kMb, kLoads = G_::kLoads;
+  constexpr int kMb = G_::kMb, kLoads = G_::kLoads;
+  constexpr int kQf = D / 16, kKs = kQf / KS;    // registers of 16 bytes of a lane's queries; MFMA steps over d of QK^T
+  constexpr int kRegs = 16 / KS, kVSteps = 2 / KS;  // scores of a lane per stage; MFMA steps over the keys of PV
   constexpr bool kExact = D == 64;  // weights of fp32 precision, in several bf16 values
   constexpr int kParts = kExact ? 3 : 1;
   static_assert(NS >= 4, "three stages are in use by the math, the rest is in flight");
@@ -564,15 +673,16 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g = lane >> 5;
-  const int t = wave * 32 + l32;  // this lane's query column
+  const int q_group = KS == 1 ? wave : wave & 1, k_part = KS == 1 ? 0 : wave >> 1;
+  const int t = q_group * 32 + l32;  // this lane's query column
 
-  const StageMap map = {p.B, p.H, p.seq_lens, p.n_nodes, p.L_max, p.T_max};
+  const StageMap map = {p.B, p.H, p.seq_lens, p.n_nodes, p.L_max, p.T_max, p.cus};
   const long long G = gridDim.x, w = blockIdx.x;
   Schedule sch;
   Walk cp;
   int n_my;
   if (p.one_pass) {
-    n_my = cp.begin_one_pass(map, sch, (int)w, (int)G);
+    n_my = cp.template begin_one_pass<KS>(map, sch, (int)w, (int)G);
   } else {
     sch = make_schedule(map, G);
     n_my = cp.start(map, sch, w, G);
@@ -645,8 +755,10 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
   // K as the A operand of S^T: lane = row l32, 8 consecutive d from 16*ks + 8*g (chunk 2*ks + g)
   uint32_t k_rd[kKs];
 #pragma unroll
-  for (int ks = 0; ks < kKs; ++ks)
-    k_rd[ks] = smem_base + l32 * kRowBytes + (((2 * ks + g) ^ G_::k_key(l32)) << 4);
+  for (int ks = 0; ks < kKs; ++ks) {
+    const int r = KS == 1 ? l32 : 16 * k_part + (lane & 15), chunk = KS == 1 ? 2 * ks + g : 4 * ks + (lane >> 4);
+    k_rd[ks] = smem_base + r * kRowBytes + ((chunk ^ G_::k_key(r)) << 4);
+  }
   // V^T as the A operand of O^T: transposing read; in each group of 16 lanes, lane i points at
   // row i/4, 4 columns from 4*(i%4), and receives column i of those 4 rows.  Per MFMA k-step
   // (16 rows): slots 0..3 = rows 4g + 0..3, slots 4..7 = those rows + 8.
@@ -655,7 +767,7 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
   for (int mb = 0; mb < kMb; ++mb)
 #pragma unroll
     for (int hi = 0; hi < 2; ++hi) {
-      const int r = 4 * g + ((lane & 15) >> 2) + 8 * hi;
+      const int r = (KS == 1 ? 4 * g + 8 * hi : 16 * k_part + 8 * g + 4 * hi) + ((lane & 15) >> 2);
       const int chunk = mb * 4 + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
       v_rd[mb][hi] = smem_base + kHalfStage + r * kRowBytes + ((chunk ^ G_::v_key(r)) << 4) + 8 * (lane & 1);
     }
@@ -680,7 +792,6 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
         slot_ld = next_slot(slot_ld);
       }
   };
-  fill_ring();
   auto acquire = [&]() -> int {
     if (n_acq + 1 < n_my) wait_vmem<2 * kLoads>(); else wait_vmem<0>();
     __builtin_amdgcn_s_barrier();
@@ -714,8 +825,8 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
     // rows after its last query are descendants or strangers of all its queries, and those
     // stages are the last of the unit.
     pc.n_cmp = 0;
-    if (wave * 32 < c.T) {
-      pc.n_cmp = c.cs + wave + 1 - c.s;
+    if (q_group * 32 < c.T) {
+      pc.n_cmp = c.cs + q_group + 1 - c.s;
       pc.n_cmp = pc.n_cmp > pc.n_st ? pc.n_st : (pc.n_cmp < 0 ? 0 : pc.n_cmp);
     }
     return pc;
@@ -724,7 +835,7 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
   // Q^T fragments (B operand: lane = query column, 8 consecutive d per K step) and the
   // ancestor set of this lane's node.  Lanes past the tree take node 0: valid memory, and
   // their columns are never stored.
-  u32x4 qf[kKs], ancv;
+  u32x4 qf[kQf], ancv;
   // D = 64: left to the compiler, whose waits come where wait_queries() waits for everything anyway
   auto load16 = [](const void *ptr) {
     if constexpr (kExact) return *reinterpret_cast<const u32x4 *>(ptr);
@@ -732,39 +843,81 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
   };
   auto load_queries = [&](const Piece &pc) {
     const int tq = t < pc.T ? t : 0;
-    const uint16_t *qrow = p.q + ((size_t)pc.unit * p.T_max + tq) * D + g * 8;
+    if constexpr (KS == 1) {
+      const uint16_t *qrow = p.q + ((size_t)pc.unit * p.T_max + tq) * D + g * 8;
 #pragma unroll
-    for (int ks = 0; ks < kKs; ++ks) qf[ks] = load16(qrow + ks * 16);
+      for (int ks = 0; ks < kKs; ++ks) qf[ks] = load16(qrow + ks * 16);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int t16 = 32 * q_group + 16 * j + (lane & 15);
+        const uint16_t *qrow = p.q + ((size_t)pc.unit * p.T_max + (t16 < pc.T ? t16 : 0)) * D + (lane >> 4) * 8;
+#pragma unroll
+        for (int ks = 0; ks < kKs; ++ks) qf[j * kKs + ks] = load16(qrow + ks * 32);
+      }
+    }
     ancv = load16(p.anc + ((size_t)pc.b * p.T_max + tq) * 2);
   };
   auto wait_queries = [&]() {
     // the registers are named so that their uses cannot be scheduled above the wait
     auto tie = [&]() {
 #pragma unroll
-      for (int ks = 0; ks < kKs; ++ks) asm volatile("" : "+v"(qf[ks]));
+      for (int ks = 0; ks < kQf; ++ks) asm volatile("" : "+v"(qf[ks]));
       asm volatile("" : "+v"(ancv));
     };
     tie();
-    wait_vmem<0>();
+    // the first piece's were requested before the ring's loads, the first stage of which has landed
+    if (kExact || n_acq != 1) wait_vmem<0>();
     tie();
   };
 
   float m_run, l_run;
   f32x16 o_acc[kMb];
-  u32x2 vt[2][2 * kMb];
+  u32x2 vt[kVSteps][2 * kMb];
   // S^T = K . Q^T of one stage
-  auto scores = [&](int sl) -> f32x16 {
+  struct Scores {
+    f32x16 all;      // KS = 1
+    f32x4 half[2];   // KS = 2: 16 keys x 16 queries, twice
+  };
+  auto scores = [&](int sl) -> Scores {
     const uint32_t so = (uint32_t)sl * kStageBytes;
-    f32x16 acc;
+    Scores acc;
+    if constexpr (KS == 1) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+      for (int r = 0; r < 16; ++r) acc.all[r] = 0.f;
+    } else {
+      acc.half[0] = acc.half[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
 #pragma unroll
     for (int ks = 0; ks < kKs; ++ks) {
       const bf16x8 a = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8 *>(
           (uintptr_t)(k_rd[ks] + so));
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, qf[ks]), acc, 0, 0, 0);
+      if constexpr (KS == 1) {
+        acc.all = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, qf[ks]), acc.all, 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc.half[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, qf[j * kKs + ks]), acc.half[j], 0, 0, 0);
+      }
     }
     return acc;
+  };
+  // The scores of this lane's query, once they are there.  KS = 1: register r is key row 8 * (r / 4) + 4 * g +
+  // r % 4 of the stage.  KS = 2: half j of a lane holds query 16 * j + lane % 16 and keys 4 * (lane / 16) + r; the
+  // odd rows of 16 lanes of half 0 and the even ones of half 1 are exchanged, after which register r is
+  // query t and key row 16 * k_part + 8 * g + r.
+  auto take_scores = [&](const Scores &acc, float (&sc)[kRegs]) {
+    if constexpr (KS == 1) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sc[r] = acc.all[r];
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc.half[0][r]), __float_as_uint(acc.half[1][r]), false, false);
+        sc[r] = __uint_as_float(x[0]);
+        sc[4 + r] = __uint_as_float(x[1]);
+      }
+    }
   };
   // start the transposing reads of a whole V stage: vt[ks2][2*mb + hi]
   auto read_v = [&](int sl) {
@@ -774,26 +927,28 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
       vt[0][2 * mb] = lds_read_tr16<0>(v_rd[mb][0] + so);
       vt[0][2 * mb + 1] = lds_read_tr16<0>(v_rd[mb][1] + so);
     }
+    if constexpr (KS == 1) {
 #pragma unroll
-    for (int mb = 0; mb < kMb; ++mb) {
-      vt[1][2 * mb] = lds_read_tr16<16 * kRowBytes>(v_rd[mb][0] + so);
-      vt[1][2 * mb + 1] = lds_read_tr16<16 * kRowBytes>(v_rd[mb][1] + so);
+      for (int mb = 0; mb < kMb; ++mb) {
+        vt[1][2 * mb] = lds_read_tr16<16 * kRowBytes>(v_rd[mb][0] + so);
+        vt[1][2 * mb + 1] = lds_read_tr16<16 * kRowBytes>(v_rd[mb][1] + so);
+      }
     }
   };
   // D = 64, a piece done for the second time: V values that are not finite are taken out of the V
   // registers read last, and what they add to O is added
   bool careful = false;
-  auto take_out = [&](const uint32_t (&pw)[kParts][8]) __attribute__((always_inline)) {
+  auto take_out = [&](const uint32_t (&pw)[kParts][kRegs / 2]) __attribute__((always_inline)) {
     if (!kExact || !careful) return;
     wait_lds<0>(vt[0]);
-    wait_lds<0>(vt[1]);
+    if constexpr (KS == 1) wait_lds<0>(vt[1]);
 #pragma unroll
     for (int mb = 0; mb < kMb; ++mb) {
       f32x16 codes;
 #pragma unroll
       for (int r = 0; r < 16; ++r) codes[r] = 0.f;
 #pragma unroll
-      for (int ks2 = 0; ks2 < 2; ++ks2) {
+      for (int ks2 = 0; ks2 < kVSteps; ++ks2) {
         uint32_t v4[4] = {vt[ks2][2 * mb].x, vt[ks2][2 * mb].y, vt[ks2][2 * mb + 1].x, vt[ks2][2 * mb + 1].y};
         u32x4 code, seen;  // seen: 1 for a weight
 #pragma unroll
@@ -813,11 +968,11 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
     }
   };
   // O^T += V^T . P^T with the V registers read last and the given weights
-  auto weighted_sum = [&](const uint32_t (&pw)[kParts][8]) {
+  auto weighted_sum = [&](const uint32_t (&pw)[kParts][kRegs / 2]) {
     wait_lds<0>(vt[0]);
-    wait_lds<0>(vt[1]);
+    if constexpr (KS == 1) wait_lds<0>(vt[1]);
 #pragma unroll
-    for (int ks2 = 0; ks2 < 2; ++ks2) {
+    for (int ks2 = 0; ks2 < kVSteps; ++ks2) {
 #pragma unroll
       for (int part = kParts - 1; part >= 0; --part) {  // the small parts first
         const u32x4 pv = {pw[part][4 * ks2], pw[part][4 * ks2 + 1], pw[part][4 * ks2 + 2], pw[part][4 * ks2 + 3]};
@@ -850,6 +1005,12 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
     return __builtin_amdgcn_readfirstlane(*word) == n_any;
   };
 
+  auto put_blocks = [&](uint32_t at, auto from) __attribute__((always_inline)) {
+    static_for_i<kMb / KS * 4>([&](auto x) __attribute__((always_inline)) {
+      constexpr int X = decltype(x)::value, mb = decltype(from)::value + X / 4, q4 = X % 4;
+      lds_write16<1024 * X>(at, f32x4{o_acc[mb][4 * q4], o_acc[mb][4 * q4 + 1], o_acc[mb][4 * q4 + 2], o_acc[mb][4 * q4 + 3]});
+    });
+  };
   const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3f803f80u);
   // a new running maximum is adopted only when it exceeds the reference by 2^8 in the
   // exponent; below that the weights simply exceed 1, by a factor fp32 sums and bf16 hold
@@ -859,7 +1020,11 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
   const float tau = kExact ? fminf(4.f / p.scale_log2e, 1e38f) : 8.f / p.scale_log2e;
 
   Piece pc = piece_at(cp, 0);
+  // D = 128: the first piece's queries in front of the ring's loads, which they then need not be waited for behind
+  // (15.8 -> 14.5 us at 32 units of 64 x 1024).  D = 64, where the compiler waits for them, the other way.
+  if (kExact) fill_ring();
   if (pc.n_cmp > 0) load_queries(pc);
+  if (!kExact) fill_ring();
   while (n_acq < n_my) {
     const int L = pc.L, T = pc.T, n_cache = pc.n_cache, s0 = pc.s0;
     m_run = -INFINITY;
@@ -876,21 +1041,24 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
       int sl_cur = acquire();
       wait_queries();
       const uint64_t anc_lo = ((uint64_t)ancv.y << 32) | ancv.x, anc_hi = ((uint64_t)ancv.w << 32) | ancv.z;
-      f32x16 sc = scores(sl_cur);
-      uint32_t pw_prev[kParts][8];
+      Scores raw = scores(sl_cur);
+      uint32_t pw_prev[kParts][kRegs / 2];
       auto clear_prev = [&]() {
 #pragma unroll
         for (int part = 0; part < kParts; ++part)
 #pragma unroll
-          for (int r = 0; r < 8; ++r) pw_prev[part][r] = 0u;
+          for (int r = 0; r < kRegs / 2; ++r) pw_prev[part][r] = 0u;
       };
       clear_prev();
+      int next_anew = sch.anew;
 
       auto stage = [&](int i, auto has_next, auto has_prev) {
         constexpr bool kNext = decltype(has_next)::value, kPrev = decltype(has_prev)::value;
         int sl_next = 0;
         if (kNext) sl_next = acquire();
-        mfma_settle();  // sc was written by MFMAs of the previous iteration or the prologue
+        mfma_settle();  // raw was written by MFMAs of the previous iteration or the prologue
+        float sc[kRegs];
+        take_scores(raw, sc);
 
         const int s = s0 + i;
         const bool is_tree = s >= n_cache;
@@ -906,21 +1074,23 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
           uint32_t vis = n_valid >= 32 ? ~0u : ((1u << n_valid) - 1u);
           const uint64_t word = j0 >= 64 ? anc_hi : anc_lo;  // tree stages start at 0, 32, 64, 96
           vis &= is_tree ? (uint32_t)(word >> (j0 & 32)) : ~0u;
-          vis >>= 4 * g;
+          vis >>= KS == 1 ? 4 * g : 16 * k_part + 8 * g;
 #pragma unroll
-          for (int r = 0; r < 16; ++r)
-            sc[r] = ((vis >> (8 * (r >> 2) + (r & 3))) & 1u) ? sc[r] : -INFINITY;
+          for (int r = 0; r < kRegs; ++r)
+            sc[r] = ((vis >> (KS == 1 ? 8 * (r >> 2) + (r & 3) : r)) & 1u) ? sc[r] : -INFINITY;
         }
         // ---- running maximum
         float m_blk = -INFINITY;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) m_blk = fmaxf(m_blk, sc[r]);
+        for (int r = 0; r < kRegs; ++r) m_blk = fmaxf(m_blk, sc[r]);
         {  // the other half of the stage's rows is in the lane 32 away
           uint32_t lo = __float_as_uint(m_blk), hi = lo;
           swap_halves(lo, hi);
           m_blk = fmaxf(__uint_as_float(lo), __uint_as_float(hi));
         }
-        if (__builtin_amdgcn_ballot_w64(m_blk > (kExact ? m_run : m_run + tau)) != 0) {
+        const bool anew = kAnew && i == next_anew;  // uniform
+        if (anew) next_anew += sch.anew;
+        if (anew || __builtin_amdgcn_ballot_w64(m_blk > (kExact ? m_run : m_run + tau)) != 0) {
           // rare: move the reference.  O must first receive the stage still pending, whose
           // weights are relative to the old reference.
           if (kPrev) {
@@ -929,7 +1099,7 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
             clear_prev();
             mfma_settle();
           }
-          const float m_new = fmaxf(m_run, kExact ? m_blk + tau : m_blk);
+          const float m_new = fmaxf(anew ? m_run - tau : m_run, kExact ? m_blk + tau : m_blk);
           const float m_safe = m_new == -INFINITY ? 0.f : m_new;
           const float alpha = fast_exp2((m_run - m_safe) * p.scale_log2e);
           l_run *= alpha;
@@ -944,11 +1114,11 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
         if (kPrev) take_out(pw_prev);
 
         // ---- one block: scores of the next stage, weights of this one, O update of the last
-        f32x16 sc_next;
-        if (kNext) sc_next = scores(sl_next);
-        uint32_t pw[kParts][8];
+        Scores raw_next;
+        if (kNext) raw_next = scores(sl_next);
+        uint32_t pw[kParts][kRegs / 2];
 #pragma unroll
-        for (int r = 0; r < 16; r += 2) {
+        for (int r = 0; r < kRegs; r += 2) {
           const float p0 = fast_exp2(fmaf(sc[r], p.scale_log2e, neg_m));
           const float p1 = fast_exp2(fmaf(sc[r + 1], p.scale_log2e, neg_m));
           if constexpr (kExact) {
@@ -972,9 +1142,9 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
 #pragma unroll
         for (int part = 0; part < kParts; ++part)
 #pragma unroll
-          for (int r = 0; r < 8; ++r) pw_prev[part][r] = pw[part][r];
+          for (int r = 0; r < kRegs / 2; ++r) pw_prev[part][r] = pw[part][r];
         if (kNext) {
-          sc = sc_next;
+          raw = raw_next;
           sl_cur = sl_next;
         }
       };
@@ -1025,32 +1195,83 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
       // this workgroup's work: its last stage lies us - n_st stages further
       const int us = n_cache + (T + kStageRows - 1) / kStageRows;
       cut.unit = done.unit;
-      cut.w_last_and_nodes = (int32_t)sch.range_owner(cp.x_end - 1 + (us - done.n_st)) | (T << 16);
+      const long long w_last = sch.pieces > 0 ? w + sch.pieces - 1 : sch.range_owner(cp.x_end - 1 + (us - done.n_st));
+      cut.w_last_and_nodes = (int32_t)w_last | (T << 16);
     }
     if (s0 == 0 && p.by_unit) leave_record(done.unit);
 
     // ---- write: lane holds d = mb*32 + 8*(r/4) + 4*g + r%4 for its query t
     l_run += __shfl_xor(l_run, 32, kWave);
     m_run *= p.scale_log2e;  // from here on the maximum is in the exponent's (log2) domain
-    if (wave * 32 < T) {
+    constexpr int kMyMb = kMb / KS;  // blocks of d this wave writes
+    if constexpr (KS == 2) {
+      // The two waves of a query group exchange halves of O and the statistics through the three ring slots of
+      // the stages acquired last: none of them is in flight, behind a barrier nobody reads them any
+      // more, and the next load into one is issued behind the next stage's barrier.
+      static_assert(NS == 5 && kAhead == 2, "two stages in flight, three slots free");
+      auto slot_before = [](int sl) { return sl == 0 ? NS - 1 : sl - 1; };
+      const int last = slot_before(slot_acq), last2 = slot_before(last), last3 = slot_before(last2);
+      const uint32_t o_at = smem_base + (uint32_t)(k_part == 0 ? last : last2) * kStageBytes + q_group * (kStageBytes / 2) + lane * 16;
+      const uint32_t o_from = smem_base + (uint32_t)(k_part == 0 ? last2 : last) * kStageBytes + q_group * (kStageBytes / 2) + lane * 16;
+      const uint32_t ml_at = smem_base + (uint32_t)last3 * kStageBytes + wave * 512 + lane * 8;
+      const uint32_t ml_from = smem_base + (uint32_t)last3 * kStageBytes + (wave ^ 2) * 512 + lane * 8;
+      __builtin_amdgcn_s_barrier();
+      if (q_group * 32 < T) {
+        if (k_part == 0) {
+          // part 0 keeps the lower half of d, part 1 the upper
+          put_blocks(o_at, std::integral_constant<int, kMyMb>{});
+        } else {
+          put_blocks(o_at, std::integral_constant<int, 0>{});
+#pragma unroll
+          for (int mb = 0; mb < kMyMb; ++mb) o_acc[mb] = o_acc[kMyMb + mb];
+        }
+        lds_write8(ml_at, u32x2{__float_as_uint(m_run), __float_as_uint(l_run)});
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      if (q_group * 32 < T) {
+        f32x4 other[kMyMb * 4];
+#pragma unroll
+        for (int x = 0; x < kMyMb * 4; ++x)
+          other[x] = *reinterpret_cast<const __attribute__((address_space(3))) f32x4 *>((uintptr_t)(o_from + 1024 * x));
+        const u32x2 ml = *reinterpret_cast<const __attribute__((address_space(3))) u32x2 *>((uintptr_t)ml_from);
+        const float m2 = __uint_as_float(ml.x), l2 = __uint_as_float(ml.y);
+        const float M = fmaxf(m_run, m2), M_safe = M == -INFINITY ? 0.f : M;
+        const float a1 = fast_exp2(m_run - M_safe), a2 = fast_exp2(m2 - M_safe);
+        l_run = l_run * a1 + l2 * a2;
+        m_run = M;
+#pragma unroll
+        for (int mb = 0; mb < kMyMb; ++mb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            o_acc[mb][r] = merge_add<D>(o_acc[mb][r], a1, other[4 * mb + r / 4][r % 4], a2);
+          }
+      }
+    }
+    if (q_group * 32 < T) {
       if (done.whole) {
-        if (t < T)
-          store_out_row<true>(p.out + ((size_t)done.unit * p.T_max + t) * D, o_acc, 1.f / l_run, g);
+        if (t < T) {
+          uint16_t *orow = p.out + ((size_t)done.unit * p.T_max + t) * D;
+#pragma unroll
+          for (int mb = 0; mb < kMyMb; ++mb) store_out_block<true>(orow, o_acc[mb], 1.f / l_run, g, k_part * kMyMb + mb);
+        }
       } else {
         // a range starts inside at most one unit and ends inside at most one
         const size_t ps = 2 * (size_t)w + (s0 > 0 ? 0 : 1);
         if (t < T) {
 #pragma unroll
-          for (int mb = 0; mb < kMb; ++mb)
+          for (int mb = 0; mb < kMyMb; ++mb)
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
               const f32x4 w4 = {o_acc[mb][4 * q4], o_acc[mb][4 * q4 + 1], o_acc[mb][4 * q4 + 2],
                                 o_acc[mb][4 * q4 + 3]};
-              global_store16_untracked(p.part_o + part_o_index(ps, wave, 4 * mb + q4, lane),
+              global_store16_untracked(p.part_o + part_o_index(ps, q_group, 4 * (k_part * kMyMb + mb) + q4, lane),
                                        __builtin_bit_cast(u32x4, w4));
             }
-          global_store4_untracked(p.part_ml + part_ml_index(ps, wave, 0, lane), m_run);
-          global_store4_untracked(p.part_ml + part_ml_index(ps, wave, 1, lane), l_run);
+          if (k_part == 0) {
+            global_store4_untracked(p.part_ml + part_ml_index(ps, q_group, 0, lane), m_run);
+            global_store4_untracked(p.part_ml + part_ml_index(ps, q_group, 1, lane), l_run);
+          }
         }
       }
     }
@@ -1076,16 +1297,6 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
 // x 70 x 300 41.1 / 38.4.
 static bool merge_by_unit(long long units, int grid) { return 4 * units <= grid; }
 constexpr int kCombinePieces = 4, kCombineManyPieces = 16;
-
-// x * a + y * b; D = 64: an infinity in a piece that counts for nothing is left out
-template <int D>
-__device__ __forceinline__ float merge_add(float x, float a, float y, float b) {
-  if constexpr (D == 64) {
-    x = a == 0.f ? 0.f : x;
-    y = b == 0.f ? 0.f : y;
-  }
-  return x * a + y * b;
-}
 
 template <int D>
 __global__ __launch_bounds__(kWave) void tree_attn_combine_kernel(AttnParams p) {
@@ -1311,17 +1522,17 @@ size_t tree_attention_workspace_bytes(int B, int H, int L_max, int T_max) {
          align_up(grid * sizeof(CutRecord), 256);
 }
 
-template <int D>
+template <int D, int KS, bool kAnew>
 static bool launch_bf16(const AttnParams &p, int grid, hipStream_t st) {
   constexpr int lds_bytes = kRingStages * Geo<D>::kStageBytes;
   static bool attr_set = false;
   if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_bf16_kernel<kRingStages, D>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_bf16_kernel<kRingStages, D, KS, kAnew>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes) != hipSuccess)
       return false;
     attr_set = true;
   }
-  hipLaunchKernelGGL((tree_attn_bf16_kernel<kRingStages, D>), dim3((unsigned)grid), dim3(kAttnThreads),
+  hipLaunchKernelGGL((tree_attn_bf16_kernel<kRingStages, D, KS, kAnew>), dim3((unsigned)grid), dim3(kAttnThreads),
                      lds_bytes, st, p);
   if (!launch_ok()) return false;
   const unsigned blocks = (unsigned)(p.T_max + 31) / 32 * Geo<D>::kMb;
@@ -1405,8 +1616,15 @@ extern "C" propd_status propd_tree_attention(const propd_tree *tree, propd_dtype
   p.cuts = reinterpret_cast<int32_t *>(ws);
   p.by_unit = merge_by_unit(units, grid) ? 1 : 0;
   const long long unit_stages = (L_max + kStageRows - 1) / kStageRows + (tree->T_max + kStageRows - 1) / kStageRows;
-  p.one_pass = tree->B <= kWave && units * unit_stages < (1ll << 31) ? 1 : 0;
-  if (!(d == 64 ? launch_bf16<64>(p, grid, st) : launch_bf16<128>(p, grid, st))) return PROPD_ERR_DEVICE;
+  p.cus = compute_units();
+  p.one_pass = tree->B <= kWave && units * unit_stages < (1ll << 31) && unit_stages < (1 << 20) ? 1 : 0;
+    // two waves per 32 queries, see KS
+  const bool split = tree->T_max <= 64 && (d == 64 || units <= grid || L_max >= 1024);
+  const bool anew = p.one_pass && units <= grid;
+  if (!(d == 64 ? (split ? launch_bf16<64, 2, false>(p, grid, st) : launch_bf16<64, 1, false>(p, grid, st))
+        : anew  ? (split ? launch_bf16<128, 2, true>(p, grid, st) : launch_bf16<128, 1, true>(p, grid, st))
+                : (split ? launch_bf16<128, 2, false>(p, grid, st) : launch_bf16<128, 1, false>(p, grid, st))))
+    return PROPD_ERR_DEVICE;
   return PROPD_OK;
 }
 

@@ -304,6 +304,30 @@ def test_attention_bf16_sequences_of_a_wave(pb, oracle, B, H, ragged):
     check_attention(oracle, x, out, sent)
 
 
+# B, H, T_max, L, ragged lengths: no more units than workgroups (512 on 256 compute units) and more; ranges of one
+# unit each (equal lengths, many pieces, one piece, few workgroups) and ranges that cross units; both sides of
+# the line between two waves per 32 queries and one, and of the line of L_max for short pieces of many units
+RANGES = [(1, 1, 64, 3000, False), (1, 8, 59, 2500, False), (2, 16, 64, 700, True), (3, 5, 65, 700, True), (1, 40, 33, 90, False),
+          (5, 12, 32, 592, False), (31, 8, 47, 300, True), (8, 64, 20, 60, False), (8, 64, 70, 60, True), (57, 9, 64, 64, True),
+          (64, 8, 31, 40, True), (65, 7, 64, 70, True), (20, 30, 64, 100, True), (27, 20, 9, 1024, True), (27, 20, 9, 1023, True),
+          (4, 3, 1, 33, True), (16, 1, 127, 136, False), (1, 300, 96, 200, False), (2, 33, 100, 0, False)]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,H,T_max,L,ragged", RANGES)
+def test_attention_bf16_ranges_of_one_unit(pb, oracle, B, H, T_max, L, ragged, d):
+    """How a call's stages are cut into ranges, at the edges of the rule, with trees of 1 to T_max nodes."""
+    rng = np.random.default_rng([B, H, T_max, L])
+    lens = rng.integers(0, L + 1, B).astype(np.int32) if ragged else np.full(B, L, np.int32)
+    lens[0] = L
+    trees = [synth.rank_product_tree(int(n), 4) for n in (rng.integers(1, T_max + 1, B) if ragged else [T_max] * B)]
+    trees[0] = synth.rank_product_tree(T_max, 4)
+    w = synth.Workload(3, "ranges", "bf16", B, H, d, T_max, L, 4096, 10, 1e-3)
+    x = synth.make_attention_inputs(w, seq_lens=lens, trees=trees)
+    out, sent = run_attention(pb, x)
+    check_attention(oracle, x, out, sent)
+
+
 @pytest.mark.parametrize("H", [127, 128, 129, 160])
 @pytest.mark.parametrize("d,T_max,L", [(64, 40, 500), (128, 33, 480)])
 def test_attention_bf16_merge_at_four_pieces(pb, oracle, H, d, T_max, L):
