@@ -18,16 +18,15 @@
 //                         probability criterion, leaves (max, sum of exponentials) per row
 //                         and column tile
 //   early_head_f32_kernel the same on the fp32 matrix instructions (early_head_f32.h)
-//   row_lse_kernel        probability criterion: log-sum-exp of every row from the tile
-//                         partials, log-probability of every child's token
-//   prune_compact_kernel  per sequence: the criterion's decision per node (rank against k, or
-//                         path marginal against the threshold / the keep count), fail bits by
+//   prune_finish_kernel   per sequence: the criterion's decision per node (rank against k, or
+//                         path marginal against the threshold / the keep count; for the latter the
+//                         log-sum-exp of every row from the tile partials first), fail bits by
 //                         ballot, branch elimination by testing the cached ancestor bitset
 //                         against the fail bits, order-preserving compaction by prefix
-//                         popcount, mask subsampling by bit extraction
-//   cu_nodes_kernel       exclusive prefix sum of survivor counts (when there are payloads
-//                         it rides along as one extra block of the gather launch)
-//   gather_rows_kernel    survivor rows of the listed payload tensors
+//                         popcount, mask subsampling by bit extraction; then the survivor rows of
+//                         the listed payload tensors, shared among the workgroups of the sequence;
+//                         the last sequence to arrive leaves the prefix sum of the survivor counts
+//   cu_nodes_kernel       that prefix sum where nothing was scored
 #include <cstdlib>
 #include <type_traits>
 #include <utility>
@@ -39,13 +38,16 @@ namespace propd {
 // ------------------------------------------------------------------------------------
 // scratch layout
 // ------------------------------------------------------------------------------------
+constexpr int kNoteTiles = 0;    // column tiles of the scoring kernel's plan
+constexpr int kNoteArrived = 1;  // sequences that have their survivor count written (prune_finish_kernel)
+
 struct PruneScratch {
   int32_t *row_src;     // [B*T_max]  score row -> b*T_max + node
   int32_t *row_base;    // [B+1]      score rows of the sequences before b; [B] = total rows
   int32_t *row_info;    // [B*T_max][2] score row -> (first position in child_list, children)
   int32_t *child_list;  // [B*T_max]  b*T_max + child, grouped by parent, per sequence slot
   float *own;           // [B*T_max]  z_parent[token] of every non-root node
-  float *logq;          // [B*T_max]  probability criterion: log q of every node's token
+  int32_t *notes;       // what the kernels leave each other, see kNote*
   float *lse_part;      // [row_cap * parts][2]  probability criterion: (max, sum exp) per tile
   int32_t *cnt_part;    // [vocab / 128][B*T_max]  top-k criterion: per column tile, the scores of the
                         //                       parent's row that beat the node's token
@@ -67,7 +69,7 @@ static PruneScratch carve_scratch(void *base, int B, int T_max, int vocab) {
   s.row_info = reinterpret_cast<int32_t *>(take(nt * 8));
   s.child_list = reinterpret_cast<int32_t *>(take(nt * 4));
   s.own = reinterpret_cast<float *>(take(nt * 4));
-  s.logq = reinterpret_cast<float *>(take(nt * 4));
+  s.notes = reinterpret_cast<int32_t *>(take(nt * 4));  // (at least 64 words)
   s.row_cap = (size_t)B * (T_max > 1 ? T_max - 1 : 1);  // a node with children is not a leaf
   s.parts = ((size_t)vocab + 127) / 128;  // column parts of a row: one per tile, of at least 128 columns
   s.lse_part = reinterpret_cast<float *>(take(s.row_cap * s.parts * 8));
@@ -131,7 +133,7 @@ struct PrepareArgs {
   int B, T_max, hidden, vocab;
   const int32_t *n_nodes, *parent, *token;
   const void *hidden_states, *head_weight;
-  int32_t *row_src, *row_base, *row_info, *child_list;
+  int32_t *row_src, *row_base, *row_info, *child_list, *notes;
   float *own;
 };
 
@@ -398,6 +400,7 @@ template <bool kBf16>
 __global__ __launch_bounds__(kScanThreads) void prune_prepare_kernel(PrepareArgs a) {
   const int table_groups = (a.B + kTableWaves - 1) / kTableWaves;
   if ((int)blockIdx.x < table_groups) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.notes[kNoteArrived] = 0;
     prepare_tables(a, blockIdx.x);
     return;
   }
@@ -415,7 +418,7 @@ struct HeadTables {
   int cnt_stride;     // B * T_max
   float *lse_part;
   int parts;  // column parts per row in lse_part
-  int32_t *n_tiles;  // top-k criterion, bf16: the column tiles of the plan, left for the decision kernel
+  int32_t *n_tiles;  // bf16: the column tiles of the plan, left for prune_finish_kernel
 };
 
 // ------------------------------------------------------------------------------------
@@ -893,7 +896,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void early_head_bf16_kernel(
   if (m_total <= 0) return;
   const HeadPlan pl = head_plan(m_total, hidden, vocab, cus, force, max_mi);
   const int m_tiles = pl.m_tiles, n_tiles = pl.n_tiles;
-  if (KIND == 0 && blockIdx.x == 0 && threadIdx.x == 0) *tb.n_tiles = n_tiles;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *tb.n_tiles = n_tiles;
   const long long total = (long long)kXcds * ((n_tiles + kXcds - 1) / kXcds) * m_tiles;
   extern __shared__ __attribute__((aligned(1024))) unsigned char gemm_smem[];
   for (long long tile = blockIdx.x; tile < total; tile += gridDim.x) {
@@ -926,41 +929,6 @@ __global__ __launch_bounds__(kGemmThreads, 1) void early_head_bf16_kernel(
 
 #include "early_head_f32.h"
 
-// ------------------------------------------------------------------------------------
-// probability-based selection (Section 4.1, "Pruning Criterion", second criterion)
-// ------------------------------------------------------------------------------------
-// One wave per score row: log sum_v exp(z[v]) from the row's tile partials (the first
-// n_parts of them were written), then logq = own score - that for every child of the
-// row's node.  A token id outside the vocabulary has probability 0 (logq = -inf).
-__global__ __launch_bounds__(kWave) void row_lse_kernel(int B, int hidden, int vocab, int cus, int force, int max_mi, int bf16,
-                                                        HeadTables tb, float *__restrict__ logq) {
-  const int m = blockIdx.x;
-  const int m_total = tb.row_base[B];
-  if (m >= m_total) return;
-  int n_parts;
-  if (bf16) {
-    n_parts = head_plan(m_total, hidden, vocab, cus, force, max_mi).n_tiles;
-  } else {
-    n_parts = f32_plan(m_total, vocab).n_tiles;
-  }
-  const int lane = threadIdx.x;
-  float mx = -INFINITY, sum = 0.f;
-  const float *part = tb.lse_part + (size_t)m * tb.parts * 2;
-  for (int i = lane; i < n_parts; i += kWave) lse_merge(mx, sum, part[2 * i], part[2 * i + 1]);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float m2 = __shfl_xor(mx, o, kWave), s2 = __shfl_xor(sum, o, kWave);
-    lse_merge(mx, sum, m2, s2);
-  }
-  const float lse = mx + logf(sum);
-  const int pos = tb.row_info[2 * m], cc = tb.row_info[2 * m + 1];
-  for (int e = lane; e < cc; e += kWave) {
-    const int c = tb.child_list[pos + e];
-    const int t = tb.token[c];
-    logq[c] = (t >= 0 && t < vocab) ? tb.own[c] - lse : -INFINITY;
-  }
-}
-
 // which criterion decides (Section 4.1, "Pruning Criterion")
 struct Criterion {
   int kind;             // 0 top-k, 1 probability threshold, 2 probability rank
@@ -971,70 +939,147 @@ struct Criterion {
 };
 
 // ------------------------------------------------------------------------------------
-// the decision, branch elimination, compaction, mask subsampling
+// the decision, branch elimination, compaction, mask subsampling, payload rows of survivors
 // ------------------------------------------------------------------------------------
-// One workgroup per sequence, one lane per node.
+struct PayloadArgs {
+  const char *src[PROPD_MAX_PAYLOADS];
+  char *dst[PROPD_MAX_PAYLOADS];
+  unsigned long long per_row[PROPD_MAX_PAYLOADS];  // pieces of a row: of 16 bytes (vec16), or bytes
+  unsigned outer[PROPD_MAX_PAYLOADS];
+  long long stride_b[PROPD_MAX_PAYLOADS], stride_outer[PROPD_MAX_PAYLOADS], stride_t[PROPD_MAX_PAYLOADS];
+  int vec16[PROPD_MAX_PAYLOADS];  // rows, strides and bases are all 16-byte multiples
+  int n;
+};
+
+struct FinishArgs {
+  int B, T_max, vocab, bf16, scored, parts, log_split;
+  Criterion crit;
+  const int32_t *n_nodes, *parent, *token, *depth;
+  const uint64_t *anc;
+  const int32_t *row_base, *row_info, *child_list, *cnt_part;
+  const float *own, *lse_part;
+  int32_t *notes;
+  uint64_t *keep_bits;
+  int32_t *new_index, *orig_index, *n_kept, *cu_nodes, *out_n_nodes, *out_parent, *out_token, *out_depth;
+  uint64_t *out_anc;
+  int32_t *rank_out;
+  PayloadArgs pa;
+};
+
+constexpr int kFinishSplit = 4;  // threads that add up one node's per-tile counts
+constexpr int kFinishThreads = PROPD_MAX_TREE * kFinishSplit;
+constexpr int kRowLanes = 8;     // threads that take the partial sums of one score row
+constexpr int kGatherItems = 4;  // pieces a thread has in flight
+
+// Workgroups per sequence (a power of two): at most one for 2048 pieces of payload (of which typically a quarter
+// to a half survive) and one per compute unit in the whole batch, since each works out its sequence's decision; two
+// per compute unit for large payloads.  Pruning call, us, at one / two per compute unit: 5 sequences x 32 heads x 70
+// nodes (545 blocks of 2048) 52.5 / 54.1 (four: 58.0), 32 x 128 nodes, hidden only (1024) 232.6 / 235.0, 27 x 16 x 128
+// (1863) 144.8 / 143.1, 16 x 40 x 128 (2560) 235.0 / 232.4.
+static int finish_log_split(int B, long long blocks, int cus) {
+  const long long most = blocks >= 6ll * cus ? 2ll * cus : cus;
+  int log_split = 0;
+  while (log_split < 10 && (2ll * B << log_split) <= most && ((long long)B << log_split) < blocks) ++log_split;
+  return log_split;
+}
+
+// The pieces [lo, hi) of one payload of one sequence, counted as (outer, survivor, piece of its row), in
+// chunks of kGatherItems per thread, all loads of a chunk in flight before its first store.  A thread divides
+// once; from piece to piece it adds the (outer, survivor, piece) that the distance comes to.
+template <typename N, typename V>
+__device__ __forceinline__ void gather_pieces(const char *src, char *dst, long long stride_outer, long long stride_t,
+                                              N lo, N hi, N kept, N per_row, const int *s_orig) {
+  const N per_outer = kept * per_row;
+  const N step_o = (N)kFinishThreads / per_outer, step_r = (N)kFinishThreads - step_o * per_outer;
+  const N step_j = step_r / per_row, step_c = step_r - step_j * per_row;
+  const N first = lo + (N)threadIdx.x;
+  N o = first / per_outer, j, c;
+  {
+    const N r = first - o * per_outer;
+    j = r / per_row;
+    c = r - j * per_row;
+  }
+  for (N x0 = first; x0 < hi; x0 += (N)(kGatherItems * kFinishThreads)) {
+    V v[kGatherItems];
+    long long to[kGatherItems];
+#pragma unroll
+    for (int k = 0; k < kGatherItems; ++k) {
+      const bool in = x0 + (N)(k * kFinishThreads) < hi;  // past the end: the first piece of the chunk once more, not stored
+      const long long at = (long long)o * stride_outer + (long long)c * (long long)sizeof(V);
+      to[k] = k == 0 || in ? at + (long long)j * stride_t : to[0];
+      const char *from = src + at + (long long)s_orig[(int)j] * stride_t;
+      from = k == 0 || in ? from : src + (long long)s_orig[0] * stride_t;
+      v[k] = *reinterpret_cast<const V *>(from);
+      c += step_c;
+      N carry = c >= per_row ? 1 : 0;
+      c -= carry ? per_row : 0;
+      j += step_j + carry;
+      carry = j >= kept ? 1 : 0;
+      j -= carry ? kept : 0;
+      o += step_o + carry;
+    }
+#pragma unroll
+    for (int k = 0; k < kGatherItems; ++k)
+      if (x0 + (N)(k * kFinishThreads) < hi) *reinterpret_cast<V *>(dst + to[k]) = v[k];
+  }
+}
+
+// Every workgroup of a sequence works out its decision for itself, four threads per node for the counts and
+// one for the rest; the first one writes it down, and all share the payload rows.
 //   top-k: a node fails when `top_k` or more scores of its parent's row beat its token's, or
 //     its token id lies outside the vocabulary.
-//   probability: the log marginal of a node's sequence is the sum of logq over its root path
-//     (the cached ancestor set, root excluded, in root-to-node order); it fails when the
-//     marginal is below the threshold, or when `keep_count` or more sequences of the tree are
-//     more probable (equal marginals: the lower node index counts as more probable); a
-//     marginal of zero probability always fails.
-constexpr int kCompactSplit = 4;  // threads that add up one node's per-tile counts
-
-__global__ __launch_bounds__(PROPD_MAX_TREE * kCompactSplit) void prune_compact_kernel(
-    int B, int T_max, int vocab, int bf16, Criterion crit, const int32_t *__restrict__ plan_tiles, const int32_t *__restrict__ n_nodes,
-    const int32_t *__restrict__ parent, const int32_t *__restrict__ token,
-    const int32_t *__restrict__ depth, const uint64_t *__restrict__ anc,
-    const int32_t *__restrict__ row_base, const int32_t *__restrict__ cnt_part,
-    const float *__restrict__ logq, uint64_t *__restrict__ keep_bits,
-    int32_t *__restrict__ new_index, int32_t *__restrict__ orig_index, int32_t *__restrict__ n_kept,
-    int32_t *__restrict__ out_n_nodes, int32_t *__restrict__ out_parent,
-    int32_t *__restrict__ out_token, int32_t *__restrict__ out_depth,
-    uint64_t *__restrict__ out_anc, int32_t *__restrict__ rank_out) {
-  const int b = blockIdx.x, i = threadIdx.x & (PROPD_MAX_TREE - 1), q = threadIdx.x / PROPD_MAX_TREE;
+//   probability: the log marginal of a node's sequence is the sum of log q over its root path
+//     (the cached ancestor set, root excluded, in root-to-node order), log q = own score - log sum exp of
+//     the parent's row; it fails when the marginal is below the threshold, or when `keep_count` or
+//     more sequences of the tree are more probable (equal marginals: the lower node index counts
+//     as more probable); a marginal of zero probability always fails.
+// The kernel is a chain of dependent reads (counts, rows), not bytes: as two kernels, three for the probability
+// criterion, it had a launch and a first read more each, and the origins of the rows went through memory.  Pruning
+// call, us: 16 sequences x 40 heads x 128 nodes 236 -> 232, probability criterion at 32 ragged trees 240 -> 233, 31 x 40 x 52
+// 118.5 -> 112, 1 x 64 nodes x 4096 76.1 -> 75.0, fp32 1 x 32 x 389 x 1011 28.2 -> 25.0.
+__global__ __launch_bounds__(kFinishThreads) void prune_finish_kernel(FinishArgs a) {
+  const int b = (int)(blockIdx.x >> a.log_split), slice = (int)(blockIdx.x & ((1u << a.log_split) - 1u));
+  const int i = threadIdx.x & (PROPD_MAX_TREE - 1), q = threadIdx.x / PROPD_MAX_TREE;
+  const int T_max = a.T_max;
   const size_t base = (size_t)b * T_max;
   // Everything this thread reads is requested before the first value is used: the tree size,
   // the tile count and the node's own words do not wait for each other.  Slots past the tree
   // are read too (they exist) and dropped.
   const bool slot = i < T_max, worker = q == 0;
-  const int T_raw = n_nodes[b];
+  const int T_raw = a.n_nodes[b];
   uint64_t a_lo = 0, a_hi = 0;
-  int my_token = -1;
+  int my_token = -1, my_depth = -1, my_parent = -1;
   if (worker && slot) {
-    a_lo = anc[(base + i) * 2];
-    a_hi = anc[(base + i) * 2 + 1];
-    my_token = token[base + i];
+    a_lo = a.anc[(base + i) * 2];
+    a_hi = a.anc[(base + i) * 2 + 1];
+    my_token = a.token[base + i];
+    my_depth = a.depth[base + i];
+    my_parent = a.parent[base + i];
   }
   __shared__ uint64_t s_fail[2], s_keep[2];
   __shared__ float s_q[PROPD_MAX_TREE], s_lm[PROPD_MAX_TREE];
-  __shared__ int s_sum[kCompactSplit][PROPD_MAX_TREE];
+  __shared__ int s_sum[kFinishSplit][PROPD_MAX_TREE], s_orig[PROPD_MAX_TREE], s_last;
 
-  if (crit.kind == 0) {
-    // rank = the counts of all column tiles (row_base == NULL: nothing was scored)
-    int n_tiles = 0;
-    if (row_base) {
-      const int m_total = row_base[B];
-      if (bf16) {
-        // left by the scoring kernel (which has nothing to do without rows): worked out here it stood
-        // 2 us in front of the first count
-        const int left = *plan_tiles;
-        if (m_total > 0) n_tiles = left;
-      } else if (m_total > 0) {
-        n_tiles = f32_plan(m_total, vocab).n_tiles;
-      }
-    }
+  int m_total = 0, n_tiles = 0;
+  if (a.scored) {
+    m_total = a.row_base[a.B];
+    // left by the scoring kernel (which has nothing to do without rows): worked out here it stood
+    // 2 us in front of the first count
+    const int left = a.notes[kNoteTiles];
+    if (m_total > 0) n_tiles = a.bf16 ? left : f32_plan(m_total, a.vocab).n_tiles;
+  }
+  if (a.crit.kind == 0) {
+    // rank = the counts of all column tiles (none where nothing was scored)
     int sum = 0;
     if (slot && i > 0) {
-      const int32_t *src = cnt_part + base + i;
-      const size_t stride = (size_t)B * T_max;
+      const int32_t *src = a.cnt_part + base + i;
+      const size_t stride = (size_t)a.B * T_max;
       constexpr int kInFlight = 32;
-      for (int t0 = q; t0 < n_tiles; t0 += kCompactSplit * kInFlight) {
+      for (int t0 = q; t0 < n_tiles; t0 += kFinishSplit * kInFlight) {
         int v[kInFlight];
 #pragma unroll
         for (int k = 0; k < kInFlight; ++k) {
-          const int t = t0 + kCompactSplit * k;
+          const int t = t0 + kFinishSplit * k;
           v[k] = t < n_tiles ? src[(size_t)t * stride] : 0;
         }
 #pragma unroll
@@ -1042,6 +1087,49 @@ __global__ __launch_bounds__(PROPD_MAX_TREE * kCompactSplit) void prune_compact_
       }
     }
     s_sum[q][i] = sum;
+  } else {
+    // log q of the children of every score row: the log-sum-exp of the row from its tile partials, eight
+    // threads per row (the largest maximum first, then one exponential per partial)
+    if (worker) s_q[i] = 0.f;
+    const int m0 = a.row_base[b], m1 = a.row_base[b + 1];
+    const int part = threadIdx.x & (kRowLanes - 1);
+    __syncthreads();
+    for (int mb = m0; mb < m1; mb += kFinishThreads / kRowLanes) {
+      const int m = mb + (int)threadIdx.x / kRowLanes;
+      const bool row = m < m1;
+      const float *src = a.lse_part + (size_t)(row ? m : m0) * a.parts * 2;
+      const int pos = a.row_info[2 * (row ? m : m0)], cc = row ? a.row_info[2 * m + 1] : 0;
+      float mx = -INFINITY, sum = 0.f;
+      constexpr int kInFlight = 16;
+      for (int t0 = part; t0 < n_tiles; t0 += kRowLanes * kInFlight) {
+        float pm[kInFlight], ps[kInFlight], top = mx;
+#pragma unroll
+        for (int k = 0; k < kInFlight; ++k) {
+          const int t = t0 + kRowLanes * k, tt = t < n_tiles ? t : t0;
+          pm[k] = src[2 * tt];
+          ps[k] = src[2 * tt + 1];
+        }
+#pragma unroll
+        for (int k = 0; k < kInFlight; ++k) top = fmaxf(top, pm[k]);  // past the end: the first once more
+        sum = mx == -INFINITY ? 0.f : sum * expf(mx - top);
+#pragma unroll
+        for (int k = 0; k < kInFlight; ++k)
+          if (t0 + kRowLanes * k < n_tiles && pm[k] != -INFINITY) sum += ps[k] * expf(pm[k] - top);
+        mx = top;
+      }
+#pragma unroll
+      for (int o = kRowLanes / 2; o > 0; o >>= 1) {
+        const float m2 = __shfl_xor(mx, o, kWave), s2 = __shfl_xor(sum, o, kWave);
+        lse_merge(mx, sum, m2, s2);
+      }
+      const float lse = mx + logf(sum);
+      for (int e = part; e < cc; e += kRowLanes) {
+        const int c = a.child_list[pos + e];
+        const int t = a.token[c], nd = c - (int)base;
+        // a token id outside the vocabulary has probability 0
+        if (nd >= 0 && nd < T_max) s_q[nd] = (t >= 0 && t < a.vocab) ? a.own[c] - lse : -INFINITY;
+      }
+    }
   }
   const int T = clamp_tree(T_raw, T_max);
   const bool valid = i < T;
@@ -1050,24 +1138,22 @@ __global__ __launch_bounds__(PROPD_MAX_TREE * kCompactSplit) void prune_compact_
     my_token = -1;
   }
   __syncthreads();
-  // from here on one thread per node does the work; the others only meet it at the barriers
+  // one thread per node does the work; the others only meet it at the barriers
   bool fail = false;
-  if (crit.kind == 0) {
+  if (a.crit.kind == 0) {
     if (worker) {
       int my_rank = -1;
       if (valid) {
         my_rank = 0;
 #pragma unroll
-        for (int k = 0; k < kCompactSplit; ++k) my_rank += s_sum[k][i];
+        for (int k = 0; k < kFinishSplit; ++k) my_rank += s_sum[k][i];
         // a token id outside the vocabulary can be in no top-k list
-        if (i > 0 && (my_token < 0 || my_token >= vocab)) my_rank = vocab;
+        if (i > 0 && (my_token < 0 || my_token >= a.vocab)) my_rank = a.vocab;
       }
-      if (rank_out && i < T_max) rank_out[base + i] = my_rank;
-      fail = valid && i > 0 && my_rank >= crit.top_k;
+      if (a.rank_out && slot && slice == 0) a.rank_out[base + i] = my_rank;
+      fail = valid && i > 0 && my_rank >= a.crit.top_k;
     }
   } else {
-    if (worker) s_q[i] = (valid && i > 0) ? logq[base + i] : 0.f;
-    __syncthreads();
     float lm = 0.f;
     if (worker && valid && i > 0) {
       uint64_t lo = a_lo & ~1ull, hi = a_hi;
@@ -1083,188 +1169,137 @@ __global__ __launch_bounds__(PROPD_MAX_TREE * kCompactSplit) void prune_compact_
     if (worker) s_lm[i] = valid ? lm : -INFINITY;
     __syncthreads();
     if (worker && valid && i > 0) {
-      if (crit.kind == 1) {
-        fail = !(lm >= crit.log_threshold);
+      if (a.crit.kind == 1) {
+        fail = !(lm >= a.crit.log_threshold);
       } else {
         int ahead = 0;
         for (int j = 0; j < T; ++j) ahead += (s_lm[j] > lm) || (s_lm[j] == lm && j < i);
-        fail = ahead >= crit.keep_count;
+        fail = ahead >= a.crit.keep_count;
       }
       fail = fail || !(lm > -INFINITY);
     }
-    if (worker && crit.log_marginal && i < T_max) crit.log_marginal[base + i] = valid ? lm : 0.f;
+    if (worker && a.crit.log_marginal && slot && slice == 0) a.crit.log_marginal[base + i] = valid ? lm : 0.f;
   }
-  if (!worker) {  // the two barriers below
-    __syncthreads();
-    __syncthreads();
-    return;
+  if (worker) {
+    const uint64_t fb = __ballot(fail);
+    if ((i & 63) == 0) s_fail[i >> 6] = fb;
   }
-  const uint64_t fb = __ballot(fail);
-  if ((i & 63) == 0) s_fail[i >> 6] = fb;
   __syncthreads();
   // a node goes as soon as any node of its root path failed
-  const bool keep = valid && ((a_lo & s_fail[0]) | (a_hi & s_fail[1])) == 0;
-  const uint64_t kb = __ballot(keep);
-  if ((i & 63) == 0) s_keep[i >> 6] = kb;
+  const bool keep = worker && valid && ((a_lo & s_fail[0]) | (a_hi & s_fail[1])) == 0;
+  if (worker) {
+    const uint64_t kb = __ballot(keep);
+    if ((i & 63) == 0) s_keep[i >> 6] = kb;
+  }
   __syncthreads();
   const uint64_t k_lo = s_keep[0], k_hi = s_keep[1];
   const int kept = __popcll(k_lo) + __popcll(k_hi);
   const int ni = keep ? popc128_below(k_lo, k_hi, i) : -1;
-  if (i < T_max) new_index[base + i] = ni;
-  if (keep) {
-    orig_index[base + ni] = i;
-    out_token[base + ni] = my_token;
-    out_depth[base + ni] = depth[base + i];
-    int p = i == 0 ? -1 : parent[base + i];
-    out_parent[base + ni] = (p >= 0 && p < T) ? popc128_below(k_lo, k_hi, p) : -1;
-    // subsample the cached mask: keep the columns of survivors, renumbered
-    uint64_t r_lo = 0, r_hi = 0;
-    uint64_t w = a_lo & k_lo;
-    while (w) {
-      const int j = __ffsll((long long)w) - 1;
-      w &= w - 1;
-      const int pos = popc128_below(k_lo, k_hi, j);
-      if (pos < 64) r_lo |= 1ull << pos; else r_hi |= 1ull << (pos - 64);
+  if (keep) s_orig[ni] = i;
+  if (worker && slice == 0) {
+    if (slot) a.new_index[base + i] = ni;
+    if (keep) {
+      a.orig_index[base + ni] = i;
+      a.out_token[base + ni] = my_token;
+      a.out_depth[base + ni] = my_depth;
+      const int p = i == 0 ? -1 : my_parent;
+      a.out_parent[base + ni] = (p >= 0 && p < T) ? popc128_below(k_lo, k_hi, p) : -1;
+      // subsample the cached mask: keep the columns of survivors, renumbered
+      uint64_t r_lo = 0, r_hi = 0;
+      uint64_t w = a_lo & k_lo;
+      while (w) {
+        const int j = __ffsll((long long)w) - 1;
+        w &= w - 1;
+        const int pos = popc128_below(k_lo, k_hi, j);
+        if (pos < 64) r_lo |= 1ull << pos; else r_hi |= 1ull << (pos - 64);
+      }
+      w = a_hi & k_hi;
+      while (w) {
+        const int j = 64 + __ffsll((long long)w) - 1;
+        w &= w - 1;
+        const int pos = popc128_below(k_lo, k_hi, j);
+        if (pos < 64) r_lo |= 1ull << pos; else r_hi |= 1ull << (pos - 64);
+      }
+      a.out_anc[(base + ni) * 2] = r_lo;
+      a.out_anc[(base + ni) * 2 + 1] = r_hi;
     }
-    w = a_hi & k_hi;
-    while (w) {
-      const int j = 64 + __ffsll((long long)w) - 1;
-      w &= w - 1;
-      const int pos = popc128_below(k_lo, k_hi, j);
-      if (pos < 64) r_lo |= 1ull << pos; else r_hi |= 1ull << (pos - 64);
+    if (i >= kept && slot) {
+      a.orig_index[base + i] = -1;
+      a.out_token[base + i] = -1;
+      a.out_depth[base + i] = -1;
+      a.out_parent[base + i] = -1;
+      a.out_anc[(base + i) * 2] = 0;
+      a.out_anc[(base + i) * 2 + 1] = 0;
     }
-    out_anc[(base + ni) * 2] = r_lo;
-    out_anc[(base + ni) * 2 + 1] = r_hi;
+    if (i == 0) {
+      a.keep_bits[2 * b] = k_lo;
+      a.keep_bits[2 * b + 1] = k_hi;
+      __hip_atomic_store(a.n_kept + b, kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (a.B > 1 && a.scored) {
+        // The prefix sum of the survivor counts is left to the workgroup that finds all other sequences arrived;
+        // nobody waits, and the counter was cleared by the preparation.  Count and arrival go through to
+        // where all workgroups see them, in this order (a fence would also write the caches back).
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        s_last = __hip_atomic_fetch_add(a.notes + kNoteArrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.B - 1;
+      }
+      if (a.out_n_nodes) a.out_n_nodes[b] = kept;
+      if (a.B == 1) {
+        a.cu_nodes[0] = 0;
+        a.cu_nodes[1] = kept;
+      }
+    }
   }
-  if (i >= kept && i < T_max) {
-    orig_index[base + i] = -1;
-    out_token[base + i] = -1;
-    out_depth[base + i] = -1;
-    out_parent[base + i] = -1;
-    out_anc[(base + i) * 2] = 0;
-    out_anc[(base + i) * 2 + 1] = 0;
+  __syncthreads();  // s_orig
+  // ---- payload rows.  The counted pieces of all payloads are one list, of which a slice takes an equal part.
+  {
+    unsigned long long total = 0, start = 0;
+    for (int p = 0; p < a.pa.n; ++p) total += (unsigned long long)a.pa.outer[p] * (unsigned)kept * a.pa.per_row[p];
+    const unsigned long long share = (total + (1u << a.log_split) - 1) >> a.log_split;
+    const unsigned long long lo = share * (unsigned)slice, hi = lo + share < total ? lo + share : total;
+    for (int p = 0; p < a.pa.n; ++p) {
+      const unsigned long long items = (unsigned long long)a.pa.outer[p] * (unsigned)kept * a.pa.per_row[p];
+      const unsigned long long from = lo > start ? lo - start : 0, to = hi > start ? (hi - start < items ? hi - start : items) : 0;
+      start += items;
+      if (from >= to) continue;  // uniform
+      const char *src = a.pa.src[p] + b * a.pa.stride_b[p];
+      char *dst = a.pa.dst[p] + b * a.pa.stride_b[p];
+      const long long so = a.pa.stride_outer[p], st = a.pa.stride_t[p];
+      if (items < (1ull << 31)) {
+        if (a.pa.vec16[p])
+          gather_pieces<uint32_t, u32x4>(src, dst, so, st, (uint32_t)from, (uint32_t)to, (uint32_t)kept, (uint32_t)a.pa.per_row[p], s_orig);
+        else
+          gather_pieces<uint32_t, uint8_t>(src, dst, so, st, (uint32_t)from, (uint32_t)to, (uint32_t)kept, (uint32_t)a.pa.per_row[p], s_orig);
+      } else {
+        if (a.pa.vec16[p])
+          gather_pieces<uint64_t, u32x4>(src, dst, so, st, from, to, (uint64_t)kept, (uint64_t)a.pa.per_row[p], s_orig);
+        else
+          gather_pieces<uint64_t, uint8_t>(src, dst, so, st, from, to, (uint64_t)kept, (uint64_t)a.pa.per_row[p], s_orig);
+      }
+    }
   }
-  if (i == 0) {
-    keep_bits[2 * b] = k_lo;
-    keep_bits[2 * b + 1] = k_hi;
-    n_kept[b] = kept;
-    if (out_n_nodes) out_n_nodes[b] = kept;
-  }
-}
-
-// ------------------------------------------------------------------------------------
-// payload rows of survivors
-// ------------------------------------------------------------------------------------
-struct PayloadArgs {
-  const char *src[PROPD_MAX_PAYLOADS];
-  char *dst[PROPD_MAX_PAYLOADS];
-  unsigned long long row_bytes[PROPD_MAX_PAYLOADS];
-  unsigned outer[PROPD_MAX_PAYLOADS];
-  long long stride_b[PROPD_MAX_PAYLOADS], stride_outer[PROPD_MAX_PAYLOADS],
-      stride_t[PROPD_MAX_PAYLOADS];
-  int vec16[PROPD_MAX_PAYLOADS];  // rows, strides and bases are all 16-byte multiples
-  int fast[PROPD_MAX_PAYLOADS];   // and the offsets within a (b, o) slot have 31 bits
-  unsigned block_end[PROPD_MAX_PAYLOADS];  // flattened grid: blocks of payloads 0..p end here
-  unsigned slices[PROPD_MAX_PAYLOADS];     // item slices per (b, o) slot
-  int n;
-};
-
-constexpr int kGatherThreads = 256;
-
-// Work items are (survivor row j, 16-byte piece c) pairs of one (b, o) slot of one payload.
-// The grid is flat: a block finds its payload from the per-payload block counts, then its
-// (b, o) slot and its slice of that slot's item list.  Every
-// thread moves up to kGatherItems independent pieces, so the copies of a long row (hidden
-// states) and of many short rows (tree K/V) are equally spread over the chip.
-// What bounds it is the chain of dependent reads in front of the copy, so there is little of it: block
-// numbers are divided in 32 bits, an item's row and piece come from one division per thread, a
-// row's origin says by itself whether it exists (the decision kernel leaves -1 in the slots past
-// the last survivor), and pieces that do not exist are asked for beyond the end of the buffer,
-// where they cost nothing.  (Left out by branches they made the compiler wait for each load: 7 us more.)
-// Pruning call, us, with divisions in 64 bits, a count in front and the first row re-read instead / now: 16
-// x 40 heads x 128 nodes, a quarter of them kept, 41 MB moved 241.6 / 237.8, 1 x 32 heads x 64 nodes 78.0 / 76.0.
-constexpr int kGatherItems = 8;
-constexpr int kBufferWord3 = 0x00027000;  // a buffer of bytes, not swizzled
-
-__global__ __launch_bounds__(kGatherThreads) void gather_rows_kernel(
-    PayloadArgs args, int B, int T_max, const int32_t *__restrict__ orig_index,
-    const int32_t *__restrict__ n_kept, int32_t *__restrict__ cu_nodes) {
-  static_assert(kGatherThreads == kScanThreads, "the extra block runs the workgroup scan");
-  if (blockIdx.x == args.block_end[args.n - 1]) {
-    // one block past the payload blocks: the prefix sum of the survivor counts rides along
-    // with this launch instead of taking one of its own
-    block_exclusive_scan(n_kept, cu_nodes, B);
-    return;
-  }
-  int pl = 0;
-  while (pl < args.n - 1 && blockIdx.x >= args.block_end[pl]) ++pl;
-  const unsigned local = blockIdx.x - (pl > 0 ? args.block_end[pl - 1] : 0);
-  const unsigned bo = local / args.slices[pl], slice = local - bo * args.slices[pl];
-  const unsigned bu = bo / args.outer[pl], o = bo - bu * args.outer[pl];
-  const int b = (int)bu;
-  if (b >= B) return;
-  const int32_t *origin = orig_index + (size_t)b * T_max;
-  const unsigned long long unit = args.vec16[pl] ? 16 : 1;  // bytes per piece
-  const unsigned long long per_row = args.row_bytes[pl] / unit;
-  const long long stride_t = args.stride_t[pl];
-  const char *sbase = args.src[pl] + b * args.stride_b[pl] + o * args.stride_outer[pl];
-  char *dbase = args.dst[pl] + b * args.stride_b[pl] + o * args.stride_outer[pl];
-  const unsigned long long first =
-      ((unsigned long long)slice * kGatherItems) * kGatherThreads + threadIdx.x;
-  if (args.fast[pl]) {
-    // the common case: 16-byte pieces, 32-bit offsets, all loads of the thread's pieces in flight
-    // before the first store.  Buffer accesses past the end of a buffer read nothing and write
-    // nothing, so a piece of a row that does not exist needs no branch.
-    constexpr uint32_t kNowhere = 0x80000000u;
-    const uint32_t extent = (uint32_t)((T_max - 1) * stride_t) + (uint32_t)args.row_bytes[pl];
-    const auto src = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(sbase), 0, (int)extent, kBufferWord3);
-    const auto dst = __builtin_amdgcn_make_buffer_rsrc(dbase, 0, (int)extent, kBufferWord3);
-    const uint32_t per32 = (uint32_t)per_row, rows = kGatherThreads / per32, rest = kGatherThreads - rows * per32;
-    const uint32_t stride32 = (uint32_t)stride_t;
-    uint32_t j = (uint32_t)first / per32, c = (uint32_t)first - j * per32, to[kGatherItems];
-    int i[kGatherItems];
-    u32x4 v[kGatherItems];
+  if (slice != 0 || a.B == 1 || !a.scored || !s_last) return;  // uniform
+  // exclusive scan, a run of sequences per thread
+  __shared__ int s_wave[kFinishThreads / kWave];
+  const int per = (a.B + kFinishThreads - 1) / kFinishThreads, x_lo = (int)threadIdx.x * per;
+  const int x_hi = x_lo + per < a.B ? x_lo + per : a.B;
+  int sum = 0;
+  for (int x = x_lo; x < x_hi; ++x) sum += __hip_atomic_load(a.n_kept + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  int incl = sum;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-    for (int k = 0; k < kGatherItems; ++k) {
-      const bool in = j < (uint32_t)T_max;
-      i[k] = origin[in ? j : 0];
-      to[k] = in ? j * stride32 + c * 16u : kNowhere;
-      const uint32_t from = c * 16u;
-      j += rows;
-      c += rest;
-      j += c >= per32 ? 1u : 0u;
-      c -= c >= per32 ? per32 : 0u;
-      v[k][0] = from;
-    }
-#pragma unroll
-    for (int k = 0; k < kGatherItems; ++k) {
-      const bool in = i[k] >= 0 && i[k] < T_max && to[k] != kNowhere;
-      const uint32_t from = in ? (uint32_t)i[k] * stride32 + v[k][0] : kNowhere;
-      to[k] = in ? to[k] : kNowhere;
-      v[k] = __builtin_amdgcn_raw_buffer_load_b128(src, from, 0, 0);
-    }
-#pragma unroll
-    for (int k = 0; k < kGatherItems; ++k) __builtin_amdgcn_raw_buffer_store_b128(v[k], dst, to[k], 0, 0);
-    return;
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int up = __shfl_up(incl, o, kWave);
+    if (lane >= o) incl += up;
   }
-  int kept = n_kept[b];
-  kept = kept > T_max ? T_max : kept;
-  const unsigned long long items = (unsigned long long)kept * per_row;
-#pragma unroll 1
-  for (int k = 0; k < kGatherItems; ++k) {
-    const unsigned long long item = first + (unsigned long long)k * kGatherThreads;
-    if (item >= items) break;
-    const int j = (int)(item / per_row);
-    const unsigned long long c = item - (unsigned long long)j * per_row;
-    const int i = origin[j];
-    if (i < 0 || i >= T_max) continue;
-    const char *s = sbase + (long long)i * stride_t + c * unit;
-    char *d = dbase + (long long)j * stride_t + c * unit;
-    if (args.vec16[pl])
-      *reinterpret_cast<u32x4 *>(d) = *reinterpret_cast<const u32x4 *>(s);
-    else
-      *d = *s;
+  if (lane == kWave - 1) s_wave[wv] = incl;
+  __syncthreads();
+  int run = incl - sum;
+  for (int w = 0; w < wv; ++w) run += s_wave[w];
+  for (int x = x_lo; x < x_hi; ++x) {
+    a.cu_nodes[x] = run;
+    run += __hip_atomic_load(a.n_kept + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  if (threadIdx.x == kFinishThreads - 1) a.cu_nodes[a.B] = run;  // its run of sequences is the last, or empty
 }
 
 }  // namespace propd
@@ -1308,7 +1343,7 @@ static propd_status prune_impl(
     return PROPD_ERR_INVALID_ARG;
   const int B = tree->B, T_max = tree->T_max;
   if ((long long)B * T_max > (1ll << 24)) return PROPD_ERR_UNSUPPORTED;
-  long long max_rows = 0, total_blocks = 0;
+  long long total_blocks = 0;  // of 2048 pieces
   PayloadArgs pa = {};
   for (int p = 0; p < n_payloads; ++p) {
     const propd_payload &pl = payloads[p];
@@ -1317,7 +1352,7 @@ static propd_status prune_impl(
       return PROPD_ERR_INVALID_ARG;
     pa.src[p] = reinterpret_cast<const char *>(pl.src);
     pa.dst[p] = reinterpret_cast<char *>(pl.dst);
-    pa.row_bytes[p] = pl.row_bytes;
+    pa.outer[p] = (unsigned)pl.outer;
     pa.stride_b[p] = pl.stride_b;
     pa.stride_outer[p] = pl.stride_outer;
     pa.stride_t[p] = pl.stride_t;
@@ -1325,20 +1360,14 @@ static propd_status prune_impl(
                           (uintptr_t)pl.row_bytes | (uintptr_t)pl.stride_b |
                           (uintptr_t)pl.stride_outer | (uintptr_t)pl.stride_t;
     pa.vec16[p] = (any & 15) == 0;
-    const long long rows = (long long)B * pl.outer;  // grid.x: one slot per (b, o)
+    pa.per_row[p] = pl.row_bytes / (pa.vec16[p] ? 16 : 1);
+    const long long rows = (long long)B * pl.outer;
     if (rows > (1ll << 31) - 1) return PROPD_ERR_UNSUPPORTED;
-    max_rows = rows > max_rows ? rows : max_rows;
-    const long long pieces = (long long)T_max * (long long)(pl.row_bytes / (pa.vec16[p] ? 16 : 1));
-    const long long slices = (pieces + kGatherThreads * kGatherItems - 1) /
-                             (kGatherThreads * kGatherItems);
+    const long long pieces = (long long)T_max * (long long)pa.per_row[p];
+    const long long slices = (pieces + 2047) / 2048;
     if (slices > (1 << 24)) return PROPD_ERR_UNSUPPORTED;
-    pa.slices[p] = (unsigned)slices;
-    pa.fast[p] = pa.vec16[p] && pl.stride_t < (1ll << 31) && pl.row_bytes < (1ull << 31) &&
-                 (T_max - 1) * (long long)pl.stride_t + (long long)pl.row_bytes < (1ll << 31) - 16 && pieces < (1ll << 30);
     total_blocks += rows * slices;
     if (total_blocks > (1ll << 31) - 2) return PROPD_ERR_UNSUPPORTED;
-    pa.outer[p] = (unsigned)pl.outer;
-    pa.block_end[p] = (unsigned)total_blocks;
   }
   const size_t need = early_prune_workspace_bytes(B, T_max, vocab);
   if (!workspace || workspace_bytes < need) return PROPD_ERR_WORKSPACE;
@@ -1373,6 +1402,7 @@ static propd_status prune_impl(
     pr.row_base = ws.row_base;
     pr.row_info = ws.row_info;
     pr.child_list = ws.child_list;
+    pr.notes = ws.notes;
     pr.own = ws.own;
     const unsigned prep_grid = (unsigned)((B + kTableWaves - 1) / kTableWaves) +
                                (unsigned)B * (unsigned)((T_max + kOwnNodes - 1) / kOwnNodes);
@@ -1392,7 +1422,7 @@ static propd_status prune_impl(
     tb.cnt_stride = B * T_max;
     tb.lse_part = ws.lse_part;
     tb.parts = (int)ws.parts;
-    tb.n_tiles = reinterpret_cast<int32_t *>(ws.logq);  // unused by the top-k criterion otherwise
+    tb.n_tiles = ws.notes + kNoteTiles;
     if (dt == PROPD_BF16) {
       static bool attr_set = false;
       if (!attr_set) {
@@ -1434,25 +1464,44 @@ static propd_status prune_impl(
                            reinterpret_cast<const float *>(hidden_states),
                            reinterpret_cast<const float *>(head_weight), tb);
     }
-    if (crit.kind != 0)
-      hipLaunchKernelGGL(row_lse_kernel, dim3((unsigned)ws.row_cap), dim3(kWave), 0, st, B, hidden, vocab, cus, force, max_mi,
-                         dt == PROPD_BF16 ? 1 : 0, tb, ws.logq);
   }
   if (!launch_ok()) return PROPD_ERR_DEVICE;
-  hipLaunchKernelGGL(prune_compact_kernel, dim3(B), dim3(PROPD_MAX_TREE * kCompactSplit), 0, st, B, T_max,
-                     vocab, dt == PROPD_BF16 ? 1 : 0, crit, reinterpret_cast<const int32_t *>(ws.logq),
-                     tree->n_nodes, tree->parent, tree->token,
-                     tree->depth, tree->anc, scored ? ws.row_base : nullptr, ws.cnt_part, ws.logq,
-                     keep_bits, new_index, orig_index, n_kept, tree_out->n_nodes, tree_out->parent,
-                     tree_out->token, tree_out->depth, tree_out->anc, rank_out);
-  if (n_payloads > 0) {
-    pa.n = n_payloads;
-    dim3 grid((unsigned)(total_blocks + 1));  // the extra block writes cu_nodes
-    hipLaunchKernelGGL(gather_rows_kernel, grid, dim3(kGatherThreads), 0, st, pa, B, T_max,
-                       orig_index, n_kept, cu_nodes);
-  } else {
-    hipLaunchKernelGGL(cu_nodes_kernel, dim3(1), dim3(kScanThreads), 0, st, B, n_kept, cu_nodes);
-  }
+  FinishArgs fa;
+  fa.B = B;
+  fa.T_max = T_max;
+  fa.vocab = vocab;
+  fa.bf16 = dt == PROPD_BF16 ? 1 : 0;
+  fa.scored = scored ? 1 : 0;
+  fa.crit = crit;
+  fa.n_nodes = tree->n_nodes;
+  fa.parent = tree->parent;
+  fa.token = tree->token;
+  fa.depth = tree->depth;
+  fa.anc = tree->anc;
+  fa.row_base = ws.row_base;
+  fa.row_info = ws.row_info;
+  fa.child_list = ws.child_list;
+  fa.cnt_part = ws.cnt_part;
+  fa.own = ws.own;
+  fa.lse_part = ws.lse_part;
+  fa.parts = (int)ws.parts;
+  fa.notes = ws.notes;
+  fa.keep_bits = keep_bits;
+  fa.new_index = new_index;
+  fa.orig_index = orig_index;
+  fa.n_kept = n_kept;
+  fa.cu_nodes = cu_nodes;
+  fa.out_n_nodes = tree_out->n_nodes;
+  fa.out_parent = tree_out->parent;
+  fa.out_token = tree_out->token;
+  fa.out_depth = tree_out->depth;
+  fa.out_anc = tree_out->anc;
+  fa.rank_out = rank_out;
+  pa.n = n_payloads;
+  fa.pa = pa;
+  fa.log_split = finish_log_split(B, total_blocks, cus);
+  hipLaunchKernelGGL(prune_finish_kernel, dim3((unsigned)B << fa.log_split), dim3(kFinishThreads), 0, st, fa);
+  if (!scored && B > 1) hipLaunchKernelGGL(cu_nodes_kernel, dim3(1), dim3(kScanThreads), 0, st, B, n_kept, cu_nodes);
   return launch_ok() ? PROPD_OK : PROPD_ERR_DEVICE;
 }
 

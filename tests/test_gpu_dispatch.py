@@ -542,6 +542,68 @@ print("ranks as counted")
 """
 
 
+@pytest.mark.parametrize("B,T", [(1, 5), (2, 128), (3, 17), (255, 6), (256, 6), (257, 6), (513, 4), (1100, 3)])
+@pytest.mark.parametrize("crit", ["topk", "prob"])
+def test_prune_sequences_of_a_batch(pb, oracle, B, T, crit):
+    """One workgroup per sequence and many: decisions, payload rows and the prefix sum of the survivor counts, which the
+    last sequence to be decided writes; twice with one workspace, whose counter the second call finds used."""
+    rng = np.random.default_rng([B, T])
+    trees = [synth.random_tree(rng, int(n)) for n in rng.integers(1, T + 1, B)]
+    trees[0] = synth.random_tree(rng, T)
+    n_nodes, parent, _ = synth.pad_trees(trees, T)
+    token = rng.integers(0, 300, (B, T)).astype(np.int32)
+    tree = dev_tree(pb, n_nodes, parent, token)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(B)
+    hid = torch.randn(B, T, 32, device="cuda", generator=gen).to(torch.bfloat16)
+    w = torch.randn(300, 32, device="cuda", generator=gen).to(torch.bfloat16)
+    pay = [hid, torch.randn(B, 3, T, 24, device="cuda", generator=gen), torch.randint(0, 255, (B, T, 7), device="cuda", generator=gen).to(torch.uint8)]
+    ws = torch.empty(pb.workspace_bytes(pb.WS_EARLY_PRUNE, B, T, hidden=32, vocab=300), dtype=torch.uint8, device="cuda")
+    ws.fill_(0xa5)
+    for again in range(2):
+        dst = [torch.full_like(x, 3) for x in pay]
+        if crit == "topk":
+            r = pb.propd_early_prune(tree, hid, w, 150, payloads=pay, payload_out=dst, want_rank=True, workspace=ws)
+            fail_rank = to_host(r.rank)
+        else:
+            r = pb.propd_early_prune_prob(tree, hid, w, keep_count=max(1, T // 2), payloads=pay, payload_out=dst,
+                                          want_log_marginal=True, workspace=ws)
+            lm = to_host(r.log_marginal)
+            fail_rank = np.zeros((B, T), np.int32)
+            for b in range(B):  # the kernel's own marginals, ranked: equal ones by node index
+                n = int(n_nodes[b])
+                for i in range(1, n):
+                    fail_rank[b, i] = 500 if sum(lm[b, j] > lm[b, i] or (lm[b, j] == lm[b, i] and j < i) for j in range(n)) >= max(1, T // 2) else 0
+        ref = oracle.prune_compact(n_nodes, parent, token, fail_rank, 150)
+        for name in ("new_index", "orig_index", "n_kept", "cu_nodes"):
+            assert (to_host(getattr(r, name)) == ref[name]).all(), (name, again)
+        for name in ("parent", "token", "depth"):
+            assert (to_host(getattr(r.tree, name)) == ref[name]).all(), (name, again)
+        assert (to_host(r.tree.anc).view(np.uint64) == ref["anc"]).all()
+        orig = torch.from_numpy(ref["orig_index"]).cuda().long()
+        bs, js = (orig >= 0).nonzero(as_tuple=True)
+        for x, y in zip(pay, dst):
+            want = torch.full_like(x, 3)
+            if x.dim() == 3:
+                want[bs, js] = x[bs, orig[bs, js]]
+            else:
+                want[bs, :, js] = x[bs, :, orig[bs, js]]
+            assert torch.equal(want, y)
+
+
+def test_prune_payload_of_more_than_2_31_pieces(pb):
+    """Rows of an odd number of bytes, one byte per piece, with nothing pruned (top_k covers the vocabulary)."""
+    T, C = 128, (1 << 24) + 1
+    n_nodes, parent, _ = synth.pad_trees([synth.chain_tree(T)], T)
+    tree = dev_tree(pb, n_nodes, parent, np.zeros((1, T), np.int32))
+    src = torch.arange(T * C, device="cuda", dtype=torch.int64).mul_(2654435761).bitwise_right_shift_(13).to(torch.uint8).view(1, T, C)
+    dst = torch.zeros_like(src)
+    hid, w = torch.zeros(1, T, 32, device="cuda"), torch.zeros(4, 32, device="cuda")
+    r = pb.propd_early_prune(tree, hid, w, 4, payloads=[src], payload_out=[dst])
+    assert to_host(r.n_kept).tolist() == [T] and to_host(r.cu_nodes).tolist() == [0, T]
+    assert torch.equal(src, dst)
+
+
 def test_prune_rows_further_apart_than_32_bits(pb):
     """Hidden states of 4 GiB: the tallest tiles, which address rows by 32-bit offsets, are asked for
     and give way to the tallest that does not; 508 score rows, the last ones beyond 4 GB."""
