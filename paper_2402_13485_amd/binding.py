@@ -4,6 +4,10 @@ Argument marshalling only: every step of the verification path runs in the HIP
 kernels of ``libpropd.so``.  PyTorch tensors supply device memory and the current
 stream; nothing here computes on them.  There is no CPU fallback: if the library
 is missing or cannot be loaded, importing the entry points raises.
+
+The calls of a decoding loop are marshalled by ``_marshal.so`` (``csrc/marshal.cpp``), which makes
+the same checks in native code.  It hands back whatever it does not take, and the Python code below, the
+statement of the checks, then takes it or says what is wrong.
 """
 from __future__ import annotations
 
@@ -48,6 +52,27 @@ class _Payload(ctypes.Structure):
 
 
 _lib: Optional[ctypes.CDLL] = None
+_marshal = None
+
+
+def _init_marshal(lib: ctypes.CDLL) -> None:
+    """Gives the native marshalling, if it is built, the entry points of this library."""
+    global _marshal
+    try:
+        from . import _marshal as native
+    except ImportError:
+        return
+    native.init(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in (
+        "propd_tree_mask", "propd_tree_attention", "propd_early_prune", "propd_early_prune_prob", "propd_accept_path",
+        "propd_commit_path", "propd_workspace_bytes")))
+    _marshal = native
+
+
+def _native():
+    """The native marshalling; None if it is not built."""
+    if _lib is None:
+        load_library()
+    return _marshal
 
 
 def load_library() -> ctypes.CDLL:
@@ -105,6 +130,7 @@ def load_library() -> ctypes.CDLL:
     lib.propd_controller_best_size.argtypes = [vp, dbl, ctypes.POINTER(i32), vp, pd, pd]
     lib.propd_status_string.restype = ctypes.c_char_p
     lib.propd_status_string.argtypes = [ctypes.c_int]
+    _init_marshal(lib)
     _lib = lib
     return lib
 
@@ -136,6 +162,13 @@ class PropdError(RuntimeError):
 def _check(code: int, where: str) -> None:
     if code != 0:
         raise PropdError(code, where)
+
+
+def _done(result, where: str):
+    """What the native marshalling returned: the outputs, or the status of a call that was refused."""
+    if type(result) is int:
+        _check(result, where)
+    return result
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
@@ -204,6 +237,11 @@ def _workspace(nbytes: int, device, workspace: Optional[torch.Tensor]) -> torch.
 
 def propd_tree_mask(n_nodes: torch.Tensor, parent: torch.Tensor):
     """-> (depth int32 [B,T_max], anc int64 [B,T_max,2])"""
+    native = _native()
+    if native is not None:
+        r = native.tree_mask(n_nodes, parent, _stream)
+        if r is not None:
+            return _done(r, "propd_tree_mask")
     _dev(n_nodes, torch.int32, "n_nodes")
     _dev(parent, torch.int32, "parent")
     B, T_max = parent.shape
@@ -229,6 +267,12 @@ def propd_validate_tree(tree: "Tree") -> torch.Tensor:
 def propd_tree_attention(tree: Tree, q, k_cache, v_cache, k_tree, v_tree, seq_lens, scale: float,
                          out: Optional[torch.Tensor] = None,
                          workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
+    native = _native()
+    if native is not None:
+        r = native.tree_attention(tree.n_nodes, tree.parent, tree.token, tree.depth, tree.anc, q, k_cache, v_cache,
+                                  k_tree, v_tree, seq_lens, scale, out, workspace, _stream)
+        if r is not None:
+            return _done(r, "propd_tree_attention")
     dt = _dt(q)
     B, H, T_max, d = q.shape
     L_max = k_cache.shape[2]
@@ -293,6 +337,16 @@ def propd_early_prune_prob(tree: Tree, hidden_states: torch.Tensor, head_weight:
 
 def _early_prune(crit, tree, hidden_states, head_weight, payloads, payload_out, want_extra,
                  workspace) -> PruneResult:
+    native = _native()
+    if native is not None:
+        mode = -1 if crit[0] == "topk" else 0 if crit[0] == "threshold" else 1
+        r = native.early_prune(tree.n_nodes, tree.parent, tree.token, tree.depth, tree.anc, hidden_states, head_weight,
+                               mode, crit[1], payloads, payload_out, want_extra, workspace, _stream)
+        if r is not None:
+            _done(r, "propd_early_prune" if mode < 0 else "propd_early_prune_prob")
+            keep_bits, new_index, orig_index, n_kept, cu_nodes, n_nodes, parent, token, depth, anc, extra, moved = r
+            return PruneResult(keep_bits, new_index, orig_index, n_kept, cu_nodes, Tree(n_nodes, parent, token, depth, anc),
+                               extra if mode < 0 else None, moved, None if mode < 0 else extra)
     want_rank = want_extra and crit[0] == "topk"
     dt = _dt(hidden_states)
     B, T_max, hidden = hidden_states.shape
@@ -357,6 +411,12 @@ def _early_prune(crit, tree, hidden_states, head_weight, payloads, payload_out, 
 def propd_accept_path(tree: Tree, logits: torch.Tensor, path_stride: Optional[int] = None,
                       workspace: Optional[torch.Tensor] = None):
     """-> (accept_len int32 [B], accept_path int32 [B,path_stride], next_token int32 [B])"""
+    native = _native()
+    if native is not None:
+        r = native.accept_path(tree.n_nodes, tree.parent, tree.token, tree.depth, tree.anc, logits, path_stride, workspace,
+                               _stream)
+        if r is not None:
+            return _done(r, "propd_accept_path")
     dt = _dt(logits)
     B, T_max, vocab = logits.shape
     _dev(logits, logits.dtype, "logits")
@@ -404,6 +464,12 @@ def propd_commit_path(tree: Tree, accept_len: torch.Tensor, accept_path: torch.T
                       out_stride: Optional[int] = None) -> torch.Tensor:
     """Appends the accepted nodes' K/V rows to the caches IN PLACE, advances ``seq_lens`` in
     place and returns the step's tokens, int32 [B,out_stride], -1 padded."""
+    native = _native()
+    if native is not None:
+        r = native.commit_path(tree.n_nodes, tree.parent, tree.token, tree.depth, tree.anc, accept_len, accept_path,
+                               next_token, k_tree, v_tree, k_cache, v_cache, seq_lens, out_stride, _stream)
+        if r is not None:
+            return _done(r, "propd_commit_path")
     dt = _dt(k_tree)
     B, H, T_max, d = k_tree.shape
     L_max = k_cache.shape[2]

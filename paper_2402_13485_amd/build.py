@@ -1,14 +1,18 @@
-"""Build the HIP library for gfx950 with hipcc (cross-compiles without a GPU)."""
+"""Build the HIP library for gfx950 with hipcc (cross-compiles without a GPU), and the native argument
+marshalling of the Python binding with the host compiler."""
 from __future__ import annotations
 
 import os
 import re
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libpropd.so")
+MARSHAL_PATH = os.path.join(HERE, "_marshal.so")
+MARSHAL_SOURCE = "marshal.cpp"
 HEADER = os.path.join(HERE, os.pardir, "include", "propd.h")
 SOURCES = ["tree_mask.hip", "tree_attention.hip", "early_prune.hip", "accept_path.hip",
            "commit_path.hip", "tree_controller.hip"]
@@ -49,7 +53,21 @@ def stale() -> bool:
     return max(map(os.path.getmtime, sources)) > os.path.getmtime(LIB_PATH)
 
 
+def marshal_command(out: str) -> list:
+    from torch.utils import cpp_extension
+    includes = cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", *("-I" + i for i in includes),
+            "-o", out, os.path.join(CSRC, MARSHAL_SOURCE), *("-L" + d for d in cpp_extension.library_paths()),
+            "-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
 def build(verbose: bool = False) -> str:
+    if os.path.exists(os.path.join(CSRC, MARSHAL_SOURCE)):
+        cmd = marshal_command(MARSHAL_PATH + ".new")
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
+        os.replace(MARSHAL_PATH + ".new", MARSHAL_PATH)
     srcs = [os.path.join(CSRC, s) for s in SOURCES]
     extra = os.environ.get("PROPD_EXTRA_HIPCC_FLAGS", "").split()  # tuning experiments only
     new = LIB_PATH + ".new"

@@ -1,0 +1,366 @@
+// Argument marshalling of the Python binding in native code (host code only): checks of the tensors,
+// output tensors and the call of the C entry point, for the calls that a decoding loop makes once
+// or several times per step.  Their kernels take 5 to 15 us on small inputs, the same work in Python
+// 5 to 20 us per call: a whole step of 1 sequence, 1 head, fp32 took 98 us, most of it here.
+//
+// Nothing is decided here that binding.py does not say: a function returns None, with nothing enqueued,
+// whenever an argument is not what the entry point wants, and binding.py then goes through its own
+// checks, which name the argument.  Tensors of other classes than torch.Tensor and Parameter are left to it
+// too.  A call that the library refuses returns its status.  No state is kept but the addresses of the
+// entry points.
+#include <ATen/ATen.h>
+#include <Python.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include "../../include/propd.h"
+
+namespace {
+
+struct Entries {
+  decltype(&propd_tree_mask) tree_mask = nullptr;
+  decltype(&propd_tree_attention) tree_attention = nullptr;
+  decltype(&propd_early_prune) early_prune = nullptr;
+  decltype(&propd_early_prune_prob) early_prune_prob = nullptr;
+  decltype(&propd_accept_path) accept_path = nullptr;
+  decltype(&propd_commit_path) commit_path = nullptr;
+  decltype(&propd_workspace_bytes) workspace_bytes = nullptr;
+};
+
+struct NotThis {};  // the Python code takes over
+struct Raised {};   // a Python error is set
+struct Refused {
+  propd_status status;
+};
+
+const at::Tensor &tensor(PyObject *o) {
+  if (!THPVariable_CheckExact(o)) throw NotThis{};
+  return THPVariable_Unpack(o);
+}
+
+void need(bool ok) {
+  if (!ok) throw NotThis{};
+}
+
+void called(propd_status status) {
+  if (status != PROPD_OK) throw Refused{status};
+}
+
+// a contiguous tensor of this type in GPU memory
+const at::Tensor &dev(PyObject *o, at::ScalarType type) {
+  const at::Tensor &t = tensor(o);
+  need(t.is_cuda() && t.scalar_type() == type && t.is_contiguous());
+  return t;
+}
+
+propd_dtype type_of(const at::Tensor &t) {
+  if (t.scalar_type() == at::kBFloat16) return PROPD_BF16;
+  need(t.scalar_type() == at::kFloat);
+  return PROPD_F32;
+}
+
+void *ptr(PyObject *o) { return o == Py_None ? nullptr : tensor(o).data_ptr(); }
+
+long long whole(PyObject *o) {
+  need(PyLong_Check(o));
+  const long long v = PyLong_AsLongLong(o);
+  if (v == -1 && PyErr_Occurred()) {
+    PyErr_Clear();
+    throw NotThis{};
+  }
+  return v;
+}
+
+int32_t whole32(PyObject *o) {
+  const long long v = whole(o);
+  need(v >= INT32_MIN && v <= INT32_MAX);
+  return (int32_t)v;
+}
+
+int32_t size32(int64_t n) {
+  need(n <= INT32_MAX);
+  return (int32_t)n;
+}
+
+float real(PyObject *o) {
+  const double v = PyFloat_AsDouble(o);
+  if (v == -1.0 && PyErr_Occurred()) {
+    PyErr_Clear();
+    throw NotThis{};
+  }
+  return (float)v;
+}
+
+// binding._stream, called once the arguments have passed
+void *stream_of(PyObject *current) {
+  PyObject *o = PyObject_CallNoArgs(current);
+  void *p = o ? PyLong_AsVoidPtr(o) : nullptr;
+  Py_XDECREF(o);
+  if (PyErr_Occurred()) throw Raised{};
+  return p;
+}
+
+// the fields of binding.Tree: n_nodes, parent, token, depth, anc
+propd_tree tree_of(PyObject *const *f) {
+  const at::Tensor &parent = tensor(f[1]);
+  need(parent.dim() >= 2);
+  propd_tree t;
+  t.B = size32(parent.size(0));
+  t.T_max = size32(parent.size(1));
+  t.n_nodes = (const int32_t *)ptr(f[0]);
+  t.parent = (const int32_t *)parent.data_ptr();
+  t.token = (const int32_t *)ptr(f[2]);
+  t.depth = (const int32_t *)ptr(f[3]);
+  t.anc = (const uint64_t *)ptr(f[4]);
+  return t;
+}
+
+struct Workspace {
+  at::Tensor own;
+  void *ptr;
+  size_t bytes;
+};
+
+Workspace workspace(PyObject *o, size_t need_bytes, const at::Tensor &like) {
+  Workspace w;
+  if (o != Py_None) {
+    const at::Tensor &t = tensor(o);
+    w.bytes = t.nbytes();
+    need(w.bytes >= need_bytes && t.numel() * t.element_size() == (int64_t)w.bytes);
+    w.ptr = t.data_ptr();
+  } else {
+    w.own = at::empty({(int64_t)(need_bytes > 256 ? need_bytes : 256)}, like.options().dtype(at::kByte));
+    w.ptr = w.own.data_ptr();
+    w.bytes = (size_t)w.own.numel();
+  }
+  return w;
+}
+
+at::Tensor int_tensor(at::IntArrayRef sizes, const at::Tensor &like) {
+  return at::empty(sizes, like.options().dtype(at::kInt));
+}
+
+// Takes over the references of the items; NULL, with the error set, if one could not be made.
+PyObject *tuple_of(std::initializer_list<PyObject *> items) {
+  bool whole_tuple = true;
+  for (PyObject *o : items) whole_tuple = whole_tuple && o != nullptr;
+  PyObject *r = whole_tuple ? PyTuple_New((Py_ssize_t)items.size()) : nullptr;
+  Py_ssize_t n = 0;
+  for (PyObject *o : items) {
+    if (r) PyTuple_SET_ITEM(r, n++, o);
+    else Py_XDECREF(o);
+  }
+  return r;
+}
+
+PyObject *object(const at::Tensor &t) {
+  if (t.defined()) return THPVariable_Wrap(t);
+  Py_INCREF(Py_None);
+  return Py_None;
+}
+
+PyObject *object(PyObject *o) {
+  Py_INCREF(o);
+  return o;
+}
+
+Entries entries;
+
+template <class F>
+PyObject *guarded(F &&f) {
+  try {
+    return f();
+  } catch (const NotThis &) {
+  } catch (const Raised &) {
+    return nullptr;
+  } catch (const Refused &r) {
+    return PyLong_FromLong((long)r.status);
+  } catch (const std::exception &e) {  // for instance out of memory: the Python code meets the same and says so
+  }
+  Py_RETURN_NONE;
+}
+
+template <class E>
+void take(PyObject *o, E &entry) {
+  entry = reinterpret_cast<E>(PyLong_AsVoidPtr(o));
+}
+
+PyObject *py_init(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  if (n != 7) {
+    PyErr_SetString(PyExc_TypeError, "init: seven addresses");
+    return nullptr;
+  }
+  take(a[0], entries.tree_mask);
+  take(a[1], entries.tree_attention);
+  take(a[2], entries.early_prune);
+  take(a[3], entries.early_prune_prob);
+  take(a[4], entries.accept_path);
+  take(a[5], entries.commit_path);
+  take(a[6], entries.workspace_bytes);
+  if (PyErr_Occurred()) return nullptr;
+  Py_RETURN_NONE;
+}
+
+// tree_mask(n_nodes, parent, stream) -> (depth, anc)
+PyObject *py_tree_mask(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  return guarded([&]() -> PyObject * {
+    need(n == 3);
+    const at::Tensor &nodes = dev(a[0], at::kInt), &parent = dev(a[1], at::kInt);
+    need(parent.dim() == 2);
+    const int64_t B = parent.size(0), T = parent.size(1);
+    at::Tensor depth = int_tensor({B, T}, parent), anc = at::empty({B, T, 2}, parent.options().dtype(at::kLong));
+    called(entries.tree_mask(size32(B), size32(T), (const int32_t *)nodes.data_ptr(), (const int32_t *)parent.data_ptr(),
+                           (int32_t *)depth.data_ptr(), (uint64_t *)anc.data_ptr(), stream_of(a[2])));
+    return tuple_of({object(depth), object(anc)});
+  });
+}
+
+// tree_attention(*tree, q, k_cache, v_cache, k_tree, v_tree, seq_lens, scale, out, workspace, stream) -> out
+PyObject *py_tree_attention(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  return guarded([&]() -> PyObject * {
+    need(n == 15);
+    const propd_tree tree = tree_of(a);
+    const at::Tensor &q = tensor(a[5]);
+    const propd_dtype dt = type_of(q);
+    need(q.dim() == 4);
+    const int64_t B = q.size(0), H = q.size(1), T = q.size(2), d = q.size(3);
+    const at::Tensor &kc = dev(a[6], q.scalar_type()), &vc = dev(a[7], q.scalar_type());
+    const at::Tensor &kt = dev(a[8], q.scalar_type()), &vt = dev(a[9], q.scalar_type()), &seq = dev(a[10], at::kInt);
+    need(q.is_cuda() && q.is_contiguous() && kc.dim() == 4);
+    const int64_t L = kc.size(2);
+    need(kc.sizes() == at::IntArrayRef({B, H, L, d}) && vc.sizes() == kc.sizes() && kt.sizes() == q.sizes() && vt.sizes() == q.sizes());
+    need(tree.B == B && tree.T_max == T);
+    const at::Tensor out = a[12] == Py_None ? at::empty_like(q) : tensor(a[12]);
+    const Workspace w = workspace(a[13], entries.workspace_bytes(PROPD_WS_TREE_ATTENTION, tree.B, tree.T_max, size32(H), size32(d),
+                                                                 size32(L), 0, 0), q);
+    called(entries.tree_attention(&tree, dt, size32(H), size32(d), real(a[11]), q.data_ptr(), L ? kc.data_ptr() : nullptr,
+                                L ? vc.data_ptr() : nullptr, kt.data_ptr(), vt.data_ptr(), (const int32_t *)seq.data_ptr(),
+                                size32(L), out.data_ptr(), w.ptr, w.bytes, stream_of(a[14])));
+    return a[12] != Py_None ? object(a[12]) : object(out);
+  });
+}
+
+// early_prune(*tree, hidden, head, mode, value, payloads, payload_out, want_extra, workspace, stream) -> (keep_bits, new_index, orig_index,
+// n_kept, cu_nodes, n_nodes, parent, token, depth, anc, rank or log_marginal or None, [payloads]); mode -1: top-k, else propd_prob_mode
+PyObject *py_early_prune(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  return guarded([&]() -> PyObject * {
+    need(n == 14);
+    const propd_tree tree = tree_of(a);
+    const at::Tensor &hid = tensor(a[5]);
+    const propd_dtype dt = type_of(hid);
+    need(hid.dim() == 3 && hid.is_cuda() && hid.is_contiguous());
+    const at::Tensor &head = dev(a[6], hid.scalar_type());
+    const int64_t B = hid.size(0), T = hid.size(1), hidden = hid.size(2);
+    need(head.dim() == 2 && head.size(1) == hidden && tree.B == B && tree.T_max == T);
+    const int64_t vocab = head.size(0);
+    const long long mode = whole(a[7]);
+    const bool top_k = mode < 0, extra = PyObject_IsTrue(a[11]) == 1;
+    const int32_t count = top_k || mode == PROPD_PROB_RANK ? whole32(a[8]) : 0;
+    const float threshold = mode == PROPD_PROB_THRESHOLD ? real(a[8]) : 0.f;
+    need(PyList_Check(a[9]) || PyTuple_Check(a[9]));
+    const Py_ssize_t n_pay = PySequence_Fast_GET_SIZE(a[9]);
+    const bool given = a[10] != Py_None;
+    need(n_pay <= PROPD_MAX_PAYLOADS);
+    need(!given || ((PyList_Check(a[10]) || PyTuple_Check(a[10])) && PySequence_Fast_GET_SIZE(a[10]) >= n_pay));
+    propd_payload pay[PROPD_MAX_PAYLOADS];
+    at::Tensor made[PROPD_MAX_PAYLOADS];
+    for (Py_ssize_t i = 0; i < n_pay; ++i) {
+      const at::Tensor &src = tensor(PySequence_Fast_GET_ITEM(a[9], i));
+      need(src.is_cuda() && src.is_contiguous() && (src.dim() == 3 || src.dim() == 4));
+      const int64_t outer = src.dim() == 3 ? 1 : src.size(1);
+      need(src.size(0) == B && src.size(-2) == T);
+      if (!given) made[i] = at::empty_like(src);
+      const at::Tensor &dst = given ? tensor(PySequence_Fast_GET_ITEM(a[10], i)) : made[i];
+      need(dst.sizes() == src.sizes() && dst.scalar_type() == src.scalar_type() && dst.is_contiguous());
+      const int64_t row = src.size(-1) * src.element_size();
+      pay[i] = propd_payload{src.data_ptr(), dst.data_ptr(), (size_t)row, outer, outer * T * row, T * row, row};
+    }
+    // per-node and per-sequence outputs in one allocation each, every one of them on a multiple of 16 bytes
+    const bool rank = top_k && extra;
+    const auto i32 = hid.options().dtype(at::kInt), i64 = hid.options().dtype(at::kLong);
+    const auto nodes = at::empty_strided({rank ? 6 : 5, B, T}, {(B * T + 3) / 4 * 4, T, 1}, i32).unbind(0);
+    const auto counts = at::empty_strided({2, B}, {(B + 3) / 4 * 4, 1}, i32).unbind(0);
+    at::Tensor keep = at::empty({B, 2}, i64), cu = at::empty({B + 1}, i32), anc = at::empty({B, T, 2}, i64), more;
+    if (rank) more = nodes[5];
+    if (!top_k && extra) more = at::empty({B, T}, hid.options().dtype(at::kFloat));
+    int32_t *node[5];
+    for (int i = 0; i < 5; ++i) node[i] = (int32_t *)nodes[i].data_ptr();
+    propd_tree_out out;
+    out.n_nodes = (int32_t *)counts[1].data_ptr();
+    out.parent = node[2];
+    out.token = node[3];
+    out.depth = node[4];
+    out.anc = (uint64_t *)anc.data_ptr();
+    const Workspace w = workspace(a[12], entries.workspace_bytes(PROPD_WS_EARLY_PRUNE, tree.B, tree.T_max, 0, 0, 0, size32(hidden),
+                                                                 size32(vocab)), hid);
+    uint64_t *keep_p = (uint64_t *)keep.data_ptr();
+    int32_t *kept_p = (int32_t *)counts[0].data_ptr(), *cu_p = (int32_t *)cu.data_ptr();
+    void *st = stream_of(a[13]);
+    const propd_status done =
+        top_k ? entries.early_prune(&tree, dt, size32(hidden), size32(vocab), count, hid.data_ptr(), head.data_ptr(), keep_p, node[0],
+                                    node[1], kept_p, cu_p, &out, rank ? (int32_t *)more.data_ptr() : nullptr, (int32_t)n_pay, pay,
+                                    w.ptr, w.bytes, st)
+              : entries.early_prune_prob(&tree, dt, size32(hidden), size32(vocab), (propd_prob_mode)mode, threshold, count,
+                                         hid.data_ptr(), head.data_ptr(), keep_p, node[0], node[1], kept_p, cu_p, &out,
+                                         more.defined() ? (float *)more.data_ptr() : nullptr, (int32_t)n_pay, pay, w.ptr, w.bytes, st);
+    called(done);
+    PyObject *payloads = PyList_New(n_pay);
+    for (Py_ssize_t i = 0; payloads && i < n_pay; ++i) {
+      PyObject *o = given ? object(PySequence_Fast_GET_ITEM(a[10], i)) : object(made[i]);
+      if (o) PyList_SET_ITEM(payloads, i, o);
+      else Py_CLEAR(payloads);
+    }
+    return tuple_of({object(keep), object(nodes[0]), object(nodes[1]), object(counts[0]), object(cu), object(counts[1]),
+                     object(nodes[2]), object(nodes[3]), object(nodes[4]), object(anc), object(more), payloads});
+  });
+}
+
+// accept_path(*tree, logits, path_stride or None, workspace, stream) -> (accept_len, path, next_token)
+PyObject *py_accept_path(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  return guarded([&]() -> PyObject * {
+    need(n == 9);
+    const propd_tree tree = tree_of(a);
+    const at::Tensor &logits = tensor(a[5]);
+    const propd_dtype dt = type_of(logits);
+    need(logits.dim() == 3 && logits.is_cuda() && logits.is_contiguous() && tree.B == logits.size(0) && tree.T_max == logits.size(1));
+    const int32_t vocab = size32(logits.size(2)), stride = a[6] == Py_None ? tree.T_max : whole32(a[6]);
+    need(stride >= 0);
+    at::Tensor len = int_tensor({tree.B}, logits), path = int_tensor({tree.B, stride}, logits), next = int_tensor({tree.B}, logits);
+    const Workspace w = workspace(a[7], entries.workspace_bytes(PROPD_WS_ACCEPT_PATH, tree.B, tree.T_max, 0, 0, 0, 0, vocab), logits);
+    called(entries.accept_path(&tree, dt, vocab, logits.data_ptr(), (int32_t *)len.data_ptr(), (int32_t *)path.data_ptr(), stride,
+                             (int32_t *)next.data_ptr(), w.ptr, w.bytes, stream_of(a[8])));
+    return tuple_of({object(len), object(path), object(next)});
+  });
+}
+
+// commit_path(*tree, accept_len, path, next_token, k_tree, v_tree, k_cache, v_cache, seq_lens, out_stride or None, stream) -> tokens
+PyObject *py_commit_path(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  return guarded([&]() -> PyObject * {
+    need(n == 15);
+    const propd_tree tree = tree_of(a);
+    const at::Tensor &len = dev(a[5], at::kInt), &path = dev(a[6], at::kInt), &next = dev(a[7], at::kInt), &seq = dev(a[12], at::kInt);
+    const at::Tensor &kt = tensor(a[8]);
+    const propd_dtype dt = type_of(kt);
+    need(kt.dim() == 4 && kt.is_cuda() && kt.is_contiguous() && path.dim() >= 2);
+    const at::Tensor &vt = dev(a[9], kt.scalar_type()), &kc = dev(a[10], kt.scalar_type()), &vc = dev(a[11], kt.scalar_type());
+    const int64_t B = kt.size(0), H = kt.size(1), T = kt.size(2), d = kt.size(3);
+    need(kc.dim() == 4);
+    const int64_t L = kc.size(2);
+    need(vt.sizes() == kt.sizes() && kc.sizes() == at::IntArrayRef({B, H, L, d}) && vc.sizes() == kc.sizes() && tree.B == B && tree.T_max == T);
+    const int32_t stride = size32(path.size(1)), out_stride = a[13] == Py_None ? stride : whole32(a[13]);
+    need(out_stride >= 0);
+    at::Tensor out = int_tensor({B, out_stride}, kt);
+    called(entries.commit_path(&tree, dt, size32(H), size32(d), (const int32_t *)len.data_ptr(), (const int32_t *)path.data_ptr(), stride,
+                             (const int32_t *)next.data_ptr(), kt.data_ptr(), vt.data_ptr(), kc.data_ptr(), vc.data_ptr(), size32(L),
+                             (int32_t *)seq.data_ptr(), (int32_t *)out.data_ptr(), out_stride, stream_of(a[14])));
+    return object(out);
+  });
+}
+
+#define METHOD(name) {#name, (PyCFunction)(void (*)(void))py_##name, METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {METHOD(init),        METHOD(tree_mask),   METHOD(tree_attention), METHOD(early_prune),
+                         METHOD(accept_path), METHOD(commit_path), {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+extern "C" __attribute__((visibility("default"))) PyObject *PyInit__marshal() { return PyModule_Create(&module); }
