@@ -68,7 +68,7 @@ __device__ __forceinline__ void early_head_f32_tile(int hidden, int vocab, int m
                                                     unsigned char *smem) {
   constexpr int BM = 16 * MT, BN = kF32Cols;
   constexpr int R = 4;  // blocks of weight rows in registers
-  constexpr int kRowsPerWave = BM / kF32Waves, kBufBytes = BM * kF32RowBytes;
+  constexpr int kBufBytes = BM * kF32RowBytes;
   static_assert(2 * kBufBytes <= kF32LdsBytes && BM * BN * 4 <= kF32LdsBytes, "LDS");
   // opaque, so that no shape's address arithmetic is hoisted out of the loop over tiles into
   // registers that stay occupied while another shape runs
@@ -127,17 +127,18 @@ __device__ __forceinline__ void early_head_f32_tile(int hidden, int vocab, int m
 #pragma unroll
       for (int i = 0; i < MT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j], wk[j], acc[i], 0, 0, 0);
   };
-  RowChildren<kRowsPerWave> ch;
-  if (KIND == 0) {
-    ch.rows(wave, m0, m_total, tb);
-    ch.list(lane, tb);
-  }
   if (n_blocks > 0) load_a(0);
   static_for<R - 1>([&](auto i) {
     if (i < n_blocks) load_w(i, i);
   });
 
-  if (KIND == 0) ch.values(lane, tb);  // while the first blocks are on their way
+  const int m1 = m0 + BM < m_total ? m0 + BM : m_total;
+  int first = 0, end = 0;
+  NodeChunk nodes = {-1, 0, 0.f};
+  if (KIND == 0) {  // while the first blocks are on their way
+    nodes_of_rows(m0, m1, m_total, tb, first, end);
+    nodes = load_nodes(first, end, wave, lane, tb);
+  }
 
   meet();  // the tile before this one has been read
   for (int b0 = 0; b0 < n_blocks; b0 += R)
@@ -171,7 +172,7 @@ __device__ __forceinline__ void early_head_f32_tile(int hidden, int vocab, int m
 #pragma unroll
     for (int r = 0; r < 4; ++r) s_z[(16 * i + 4 * kq + r) * BN + col] = acc[i][r];
   __syncthreads();
-  rows_epilogue<KIND, kRowsPerWave>(ch, s_z, wave, lane, m0, m_total, v0, vocab, n_tile, tb);
+  rows_epilogue<KIND>(nodes, first, end, s_z, wave, lane, m0, m1, v0, vocab, n_tile, tb);
 }
 
 // Persistent over the tiles, XCD-aware like the bf16 kernel: the row tiles of one column tile are

@@ -49,6 +49,7 @@ struct PruneScratch {
   float *own;           // [B*T_max]  z_parent[token] of every non-root node
   int32_t *notes;       // what the kernels leave each other, see kNote*
   float *lse_part;      // [row_cap * parts][2]  probability criterion: (max, sum exp) per tile
+  int32_t *node_row;    // [B*T_max]  top-k criterion: node -> score row of its parent, or -1 (in the place of lse_part)
   int32_t *cnt_part;    // [vocab / 128][B*T_max]  top-k criterion: per column tile, the scores of the
                         //                       parent's row that beat the node's token
   size_t row_cap, parts, total_bytes;
@@ -73,6 +74,7 @@ static PruneScratch carve_scratch(void *base, int B, int T_max, int vocab) {
   s.row_cap = (size_t)B * (T_max > 1 ? T_max - 1 : 1);  // a node with children is not a leaf
   s.parts = ((size_t)vocab + 127) / 128;  // column parts of a row: one per tile, of at least 128 columns
   s.lse_part = reinterpret_cast<float *>(take(s.row_cap * s.parts * 8));
+  s.node_row = reinterpret_cast<int32_t *>(s.lse_part);  // row_cap * 8 bytes are never less than B*T_max * 4
   s.cnt_part = reinterpret_cast<int32_t *>(take(s.parts * nt * 4));
   s.total_bytes = off;
   return s;
@@ -134,6 +136,7 @@ struct PrepareArgs {
   const int32_t *n_nodes, *parent, *token;
   const void *hidden_states, *head_weight;
   int32_t *row_src, *row_base, *row_info, *child_list, *notes;
+  int32_t *node_row;  // top-k criterion, otherwise NULL
   float *own;
 };
 
@@ -256,6 +259,15 @@ __device__ void prepare_tables(const PrepareArgs &a, int g) {
       a.row_info[2 * r] = (int)base + incl[h] - mine[h];
       a.row_info[2 * r + 1] = mine[h];
     }
+  if (a.node_row) {
+    // the score row of every node's parent, -1 for nodes (and padding) without one
+    cnt[node[0]] = par_before[0];
+    cnt[node[1]] = par_before[1];
+    wave_lds_fence();
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (node[h] < a.T_max) a.node_row[base + node[h]] = par[h] >= 0 ? first + cnt[par[h]] : -1;
+  }
   if (lane == 0) {
     a.row_base[b] = first;
     if (b == a.B - 1) a.row_base[a.B] = first + run_par;
@@ -412,10 +424,11 @@ __global__ __launch_bounds__(kScanThreads) void prune_prepare_kernel(PrepareArgs
 
 // What the scoring kernels need besides the operands.
 struct HeadTables {
-  const int32_t *row_src, *row_base, *row_info, *child_list, *token;
+  const int32_t *row_src, *row_base, *row_info, *child_list, *token, *node_row;
   const float *own;
   int32_t *cnt_part;  // [column tile][cnt_stride]
   int cnt_stride;     // B * T_max
+  int T_max;
   float *lse_part;
   int parts;  // column parts per row in lse_part
   int32_t *n_tiles;  // bf16: the column tiles of the plan, left for prune_finish_kernel
@@ -511,80 +524,91 @@ __device__ __forceinline__ void lse_merge(float &m, float &s, float m2, float s2
 }
 
 // ---- epilogues over whole rows, for the tiles of few score rows (the fp32 tiles and the bf16 tile
-//      of at most 128 rows): the scores of the tile, rows x 128 columns, pass through LDS, and a wave
-//      takes a whole row (row = wave + 8 r of the workgroup's eight waves) against all children
-//      of its node.  The children's tokens and own scores were fetched before the K loop, one
-//      child per lane, so that nothing is waited for here.
+//      of few rows): the scores of the tile, rows x 128 columns, pass through LDS.
+//   top-k: a wave takes a child (every eighth node) against the 128 scores of its parent's row, four
+//     children's scores in flight.  The nodes' rows, tokens and own scores, one node per lane, are fetched
+//     while the first operands are on their way.
+//   probability: a wave takes a row (every eighth).
+// The loops are not unrolled over the rows: this code runs once per tile, and instructions cost their
+// fetch.  As an unrolled loop over up to 16 rows per wave, with the children of each in registers of its own, it
+// took 8 us at 88 rows with 248 children, and its tables 4 us in front of the first load.  Pruning call, us: 5 ragged
+// trees of up to 70 nodes x 2304 x 8192 52.4 -> 45.9, 9 x 31 x 3232 x 16001 72.1 -> 64.4, 1 x 64 x 4096 x 32000 71.7 ->
+// 69.0, fp32 2 x 32 x 1024 x 32000 58.3 -> 56.8.
 constexpr int kRowsCols = 128;
 
-template <int R>
-struct RowChildren {
-  int cc[R], pos[R], child[R], tok[R];
-  float own[R];
-  // A row's first 64 children (the epilogue fetches the rest), in three steps that depend on each
-  // other, so that the tile's first operand loads can be issued between them.  Lanes without a
-  // child read slot 0 and drop it.
-  __device__ __forceinline__ void rows(int wave, int m0, int m_total, const HeadTables &tb) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int m = m0 + wave + kGemmWaves * r;
-      pos[r] = __builtin_amdgcn_readfirstlane(m < m_total ? tb.row_info[2 * m] : 0);
-      cc[r] = __builtin_amdgcn_readfirstlane(m < m_total ? tb.row_info[2 * m + 1] : 0);
-    }
-  }
-  __device__ __forceinline__ void list(int lane, const HeadTables &tb) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) child[r] = tb.child_list[lane < cc[r] ? pos[r] + lane : 0];
-  }
-  __device__ __forceinline__ void values(int lane, const HeadTables &tb) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      child[r] = lane < cc[r] ? child[r] : -1;
-      const int c = child[r] >= 0 ? child[r] : 0;
-      tok[r] = tb.token[c];
-      own[r] = tb.own[c];
-    }
-  }
+struct NodeChunk {  // as loaded: nodes first + 8 * lane + wave, the first node past the end
+  int row, tok;
+  float own;
 };
 
-template <int KIND, int R>
-__device__ __forceinline__ void rows_epilogue(RowChildren<R> &ch, const float *s_z, int wave, int lane, int m0,
-                                              int m_total, int v0, int vocab, int n_tile, const HeadTables &tb) {
+__device__ __forceinline__ NodeChunk load_nodes(int first, int end, int wave, int lane, const HeadTables &tb) {
+  const int x = first + kGemmWaves * lane + wave, at = x < end ? x : first;
+  NodeChunk c;
+  c.row = tb.node_row[at];
+  c.tok = tb.token[at];
+  c.own = tb.own[at];
+  return c;
+}
+
+// The nodes whose parents may have score rows of m0 .. m1 - 1: those of the sequences of these rows.
+__device__ __forceinline__ void nodes_of_rows(int m0, int m1, int m_total, const HeadTables &tb, int &first, int &end) {
+  first = 0;
+  end = tb.cnt_stride;
+  if (m0 > 0) first = tb.row_src[m0] / tb.T_max * tb.T_max;
+  if (m1 < m_total) end = tb.row_src[m1 - 1] / tb.T_max * tb.T_max + tb.T_max;
+}
+
+// rows m0 .. m1 - 1 of the tile lie in s_z from its start
+template <int KIND>
+__device__ __forceinline__ void rows_epilogue(NodeChunk nodes, int first, int end, const float *s_z, int wave, int lane,
+                                              int m0, int m1, int v0, int vocab, int n_tile, const HeadTables &tb) {
   constexpr int kX = kRowsCols / kWave;
+  if (KIND == 0) {
+    int32_t *dst = tb.cnt_part + (size_t)n_tile * tb.cnt_stride;
+    for (int x0 = first; x0 < end; x0 += kGemmWaves * kWave) {
+      if (x0 > first) nodes = load_nodes(x0, end, wave, lane, tb);
+      const bool mine = x0 + kGemmWaves * lane + wave < end && nodes.row >= m0 && nodes.row < m1;
+      uint64_t rest = __builtin_amdgcn_ballot_w64(mine);
+      int count = 0;
+      constexpr int N = 4;  // children at a time; past the last one the same once more
+      while (rest) {
+        int src[N], t[N];
+        float zo[N], z[N][kX];
+        uint64_t cur = rest;
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int row = wave + kGemmWaves * r, m = m0 + row;
-    if (m >= m_total) break;  // uniform
-    // columns past the vocabulary beat nothing and add nothing to a sum of exponentials
-    float z[kX];
+        for (int j = 0; j < N; ++j) {
+          src[j] = __builtin_ctzll(cur);
+          rest = cur & (cur - 1);
+          cur = rest ? rest : cur;
+          const int row = __builtin_amdgcn_readlane(nodes.row, src[j]) - m0;
+          t[j] = __builtin_amdgcn_readlane(nodes.tok, src[j]);
+          zo[j] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(nodes.own), src[j]));
 #pragma unroll
-    for (int x = 0; x < kX; ++x) z[x] = v0 + kWave * x + lane < vocab ? s_z[row * kRowsCols + kWave * x + lane] : -INFINITY;
-    if (KIND == 0) {
-      for (int e0 = 0; e0 < ch.cc[r]; e0 += kWave) {
-        if (e0 > 0) {
-          ch.child[r] = e0 + lane < ch.cc[r] ? tb.child_list[ch.pos[r] + e0 + lane] : -1;
-          ch.tok[r] = ch.child[r] >= 0 ? tb.token[ch.child[r]] : -1;
-          ch.own[r] = ch.child[r] >= 0 ? tb.own[ch.child[r]] : INFINITY;
+          for (int x = 0; x < kX; ++x) z[j][x] = s_z[row * kRowsCols + kWave * x + lane];
         }
-        const int n = ch.cc[r] - e0 < kWave ? ch.cc[r] - e0 : kWave;
-        int count = 0;
-        for (int e = 0; e < n; ++e) {
-          const float zo = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(ch.own[r]), e));
-          const int t = __builtin_amdgcn_readlane(ch.tok[r], e);
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
           int c = 0;
 #pragma unroll
           for (int x = 0; x < kX; ++x) {
-            const int v = v0 + kWave * x + lane;  // the token's own column never counts
-            c += __popcll(__ballot(v != t && (z[x] > zo || (z[x] == zo && v < t))));
+            const int v = v0 + kWave * x + lane;  // the token's own column and columns past the vocabulary never count
+            c += __popcll(__builtin_amdgcn_ballot_w64(v < vocab && v != t[j] && (z[j][x] > zo[j] || (z[j][x] == zo[j] && v < t[j]))));
           }
-          count = lane == e ? c : count;
+          count = lane == src[j] ? c : count;
         }
-        if (lane < n) tb.cnt_part[(size_t)n_tile * tb.cnt_stride + ch.child[r]] = count;
       }
-    } else {
-      float mx = z[0];
+      if (mine) dst[x0 + kGemmWaves * lane + wave] = count;
+    }
+  } else {
+#pragma unroll 1
+    for (int m = m0 + wave; m < m1; m += kGemmWaves) {
+      // columns past the vocabulary add nothing to a sum of exponentials
+      float z[kX], mx = -INFINITY;
 #pragma unroll
-      for (int x = 1; x < kX; ++x) mx = fmaxf(mx, z[x]);
+      for (int x = 0; x < kX; ++x) {
+        z[x] = v0 + kWave * x + lane < vocab ? s_z[(m - m0) * kRowsCols + kWave * x + lane] : -INFINITY;
+        mx = fmaxf(mx, z[x]);
+      }
       mx = wave_reduce_max(mx);
       float sum = 0.f;
 #pragma unroll
@@ -657,9 +681,6 @@ __device__ __forceinline__ void early_head_small_tile(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int l32 = lane & 31, g = lane >> 5;
-  constexpr int kRows = RA > 128 ? 128 : RA;  // of the epilogue at a time
-  RowChildren<kRows / kGemmWaves> ch;
-  if (KIND == 0) ch.rows(wave, 0, m_total, tb);
   // ---- loader: a load instruction fills 8 rows of 128 bytes (1 KB).  A stage has RA / 8 such
   //      groups of score rows, fetched by wave g / kALoads, and 16 of weight rows; wave w takes
   //      groups 2w and 2w + 1 of those.  Groups of score rows wholly past the last are not fetched.
@@ -751,13 +772,13 @@ __device__ __forceinline__ void early_head_small_tile(
   const int n_pro = n_steps < kStages ? n_steps : kStages;
   constexpr int kMaxOutstanding = (kStages - 1) * (kALoads + 2);
   int slot_ld = 0;
-  if (KIND == 0) ch.list(lane, tb);
   for (int i = 0; i < n_pro; ++i) {
     issue(slot_ld, i);
     slot_ld = slot_ld + 1 == kStages ? 0 : slot_ld + 1;
   }
   // (loads younger than the ring's only make the counted waits below stricter)
-  if (KIND == 0) ch.values(lane, tb);
+  NodeChunk nodes = {-1, 0, 0.f};
+  if (KIND == 0) nodes = load_nodes(0, tb.cnt_stride, wave, lane, tb);
   gemm_wait_outstanding<kMaxOutstanding>((n_pro - 1) * per_step);
   __builtin_amdgcn_s_barrier();
   constexpr int kReads = kX + FN;  // LDS reads of one K sub-step
@@ -814,20 +835,7 @@ __device__ __forceinline__ void early_head_small_tile(
           s_z[(wm * 64 + 32 * x + 8 * (r >> 2) + 4 * g + (r & 3)) * kRowsCols + wn * 64 + 32 * y + l32] = acc[x][y][r];
   }
   __syncthreads();
-  if constexpr (RA > kRows) {
-    // the children of the other rows are on their way while the first rows' are counted
-    constexpr int kMore = (RA - kRows) / kGemmWaves;
-    RowChildren<kMore> ch2;
-    if (KIND == 0) {
-      ch2.rows(wave, kRows, m_total, tb);
-      ch2.list(lane, tb);
-    }
-    rows_epilogue<KIND, kRows / kGemmWaves>(ch, s_z, wave, lane, 0, m_total, v0, vocab, n_tile, tb);
-    if (KIND == 0) ch2.values(lane, tb);
-    rows_epilogue<KIND, kMore>(ch2, s_z + kRows * kRowsCols, wave, lane, kRows, m_total, v0, vocab, n_tile, tb);
-  } else {
-    rows_epilogue<KIND, kRows / kGemmWaves>(ch, s_z, wave, lane, 0, m_total, v0, vocab, n_tile, tb);
-  }
+  rows_epilogue<KIND>(nodes, 0, tb.cnt_stride, s_z, wave, lane, 0, m_total, v0, vocab, n_tile, tb);
   __syncthreads();  // the next tile's loads reuse this memory
 }
 
@@ -1403,6 +1411,7 @@ static propd_status prune_impl(
     pr.row_info = ws.row_info;
     pr.child_list = ws.child_list;
     pr.notes = ws.notes;
+    pr.node_row = crit.kind == 0 ? ws.node_row : nullptr;
     pr.own = ws.own;
     const unsigned prep_grid = (unsigned)((B + kTableWaves - 1) / kTableWaves) +
                                (unsigned)B * (unsigned)((T_max + kOwnNodes - 1) / kOwnNodes);
@@ -1418,6 +1427,8 @@ static propd_status prune_impl(
     tb.child_list = ws.child_list;
     tb.token = tree->token;
     tb.own = ws.own;
+    tb.node_row = ws.node_row;
+    tb.T_max = T_max;
     tb.cnt_part = ws.cnt_part;
     tb.cnt_stride = B * T_max;
     tb.lse_part = ws.lse_part;
