@@ -257,6 +257,33 @@ def test_attention_f32_matches_oracle(pb, oracle, d, T_max, H, lens):
 # ------------------------------------------------------------------ bf16 scoring, few rows
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,H,T,L,room", [(1, 16, 115, 561, None), (1, 8, 100, 198, None), (1, 1, 16, 128, None), (1, 12, 48, 2129, None),
+                                          (2, 16, 48, 1000, None), (5, 8, 43, 458, None), (1, 3, 20, 700, 2), (1, 3, 20, 700, 1), (1, 40, 33, 90, 3)])
+def test_attention_f32_splits(pb, oracle, B, H, T, L, room, d):
+    """How many workgroups share a unit's keys: one per compute unit and two, fewer and more than the plain rule says, and as many
+    as a small workspace has room for."""
+    rng = np.random.default_rng([B, H, T])
+    lens = rng.integers(0, L + 1, B).astype(np.int32)
+    lens[0] = L
+    w = synth.Workload(83, "case", "f32", B, H, d, T, 0, 0, 0, 1e-5)
+    x = synth.make_attention_inputs(w, seq_lens=lens, trees=[synth.random_tree(rng, T)] * B)
+    if room is None:
+        out, sent = run_attention(pb, x)
+    else:
+        dev = {k: to_dev(x[k]) for k in ("q", "k_cache", "v_cache", "k_tree", "v_tree", "seq_lens")}
+        sent = sentinel_like(x["q"])
+        out = to_dev(sent)
+        ws = torch.empty(room * H * ((T + 31) // 32) * 32 * (d + 2) * 4, dtype=torch.uint8, device="cuda")
+        tree = dev_tree(pb, x["n_nodes"], x["parent"], np.zeros_like(x["parent"]))
+        with pytest.MonkeyPatch.context() as m:  # the call itself takes any workspace
+            m.setattr(pb, "_marshal", None)
+            m.setattr(pb, "workspace_bytes", lambda *a, **k: 0)
+            pb.propd_tree_attention(tree, dev["q"], dev["k_cache"], dev["v_cache"], dev["k_tree"], dev["v_tree"], dev["seq_lens"],
+                                    x["scale"], out=out, workspace=ws)
+    check_attention(oracle, x, out, sent)
+
+
 @pytest.mark.parametrize("T", [2, 9, 33, 34, 65, 66, 127, 128])
 @pytest.mark.parametrize("Hd,V", [(64, 300), (192, 1003), (640, 257)])
 def test_prune_bf16_few_rows_edges(pb, oracle, T, Hd, V):
