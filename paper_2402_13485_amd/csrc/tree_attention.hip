@@ -500,14 +500,17 @@ struct Walk {
         pick = __builtin_ctzll(fit);
         const float pieces = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(total), pick));
         const float longest = (float)(least_q + (uint32_t)pick);
-        // How much longer: the more units there are for each workgroup, the more of them a range crosses.  Whole calls, us, at mean /
-        // longest stages, crossing / not: ragged lengths, 496 units 9.0 / 17 35.5 / 30.4, 352 11.9 / 19 38.9 / 31.1, 280 22.9 / 32
-        // 57.8 / 48.5, 256 32.8 / 46 64.3 / 60.0, 240 14.1 / 18 43.2 / 38.3, 160 44 / 60 70.3 / 73.9; equal ones, 80 7.3 / 8 29.8 /
-        // 26.8, 208 72 / 89 130.7 / 133.7, 176 6.2 / 9 22.1 / 23.6.  In one piece each: 312 units of 57 queries 28.6 / 47 59.5 /
-        // 53.7, 320 of 89 4.4 / 7 26.9 / 21.5, 320 of 104 86 / 137 153.8 / 165.4.
+        // How much longer: the more units there are for each workgroup, the more of them a range crosses, at a cost that does not grow
+        // with its length.  Whole calls, us, at mean / longest stages, crossing / not: ragged lengths, 496 units 9.0 / 17 35.5 / 30.4,
+        // 352 11.9 / 19 38.9 / 31.1, 280 22.9 / 32 57.8 / 48.5, 336 48.2 / 66 96.0 / 90.1, 256 32.8 / 46 64.3 / 60.0, 320 37.3 / 63
+        // 73.7 / 86.5, 160 44 / 60 70.3 / 73.9; equal ones, 80 7.3 / 8 29.8 / 26.8, 200 (two waves per 32 queries) 84.8 / 109 134.1 /
+        // 126.1, 200 (one) 67 / 86 120.3 / 126.2, 176 6.2 / 9 22.1 / 23.6.  In one piece each: 312 units of 57 queries 28.6 / 47 59.5 /
+        // 53.7, 320 of 61 34.4 / 55 66.3 / 61.3, 352 of 15 105 / 153 150.9 / 156.2, 320 of 89 4.4 / 7 26.9 / 21.5, 320 of 104 86 / 137
+        // 153.8 / 165.4.
         const float share = (float)U * __builtin_amdgcn_rcpf((float)G);
-        const float limit = pieces <= (float)U ? (KS == 2 ? 1.65f : 1.2f) * mean + 8.f
-                                               : (1.f + (share < .5f ? .8f : 1.1f) * share) * mean + 1.f;
+        const float one_each = KS == 2 ? 1.3f * mean + 11.f : 1.2f * mean + 8.f;
+        const float several = fminf((1.f + (share < .5f ? .8f : 1.1f) * share) * mean + 1.f, (KS == 2 ? 1.25f : 1.15f) * mean + 17.f * share);
+        const float limit = pieces <= (float)U ? one_each : several;
         // One wave per 32 queries and fewer workgroups left than half the chip: 16 units of 127 x 136 (d = 64) 12.5 / 13.9.
         if (longest > limit || (KS == 1 && pieces < .5f * (float)m.cus && pick > 0)) pick = -1;
         // Fewer, longer pieces, one workgroup per compute unit, where a unit would be cut into many: 32 units of 34 stages in 12 / 7
