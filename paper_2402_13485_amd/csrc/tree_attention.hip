@@ -1232,6 +1232,7 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");  // the reads below stay below
       if (q_group * 32 < T) {
         f32x4 other[kMyMb * 4];
 #pragma unroll
