@@ -324,7 +324,8 @@ struct Schedule {
   // call).  The largest weight of such a stage is exactly 1 and rounds to bf16 without error, like that of
   // a piece's first stage: with ranges that cross no unit there would be fewer of these, and the error against
   // 64 bits up to 4 % larger than with ranges that do (6 x 8 ragged units of 107 queries: 1.887e-3, 1.965e-3 without
-  // this).  Set often enough that it is no larger; once per stage costs 1.1 us of 14.
+  // this).  Set often enough that it is no larger; once per stage costs 1.1 us of 14.  A stage whose scores lie more than
+  // 2^8 in the exponent below the highest one of the piece gets no such weight: see m_top.
   int anew = 1 << 30;
   __device__ __forceinline__ long long range_start(long long w) const {
     return w * quot + (w < rem ? w : rem);
@@ -874,7 +875,7 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
     tie();
   };
 
-  float m_run, l_run;
+  float m_run, l_run, m_top;  // the softmax reference, the sum of the weights, the piece's highest score so far (kAnew)
   f32x16 o_acc[kMb];
   u32x2 vt[kVSteps][2 * kMb];
   // S^T = K . Q^T of one stage
@@ -1020,7 +1021,7 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
   // D = 64: the reference is put 2^4 above the maximum instead, and adopted anew when that is
   // exceeded, so that weights are at most 1 and no product leaves the range of its V value
   // (finite, also where the scale is next to nothing)
-  const float tau = kExact ? fminf(4.f / p.scale_log2e, 1e38f) : 8.f / p.scale_log2e;
+  const float tau = fminf((kExact ? 4.f : 8.f) / p.scale_log2e, 1e38f);
 
   Piece pc = piece_at(cp, 0);
   // D = 128: the first piece's queries in front of the ring's loads, which they then need not be waited for behind
@@ -1030,7 +1031,7 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
   if (!kExact) fill_ring();
   while (n_acq < n_my) {
     const int L = pc.L, T = pc.T, n_cache = pc.n_cache, s0 = pc.s0;
-    m_run = -INFINITY;
+    m_run = m_top = -INFINITY;
     l_run = 0.f;
 #pragma unroll
     for (int mb = 0; mb < kMb; ++mb)
@@ -1091,6 +1092,7 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
           swap_halves(lo, hi);
           m_blk = fmaxf(__uint_as_float(lo), __uint_as_float(hi));
         }
+        if constexpr (kAnew) m_top = fmaxf(m_top, m_blk);
         const bool anew = kAnew && i == next_anew;  // uniform
         if (anew) next_anew += sch.anew;
         if (anew || __builtin_amdgcn_ballot_w64(m_blk > (kExact ? m_run : m_run + tau)) != 0) {
@@ -1102,7 +1104,9 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
             clear_prev();
             mfma_settle();
           }
-          const float m_new = fmaxf(anew ? m_run - tau : m_run, kExact ? m_blk + tau : m_blk);
+          // Set anew it may come down, but to no less than the highest score so far - tau: no weight exceeds
+          // 2^8 then, however many stages of low scores follow a high one.
+          const float m_new = fmaxf(anew ? m_top - tau : m_run, kExact ? m_blk + tau : m_blk);
           const float m_safe = m_new == -INFINITY ? 0.f : m_new;
           const float alpha = fast_exp2((m_run - m_safe) * p.scale_log2e);
           l_run *= alpha;

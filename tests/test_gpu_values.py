@@ -293,3 +293,43 @@ def test_attention_replayed_with_values_that_come_and_go(pb, dtype, d):
         torch.cuda.synchronize()
         assert torch.equal(out.view(torch.int16 if dtype == "bf16" else torch.int32),
                            want.view(torch.int16 if dtype == "bf16" else torch.int32))
+
+
+@pytest.mark.parametrize("T", [40, 70])  # two waves per 32 queries and one
+@pytest.mark.parametrize("B,H,L", [(16, 32, 16640), (4, 32, 65100)])  # 512 workgroups: whole units, units of four pieces
+@pytest.mark.parametrize("scores", ["one", "falling"])
+def test_attention_high_scores_in_front_of_long_pieces(pb, scores, B, H, L, T):
+    """Pieces of 500 stages and more, in which the softmax reference is set anew sixteen times and more, while
+    their scores lie up to 2^288 below that of the first key ("one"), or fall with every stage.  Query t has its own distance,
+    t * 4 in natural units at most 200, so that the other keys count for some queries and for some they do not."""
+    d = 128
+    gap = np.minimum(4.0 * np.arange(T), 200.0)
+    # a key's score is gap * fall, exact in bf16 and fp32
+    fall = np.zeros(L) if scores == "one" else bf16(1.0 - np.arange(L) // 32 * 32 / L)
+    fall[0] = 1.0
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    kc = torch.zeros(B, H, L, d, device="cuda", dtype=torch.bfloat16)
+    kc[..., 0] = torch.from_numpy(fall).to(torch.bfloat16).cuda()
+    vc = torch.empty(B, H, L, d, device="cuda", dtype=torch.bfloat16).normal_(generator=gen)
+    kt = torch.zeros(B, H, T, d, device="cuda", dtype=torch.bfloat16)
+    vt = torch.empty(B, H, T, d, device="cuda", dtype=torch.bfloat16).normal_(generator=gen)
+    q = torch.zeros(B, H, T, d, device="cuda", dtype=torch.bfloat16)
+    q[..., 0] = torch.from_numpy(gap).cuda()
+    n, parent, _ = synth.pad_trees([synth.chain_tree(T)] * B, T)
+    tree = dev_tree(pb, n, parent)
+    out = pb.propd_tree_attention(tree, q, kc, vc, kt, vt, torch.full((B,), L, dtype=torch.int32, device="cuda"), 1.0)
+    # the weights are the same for all units; node t sees the tree rows 0..t
+    w = torch.exp(torch.from_numpy(gap[:, None] * (fall[None] - 1.0)).cuda())
+    wt = torch.exp(torch.from_numpy(-gap).cuda())[:, None] * torch.ones(T, T, device="cuda", dtype=torch.float64).tril()
+    total = (w.sum(1) + wt.sum(1))[:, None]
+    for b, h in ((0, 0), (0, 1), (B // 2, H - 1), (B - 1, H - 1)):
+        v, v2 = vc[b, h].double(), vt[b, h].double()
+        ref = (w @ v + wt @ v2) / total
+        # a weight and the sum of the rounded weights: 2^-9 each, so 2^-8 of the sum of all terms; 2^-9 for the result,
+        # and fp32 sums
+        bound = (2 ** -8 + 2 ** -14) * (w @ v.abs() + wt @ v2.abs()) / total + 2 ** -9 * ref.abs() + 1e-6
+        got = out[b, h].double()
+        assert bool(torch.isfinite(got).all()), (b, h)
+        assert bool(((got - ref).abs() <= bound).all()), (b, h, ((got - ref).abs() - bound).max().item())
+    assert bool(torch.isfinite(out).all())
