@@ -6,11 +6,14 @@
 // Nothing is decided here that binding.py does not say: a function returns None, with nothing enqueued,
 // whenever an argument is not what the entry point wants, and binding.py then goes through its own
 // checks, which name the argument.  Tensors of other classes than torch.Tensor and Parameter are left to it
-// too.  A call that the library refuses returns its status.  No state is kept but the addresses of the
-// entry points.
+// too.  What can fail stands in front of the C call, the Python objects of its results among it: a call
+// that has been enqueued returns them and is never made again.  A call that the library refuses returns its
+// status.  No state is kept but the addresses of the entry points.
 #include <ATen/ATen.h>
 #include <Python.h>
 #include <torch/csrc/autograd/python_variable.h>
+
+#include <memory>
 
 #include "../../include/propd.h"
 
@@ -139,28 +142,33 @@ at::Tensor int_tensor(at::IntArrayRef sizes, const at::Tensor &like) {
   return at::empty(sizes, like.options().dtype(at::kInt));
 }
 
-// Takes over the references of the items; NULL, with the error set, if one could not be made.
-PyObject *tuple_of(std::initializer_list<PyObject *> items) {
-  bool whole_tuple = true;
-  for (PyObject *o : items) whole_tuple = whole_tuple && o != nullptr;
-  PyObject *r = whole_tuple ? PyTuple_New((Py_ssize_t)items.size()) : nullptr;
-  Py_ssize_t n = 0;
-  for (PyObject *o : items) {
-    if (r) PyTuple_SET_ITEM(r, n++, o);
-    else Py_XDECREF(o);
-  }
-  return r;
+struct Release {
+  void operator()(PyObject *o) const { Py_DECREF(o); }
+};
+using Owned = std::unique_ptr<PyObject, Release>;
+
+Owned owned(PyObject *o) {
+  if (!o) throw Raised{};
+  return Owned(o);
 }
 
-PyObject *object(const at::Tensor &t) {
-  if (t.defined()) return THPVariable_Wrap(t);
+Owned object(const at::Tensor &t) {
+  if (t.defined()) return owned(THPVariable_Wrap(t));
   Py_INCREF(Py_None);
-  return Py_None;
+  return Owned(Py_None);
 }
 
-PyObject *object(PyObject *o) {
+Owned object(PyObject *o) {
   Py_INCREF(o);
-  return o;
+  return Owned(o);
+}
+
+template <class... Items>
+Owned tuple_of(Items... items) {
+  Owned r = owned(PyTuple_New((Py_ssize_t)sizeof...(items)));
+  Py_ssize_t n = 0;
+  (PyTuple_SET_ITEM(r.get(), n++, items.release()), ...);
+  return r;
 }
 
 Entries entries;
@@ -168,13 +176,14 @@ Entries entries;
 template <class F>
 PyObject *guarded(F &&f) {
   try {
-    return f();
+    return f().release();
   } catch (const NotThis &) {
   } catch (const Raised &) {
     return nullptr;
   } catch (const Refused &r) {
     return PyLong_FromLong((long)r.status);
   } catch (const std::exception &e) {  // for instance out of memory: the Python code meets the same and says so
+    PyErr_Clear();
   }
   Py_RETURN_NONE;
 }
@@ -202,21 +211,22 @@ PyObject *py_init(PyObject *, PyObject *const *a, Py_ssize_t n) {
 
 // tree_mask(n_nodes, parent, stream) -> (depth, anc)
 PyObject *py_tree_mask(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  return guarded([&]() -> PyObject * {
+  return guarded([&]() -> Owned {
     need(n == 3);
     const at::Tensor &nodes = dev(a[0], at::kInt), &parent = dev(a[1], at::kInt);
     need(parent.dim() == 2);
     const int64_t B = parent.size(0), T = parent.size(1);
     at::Tensor depth = int_tensor({B, T}, parent), anc = at::empty({B, T, 2}, parent.options().dtype(at::kLong));
+    Owned result = tuple_of(object(depth), object(anc));
     called(entries.tree_mask(size32(B), size32(T), (const int32_t *)nodes.data_ptr(), (const int32_t *)parent.data_ptr(),
                            (int32_t *)depth.data_ptr(), (uint64_t *)anc.data_ptr(), stream_of(a[2])));
-    return tuple_of({object(depth), object(anc)});
+    return result;
   });
 }
 
 // tree_attention(*tree, q, k_cache, v_cache, k_tree, v_tree, seq_lens, scale, out, workspace, stream) -> out
 PyObject *py_tree_attention(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  return guarded([&]() -> PyObject * {
+  return guarded([&]() -> Owned {
     need(n == 15);
     const propd_tree tree = tree_of(a);
     const at::Tensor &q = tensor(a[5]);
@@ -232,17 +242,18 @@ PyObject *py_tree_attention(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const at::Tensor out = a[12] == Py_None ? at::empty_like(q) : tensor(a[12]);
     const Workspace w = workspace(a[13], entries.workspace_bytes(PROPD_WS_TREE_ATTENTION, tree.B, tree.T_max, size32(H), size32(d),
                                                                  size32(L), 0, 0), q);
+    Owned result = a[12] != Py_None ? object(a[12]) : object(out);
     called(entries.tree_attention(&tree, dt, size32(H), size32(d), real(a[11]), q.data_ptr(), L ? kc.data_ptr() : nullptr,
                                 L ? vc.data_ptr() : nullptr, kt.data_ptr(), vt.data_ptr(), (const int32_t *)seq.data_ptr(),
                                 size32(L), out.data_ptr(), w.ptr, w.bytes, stream_of(a[14])));
-    return a[12] != Py_None ? object(a[12]) : object(out);
+    return result;
   });
 }
 
 // early_prune(*tree, hidden, head, mode, value, payloads, payload_out, want_extra, workspace, stream) -> (keep_bits, new_index, orig_index,
 // n_kept, cu_nodes, n_nodes, parent, token, depth, anc, rank or log_marginal or None, [payloads]); mode -1: top-k, else propd_prob_mode
 PyObject *py_early_prune(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  return guarded([&]() -> PyObject * {
+  return guarded([&]() -> Owned {
     need(n == 14);
     const propd_tree tree = tree_of(a);
     const at::Tensor &hid = tensor(a[5]);
@@ -294,6 +305,11 @@ PyObject *py_early_prune(PyObject *, PyObject *const *a, Py_ssize_t n) {
                                                                  size32(vocab)), hid);
     uint64_t *keep_p = (uint64_t *)keep.data_ptr();
     int32_t *kept_p = (int32_t *)counts[0].data_ptr(), *cu_p = (int32_t *)cu.data_ptr();
+    Owned moved = owned(PyList_New(n_pay));
+    for (Py_ssize_t i = 0; i < n_pay; ++i)
+      PyList_SET_ITEM(moved.get(), i, (given ? object(PySequence_Fast_GET_ITEM(a[10], i)) : object(made[i])).release());
+    Owned result = tuple_of(object(keep), object(nodes[0]), object(nodes[1]), object(counts[0]), object(cu), object(counts[1]),
+                            object(nodes[2]), object(nodes[3]), object(nodes[4]), object(anc), object(more), std::move(moved));
     void *st = stream_of(a[13]);
     const propd_status done =
         top_k ? entries.early_prune(&tree, dt, size32(hidden), size32(vocab), count, hid.data_ptr(), head.data_ptr(), keep_p, node[0],
@@ -303,20 +319,13 @@ PyObject *py_early_prune(PyObject *, PyObject *const *a, Py_ssize_t n) {
                                          hid.data_ptr(), head.data_ptr(), keep_p, node[0], node[1], kept_p, cu_p, &out,
                                          more.defined() ? (float *)more.data_ptr() : nullptr, (int32_t)n_pay, pay, w.ptr, w.bytes, st);
     called(done);
-    PyObject *payloads = PyList_New(n_pay);
-    for (Py_ssize_t i = 0; payloads && i < n_pay; ++i) {
-      PyObject *o = given ? object(PySequence_Fast_GET_ITEM(a[10], i)) : object(made[i]);
-      if (o) PyList_SET_ITEM(payloads, i, o);
-      else Py_CLEAR(payloads);
-    }
-    return tuple_of({object(keep), object(nodes[0]), object(nodes[1]), object(counts[0]), object(cu), object(counts[1]),
-                     object(nodes[2]), object(nodes[3]), object(nodes[4]), object(anc), object(more), payloads});
+    return result;
   });
 }
 
 // accept_path(*tree, logits, path_stride or None, workspace, stream) -> (accept_len, path, next_token)
 PyObject *py_accept_path(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  return guarded([&]() -> PyObject * {
+  return guarded([&]() -> Owned {
     need(n == 9);
     const propd_tree tree = tree_of(a);
     const at::Tensor &logits = tensor(a[5]);
@@ -326,15 +335,16 @@ PyObject *py_accept_path(PyObject *, PyObject *const *a, Py_ssize_t n) {
     need(stride >= 0);
     at::Tensor len = int_tensor({tree.B}, logits), path = int_tensor({tree.B, stride}, logits), next = int_tensor({tree.B}, logits);
     const Workspace w = workspace(a[7], entries.workspace_bytes(PROPD_WS_ACCEPT_PATH, tree.B, tree.T_max, 0, 0, 0, 0, vocab), logits);
+    Owned result = tuple_of(object(len), object(path), object(next));
     called(entries.accept_path(&tree, dt, vocab, logits.data_ptr(), (int32_t *)len.data_ptr(), (int32_t *)path.data_ptr(), stride,
                              (int32_t *)next.data_ptr(), w.ptr, w.bytes, stream_of(a[8])));
-    return tuple_of({object(len), object(path), object(next)});
+    return result;
   });
 }
 
 // commit_path(*tree, accept_len, path, next_token, k_tree, v_tree, k_cache, v_cache, seq_lens, out_stride or None, stream) -> tokens
 PyObject *py_commit_path(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  return guarded([&]() -> PyObject * {
+  return guarded([&]() -> Owned {
     need(n == 15);
     const propd_tree tree = tree_of(a);
     const at::Tensor &len = dev(a[5], at::kInt), &path = dev(a[6], at::kInt), &next = dev(a[7], at::kInt), &seq = dev(a[12], at::kInt);
@@ -349,10 +359,11 @@ PyObject *py_commit_path(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const int32_t stride = size32(path.size(1)), out_stride = a[13] == Py_None ? stride : whole32(a[13]);
     need(out_stride >= 0);
     at::Tensor out = int_tensor({B, out_stride}, kt);
+    Owned result = object(out);
     called(entries.commit_path(&tree, dt, size32(H), size32(d), (const int32_t *)len.data_ptr(), (const int32_t *)path.data_ptr(), stride,
                              (const int32_t *)next.data_ptr(), kt.data_ptr(), vt.data_ptr(), kc.data_ptr(), vc.data_ptr(), size32(L),
                              (int32_t *)seq.data_ptr(), (int32_t *)out.data_ptr(), out_stride, stream_of(a[14])));
-    return object(out);
+    return result;
   });
 }
 

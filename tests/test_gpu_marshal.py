@@ -170,3 +170,27 @@ def test_other_tensor_classes_and_streams(pb, monkeypatch, x):
     with torch.cuda.stream(stream):
         got = both(pb, monkeypatch, call(lambda q: q))
     assert seen == [real, real] and all(torch.equal(g, want) for g in got)
+
+
+def test_out_of_host_memory_leaves_no_call_behind(pb, x):
+    """Wherever host memory ends, a call that did not return its results was not made: the Python code makes it
+    then, and a commit made twice would append its rows twice."""
+    testcapi = pytest.importorskip("_testcapi")
+    t, kc, vc, seq = x["tree"], x["kc"].clone(), x["vc"].clone(), x["seq"].clone()
+    commit = pb._native().commit_path
+    args = (t.n_nodes, t.parent, t.token, t.depth, t.anc, *x["acc"], x["kt"], x["vt"], kc, vc, seq, None, pb._stream)
+    made = []
+    for n in range(40):  # the n-th request for memory fails
+        result = None
+        testcapi.set_nomemory(n, n + 1)
+        try:
+            result = commit(*args)
+        except (MemoryError, RuntimeError):
+            pass
+        finally:
+            testcapi.remove_mem_hooks()
+        torch.cuda.synchronize()
+        made.append(result is not None)
+        assert (seq.tolist() != x["seq"].tolist()) == made[-1], n
+        seq.copy_(x["seq"])
+    assert made[-1] and not all(made)
