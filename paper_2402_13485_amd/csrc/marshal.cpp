@@ -93,6 +93,12 @@ float real(PyObject *o) {
   return (float)v;
 }
 
+bool truth(PyObject *o) {
+  const int t = PyObject_IsTrue(o);
+  if (t < 0) throw Raised{};
+  return t == 1;
+}
+
 // binding._stream, called once the arguments have passed
 void *stream_of(PyObject *current) {
   PyObject *o = PyObject_CallNoArgs(current);
@@ -264,7 +270,7 @@ PyObject *py_early_prune(PyObject *, PyObject *const *a, Py_ssize_t n) {
     need(head.dim() == 2 && head.size(1) == hidden && tree.B == B && tree.T_max == T);
     const int64_t vocab = head.size(0);
     const long long mode = whole(a[7]);
-    const bool top_k = mode < 0, extra = PyObject_IsTrue(a[11]) == 1;
+    const bool top_k = mode < 0, extra = truth(a[11]);
     const int32_t count = top_k || mode == PROPD_PROB_RANK ? whole32(a[8]) : 0;
     const float threshold = mode == PROPD_PROB_THRESHOLD ? real(a[8]) : 0.f;
     need(PyList_Check(a[9]) || PyTuple_Check(a[9]));

@@ -134,6 +134,7 @@ def test_same_errors(pb, monkeypatch, x):
         lambda: pb.propd_early_prune(t, x["hid"], x["head"], 5, payloads=[q], payload_out=[q]),
         lambda: pb.propd_early_prune(t, x["hid"], x["head"], 5, payloads=[q] * 9),
         lambda: pb.propd_early_prune(t, x["hid"], x["head"], 5, workspace=half),
+        lambda: pb.propd_early_prune(t, x["hid"], x["head"], 5, want_rank=np.zeros(2)),
         lambda: pb.propd_early_prune_prob(t, x["hid"], x["head"], threshold=2.0),
         lambda: pb.propd_early_prune_prob(t, x["hid"], x["head"], keep_count=0),
         lambda: pb.propd_accept_path(t, x["logits"].half()),
