@@ -8,12 +8,14 @@
 // checks, which name the argument.  Tensors of other classes than torch.Tensor and Parameter are left to it
 // too.  What can fail stands in front of the C call, the Python objects of its results among it: a call
 // that has been enqueued returns them and is never made again.  A call that the library refuses returns its
-// status.  No state is kept but the addresses of the entry points.
+// status.  The interpreter is left to other threads during allocations and the C call, as torch and ctypes
+// do.  No state is kept but the addresses of the entry points.
 #include <ATen/ATen.h>
 #include <Python.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <memory>
+#include <vector>
 
 #include "../../include/propd.h"
 
@@ -44,7 +46,22 @@ void need(bool ok) {
   if (!ok) throw NotThis{};
 }
 
-void called(propd_status status) {
+// Other threads may run Python meanwhile: a launch waits where the queue is full, an allocation where memory has to be
+// given back first, and what they wait for may need the interpreter.
+struct Unlocked {
+  PyThreadState *const state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
+template <class F>
+auto unlocked(F &&f) {
+  const Unlocked u;
+  return f();
+}
+
+template <class Entry, class... Args>
+void call(Entry entry, Args... args) {
+  const propd_status status = unlocked([&] { return entry(args...); });
   if (status != PROPD_OK) throw Refused{status};
 }
 
@@ -137,15 +154,11 @@ Workspace workspace(PyObject *o, size_t need_bytes, const at::Tensor &like) {
     need(w.bytes >= need_bytes && t.numel() * t.element_size() == (int64_t)w.bytes);
     w.ptr = t.data_ptr();
   } else {
-    w.own = at::empty({(int64_t)(need_bytes > 256 ? need_bytes : 256)}, like.options().dtype(at::kByte));
+    w.own = unlocked([&] { return at::empty({(int64_t)(need_bytes > 256 ? need_bytes : 256)}, like.options().dtype(at::kByte)); });
     w.ptr = w.own.data_ptr();
     w.bytes = (size_t)w.own.numel();
   }
   return w;
-}
-
-at::Tensor int_tensor(at::IntArrayRef sizes, const at::Tensor &like) {
-  return at::empty(sizes, like.options().dtype(at::kInt));
 }
 
 struct Release {
@@ -222,10 +235,15 @@ PyObject *py_tree_mask(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const at::Tensor &nodes = dev(a[0], at::kInt), &parent = dev(a[1], at::kInt);
     need(parent.dim() == 2);
     const int64_t B = parent.size(0), T = parent.size(1);
-    at::Tensor depth = int_tensor({B, T}, parent), anc = at::empty({B, T, 2}, parent.options().dtype(at::kLong));
+    at::Tensor depth, anc;
+    {
+      const Unlocked u;
+      depth = at::empty({B, T}, parent.options());
+      anc = at::empty({B, T, 2}, parent.options().dtype(at::kLong));
+    }
     Owned result = tuple_of(object(depth), object(anc));
-    called(entries.tree_mask(size32(B), size32(T), (const int32_t *)nodes.data_ptr(), (const int32_t *)parent.data_ptr(),
-                           (int32_t *)depth.data_ptr(), (uint64_t *)anc.data_ptr(), stream_of(a[2])));
+    call(entries.tree_mask, size32(B), size32(T), (const int32_t *)nodes.data_ptr(), (const int32_t *)parent.data_ptr(),
+         (int32_t *)depth.data_ptr(), (uint64_t *)anc.data_ptr(), stream_of(a[2]));
     return result;
   });
 }
@@ -245,13 +263,13 @@ PyObject *py_tree_attention(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const int64_t L = kc.size(2);
     need(kc.sizes() == at::IntArrayRef({B, H, L, d}) && vc.sizes() == kc.sizes() && kt.sizes() == q.sizes() && vt.sizes() == q.sizes());
     need(tree.B == B && tree.T_max == T);
-    const at::Tensor out = a[12] == Py_None ? at::empty_like(q) : tensor(a[12]);
+    const at::Tensor out = a[12] == Py_None ? unlocked([&] { return at::empty_like(q); }) : tensor(a[12]);
     const Workspace w = workspace(a[13], entries.workspace_bytes(PROPD_WS_TREE_ATTENTION, tree.B, tree.T_max, size32(H), size32(d),
                                                                  size32(L), 0, 0), q);
     Owned result = a[12] != Py_None ? object(a[12]) : object(out);
-    called(entries.tree_attention(&tree, dt, size32(H), size32(d), real(a[11]), q.data_ptr(), L ? kc.data_ptr() : nullptr,
-                                L ? vc.data_ptr() : nullptr, kt.data_ptr(), vt.data_ptr(), (const int32_t *)seq.data_ptr(),
-                                size32(L), out.data_ptr(), w.ptr, w.bytes, stream_of(a[14])));
+    call(entries.tree_attention, &tree, dt, size32(H), size32(d), real(a[11]), q.data_ptr(), L ? kc.data_ptr() : nullptr,
+         L ? vc.data_ptr() : nullptr, kt.data_ptr(), vt.data_ptr(), (const int32_t *)seq.data_ptr(),
+         size32(L), out.data_ptr(), w.ptr, w.bytes, stream_of(a[14]));
     return result;
   });
 }
@@ -278,27 +296,41 @@ PyObject *py_early_prune(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const bool given = a[10] != Py_None;
     need(n_pay <= PROPD_MAX_PAYLOADS);
     need(!given || ((PyList_Check(a[10]) || PyTuple_Check(a[10])) && PySequence_Fast_GET_SIZE(a[10]) >= n_pay));
-    propd_payload pay[PROPD_MAX_PAYLOADS];
-    at::Tensor made[PROPD_MAX_PAYLOADS];
+    // held here: the lists are not looked at again, other threads may change them
+    at::Tensor src[PROPD_MAX_PAYLOADS], dst[PROPD_MAX_PAYLOADS];
+    Owned dst_object[PROPD_MAX_PAYLOADS];
     for (Py_ssize_t i = 0; i < n_pay; ++i) {
-      const at::Tensor &src = tensor(PySequence_Fast_GET_ITEM(a[9], i));
-      need(src.is_cuda() && src.is_contiguous() && (src.dim() == 3 || src.dim() == 4));
-      const int64_t outer = src.dim() == 3 ? 1 : src.size(1);
-      need(src.size(0) == B && src.size(-2) == T);
-      if (!given) made[i] = at::empty_like(src);
-      const at::Tensor &dst = given ? tensor(PySequence_Fast_GET_ITEM(a[10], i)) : made[i];
-      need(dst.sizes() == src.sizes() && dst.scalar_type() == src.scalar_type() && dst.is_contiguous());
-      const int64_t row = src.size(-1) * src.element_size();
-      pay[i] = propd_payload{src.data_ptr(), dst.data_ptr(), (size_t)row, outer, outer * T * row, T * row, row};
+      src[i] = tensor(PySequence_Fast_GET_ITEM(a[9], i));
+      need(src[i].is_cuda() && src[i].is_contiguous() && (src[i].dim() == 3 || src[i].dim() == 4));
+      need(src[i].size(0) == B && src[i].size(-2) == T);
+      if (!given) continue;
+      PyObject *const o = PySequence_Fast_GET_ITEM(a[10], i);
+      dst[i] = tensor(o);
+      need(dst[i].sizes() == src[i].sizes() && dst[i].scalar_type() == src[i].scalar_type() && dst[i].is_contiguous());
+      dst_object[i] = object(o);
     }
     // per-node and per-sequence outputs in one allocation each, every one of them on a multiple of 16 bytes
     const bool rank = top_k && extra;
-    const auto i32 = hid.options().dtype(at::kInt), i64 = hid.options().dtype(at::kLong);
-    const auto nodes = at::empty_strided({rank ? 6 : 5, B, T}, {(B * T + 3) / 4 * 4, T, 1}, i32).unbind(0);
-    const auto counts = at::empty_strided({2, B}, {(B + 3) / 4 * 4, 1}, i32).unbind(0);
-    at::Tensor keep = at::empty({B, 2}, i64), cu = at::empty({B + 1}, i32), anc = at::empty({B, T, 2}, i64), more;
-    if (rank) more = nodes[5];
-    if (!top_k && extra) more = at::empty({B, T}, hid.options().dtype(at::kFloat));
+    std::vector<at::Tensor> nodes, counts;
+    at::Tensor keep, cu, anc, more;
+    {
+      const Unlocked u;
+      const auto i32 = hid.options().dtype(at::kInt), i64 = hid.options().dtype(at::kLong);
+      nodes = at::empty_strided({rank ? 6 : 5, B, T}, {(B * T + 3) / 4 * 4, T, 1}, i32).unbind(0);
+      counts = at::empty_strided({2, B}, {(B + 3) / 4 * 4, 1}, i32).unbind(0);
+      keep = at::empty({B, 2}, i64);
+      cu = at::empty({B + 1}, i32);
+      anc = at::empty({B, T, 2}, i64);
+      if (rank) more = nodes[5];
+      if (!top_k && extra) more = at::empty({B, T}, hid.options().dtype(at::kFloat));
+      for (Py_ssize_t i = 0; i < n_pay && !given; ++i) dst[i] = at::empty_like(src[i]);
+    }
+    propd_payload pay[PROPD_MAX_PAYLOADS];
+    for (Py_ssize_t i = 0; i < n_pay; ++i) {
+      const int64_t outer = src[i].dim() == 3 ? 1 : src[i].size(1), row = src[i].size(-1) * src[i].element_size();
+      pay[i] = propd_payload{src[i].data_ptr(), dst[i].data_ptr(), (size_t)row, outer, outer * T * row, T * row, row};
+      if (!given) dst_object[i] = object(dst[i]);
+    }
     int32_t *node[5];
     for (int i = 0; i < 5; ++i) node[i] = (int32_t *)nodes[i].data_ptr();
     propd_tree_out out;
@@ -312,19 +344,17 @@ PyObject *py_early_prune(PyObject *, PyObject *const *a, Py_ssize_t n) {
     uint64_t *keep_p = (uint64_t *)keep.data_ptr();
     int32_t *kept_p = (int32_t *)counts[0].data_ptr(), *cu_p = (int32_t *)cu.data_ptr();
     Owned moved = owned(PyList_New(n_pay));
-    for (Py_ssize_t i = 0; i < n_pay; ++i)
-      PyList_SET_ITEM(moved.get(), i, (given ? object(PySequence_Fast_GET_ITEM(a[10], i)) : object(made[i])).release());
+    for (Py_ssize_t i = 0; i < n_pay; ++i) PyList_SET_ITEM(moved.get(), i, dst_object[i].release());
     Owned result = tuple_of(object(keep), object(nodes[0]), object(nodes[1]), object(counts[0]), object(cu), object(counts[1]),
                             object(nodes[2]), object(nodes[3]), object(nodes[4]), object(anc), object(more), std::move(moved));
     void *st = stream_of(a[13]);
-    const propd_status done =
-        top_k ? entries.early_prune(&tree, dt, size32(hidden), size32(vocab), count, hid.data_ptr(), head.data_ptr(), keep_p, node[0],
-                                    node[1], kept_p, cu_p, &out, rank ? (int32_t *)more.data_ptr() : nullptr, (int32_t)n_pay, pay,
-                                    w.ptr, w.bytes, st)
-              : entries.early_prune_prob(&tree, dt, size32(hidden), size32(vocab), (propd_prob_mode)mode, threshold, count,
-                                         hid.data_ptr(), head.data_ptr(), keep_p, node[0], node[1], kept_p, cu_p, &out,
-                                         more.defined() ? (float *)more.data_ptr() : nullptr, (int32_t)n_pay, pay, w.ptr, w.bytes, st);
-    called(done);
+    if (top_k)
+      call(entries.early_prune, &tree, dt, size32(hidden), size32(vocab), count, hid.data_ptr(), head.data_ptr(), keep_p, node[0], node[1],
+           kept_p, cu_p, &out, rank ? (int32_t *)more.data_ptr() : nullptr, (int32_t)n_pay, pay, w.ptr, w.bytes, st);
+    else
+      call(entries.early_prune_prob, &tree, dt, size32(hidden), size32(vocab), (propd_prob_mode)mode, threshold, count, hid.data_ptr(),
+           head.data_ptr(), keep_p, node[0], node[1], kept_p, cu_p, &out, more.defined() ? (float *)more.data_ptr() : nullptr,
+           (int32_t)n_pay, pay, w.ptr, w.bytes, st);
     return result;
   });
 }
@@ -339,11 +369,18 @@ PyObject *py_accept_path(PyObject *, PyObject *const *a, Py_ssize_t n) {
     need(logits.dim() == 3 && logits.is_cuda() && logits.is_contiguous() && tree.B == logits.size(0) && tree.T_max == logits.size(1));
     const int32_t vocab = size32(logits.size(2)), stride = a[6] == Py_None ? tree.T_max : whole32(a[6]);
     need(stride >= 0);
-    at::Tensor len = int_tensor({tree.B}, logits), path = int_tensor({tree.B, stride}, logits), next = int_tensor({tree.B}, logits);
+    at::Tensor len, path, next;
+    {
+      const Unlocked u;
+      const auto i32 = logits.options().dtype(at::kInt);
+      len = at::empty({tree.B}, i32);
+      path = at::empty({tree.B, stride}, i32);
+      next = at::empty({tree.B}, i32);
+    }
     const Workspace w = workspace(a[7], entries.workspace_bytes(PROPD_WS_ACCEPT_PATH, tree.B, tree.T_max, 0, 0, 0, 0, vocab), logits);
     Owned result = tuple_of(object(len), object(path), object(next));
-    called(entries.accept_path(&tree, dt, vocab, logits.data_ptr(), (int32_t *)len.data_ptr(), (int32_t *)path.data_ptr(), stride,
-                             (int32_t *)next.data_ptr(), w.ptr, w.bytes, stream_of(a[8])));
+    call(entries.accept_path, &tree, dt, vocab, logits.data_ptr(), (int32_t *)len.data_ptr(), (int32_t *)path.data_ptr(), stride,
+         (int32_t *)next.data_ptr(), w.ptr, w.bytes, stream_of(a[8]));
     return result;
   });
 }
@@ -364,11 +401,11 @@ PyObject *py_commit_path(PyObject *, PyObject *const *a, Py_ssize_t n) {
     need(vt.sizes() == kt.sizes() && kc.sizes() == at::IntArrayRef({B, H, L, d}) && vc.sizes() == kc.sizes() && tree.B == B && tree.T_max == T);
     const int32_t stride = size32(path.size(1)), out_stride = a[13] == Py_None ? stride : whole32(a[13]);
     need(out_stride >= 0);
-    at::Tensor out = int_tensor({B, out_stride}, kt);
+    const at::Tensor out = unlocked([&] { return at::empty({B, out_stride}, kt.options().dtype(at::kInt)); });
     Owned result = object(out);
-    called(entries.commit_path(&tree, dt, size32(H), size32(d), (const int32_t *)len.data_ptr(), (const int32_t *)path.data_ptr(), stride,
-                             (const int32_t *)next.data_ptr(), kt.data_ptr(), vt.data_ptr(), kc.data_ptr(), vc.data_ptr(), size32(L),
-                             (int32_t *)seq.data_ptr(), (int32_t *)out.data_ptr(), out_stride, stream_of(a[14])));
+    call(entries.commit_path, &tree, dt, size32(H), size32(d), (const int32_t *)len.data_ptr(), (const int32_t *)path.data_ptr(), stride,
+         (const int32_t *)next.data_ptr(), kt.data_ptr(), vt.data_ptr(), kc.data_ptr(), vc.data_ptr(), size32(L),
+         (int32_t *)seq.data_ptr(), (int32_t *)out.data_ptr(), out_stride, stream_of(a[14]));
     return result;
   });
 }

@@ -1,6 +1,8 @@
 """The native argument marshalling against the Python code of the binding: the same outputs, and the same
 errors for what is refused."""
 import ctypes
+import threading
+import time
 
 import numpy as np
 import pytest
@@ -195,3 +197,31 @@ def test_out_of_host_memory_leaves_no_call_behind(pb, x):
         assert (seq.tolist() != x["seq"].tolist()) == made[-1], n
         seq.copy_(x["seq"])
     assert made[-1] and not all(made)
+
+
+def test_other_threads_run_during_a_call(pb, x):
+    """The C call (here one that sleeps in place of a launch that waits) and the allocations leave the interpreter to
+    other threads, as calls through ctypes do."""
+    native, lib = pb._native(), pb.load_library()
+    address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    sleep = address(ctypes.CDLL(None).sleep)  # of the seconds that its first argument says: B
+    n, parent = torch.ones(1, dtype=torch.int32, device="cuda"), -torch.ones(1, 1, dtype=torch.int32, device="cuda")
+    ticks, stop = [], threading.Event()
+
+    def tick():
+        while not stop.wait(0.01):
+            ticks.append(time.perf_counter())
+
+    thread = threading.Thread(target=tick)
+    try:
+        native.init(sleep, *[address(lib.propd_tree_attention)] * 6)
+        thread.start()
+        start = time.perf_counter()
+        native.tree_mask(n, parent, pb._stream)
+        end = time.perf_counter()
+    finally:
+        stop.set()
+        thread.join()
+        pb._init_marshal(lib)
+    assert end - start > 0.9
+    assert sum(start + 0.1 < at < end - 0.1 for at in ticks) > 10
