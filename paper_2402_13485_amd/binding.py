@@ -13,6 +13,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from dataclasses import dataclass
 from typing import Optional, Sequence
 
@@ -60,7 +61,9 @@ def _init_marshal(lib: ctypes.CDLL) -> None:
     global _marshal
     try:
         from . import _marshal as native
-    except ImportError:
+    except ImportError as e:
+        warnings.warn(f"the native argument marshalling is not there ({e}): calls are marshalled in Python, which takes "
+                      "two to three times as long on the host", RuntimeWarning, stacklevel=3)
         return
     native.init(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in (
         "propd_tree_mask", "propd_tree_attention", "propd_early_prune", "propd_early_prune_prob", "propd_accept_path",

@@ -45,12 +45,16 @@ def unsafe_kernels(remarks: str) -> list:
     return found + [f"{kernel}: no resource usage reported" for kernel in HAND_WAITED if kernel not in seen]
 
 
+def has_marshal() -> bool:
+    return os.path.exists(os.path.join(CSRC, MARSHAL_SOURCE))
+
+
 def stale() -> bool:
-    """Whether there is no library, or one that is older than a source."""
-    if not os.path.exists(LIB_PATH):
-        return True
+    """Whether the library or the native marshalling is missing, or older than a source."""
     sources = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [HEADER, os.path.abspath(__file__)]
-    return max(map(os.path.getmtime, sources)) > os.path.getmtime(LIB_PATH)
+    newest = max(map(os.path.getmtime, sources))
+    return any(not os.path.exists(made) or os.path.getmtime(made) < newest
+               for made in [LIB_PATH] + [MARSHAL_PATH] * has_marshal())
 
 
 def marshal_command(out: str) -> list:
@@ -61,13 +65,39 @@ def marshal_command(out: str) -> list:
             "-ltorch_python", "-ltorch_cpu", "-lc10"]
 
 
-def build(verbose: bool = False) -> str:
-    if os.path.exists(os.path.join(CSRC, MARSHAL_SOURCE)):
+def build_marshal(verbose: bool) -> bool:
+    """The native marshalling as MARSHAL_PATH + ".new"; False if it cannot be built here (no host compiler, no
+    PyTorch headers): the binding marshals in Python then, and says so."""
+    try:
         cmd = marshal_command(MARSHAL_PATH + ".new")
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.run(cmd, check=True)
+        return True
+    except (ImportError, OSError, subprocess.CalledProcessError) as e:
+        print(f"the native marshalling is not built: {e}", file=sys.stderr, flush=True)
+        return False
+
+
+def build(verbose: bool = False) -> str:
+    """Both are replaced only when the library is built: they share the structures of the header."""
+    marshal = has_marshal() and build_marshal(verbose)
+    try:
+        build_library(verbose)
+    except BaseException:
+        if marshal:
+            os.remove(MARSHAL_PATH + ".new")
+        raise
+    os.replace(LIB_PATH + ".new", LIB_PATH)
+    if marshal:
         os.replace(MARSHAL_PATH + ".new", MARSHAL_PATH)
+    elif has_marshal() and os.path.exists(MARSHAL_PATH):
+        os.remove(MARSHAL_PATH)  # made for the library before
+    return LIB_PATH
+
+
+def build_library(verbose: bool) -> None:
+    """The library as LIB_PATH + ".new"."""
     srcs = [os.path.join(CSRC, s) for s in SOURCES]
     extra = os.environ.get("PROPD_EXTRA_HIPCC_FLAGS", "").split()  # tuning experiments only
     new = LIB_PATH + ".new"
@@ -90,8 +120,6 @@ def build(verbose: bool = False) -> str:
     if bad:
         os.remove(new)
         raise RuntimeError("these kernels must not spill, the library is not replaced:\n" + "\n".join(bad))
-    os.replace(new, LIB_PATH)
-    return LIB_PATH
 
 
 if __name__ == "__main__":

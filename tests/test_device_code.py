@@ -3,6 +3,7 @@ import os
 import re
 import shutil
 import subprocess
+import sys
 
 import pytest
 
@@ -88,3 +89,54 @@ def test_library_older_than_a_source_is_stale(tmp_path, monkeypatch):
     assert hip_build.stale()
     os.remove(tmp_path / "lib.so")
     assert hip_build.stale()
+
+
+@pytest.mark.parametrize("library,marshal", [(True, True), (True, False), (False, True)])
+def test_library_and_marshalling_are_replaced_together(tmp_path, monkeypatch, capfd, library, marshal):
+    """The library is built where the marshalling cannot be, which then goes: it was made for the library before.
+    A library that is not replaced keeps the marshalling it came with."""
+    (tmp_path / "one.hip").write_text(SPILLING % ((16 if library else 200,) * 4))
+    (tmp_path / "marshal.cpp").write_text("int one() { return 1; }")
+    for name in ("lib.so", "marshal.so"):
+        (tmp_path / name).write_text("the one before")
+    monkeypatch.setattr(hip_build, "CSRC", str(tmp_path))
+    monkeypatch.setattr(hip_build, "SOURCES", ["one.hip"])
+    monkeypatch.setattr(hip_build, "LIB_PATH", str(tmp_path / "lib.so"))
+    monkeypatch.setattr(hip_build, "MARSHAL_PATH", str(tmp_path / "marshal.so"))
+    if not marshal:
+        monkeypatch.setattr(hip_build, "marshal_command", lambda out: ["/nowhere/g++", out])
+    if library:
+        hip_build.build()
+    else:
+        with pytest.raises(RuntimeError, match="tree_attn_bf16_kernel"):
+            hip_build.build()
+    left = {name: (tmp_path / name).read_bytes()[:4] for name in os.listdir(tmp_path) if ".so" in name}
+    elf, before = b"\x7fELF", b"the "
+    assert left == ({"lib.so": elf, "marshal.so": elf} if library and marshal else {"lib.so": elf} if library else
+                    {"lib.so": before, "marshal.so": before})
+    assert ("not built" in capfd.readouterr().err) == (not marshal)
+
+
+def test_missing_or_old_marshalling_is_stale(tmp_path, monkeypatch):
+    now = 2e9 if os.path.getmtime(hip_build.__file__) < 2e9 else 4e9
+    for name, time in (("lib.so", now), ("marshal.so", now), ("marshal.cpp", 1e9)):
+        (tmp_path / name).write_text("")
+        os.utime(tmp_path / name, (time, time))
+    monkeypatch.setattr(hip_build, "CSRC", str(tmp_path))
+    monkeypatch.setattr(hip_build, "LIB_PATH", str(tmp_path / "lib.so"))
+    monkeypatch.setattr(hip_build, "MARSHAL_PATH", str(tmp_path / "marshal.so"))
+    assert not hip_build.stale()
+    os.utime(tmp_path / "marshal.so", (1e9 - 1, 1e9 - 1))
+    assert hip_build.stale()
+    os.remove(tmp_path / "marshal.so")
+    assert hip_build.stale()
+
+
+def test_missing_marshalling_is_reported(tmp_path):
+    """A copy of the package without it: the library loads, with a warning."""
+    from paper_2402_13485_amd import binding
+    shutil.copytree(os.path.dirname(binding.__file__), tmp_path / "pkg", ignore=shutil.ignore_patterns("_marshal.so", "csrc"))
+    code = ("import warnings; warnings.simplefilter('error'); from pkg import binding\n"
+            "try: binding.load_library()\nexcept RuntimeWarning as e: print(e)")
+    done = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True)
+    assert "marshalling is not there" in done.stdout, done
