@@ -27,6 +27,7 @@
 //                         the listed payload tensors, shared among the workgroups of the sequence;
 //                         the last sequence to arrive leaves the prefix sum of the survivor counts
 //   cu_nodes_kernel       that prefix sum where nothing was scored
+#include <atomic>
 #include <cstdlib>
 #include <type_traits>
 #include <utility>
@@ -1313,14 +1314,13 @@ __global__ __launch_bounds__(kFinishThreads) void prune_finish_kernel(FinishArgs
 }  // namespace propd
 
 static int prune_compute_units() {
-  static int cus = 0;
-  if (cus == 0) {
+  static const int cus = [] {
     int dev = 0;
     hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-      cus = prop.multiProcessorCount;
-    if (cus <= 0) cus = 256;
-  }
+    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0)
+      return prop.multiProcessorCount;
+    return 256;
+  }();
   return cus;
 }
 
@@ -1435,7 +1435,7 @@ static propd_status prune_impl(
     tb.parts = (int)ws.parts;
     tb.n_tiles = ws.notes + kNoteTiles;
     if (dt == PROPD_BF16) {
-      static bool attr_set = false;
+      static std::atomic<bool> attr_set{false};  // calls may come from several threads
       if (!attr_set) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(&early_head_bf16_kernel<0>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kHeadLdsBytes) != hipSuccess ||

@@ -31,6 +31,7 @@
 // of its own): 8 x 16 units of 64 queries x 2048 keys, 4150 -> 31 us + 5 us merge (67 MB of K/V).
 // Without a workspace or 16-byte alignment d = 64 runs a plain one-wave-per-query kernel.
 // fp32 path: tree_attention_f32.h.
+#include <atomic>
 #include <type_traits>
 #include <utility>
 
@@ -1493,14 +1494,13 @@ static void fill_plain(AttnParamsPlain<E> &p, const propd_tree *tree, int H, flo
 // host side
 // ------------------------------------------------------------------------------------
 static int compute_units() {
-  static int cus = 0;
-  if (cus == 0) {
+  static const int cus = [] {
     int dev = 0;
     hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-      cus = prop.multiProcessorCount;
-    if (cus <= 0) cus = 256;
-  }
+    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0)
+      return prop.multiProcessorCount;
+    return 256;
+  }();
   return cus;
 }
 
@@ -1533,7 +1533,7 @@ size_t tree_attention_workspace_bytes(int B, int H, int L_max, int T_max) {
 template <int D, int KS, bool kAnew>
 static bool launch_bf16(const AttnParams &p, int grid, hipStream_t st) {
   constexpr int lds_bytes = kRingStages * Geo<D>::kStageBytes;
-  static bool attr_set = false;
+  static std::atomic<bool> attr_set{false};  // calls may come from several threads
   if (!attr_set) {
     if (hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_bf16_kernel<kRingStages, D, KS, kAnew>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes) != hipSuccess)
