@@ -133,11 +133,12 @@ __device__ __forceinline__ void early_head_f32_tile(int hidden, int vocab, int m
   });
 
   const int m1 = m0 + BM < m_total ? m0 + BM : m_total;
-  int first = 0, end = 0;
-  NodeChunk nodes = {-1, 0, 0.f};
+  NodeChunk nodes = {0, -1, 0, 0.f};
+  NodeRange range = {0, 0, false};
   if (KIND == 0) {  // while the first blocks are on their way
-    nodes_of_rows(m0, m1, m_total, tb, first, end);
-    nodes = load_nodes(first, end, wave, lane, tb);
+    range = nodes_of_rows(m0, m1, m_total, tb);
+    nodes.node = chunk_node(range, range.first, wave, lane, tb);
+    if (!range.listed) load_values(nodes, tb);
   }
 
   meet();  // the tile before this one has been read
@@ -163,6 +164,7 @@ __device__ __forceinline__ void early_head_f32_tile(int hidden, int vocab, int m
       chunk(n_blocks, k, f32_piece(wp + x0 + 16 * k, hidden - x0 - 16 * k - 4 * kq));
   }
   mfma_settle();
+  if (KIND == 0 && range.listed) load_values(nodes, tb);
 
   float *s_z = reinterpret_cast<float *>(smem);
   __syncthreads();  // the score rows have been read
@@ -172,7 +174,7 @@ __device__ __forceinline__ void early_head_f32_tile(int hidden, int vocab, int m
 #pragma unroll
     for (int r = 0; r < 4; ++r) s_z[(16 * i + 4 * kq + r) * BN + col] = acc[i][r];
   __syncthreads();
-  rows_epilogue<KIND>(nodes, first, end, s_z, wave, lane, m0, m1, v0, vocab, n_tile, tb);
+  rows_epilogue<KIND>(nodes, range, s_z, wave, lane, m0, m1, v0, vocab, n_tile, tb);
 }
 
 // Persistent over the tiles, XCD-aware like the bf16 kernel: the row tiles of one column tile are

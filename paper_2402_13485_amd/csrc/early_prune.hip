@@ -46,7 +46,7 @@ struct PruneScratch {
   int32_t *row_src;     // [B*T_max]  score row -> b*T_max + node
   int32_t *row_base;    // [B+1]      score rows of the sequences before b; [B] = total rows
   int32_t *row_info;    // [B*T_max][2] score row -> (first position in child_list, children)
-  int32_t *child_list;  // [B*T_max]  b*T_max + child, grouped by parent, per sequence slot
+  int32_t *child_list;  // [B*T_max]  b*T_max + child, grouped by parent, in the order of the score rows, without gaps
   float *own;           // [B*T_max]  z_parent[token] of every non-root node
   int32_t *notes;       // what the kernels leave each other, see kNote*
   float *lse_part;      // [row_cap * parts][2]  probability criterion: (max, sum exp) per tile
@@ -154,23 +154,23 @@ __device__ __forceinline__ int valid_parent(int nd, int T, int p) {
 }
 
 // Table workgroup g, wave wv: the tables of sequence b = kTableWaves * g + wv, two nodes per lane
-// (lane and lane + 64).  A sequence's score rows follow those of all sequences before it, so the
-// wave needs the number of nodes with children of every earlier sequence: the waves of the
+// (lane and lane + 64).  A sequence's score rows, and their children in the list, follow those of all sequences
+// before it, so the wave needs the numbers of nodes with children, and of children, of every earlier sequence: the waves of the
 // workgroup count them together (sequence x by wave x % kTableWaves, a mark per parent in LDS,
 // all loads of a wave's sequences in flight before the first is used) and exchange the counts
 // through LDS.  No workgroup waits for another: each one counts for itself what it needs.
 __device__ void prepare_tables(const PrepareArgs &a, int g) {
   constexpr int kBatch = 8;  // sequences a wave counts per round
   __shared__ int s_cnt[kTableWaves][PROPD_MAX_TREE];
-  __shared__ int s_rows[kTableWaves];  // score rows before this workgroup's sequences, per counting wave
-  __shared__ int s_own[kTableWaves];   // nodes with children of the workgroup's own sequences
+  __shared__ int s_rows[kTableWaves], s_kids[kTableWaves];  // rows and children before this workgroup's sequences, per counting wave
+  __shared__ int s_own[kTableWaves], s_own_kids[kTableWaves];  // of the workgroup's own sequences
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   int *cnt = s_cnt[wv];
   const int b = kTableWaves * g + wv;
   const int node[2] = {lane, lane + 64};
 
   // ---- nodes with children of the earlier sequences this wave counts: x = wv, wv + 4, ... < 4 g
-  int rows_before = 0;
+  int rows_before = 0, kids_before = 0;
   for (int x0 = wv; x0 < kTableWaves * g; x0 += kTableWaves * kBatch) {
     int Tx[kBatch], px[kBatch][2];
 #pragma unroll
@@ -192,6 +192,7 @@ __device__ void prepare_tables(const PrepareArgs &a, int g) {
       for (int h = 0; h < 2; ++h) {
         const int p = valid_parent(node[h], Tx[i], px[i][h]);
         if (p >= 0) cnt[p] = 1;
+        kids_before += __popcll(__ballot(p >= 0));
       }
       wave_lds_fence();
       rows_before += __popcll(__ballot(cnt[node[0]] != 0)) + __popcll(__ballot(cnt[node[1]] != 0));
@@ -201,7 +202,7 @@ __device__ void prepare_tables(const PrepareArgs &a, int g) {
 
   // ---- this wave's own sequence
   int T = 0, par[2] = {-1, -1}, slot[2] = {0, 0}, mine[2] = {0, 0}, incl[2] = {0, 0}, par_before[2] = {0, 0};
-  int run_par = 0;
+  int run_par = 0, run_kids = 0;
   const size_t base = (size_t)(b < a.B ? b : 0) * a.T_max;
   if (b < a.B) {  // uniform over the wave
     T = clamp_tree(a.n_nodes[b], a.T_max);
@@ -219,7 +220,6 @@ __device__ void prepare_tables(const PrepareArgs &a, int g) {
     mine[1] = cnt[node[1]];
     wave_lds_fence();
     // exclusive prefix of the child counts over the nodes, and of "has children"
-    int run = 0;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       incl[h] = mine[h];
@@ -229,39 +229,42 @@ __device__ void prepare_tables(const PrepareArgs &a, int g) {
         if (lane >= o) incl[h] += up;
       }
       const int total = __shfl(incl[h], 63, kWave);
-      incl[h] += run;
-      run += total;
+      incl[h] += run_kids;
+      run_kids += total;
       const uint64_t has = __ballot(mine[h] > 0);
       par_before[h] = run_par + __popcll(has & ((1ull << lane) - 1ull));
       run_par += __popcll(has);
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) cnt[node[h]] = incl[h] - mine[h];  // first position of this node's children
-    wave_lds_fence();
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-      if (par[h] >= 0) a.child_list[base + cnt[par[h]] + slot[h]] = (int)base + node[h];
   }
   if (lane == 0) {
     s_rows[wv] = rows_before;
+    s_kids[wv] = kids_before;
     s_own[wv] = run_par;
+    s_own_kids[wv] = run_kids;
   }
   __syncthreads();
   if (b >= a.B) return;
-  int first = 0;
+  int first = 0, first_kid = 0;
 #pragma unroll
-  for (int w = 0; w < kTableWaves; ++w) first += s_rows[w] + (w < wv ? s_own[w] : 0);
-  // positions are global: b*T_max + position in the sequence's slot
+  for (int w = 0; w < kTableWaves; ++w) {
+    first += s_rows[w] + (w < wv ? s_own[w] : 0);
+    first_kid += s_kids[w] + (w < wv ? s_own_kids[w] : 0);
+  }
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
+  for (int h = 0; h < 2; ++h) {
+    if (par[h] >= 0) a.child_list[first_kid + cnt[par[h]] + slot[h]] = (int)base + node[h];
     if (mine[h] > 0) {
       const int r = first + par_before[h];
       a.row_src[r] = (int)base + node[h];
-      a.row_info[2 * r] = (int)base + incl[h] - mine[h];
+      a.row_info[2 * r] = first_kid + incl[h] - mine[h];
       a.row_info[2 * r + 1] = mine[h];
     }
+  }
   if (a.node_row) {
     // the score row of every node's parent, -1 for nodes (and padding) without one
+    wave_lds_fence();
     cnt[node[0]] = par_before[0];
     cnt[node[1]] = par_before[1];
     wave_lds_fence();
@@ -528,7 +531,7 @@ __device__ __forceinline__ void lse_merge(float &m, float &s, float m2, float s2
 //      of few rows): the scores of the tile, rows x 128 columns, pass through LDS.
 //   top-k: a wave takes a child (every eighth node) against the 128 scores of its parent's row, four
 //     children's scores in flight.  The nodes' rows, tokens and own scores, one node per lane, are fetched
-//     while the first operands are on their way.
+//     while the first operands are on their way (of listed nodes, see NodeRange, behind the products).
 //   probability: a wave takes a row (every eighth).
 // The loops are not unrolled over the rows: this code runs once per tile, and instructions cost their
 // fetch.  As an unrolled loop over up to 16 rows per wave, with the children of each in registers of its own, it
@@ -537,38 +540,64 @@ __device__ __forceinline__ void lse_merge(float &m, float &s, float m2, float s2
 // 69.0, fp32 2 x 32 x 1024 x 32000 58.3 -> 56.8.
 constexpr int kRowsCols = 128;
 
-struct NodeChunk {  // as loaded: nodes first + 8 * lane + wave, the first node past the end
-  int row, tok;
+// Where the nodes come from: the slots of the sequences that the tile's rows belong to, if these are one chunk; else
+// the list of the rows' children, whose entries are fetched in front, and what they name behind the products (in
+// slots that are mostly empty most chunks held nothing: a call of 128 trees of 2 nodes in slots of 128, x 1024 x 8192, took
+// 71 us, 39 from the list).
+constexpr int kChunkNodes = kGemmWaves * kWave;
+struct NodeChunk {  // one node per lane
+  int node, row, tok;
   float own;
 };
+struct NodeRange {  // slots, or positions in child_list
+  int first, end;
+  bool listed;
+};
 
-__device__ __forceinline__ NodeChunk load_nodes(int first, int end, int wave, int lane, const HeadTables &tb) {
-  const int x = first + kGemmWaves * lane + wave, at = x < end ? x : first;
-  NodeChunk c;
-  c.row = tb.node_row[at];
-  c.tok = tb.token[at];
-  c.own = tb.own[at];
-  return c;
+__device__ __forceinline__ void load_values(NodeChunk &c, const HeadTables &tb) {
+  c.row = tb.node_row[c.node];
+  c.tok = tb.token[c.node];
+  c.own = tb.own[c.node];
 }
 
-// The nodes whose parents may have score rows of m0 .. m1 - 1: those of the sequences of these rows.
-__device__ __forceinline__ void nodes_of_rows(int m0, int m1, int m_total, const HeadTables &tb, int &first, int &end) {
-  first = 0;
-  end = tb.cnt_stride;
-  if (m0 > 0) first = tb.row_src[m0] / tb.T_max * tb.T_max;
-  if (m1 < m_total) end = tb.row_src[m1 - 1] / tb.T_max * tb.T_max + tb.T_max;
+// The lane's place in a chunk: eight neighbours go to eight waves, in another order each time, so that nodes at the
+// same place of every slot do not all come to one wave (64 trees of 2 nodes in slots of 8, x 256 x 16384: 35 us for the
+// call, 25 so).
+__device__ __forceinline__ int chunk_place(int wave, int lane) {
+  static_assert(kGemmWaves == 8, "eight neighbours, eight waves");
+  return kGemmWaves * lane + ((wave + lane + (lane >> 3)) & 7);
+}
+
+// the lane's node of the chunk that starts at x0; past the end the first one of the range
+__device__ __forceinline__ int chunk_node(const NodeRange &r, int x0, int wave, int lane, const HeadTables &tb) {
+  const int x = x0 + chunk_place(wave, lane), at = x < r.end ? x : r.first;
+  return r.listed ? tb.child_list[at] : at;
+}
+
+// the nodes whose parents have (slots: may have) score rows of m0 .. m1 - 1
+__device__ __forceinline__ NodeRange nodes_of_rows(int m0, int m1, int m_total, const HeadTables &tb) {
+  NodeRange r = {0, tb.cnt_stride, false};
+  if (r.end > kChunkNodes) {
+    if (m0 > 0) r.first = tb.row_src[m0] / tb.T_max * tb.T_max;
+    if (m1 < m_total) r.end = tb.row_src[m1 - 1] / tb.T_max * tb.T_max + tb.T_max;
+    r.listed = r.end - r.first > kChunkNodes;
+  }
+  if (r.listed) {
+    r.first = tb.row_info[2 * m0];
+    r.end = tb.row_info[2 * m1 - 2] + tb.row_info[2 * m1 - 1];
+  }
+  return r;
 }
 
 // rows m0 .. m1 - 1 of the tile lie in s_z from its start
 template <int KIND>
-__device__ __forceinline__ void rows_epilogue(NodeChunk nodes, int first, int end, const float *s_z, int wave, int lane,
+__device__ __forceinline__ void rows_epilogue(NodeChunk nodes, const NodeRange &range, const float *s_z, int wave, int lane,
                                               int m0, int m1, int v0, int vocab, int n_tile, const HeadTables &tb) {
   constexpr int kX = kRowsCols / kWave;
   if (KIND == 0) {
     int32_t *dst = tb.cnt_part + (size_t)n_tile * tb.cnt_stride;
-    for (int x0 = first; x0 < end; x0 += kGemmWaves * kWave) {
-      if (x0 > first) nodes = load_nodes(x0, end, wave, lane, tb);
-      const bool mine = x0 + kGemmWaves * lane + wave < end && nodes.row >= m0 && nodes.row < m1;
+    for (int x0 = range.first;;) {
+      const bool mine = x0 + chunk_place(wave, lane) < range.end && nodes.row >= m0 && nodes.row < m1;
       uint64_t rest = __builtin_amdgcn_ballot_w64(mine);
       int count = 0;
       constexpr int N = 4;  // children at a time; past the last one the same once more
@@ -598,7 +627,11 @@ __device__ __forceinline__ void rows_epilogue(NodeChunk nodes, int first, int en
           count = lane == src[j] ? c : count;
         }
       }
-      if (mine) dst[x0 + kGemmWaves * lane + wave] = count;
+      if (mine) dst[nodes.node] = count;
+      x0 += kChunkNodes;
+      if (x0 >= range.end) break;
+      nodes.node = chunk_node(range, x0, wave, lane, tb);
+      load_values(nodes, tb);
     }
   } else {
 #pragma unroll 1
@@ -773,13 +806,21 @@ __device__ __forceinline__ void early_head_small_tile(
   const int n_pro = n_steps < kStages ? n_steps : kStages;
   constexpr int kMaxOutstanding = (kStages - 1) * (kALoads + 2);
   int slot_ld = 0;
+  NodeChunk nodes = {0, -1, 0, 0.f};
+  NodeRange range = {0, tb.cnt_stride, false};
+  if (KIND == 0 && range.end > kChunkNodes) {
+    range = nodes_of_rows(0, m_total, m_total, tb);
+    nodes.node = chunk_node(range, range.first, wave, lane, tb);
+  }
   for (int i = 0; i < n_pro; ++i) {
     issue(slot_ld, i);
     slot_ld = slot_ld + 1 == kStages ? 0 : slot_ld + 1;
   }
   // (loads younger than the ring's only make the counted waits below stricter)
-  NodeChunk nodes = {-1, 0, 0.f};
-  if (KIND == 0) nodes = load_nodes(0, tb.cnt_stride, wave, lane, tb);
+  if (KIND == 0 && !range.listed) {
+    nodes.node = chunk_node(range, 0, wave, lane, tb);
+    load_values(nodes, tb);
+  }
   gemm_wait_outstanding<kMaxOutstanding>((n_pro - 1) * per_step);
   __builtin_amdgcn_s_barrier();
   constexpr int kReads = kX + FN;  // LDS reads of one K sub-step
@@ -823,6 +864,7 @@ __device__ __forceinline__ void early_head_small_tile(
     __builtin_amdgcn_sched_barrier(0);
   }
   mfma_settle();
+  if (KIND == 0 && range.listed) load_values(nodes, tb);
   // element (row, col) of a 32 x 32 tile: lane col + 32 * (row / 4 % 2), register 4 * (row / 8) + row % 4
   float *s_z = reinterpret_cast<float *>(gemm_smem);
   __syncthreads();  // every wave is done with the ring
@@ -836,7 +878,7 @@ __device__ __forceinline__ void early_head_small_tile(
           s_z[(wm * 64 + 32 * x + 8 * (r >> 2) + 4 * g + (r & 3)) * kRowsCols + wn * 64 + 32 * y + l32] = acc[x][y][r];
   }
   __syncthreads();
-  rows_epilogue<KIND>(nodes, 0, tb.cnt_stride, s_z, wave, lane, 0, m_total, v0, vocab, n_tile, tb);
+  rows_epilogue<KIND>(nodes, range, s_z, wave, lane, 0, m_total, v0, vocab, n_tile, tb);
   __syncthreads();  // the next tile's loads reuse this memory
 }
 

@@ -296,15 +296,16 @@ def test_prune_bf16_few_rows_edges(pb, oracle, T, Hd, V):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("trees", ["star", "mixed", "small", "rows"])
+@pytest.mark.parametrize("trees", ["star", "mixed", "small", "rows", "wide"])
 def test_prune_children_of_many_sequences(pb, oracle, dtype, trees):
-    """The epilogue over whole rows takes the nodes of a tile's rows 512 at a time: more nodes than that for a few rows
-    (stars), sequences without score rows between others, slots of an odd number of nodes, and (fp32) rows of one
-    sequence in two row tiles."""
+    """The epilogue over whole rows takes the nodes of a tile's rows 512 at a time, from the slots or from the list of
+    children: more nodes than that for a few rows (stars), sequences without score rows between others, slots of an odd
+    number of nodes or nearly empty ones, and (fp32) rows of one sequence in two row tiles."""
     rng = np.random.default_rng(len(trees))
     shapes = {"star": [synth.star_tree(128)] * 9, "mixed": [synth.star_tree(101), synth.chain_tree(1), synth.chain_tree(30),
               synth.random_tree(rng, 101), synth.chain_tree(1), synth.star_tree(2), synth.chain_tree(40), synth.star_tree(77)],
               "small": [synth.random_tree(rng, int(n)) for n in rng.integers(1, 6, 40)],
+              "wide": [synth.random_tree(rng, int(n)) for n in rng.integers(1, 4, 48)] + [synth.rank_product_tree(128, 4)],
               "rows": [synth.chain_tree(51), synth.star_tree(99), synth.chain_tree(61), synth.random_tree(rng, 99)]}[trees]
     T = max(len(t.parent) for t in shapes)
     w = synth.Workload(79, "case", dtype, len(shapes), 1, 128 if dtype == "bf16" else 64, T, 96, 300, 4, 1e-3 if dtype == "bf16" else 1e-5)
