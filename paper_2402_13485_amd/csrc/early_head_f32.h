@@ -134,11 +134,11 @@ __device__ __forceinline__ void early_head_f32_tile(int hidden, int vocab, int m
 
   const int m1 = m0 + BM < m_total ? m0 + BM : m_total;
   NodeChunk nodes = {0, -1, 0, 0.f};
-  NodeRange range = {0, 0, false};
+  NodeRange range = {0, 0, 1, false};
   if (KIND == 0) {  // while the first blocks are on their way
     range = nodes_of_rows(m0, m1, m_total, tb);
     nodes.node = chunk_node(range, range.first, wave, lane, tb);
-    if (!range.listed) load_values(nodes, tb);
+    if (__builtin_expect(!range.listed, 1)) load_values(nodes, tb);
   }
 
   meet();  // the tile before this one has been read
@@ -164,7 +164,7 @@ __device__ __forceinline__ void early_head_f32_tile(int hidden, int vocab, int m
       chunk(n_blocks, k, f32_piece(wp + x0 + 16 * k, hidden - x0 - 16 * k - 4 * kq));
   }
   mfma_settle();
-  if (KIND == 0 && range.listed) load_values(nodes, tb);
+  if (KIND == 0 && __builtin_expect(range.listed, 0)) load_values(nodes, tb);
 
   float *s_z = reinterpret_cast<float *>(smem);
   __syncthreads();  // the score rows have been read

@@ -46,7 +46,8 @@ struct PruneScratch {
   int32_t *row_src;     // [B*T_max]  score row -> b*T_max + node
   int32_t *row_base;    // [B+1]      score rows of the sequences before b; [B] = total rows
   int32_t *row_info;    // [B*T_max][2] score row -> (first position in child_list, children)
-  int32_t *child_list;  // [B*T_max]  b*T_max + child, grouped by parent, in the order of the score rows, without gaps
+  int32_t *child_list;  // [B*T_max]  b*T_max + child, grouped by parent, in the order of the score rows; as many places
+                        //            for a sequence as it has nodes, -1 in those left over
   float *own;           // [B*T_max]  z_parent[token] of every non-root node
   int32_t *notes;       // what the kernels leave each other, see kNote*
   float *lse_part;      // [row_cap * parts][2]  probability criterion: (max, sum exp) per tile
@@ -154,23 +155,23 @@ __device__ __forceinline__ int valid_parent(int nd, int T, int p) {
 }
 
 // Table workgroup g, wave wv: the tables of sequence b = kTableWaves * g + wv, two nodes per lane
-// (lane and lane + 64).  A sequence's score rows, and their children in the list, follow those of all sequences
-// before it, so the wave needs the numbers of nodes with children, and of children, of every earlier sequence: the waves of the
+// (lane and lane + 64).  A sequence's score rows, and its places in the list of children, follow those of all sequences
+// before it, so the wave needs the numbers of nodes with children, and of nodes, of every earlier sequence: the waves of the
 // workgroup count them together (sequence x by wave x % kTableWaves, a mark per parent in LDS,
 // all loads of a wave's sequences in flight before the first is used) and exchange the counts
 // through LDS.  No workgroup waits for another: each one counts for itself what it needs.
 __device__ void prepare_tables(const PrepareArgs &a, int g) {
   constexpr int kBatch = 8;  // sequences a wave counts per round
   __shared__ int s_cnt[kTableWaves][PROPD_MAX_TREE];
-  __shared__ int s_rows[kTableWaves], s_kids[kTableWaves];  // rows and children before this workgroup's sequences, per counting wave
-  __shared__ int s_own[kTableWaves], s_own_kids[kTableWaves];  // of the workgroup's own sequences
+  __shared__ int s_rows[kTableWaves], s_nodes[kTableWaves];  // rows and nodes before this workgroup's sequences, per counting wave
+  __shared__ int s_own[kTableWaves], s_own_nodes[kTableWaves];  // of the workgroup's own sequences
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   int *cnt = s_cnt[wv];
   const int b = kTableWaves * g + wv;
   const int node[2] = {lane, lane + 64};
 
   // ---- nodes with children of the earlier sequences this wave counts: x = wv, wv + 4, ... < 4 g
-  int rows_before = 0, kids_before = 0;
+  int rows_before = 0, nodes_before = 0;
   for (int x0 = wv; x0 < kTableWaves * g; x0 += kTableWaves * kBatch) {
     int Tx[kBatch], px[kBatch][2];
 #pragma unroll
@@ -185,6 +186,7 @@ __device__ void prepare_tables(const PrepareArgs &a, int g) {
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
       if (x0 + kTableWaves * i >= kTableWaves * g) break;  // uniform
+      nodes_before += Tx[i];
       cnt[node[0]] = 0;
       cnt[node[1]] = 0;
       wave_lds_fence();
@@ -192,7 +194,6 @@ __device__ void prepare_tables(const PrepareArgs &a, int g) {
       for (int h = 0; h < 2; ++h) {
         const int p = valid_parent(node[h], Tx[i], px[i][h]);
         if (p >= 0) cnt[p] = 1;
-        kids_before += __popcll(__ballot(p >= 0));
       }
       wave_lds_fence();
       rows_before += __popcll(__ballot(cnt[node[0]] != 0)) + __popcll(__ballot(cnt[node[1]] != 0));
@@ -240,25 +241,26 @@ __device__ void prepare_tables(const PrepareArgs &a, int g) {
   }
   if (lane == 0) {
     s_rows[wv] = rows_before;
-    s_kids[wv] = kids_before;
+    s_nodes[wv] = nodes_before;
     s_own[wv] = run_par;
-    s_own_kids[wv] = run_kids;
+    s_own_nodes[wv] = T;
   }
   __syncthreads();
   if (b >= a.B) return;
-  int first = 0, first_kid = 0;
+  int first = 0, place = 0;
 #pragma unroll
   for (int w = 0; w < kTableWaves; ++w) {
     first += s_rows[w] + (w < wv ? s_own[w] : 0);
-    first_kid += s_kids[w] + (w < wv ? s_own_kids[w] : 0);
+    place += s_nodes[w] + (w < wv ? s_own_nodes[w] : 0);
   }
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    if (par[h] >= 0) a.child_list[first_kid + cnt[par[h]] + slot[h]] = (int)base + node[h];
+    if (par[h] >= 0) a.child_list[place + cnt[par[h]] + slot[h]] = (int)base + node[h];
+    if (node[h] >= run_kids && node[h] < T) a.child_list[place + node[h]] = -1;
     if (mine[h] > 0) {
       const int r = first + par_before[h];
       a.row_src[r] = (int)base + node[h];
-      a.row_info[2 * r] = first_kid + incl[h] - mine[h];
+      a.row_info[2 * r] = place + incl[h] - mine[h];
       a.row_info[2 * r + 1] = mine[h];
     }
   }
@@ -550,39 +552,42 @@ struct NodeChunk {  // one node per lane
   float own;
 };
 struct NodeRange {  // slots, or positions in child_list
-  int first, end;
+  int first, end, T;  // T: entries of a sequence (list: as if there were eight)
   bool listed;
 };
 
 __device__ __forceinline__ void load_values(NodeChunk &c, const HeadTables &tb) {
-  c.row = tb.node_row[c.node];
-  c.tok = tb.token[c.node];
-  c.own = tb.own[c.node];
+  const int at = c.node < 0 ? 0 : c.node;  // no node: as the first root, which has no parent either
+  c.row = tb.node_row[at];
+  c.tok = tb.token[at];
+  c.own = tb.own[at];
 }
 
-// The lane's place in a chunk: eight neighbours go to eight waves, in another order each time, so that nodes at the
-// same place of every slot do not all come to one wave (64 trees of 2 nodes in slots of 8, x 256 x 16384: 35 us for the
-// call, 25 so).
-__device__ __forceinline__ int chunk_place(int wave, int lane) {
+// The lane's place in a chunk: eight neighbours go to eight waves, node i of sequence b to wave i + b + b / 8 (for the sequence
+// of the first of the eight), so that the nodes of a tree and the same nodes of many trees are spread evenly: 64 trees of 2
+// nodes in slots of 8, x 256 x 16384, 35 us for the call with wave i + 8 b, 25 so.
+__device__ __forceinline__ int chunk_place(int T, int wave, int lane) {
   static_assert(kGemmWaves == 8, "eight neighbours, eight waves");
-  return kGemmWaves * lane + ((wave + lane + (lane >> 3)) & 7);
+  const int b = (int)(((float)(8 * lane) + .5f) * __builtin_amdgcn_rcpf((float)T));
+  return 8 * lane + ((wave - b * (1 - T) - (b >> 3)) & 7);
 }
 
 // the lane's node of the chunk that starts at x0; past the end the first one of the range
 __device__ __forceinline__ int chunk_node(const NodeRange &r, int x0, int wave, int lane, const HeadTables &tb) {
-  const int x = x0 + chunk_place(wave, lane), at = x < r.end ? x : r.first;
+  const int x = x0 + chunk_place(r.T, wave, lane), at = x < r.end ? x : r.first;
   return r.listed ? tb.child_list[at] : at;
 }
 
 // the nodes whose parents have (slots: may have) score rows of m0 .. m1 - 1
 __device__ __forceinline__ NodeRange nodes_of_rows(int m0, int m1, int m_total, const HeadTables &tb) {
-  NodeRange r = {0, tb.cnt_stride, false};
+  NodeRange r = {0, tb.cnt_stride, tb.T_max, false};
   if (r.end > kChunkNodes) {
     if (m0 > 0) r.first = tb.row_src[m0] / tb.T_max * tb.T_max;
     if (m1 < m_total) r.end = tb.row_src[m1 - 1] / tb.T_max * tb.T_max + tb.T_max;
     r.listed = r.end - r.first > kChunkNodes;
   }
   if (r.listed) {
+    r.T = 8;
     r.first = tb.row_info[2 * m0];
     r.end = tb.row_info[2 * m1 - 2] + tb.row_info[2 * m1 - 1];
   }
@@ -597,7 +602,7 @@ __device__ __forceinline__ void rows_epilogue(NodeChunk nodes, const NodeRange &
   if (KIND == 0) {
     int32_t *dst = tb.cnt_part + (size_t)n_tile * tb.cnt_stride;
     for (int x0 = range.first;;) {
-      const bool mine = x0 + chunk_place(wave, lane) < range.end && nodes.row >= m0 && nodes.row < m1;
+      const bool mine = x0 + chunk_place(range.T, wave, lane) < range.end && nodes.row >= m0 && nodes.row < m1;
       uint64_t rest = __builtin_amdgcn_ballot_w64(mine);
       int count = 0;
       constexpr int N = 4;  // children at a time; past the last one the same once more
@@ -629,7 +634,7 @@ __device__ __forceinline__ void rows_epilogue(NodeChunk nodes, const NodeRange &
       }
       if (mine) dst[nodes.node] = count;
       x0 += kChunkNodes;
-      if (x0 >= range.end) break;
+      if (__builtin_expect(x0 >= range.end, 1)) break;
       nodes.node = chunk_node(range, x0, wave, lane, tb);
       load_values(nodes, tb);
     }
@@ -807,8 +812,8 @@ __device__ __forceinline__ void early_head_small_tile(
   constexpr int kMaxOutstanding = (kStages - 1) * (kALoads + 2);
   int slot_ld = 0;
   NodeChunk nodes = {0, -1, 0, 0.f};
-  NodeRange range = {0, tb.cnt_stride, false};
-  if (KIND == 0 && range.end > kChunkNodes) {
+  NodeRange range = {0, tb.cnt_stride, tb.T_max, false};
+  if (KIND == 0 && __builtin_expect(range.end > kChunkNodes, 0)) {
     range = nodes_of_rows(0, m_total, m_total, tb);
     nodes.node = chunk_node(range, range.first, wave, lane, tb);
   }
@@ -817,7 +822,7 @@ __device__ __forceinline__ void early_head_small_tile(
     slot_ld = slot_ld + 1 == kStages ? 0 : slot_ld + 1;
   }
   // (loads younger than the ring's only make the counted waits below stricter)
-  if (KIND == 0 && !range.listed) {
+  if (KIND == 0 && __builtin_expect(!range.listed, 1)) {
     nodes.node = chunk_node(range, 0, wave, lane, tb);
     load_values(nodes, tb);
   }
@@ -864,7 +869,7 @@ __device__ __forceinline__ void early_head_small_tile(
     __builtin_amdgcn_sched_barrier(0);
   }
   mfma_settle();
-  if (KIND == 0 && range.listed) load_values(nodes, tb);
+  if (KIND == 0 && __builtin_expect(range.listed, 0)) load_values(nodes, tb);
   // element (row, col) of a 32 x 32 tile: lane col + 32 * (row / 4 % 2), register 4 * (row / 8) + row % 4
   float *s_z = reinterpret_cast<float *>(gemm_smem);
   __syncthreads();  // every wave is done with the ring
