@@ -40,7 +40,19 @@ namespace propd {
 // scratch layout
 // ------------------------------------------------------------------------------------
 constexpr int kNoteTiles = 0;    // column tiles of the scoring kernel's plan
-constexpr int kNoteArrived = 1;  // sequences that have their survivor count written (prune_finish_kernel)
+constexpr int kNoteArrived = 1;  // sequences, or lines of them, whose survivor counts are written (prune_finish_kernel)
+constexpr int kNoteLine = 32;    // words of a line; in the lines behind the first one arrive some of the sequences each
+
+// Lines on which the sequences of a batch arrive (a power of two; 0: all on the first).  Arrivals on one line pass one by
+// one, about 8 ns each: prune_finish_kernel at 1000 sequences of 16 nodes 26.7 us with one line, 21.7 with 32.  The notes
+// have room for one word per node slot.
+__host__ __device__ inline int arrival_lines(int B, int T_max) {
+  int lines = 0;
+  if (B > 64)
+    for (lines = 32; lines > 0 && (long long)(lines + 1) * kNoteLine > (long long)B * T_max; lines >>= 1) {
+    }
+  return lines;
+}
 
 struct PruneScratch {
   int32_t *row_src;     // [B*T_max]  score row -> b*T_max + node
@@ -418,7 +430,10 @@ template <bool kBf16>
 __global__ __launch_bounds__(kScanThreads) void prune_prepare_kernel(PrepareArgs a) {
   const int table_groups = (a.B + kTableWaves - 1) / kTableWaves;
   if ((int)blockIdx.x < table_groups) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.notes[kNoteArrived] = 0;
+    if (blockIdx.x == 0) {
+      if (threadIdx.x == 0) a.notes[kNoteArrived] = 0;
+      if (threadIdx.x >= 1 && (int)threadIdx.x <= arrival_lines(a.B, a.T_max)) a.notes[threadIdx.x * kNoteLine] = 0;
+    }
     prepare_tables(a, blockIdx.x);
     return;
   }
@@ -1008,7 +1023,8 @@ struct PayloadArgs {
 };
 
 struct FinishArgs {
-  int B, T_max, vocab, bf16, scored, parts, log_split;
+  int B, T_max, vocab, bf16, scored, parts, lines, slices;  // slices: workgroups per sequence, in x if there are several
+  unsigned long long inv_slices;  // 2^64 / slices
   Criterion crit;
   const int32_t *n_nodes, *parent, *token, *depth;
   const uint64_t *anc;
@@ -1027,16 +1043,19 @@ constexpr int kFinishThreads = PROPD_MAX_TREE * kFinishSplit;
 constexpr int kRowLanes = 8;     // threads that take the partial sums of one score row
 constexpr int kGatherItems = 4;  // pieces a thread has in flight
 
-// Workgroups per sequence (a power of two): at most one for 2048 pieces of payload (of which typically a quarter
+// Workgroups per sequence: at most one for 2048 pieces of payload (of which typically a quarter
 // to a half survive) and one per compute unit in the whole batch, since each works out its sequence's decision; two
-// per compute unit for large payloads.  Pruning call, us, at one / two per compute unit: 5 sequences x 32 heads x 70
-// nodes (545 blocks of 2048) 52.5 / 54.1 (four: 58.0), 32 x 128 nodes, hidden only (1024) 232.6 / 235.0, 27 x 16 x 128
-// (1863) 144.8 / 143.1, 16 x 40 x 128 (2560) 235.0 / 232.4.
-static int finish_log_split(int B, long long blocks, int cus) {
-  const long long most = blocks >= 6ll * cus ? 2ll * cus : cus;
-  int log_split = 0;
-  while (log_split < 10 && (2ll * B << log_split) <= most && ((long long)B << log_split) < blocks) ++log_split;
-  return log_split;
+// per compute unit for large payloads, and no fewer than three for two units.  Pruning call, us, at one / two per compute
+// unit: 5 sequences x 32 heads x 70 nodes (545 blocks of 2048) 52.5 / 54.1 (four: 58.0), 32 x 128 nodes, hidden only (1024)
+// 232.6 / 235.0, 27 x 16 x 128 (1863) 144.8 / 143.1, 16 x 40 x 128 (2560) 235.0 / 232.4.  Rows of 41 KB per node, by
+// workgroups in the batch: 129 sequences of 128 nodes 258 163, 387 143, 516 155; 65 260 87, 455 81, 520 86; 257 of 64 257 171, 514
+// 143.
+static int finish_slices(int B, long long blocks, int cus) {
+  const bool large = blocks >= 6ll * cus;
+  long long slices = (large ? 2ll * cus : cus) / B;
+  if (large && 2 * slices * B < 3ll * cus) ++slices;
+  if (slices > (blocks + B - 1) / B) slices = (blocks + B - 1) / B;
+  return (int)(slices < 1 ? 1 : (slices > 1024 ? 1024 : slices));
 }
 
 // The pieces [lo, hi) of one payload of one sequence, counted as (outer, survivor, piece of its row), in
@@ -1094,7 +1113,7 @@ __device__ __forceinline__ void gather_pieces(const char *src, char *dst, long l
 // call, us: 16 sequences x 40 heads x 128 nodes 236 -> 232, probability criterion at 32 ragged trees 240 -> 233, 31 x 40 x 52
 // 118.5 -> 112, 1 x 64 nodes x 4096 76.1 -> 75.0, fp32 1 x 32 x 389 x 1011 28.2 -> 25.0.
 __global__ __launch_bounds__(kFinishThreads) void prune_finish_kernel(FinishArgs a) {
-  const int b = (int)(blockIdx.x >> a.log_split), slice = (int)(blockIdx.x & ((1u << a.log_split) - 1u));
+  const int b = (int)(a.slices > 1 ? blockIdx.y : blockIdx.x), slice = (int)(a.slices > 1 ? blockIdx.x : 0);
   const int i = threadIdx.x & (PROPD_MAX_TREE - 1), q = threadIdx.x / PROPD_MAX_TREE;
   const int T_max = a.T_max;
   const size_t base = (size_t)b * T_max;
@@ -1296,7 +1315,15 @@ __global__ __launch_bounds__(kFinishThreads) void prune_finish_kernel(FinishArgs
         // nobody waits, and the counter was cleared by the preparation.  Count and arrival go through to
         // where all workgroups see them, in this order (a fence would also write the caches back).
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        s_last = __hip_atomic_fetch_add(a.notes + kNoteArrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.B - 1;
+        auto arrive = [&](int word, int all) {
+          return __hip_atomic_fetch_add(a.notes + word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == all - 1;
+        };
+        if (a.lines == 0) {
+          s_last = arrive(kNoteArrived, a.B);
+        } else {  // the last one on a line arrives for it on the first
+          const int l = b & (a.lines - 1);
+          s_last = arrive((l + 1) * kNoteLine, (a.B - l + a.lines - 1) >> __builtin_ctz(a.lines)) && arrive(kNoteArrived, a.lines);
+        }
       }
       if (a.out_n_nodes) a.out_n_nodes[b] = kept;
       if (a.B == 1) {
@@ -1310,7 +1337,7 @@ __global__ __launch_bounds__(kFinishThreads) void prune_finish_kernel(FinishArgs
   {
     unsigned long long total = 0, start = 0;
     for (int p = 0; p < a.pa.n; ++p) total += (unsigned long long)a.pa.outer[p] * (unsigned)kept * a.pa.per_row[p];
-    const unsigned long long share = (total + (1u << a.log_split) - 1) >> a.log_split;
+    const unsigned long long share = a.slices > 1 ? __umul64hi(total, a.inv_slices) + 1 : total;  // no less than total / slices
     const unsigned long long lo = share * (unsigned)slice, hi = lo + share < total ? lo + share : total;
     for (int p = 0; p < a.pa.n; ++p) {
       const unsigned long long items = (unsigned long long)a.pa.outer[p] * (unsigned)kept * a.pa.per_row[p];
@@ -1557,8 +1584,11 @@ static propd_status prune_impl(
   fa.rank_out = rank_out;
   pa.n = n_payloads;
   fa.pa = pa;
-  fa.log_split = finish_log_split(B, total_blocks, cus);
-  hipLaunchKernelGGL(prune_finish_kernel, dim3((unsigned)B << fa.log_split), dim3(kFinishThreads), 0, st, fa);
+  fa.lines = arrival_lines(B, T_max);
+  fa.slices = finish_slices(B, total_blocks, cus);
+  fa.inv_slices = ~0ull / (unsigned)fa.slices;
+  hipLaunchKernelGGL(prune_finish_kernel, fa.slices > 1 ? dim3((unsigned)fa.slices, (unsigned)B) : dim3((unsigned)B),
+                     dim3(kFinishThreads), 0, st, fa);
   if (!scored && B > 1) hipLaunchKernelGGL(cu_nodes_kernel, dim3(1), dim3(kScanThreads), 0, st, B, n_kept, cu_nodes);
   return launch_ok() ? PROPD_OK : PROPD_ERR_DEVICE;
 }

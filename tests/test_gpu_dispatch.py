@@ -589,11 +589,13 @@ print("ranks as counted")
 """
 
 
-@pytest.mark.parametrize("B,T", [(1, 5), (2, 128), (3, 17), (255, 6), (256, 6), (257, 6), (513, 4), (1100, 3)])
+@pytest.mark.parametrize("B,T", [(1, 5), (2, 128), (3, 17), (64, 9), (65, 1), (66, 2), (131, 3), (255, 6), (256, 6), (257, 6), (513, 4),
+                                 (1100, 3)])
 @pytest.mark.parametrize("crit", ["topk", "prob"])
 def test_prune_sequences_of_a_batch(pb, oracle, B, T, crit):
     """One workgroup per sequence and many: decisions, payload rows and the prefix sum of the survivor counts, which the
-    last sequence to be decided writes; twice with one workspace, whose counter the second call finds used."""
+    last sequence to be decided writes (sequences arrive on one line up to 64, then on as many as there is room for);
+    twice with one workspace, whose counters the second call finds used."""
     rng = np.random.default_rng([B, T])
     trees = [synth.random_tree(rng, int(n)) for n in rng.integers(1, T + 1, B)]
     trees[0] = synth.random_tree(rng, T)
