@@ -325,27 +325,33 @@ __global__ __launch_bounds__(kF32AttnThreads) void tree_attn_f32_combine_kernel(
 // another number makes the longest chain shorter.  A chain is counted in rounds of 16-row tiles that a wave takes (about
 // 2.1 us each at d = 128); a second workgroup on a compute unit costs about two rounds, its loads and matrix
 // instructions being in the way of the first one's (one round at d = 64, and where sequences may be shorter than the
-// longest), and the merge kernel two.  Considered are all numbers that leave one workgroup per compute unit, and
-// those beyond `full` that leave two; of equal cost `full`, then the least.  Splits
-// also shorten the chains of the sums: no less than three quarters of `full` are taken, and the mean error against 64 bits
-// over 40 calls of random sizes is what it was (0.997 of it).
-// Calls, us, with `full` / now: 16 units of 115 x 561 25.2 / 19.2 (320 / 256 workgroups), 16 x 63 x 1082 22.7 / 19.6 (288 /
+// longest), and the merge kernel two (three of the short ones at d = 64 and at most 16 queries).  Considered are all
+// numbers that leave one workgroup per compute unit, and those beyond `full` that leave two; of equal cost `full`, then the least.
+// Where `full` leaves two already and the last of several groups of 32 queries has 16 or fewer, so that its workgroups end
+// early, more of them pay now and then only: `full` then.  Splits also shorten the chains of the sums: no less than three quarters
+// of `full` are taken, and the mean error against 64 bits over 40 calls of random sizes is what it was (0.997 of it).
+// Calls, us, with `full` / this rule: 16 units of 115 x 561 25.2 / 19.2 (320 / 256 workgroups), 16 x 63 x 1082 22.7 / 19.6 (288 /
 // 256), 8 x 115 x 198 18.0 / 13.4 (64 / 160), 12 x 86 x 1063 (d = 64) 16.6 / 14.1, 40 x 20 x 1279 (d = 64) 17.1 / 15.9 (400 / 440).
+// With `full` / the other number where `full` is kept: 40 x 108 x 158 23.4 / 26.1 (320 / 480), 16 x 65 x 980 (d = 64) 14.6 / 15.7
+// (384 / 432), 32 x 78 x 484 23.8 / 25.1 (384 / 480), 64 x 12 x 211 (d = 64) 8.0 / 8.6 (64 / 256).  308 calls of random sizes for
+// which another number is taken: geometric mean 1.157, and none more than 2 % slower but four ragged batches, whose lengths
+// the host does not know (36 x 51 x up to 623 0.89 to 1.12, 96 x 29 x up to 551 0.91 to 1.04).
 constexpr int kF32MinTiles = 8;
-static int f32_splits(long long base, int tiles, int cus, size_t workspace_bytes, int D, bool one_sequence) {
+static int f32_splits(long long base, int tiles, int cus, size_t workspace_bytes, int D, int T_max, bool one_sequence) {
   long long most = (long long)(workspace_bytes / (f32_part_floats(D) * 4)) / base;  // room for the partial results
   if (most > kF32MaxSplits) most = kF32MaxSplits;
   long long full = (2ll * cus + base - 1) / base;
   if (full > tiles / kF32MinTiles) full = tiles / kF32MinTiles;
   if (full > most) full = most;
   if (full < 1) full = 1;
+  const bool short_last = T_max > 32 && (T_max - 1) % 32 < 16;
   auto cost = [&](long long s) {
     const long long rounds = ((tiles + s - 1) / s + kF32AttnWaves - 1) / kF32AttnWaves;
-    return rounds + (s > 1 ? 2 : 0) + (base * s > cus ? (D == 128 && one_sequence ? 2 : 1) : 0);
+    return rounds + (s > 1 ? (D == 64 && T_max <= 16 ? 3 : 2) : 0) + (base * s > cus ? (D == 128 && one_sequence ? 2 : 1) : 0);
   };
   long long best = full;
   for (long long s = (3 * full + 3) / 4; s <= most && base * s <= 2ll * cus; ++s) {
-    if (s < full && base * s > cus) continue;
+    if (base * s > cus && (s < full || (short_last && base * full > cus))) continue;
     if (cost(s) < cost(best)) best = s;
   }
   return (int)best;
@@ -357,7 +363,8 @@ static bool launch_f32(AttnParamsF32 p, int cus, void *workspace, size_t workspa
   // records are read and written 16 bytes at a time
   if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 16 != 0) workspace_bytes = 0;
   p.part = reinterpret_cast<float *>(workspace);
-  p.splits = f32_splits((long long)p.units * pairs, (p.L_max + 15) / 16 + (p.T_max + 15) / 16, cus, workspace_bytes, D, p.units == p.H);
+  p.splits = f32_splits((long long)p.units * pairs, (p.L_max + 15) / 16 + (p.T_max + 15) / 16, cus, workspace_bytes, D,
+                        p.T_max, p.units == p.H);
   // a dimension of the grid holds fewer than 2^32 threads, and there may be 2^28 units
   constexpr unsigned kGridX = 1u << 22;
   const unsigned blocks = (unsigned)p.units * (unsigned)pairs * (unsigned)p.splits;
