@@ -467,7 +467,7 @@ struct Walk {
   static __device__ __forceinline__ float floor_quotient(float n, float inv) { return floorf((n + .5f) * inv); }
   // n / d rounded up, up = (d - 1/2) / d
   static __device__ __forceinline__ float ceil_quotient(float n, float inv, float up) { return floorf(fmaf(n, inv, up)); }
-  template <int KS>
+  template <int D, int KS>
   __device__ __forceinline__ int begin_one_pass(const StageMap &m, Schedule &sc, int w, int G) {
     const int lane = threadIdx.x & 63, H = m.H;
     int len_l = m.seq_lens[lane < m.B ? lane : 0], nodes_l = m.n_nodes[lane < m.B ? lane : 0];
@@ -512,7 +512,17 @@ struct Walk {
         const float share = (float)U * __builtin_amdgcn_rcpf((float)G);
         const float one_each = KS == 2 ? 1.3f * mean + 11.f : 1.2f * mean + 8.f;
         const float several = fminf((1.f + (share < .5f ? .8f : 1.1f) * share) * mean + 1.f, (KS == 2 ? 1.25f : 1.15f) * mean + 17.f * share);
-        const float limit = pieces <= (float)U ? one_each : several;
+        // And by how many stages at most: a stage more costs 0.5 us and up where stages are bound by their chain (d = 64) and where
+        // the trees are so small that rows come faster (T_max <= 8), against the 3 to 5 us that a crossing costs.  Whole calls, us, at
+        // mean / longest stages, crossing / not: d = 64, equal lengths, 432 units 34.6 / 41 48.7 / 47.2, 372 27.6 / 38 37.8 / 40.1,
+        // 336 40 / 61 47.2 / 57.5, two pieces each (one wave per 32 queries) 120 34 / 37 67.9 / 64.5, 152 29.4 / 33 52.5 / 54.3, 208 50 / 62 77.0
+        // / 84.5; ragged, 416 19.1 / 30 34.3 / 28.9, 264 47.7 / 61 58.0 / 61.2.  d = 128, 1 to 8 queries, 416 27.6 / 34 45.2 / 43.9, 264 8.2 / 16
+        // 19.1 / 21.0, 304 24.3 / 41 40.1 / 43.6, 444 51 / 59 79.4 / 72.8; several pieces each, 480 15.9 / 30 41.8 / 37.2, 208 61.8 / 76 91.1 /
+        // 93.2, 296 48.1 / 68 78.7 / 83.0 (one each: 376 63.9 / 87 101.5 / 93.0).
+        const bool same = __ballot(lane < m.B && us_l != __builtin_amdgcn_readfirstlane(us_l)) == 0;
+        const bool one = pieces <= (float)U;
+        const float more = D == 64 ? (same ? (KS == 1 && !one ? 3.3f : 6.5f) : 11.f) : (m.T_max <= 8 ? 14.f * share : one ? 1e9f : 14.15f);
+        const float limit = fminf(one ? one_each : several, mean + more);
         // One wave per 32 queries and fewer workgroups left than half the chip: 16 units of 127 x 136 (d = 64) 12.5 / 13.9.
         if (longest > limit || (KS == 1 && pieces < .5f * (float)m.cus && pick > 0)) pick = -1;
         // Fewer, longer pieces, one workgroup per compute unit, where a unit would be cut into many: 32 units of 34 stages in 12 / 7
@@ -687,7 +697,7 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
   Walk cp;
   int n_my;
   if (p.one_pass) {
-    n_my = cp.template begin_one_pass<KS>(map, sch, (int)w, (int)G);
+    n_my = cp.template begin_one_pass<D, KS>(map, sch, (int)w, (int)G);
   } else {
     sch = make_schedule(map, G);
     n_my = cp.start(map, sch, w, G);

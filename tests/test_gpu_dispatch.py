@@ -353,11 +353,13 @@ def test_attention_bf16_sequences_of_a_wave(pb, oracle, B, H, ragged):
 
 # B, H, T_max, L, ragged lengths: no more units than workgroups (512 on 256 compute units) and more; ranges of one
 # unit each (equal lengths, many pieces, one piece, few workgroups) and ranges that cross units; both sides of
-# the line between two waves per 32 queries and one, and of the line of L_max for short pieces of many units
+# the line between two waves per 32 queries and one, of the line of L_max for short pieces of many units, and of
+# the limits of the longest range by head size and tree size
 RANGES = [(1, 1, 64, 3000, False), (1, 8, 59, 2500, False), (2, 16, 64, 700, True), (3, 5, 65, 700, True), (1, 40, 33, 90, False),
           (5, 12, 32, 592, False), (31, 8, 47, 300, True), (8, 64, 20, 60, False), (8, 64, 70, 60, True), (57, 9, 64, 64, True),
           (64, 8, 31, 40, True), (65, 7, 64, 70, True), (20, 30, 64, 100, True), (27, 20, 9, 1024, True), (27, 20, 9, 1023, True),
-          (4, 3, 1, 33, True), (16, 1, 127, 136, False), (1, 300, 96, 200, False), (2, 33, 100, 0, False)]
+          (4, 3, 1, 33, True), (16, 1, 127, 136, False), (1, 300, 96, 200, False), (2, 33, 100, 0, False),
+          (48, 8, 7, 900, False), (40, 8, 30, 700, True), (19, 8, 65, 980, False)]
 
 
 @pytest.mark.parametrize("d", [64, 128])
