@@ -54,9 +54,10 @@ struct Geo {
   static constexpr int kLdRows = 1024 / kRowBytes;            // rows that one direct load of a wave fills
   static constexpr int kLoads = kHalfStage / 4096;            // direct loads of a wave per half stage
   static constexpr int kMb = D / 32;                          // 32-wide blocks of d of PV
-  // Workgroups resident on a compute unit: what LDS (two rings of 80 KB at D = 128) and registers
-  // (254; 195 at D = 64) allow.  A bound of more workgroups spills, which this kernel must not:
-  // loads that it waits for by hand would land in registers given away meanwhile.
+  // Workgroups resident on a compute unit: what LDS (two rings of 80 KB) and registers (one wave per 32 queries 253
+  // or, with kAnew, all 256; two 215 to 218) allow at D = 128, and registers at D = 64 with one wave (208).  With two it
+  // takes 165 and 41 KB of LDS, and a third workgroup would fit (not measured).  A bound of four spilled at D = 64, which this
+  // kernel must not: loads that it waits for by hand would land in registers given away meanwhile.
   static constexpr int kPerCu = 2;
   // Chunk c of row r of a stage lies at chunk position c ^ key(r).
   //   K: the 16 rows x 16 bytes that one pass of a fragment read takes (one chunk column) fall
@@ -191,12 +192,6 @@ __device__ __forceinline__ void store_out_block(uint16_t *orow, const f32x16 &o,
     if (kUntracked) global_store16_untracked(orow + mb * 32 + 16 * jp + 8 * g, w4);
     else *reinterpret_cast<u32x4 *>(orow + mb * 32 + 16 * jp + 8 * g) = w4;
   }
-}
-
-template <bool kUntracked, int MB>
-__device__ __forceinline__ void store_out_row(uint16_t *orow, const f32x16 (&o)[MB], float inv, int g) {
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) store_out_block<kUntracked>(orow, o[mb], inv, g, mb);
 }
 
 // Partial results keep the register layout, so that a wave writes and reads them as
@@ -456,17 +451,17 @@ struct Walk {
     }
     return n_my;
   }
+  // n / d rounded down, for whole n below 2^20 and inv = 1 / d to one unit in the last place: n + 1/2 is half a
+  // d-th away from the next whole quotient, the error of the product at most n / d / 2^22
+  static __device__ __forceinline__ float floor_quotient(float n, float inv) { return floorf((n + .5f) * inv); }
+  // n / d rounded up, up = (d - 1/2) / d
+  static __device__ __forceinline__ float ceil_quotient(float n, float inv, float up) { return floorf(fmaf(n, inv, up)); }
   // The schedule and the first stage at once, for at most 64 sequences and fewer than 2^31 stages:
   // every sequence's sizes are read once, into a lane, and what follows from them is 32-bit
   // arithmetic on registers.  It stands in front of a workgroup's first load, and a small call is
   // little else: 1 x 32 units of 64 queries x 1024 keys 19.8 -> 18.2 us for the call, 8 x 16 x 64 x 2048 (d =
   // 64) 35.0 -> 33.1, against loads per question, sums through LDS and 64-bit divisions.  (With ranges
   // that cross no unit and two waves per 32 queries these calls take 14.2 and 26.4 us now.)
-  // n / d rounded down, for whole n below 2^20 and inv = 1 / d to one unit in the last place: n + 1/2 is half a
-  // d-th away from the next whole quotient, the error of the product at most n / d / 2^22
-  static __device__ __forceinline__ float floor_quotient(float n, float inv) { return floorf((n + .5f) * inv); }
-  // n / d rounded up, up = (d - 1/2) / d
-  static __device__ __forceinline__ float ceil_quotient(float n, float inv, float up) { return floorf(fmaf(n, inv, up)); }
   template <int D, int KS>
   __device__ __forceinline__ int begin_one_pass(const StageMap &m, Schedule &sc, int w, int G) {
     const int lane = threadIdx.x & 63, H = m.H;
@@ -1081,8 +1076,8 @@ __global__ __launch_bounds__(kAttnThreads, Geo<D>::kPerCu) void tree_attn_bf16_k
         int n_valid = (is_tree ? T : L) - j0;
         n_valid = n_valid > kStageRows ? kStageRows : n_valid;
         // ---- mask (the softmax scale is positive, so it commutes with max and is applied
-        //      inside the exponent).  Register r of a 32x32 accumulator holds row
-        //      8*(r/4) + 4*g + r%4 of the block, i.e. K/V row j0 + that.
+        //      inside the exponent).  Register r holds K/V row j0 + 8*(r/4) + 4*g + r%4 (KS = 1) or
+        //      j0 + 16*k_part + 8*g + r (KS = 2), see take_scores.
         if (is_tree || n_valid < kStageRows) {  // uniform over the workgroup
           // visibility of the stage's rows to this lane's query: cached rows below L for
           // every query, tree rows only where the node's ancestor set has the bit
