@@ -518,10 +518,14 @@ struct Walk {
         const bool one = pieces <= (float)U;
         const float more = D == 64 ? (same ? (KS == 1 && !one ? 3.3f : 6.5f) : 11.f) : (m.T_max <= 8 ? 14.f * share : one ? 1e9f : 14.15f);
         const float limit = fminf(one ? one_each : several, mean + more);
-        // One wave per 32 queries and fewer workgroups left than half the chip: 16 units of 127 x 136 (d = 64) 12.5 / 13.9.
+        // One wave per 32 queries and fewer workgroups left than half the chip: ranges that cross units stay, since which side is
+        // faster depends on the number of stages.  Whole calls, us, crossing / not: 9 to 21 stages per unit 12.8 / 14.1 (1 x 8 units of 92 x 362), 14.2 / 14.9 (5 x 4 of 68 x 384), 12.5 /
+        // 13.1 (d = 64, 3 of 85 x 180), 12.5 / 13.9 (d = 64, 16 of 127 x 136); 5 to 7 13.1 / 12.0 (3 of 74 x 100), 13.9 / 14.5 (2 x 16 of
+        // 113 x up to 31); 27 and more 13.3 / 12.3 (2 x 2 of 69 x 754).  24 of random sizes: not crossing 0.89 to 1.10 of the time, 0.96 on average.
         if (longest > limit || (KS == 1 && pieces < .5f * (float)m.cus && pick > 0)) pick = -1;
         // Fewer, longer pieces, one workgroup per compute unit, where a unit would be cut into many: 32 units of 34 stages in 12 / 7
-        // pieces 15.5 / 14.2, 8 of 247 in 62 / 31 22.7 / 18.6; 64 units in 8 / 4 20.8 / 21.4.
+        // pieces 15.5 / 14.2, 8 of 247 in 62 / 31 22.7 / 18.6; 64 units in 8 / 4 20.8 / 21.4.  24 calls of random sizes to which it
+        // applies: 1.10 times as fast on average, 0.94 to 1.35 (1 x 2 units of 33 x 2065 13.2 / 14.0, 5 x 4 of 114 x up to 1482 23.0 / 17.1).
         if (pick >= 0 && pieces > 8.f * (float)U && fit_cus != 0 && least_q + (uint32_t)__builtin_ctzll(fit_cus) <= 8u)
           pick = __builtin_ctzll(fit_cus);
       }
@@ -660,8 +664,8 @@ __device__ __forceinline__ float merge_add(float x, float a, float y, float b) {
 // scores and 32x32x16, 16 keys deep, for the weighted sum, and the two waves of a query group merge
 // their results through LDS at the end of a piece.  That halves the chain of a stage, which bounds
 // the kernel at D = 64 (8 x 16 units, 64 queries, 2048 keys: 29.2 -> 26.4 us for the call; 96 x 50 x 2135 26.4 ->
-// 23.4) and costs at D = 128 where pieces are short and many (800 ragged units of up to 834 keys 37.2 -> 37.9;
-// 372 units x 49 x 5383 187 -> 178).
+// 23.4), pays at D = 128 where a workgroup has one piece (372 units x 49 x 5383 187 -> 178) and costs where it has
+// many short ones (800 ragged units of up to 834 keys 37.2 -> 37.9, see propd_tree_attention).
 // kAnew: see Schedule::anew.
 // D = 128 multiplies bf16 weights with V.  D = 64 keeps them in fp32: a weight is the sum of three
 // bf16 values, 8 of its 24 bits each, all of which are multiplied.  (With two of them a weight
@@ -1631,8 +1635,11 @@ extern "C" propd_status propd_tree_attention(const propd_tree *tree, propd_dtype
   const long long unit_stages = (L_max + kStageRows - 1) / kStageRows + (tree->T_max + kStageRows - 1) / kStageRows;
   p.cus = compute_units();
   p.one_pass = tree->B <= kWave && units * unit_stages < (1ll << 31) && unit_stages < (1 << 20) ? 1 : 0;
-    // two waves per 32 queries, see KS
-  const bool split = tree->T_max <= 64 && (d == 64 || units <= grid || L_max >= 1024);
+  // Two waves per 32 queries, see KS.  By sizes alone: the lengths are not known here.  d = 128 with more units than
+  // workgroups keeps one, whatever L_max (the slot's size): over 46 calls of 540 to 2048 units it takes 0.99 to 1.02 of two
+  // waves' time where units have 8 stages and more on average (64 x 32 units of 64 x up to 776 101.9 / 100.3 us, 128 x 16 of 32 x up to
+  // 3380 245.2 / 240.1), and 0.92 to 1.00 with fewer (17 x 32 of 64 x up to 32 16.2 / 17.6, 128 x 16 of 16 x up to 75 30.9 / 32.8).
+  const bool split = tree->T_max <= 64 && (d == 64 || units <= grid);
   const bool anew = p.one_pass && units <= grid;
   if (!(d == 64 ? (split ? launch_bf16<64, 2, false>(p, grid, st) : launch_bf16<64, 1, false>(p, grid, st))
         : anew  ? (split ? launch_bf16<128, 2, true>(p, grid, st) : launch_bf16<128, 1, true>(p, grid, st))

@@ -353,7 +353,7 @@ def test_attention_bf16_sequences_of_a_wave(pb, oracle, B, H, ragged):
 
 # B, H, T_max, L, ragged lengths: no more units than workgroups (512 on 256 compute units) and more; ranges of one
 # unit each (equal lengths, many pieces, one piece, few workgroups) and ranges that cross units; both sides of
-# the line between two waves per 32 queries and one, of the line of L_max for short pieces of many units, and of
+# the line between two waves per 32 queries and one (64 queries; at d = 128 as many units as workgroups), and of
 # the limits of the longest range by head size and tree size
 RANGES = [(1, 1, 64, 3000, False), (1, 8, 59, 2500, False), (2, 16, 64, 700, True), (3, 5, 65, 700, True), (1, 40, 33, 90, False),
           (5, 12, 32, 592, False), (31, 8, 47, 300, True), (8, 64, 20, 60, False), (8, 64, 70, 60, True), (57, 9, 64, 64, True),
@@ -375,6 +375,20 @@ def test_attention_bf16_ranges_of_one_unit(pb, oracle, B, H, T_max, L, ragged, d
     x = synth.make_attention_inputs(w, seq_lens=lens, trees=trees)
     out, sent = run_attention(pb, x)
     check_attention(oracle, x, out, sent)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_attention_bf16_by_lengths_not_by_slots(pb, d):
+    """600 units of up to 200 cached rows in slots of 200 and of 1100: the same kernel and ranges, so the same bits."""
+    w = synth.Workload(5, "slots", "bf16", 20, 30, d, 40, 200, 4096, 10, 1e-3)
+    lens = np.random.default_rng(d).integers(0, 201, 20).astype(np.int32)
+    lens[3] = 200
+    x = synth.make_attention_inputs(w, seq_lens=lens, trees=[synth.rank_product_tree(40, 4)] * 20)
+    outs = [run_attention(pb, x)[0]]
+    for name in ("k_cache", "v_cache"):
+        x[name] = np.concatenate([x[name], np.zeros((20, 30, 1100 - x[name].shape[2], d), x[name].dtype)], 2)
+    outs.append(run_attention(pb, x)[0])
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
 
 
 @pytest.mark.parametrize("H", [127, 128, 129, 160])
