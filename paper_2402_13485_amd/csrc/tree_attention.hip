@@ -1639,6 +1639,8 @@ extern "C" propd_status propd_tree_attention(const propd_tree *tree, propd_dtype
   // workgroups keeps one, whatever L_max (the slot's size): over 46 calls of 540 to 2048 units it takes 0.99 to 1.02 of two
   // waves' time where units have 8 stages and more on average (64 x 32 units of 64 x up to 776 101.9 / 100.3 us, 128 x 16 of 32 x up to
   // 3380 245.2 / 240.1), and 0.92 to 1.00 with fewer (17 x 32 of 64 x up to 32 16.2 / 17.6, 128 x 16 of 16 x up to 75 30.9 / 32.8).
+  // d = 64 gains more than it loses: 40 such calls 0.95 (27 x 20 units of 33 x up to 101 15.2 / 16.0) to 1.27 (20 x 40 of 64 x 1985 140.1 /
+  // 110.5), mean 1.03.  No more units than workgroups, both head sizes: 50 calls 0.96 to 1.25, mean 1.02.
   const bool split = tree->T_max <= 64 && (d == 64 || units <= grid);
   const bool anew = p.one_pass && units <= grid;
   if (!(d == 64 ? (split ? launch_bf16<64, 2, false>(p, grid, st) : launch_bf16<64, 1, false>(p, grid, st))
